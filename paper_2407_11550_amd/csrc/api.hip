@@ -66,7 +66,7 @@ static int build_tables(const adakv_layer *L, SeqTab &st, Dims &dm) {
 // pipeline mode the scoring call already writes into the Top-k part).
 static bool pool_first(const adakv_layer *L) { return (L->flags & ADAKV_FLAG_POOL_THEN_MEAN) != 0; }
 // Which kernel family scores the layer: the matrix cores (16-bit inputs, at most 512 window rows
-// per KV head; with ADAKV_FLAG_POOL_THEN_MEAN a pool radius of at most 7), else the plain-FMA path.
+// per KV head; with ADAKV_FLAG_POOL_THEN_MEAN a pool radius of at most 7), else the fp32 kernels.
 static bool on_mfma(const Dims &dm, const adakv_layer *L) {
   return pool_first(L) ? mfma_pool_rows_supported(dm, L->dtype) : mfma_path_supported(dm, L->dtype);
 }
@@ -401,9 +401,10 @@ int adakv_describe(const adakv_layer *L, int have_row_lse, char *out, size_t out
                    v.chunk, stats, have_row_lse ? "caller" : v.fuse_lse ? "fused" : "kernel",
                    pool_first(L) ? "rows" : v.fuse_pool ? "fused" : "kernel", topk);
   } else {
-    len = snprintf(out, out_bytes, "score=%s dtype=%s d=%d rows=%d stats=%s lse=%s pool=kernel topk=%s",
+    len = snprintf(out, out_bytes, "score=%s dtype=%s d=%d rows=%d stats=%s lse=%s pool=%s topk=%s",
                    pool_first(L) ? "fma-pool-first" : "fma", dt, dm.d, dm.g * dm.w, stats,
-                   have_row_lse ? "caller" : "kernel", topk);
+                   have_row_lse ? "caller" : "kernel",
+                   !pool_first(L) && f32_pool_fused(st, dm) ? "fused" : "kernel", topk);
   }
   return (len < 0 || (size_t)len >= out_bytes) ? ADAKV_EINVAL : ADAKV_OK;
 }

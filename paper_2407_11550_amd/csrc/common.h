@@ -52,7 +52,7 @@ struct Dims {
 
 constexpr int RADIX_BINS = 2048;   // 11-bit digits: passes take bits 31..21, 20..10, 9..0
 constexpr int SEL_CHUNK = 4096;    // positions per block in the histogram and emit kernels
-constexpr int GEN_CHUNK = 256;     // keys per block in the plain-FMA scoring kernels
+constexpr int GEN_CHUNK = 256;     // keys per block in the kernel that only pools
 
 struct TopkCarry;
 
@@ -75,6 +75,7 @@ struct ScorePlan {                  // byte offsets into the workspace
 };
 ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma);
 bool mfma_path_supported(const Dims &dm, int dtype);
+bool f32_pool_fused(const SeqTab &st, const Dims &dm);   // the fp32 weights sweep applies the max-pool itself
 
 hipError_t launch_score_generic(const SeqTab &st, const Dims &dm, int dtype, const void *q,
                                 const void *K, const float *row_lse, float *scores, char *ws,

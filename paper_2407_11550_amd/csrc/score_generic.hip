@@ -1,12 +1,10 @@
-// Observation-window scoring (Alg. 2 lines 1-5, group mean of Section 3.5) with plain fp32 FMA
-// arithmetic: one thread per prefix key.  This path serves fp32 inputs and every shape the
-// MFMA path does not take; it also hosts the two small kernels both paths share (the
-// combination of partial softmax statistics, and the max-pool).
+// Observation-window scoring (Alg. 2 lines 1-5, group mean of Section 3.5) with fp32 multiply-adds:
+// fp32 inputs and every shape the 16-bit matrix kernels do not take.  It also hosts the two small
+// kernels both paths share (the combination of partial softmax statistics, and the max-pool).
 //
 // The softmax of Alg. 2 l.3 needs each window row's denominator before rows can be added up,
 // so the keys are swept twice: once for per-row (max, sum of exp) and once for the normalised
-// weights.  Both sweeps compute a logit with the same instruction sequence, so it is the same
-// number in both.
+// weights.
 #include <math.h>
 
 #include "common.h"
@@ -83,90 +81,199 @@ __device__ __forceinline__ float logit(const float *qrow, const float *k, float 
   return acc * scale;
 }
 
-// Sweep 1: partial (max, sum exp(s - max)) of every window row over this block's 256 keys.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void stats_generic_kernel(
-    SeqTab st, ChunkTab ct, Dims dm, const T *__restrict__ q, const T *__restrict__ K,
-    float2 *__restrict__ part) {
-  __shared__ float qs[ROW_TILE][D];
-  __shared__ float sm[4][ROW_TILE], sl[4][ROW_TILE];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// ---- both sweeps in 32-bit arithmetic on the matrix cores --------------------------------------
+//
+// v_mfma_f32_32x32x2_f32 multiplies and accumulates in fp32, 64 fused multiply-adds per cycle and
+// SIMD: twice the rate of the vector ALUs (packed fp32 is not used here) and no LDS operand per
+// multiply-add.  The kernels are bound by it: 2 g w d h n flops per sweep at the 154 TFLOP/s that
+// an fp32 matrix product reaches on this part.
+//
+// A wavefront keeps 32 keys in registers for its whole life (d/2 words per lane, straight from
+// memory: every byte of K is read once per sweep) and the window rows stream past them through
+// LDS, 32 at a time, converted to fp32 on the way in, one barrier per row block.  So any number
+// of window rows per head works, and in sweep 2 the sum over them never leaves a lane's register.
+// (Q resident and K streaming, the split of the 16-bit kernels, needs d/2 registers per 32 rows
+// and wavefront in fp32, which ends at 256 rows.)  128 keys per workgroup: 8191 keys x 8 heads
+// make 512 workgroups, two per compute unit; with 64 keys every workgroup would read all of Q for
+// half the work.  (Sweep 1 has a form with eight wavefronts and 256 keys, which leaves half as many
+// partial statistics behind; see plan_score.)  32 query heads x 32 rows over 8 KV heads, d = 128, 8191 keys, fp32: the scalar
+// kernels before (one thread per key, every operand of Q an LDS broadcast) took 229 + 171 us for
+// the two sweeps, these take 25 + 24 us (85 TFLOP/s, launch included).
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
+constexpr float LOG2E = 1.4426950408889634f;
+constexpr float LN2 = 0.6931471805599453f;
+constexpr int F32_KEYS = 128;                          // keys per workgroup: four wavefronts of 32 (sweep 1 also: eight)
+constexpr int F32_POOL_MAX = 16;                       // largest pool radius that sweep 2 applies itself
+
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// The 32 window rows r0 .. r0+31 travel memory -> registers (fetch) -> LDS as fp32 (store).  Rows
+// past R are fetched from row R-1; their products are never used.
+template <typename T, int D, int NT>
+struct RowBlock {
+  static constexpr int P = Elem<T>::PER16;
+  static constexpr int WORDS = 32 * D / P;             // 16-byte words of the block
+  static constexpr int LD = (WORDS + NT - 1) / NT;     // per thread
+  static constexpr int STRIDE = D + 4;                 // padded LDS row, in floats (16-byte aligned)
+  static_assert(WORDS % NT == 0 || WORDS < NT, "the row block must split evenly over the threads");
+  uint4 g[LD];
+  __device__ __forceinline__ void fetch(const T *qhead, int r0, int R) {
+#pragma unroll
+    for (int i = 0; i < LD; ++i) {
+      const int wi = min((int)threadIdx.x + i * NT, WORDS - 1);
+      const int row = min(r0 + wi / (D / P), R - 1);
+      g[i] = *reinterpret_cast<const uint4 *>(qhead + (size_t)row * D + (wi % (D / P)) * P);
+    }
+  }
+  __device__ __forceinline__ void store(float *buf) const {
+#pragma unroll
+    for (int i = 0; i < LD; ++i) {
+      const int wi = threadIdx.x + i * NT;
+      if (WORDS < NT && wi >= WORDS) break;
+      float f[P];
+      Elem<T>::unpack(g[i], f);
+      float *dst = buf + (wi / (D / P)) * STRIDE + (wi % (D / P)) * P;
+#pragma unroll
+      for (int e = 0; e < P; e += 4) *reinterpret_cast<float4 *>(dst + e) = make_float4(f[e], f[e + 1], f[e + 2], f[e + 3]);
+    }
+  }
+};
+
+// Sweep 1 (PASS 1): partial (reference, sum of exp2(logit - reference)) of every window row over
+// the workgroup's 32 NW keys, logits in the base-2 domain.  D = K Q^T: a lane owns one window row and
+// 16 keys.  Sweep 2 (PASS 2): weights summed over the rows, divided by g*w, then (pool_r >= 0) the
+// max-pool.  D = Q K^T: a lane owns one key and 16 rows.  With the pool applied here a workgroup
+// owns the inner 128 - 2 pool_r of its keys; pool_r < 0 leaves the pool to a kernel of its own.
+//
+// The operands' k index is permuted alike in both: of every two 16-byte words of a row the lower
+// half of the wavefront takes the first, the upper half the second.
+template <typename T, int D, int PASS, int NW>
+__global__ __launch_bounds__(64 * NW) void score_f32_kernel(
+    SeqTab st, ChunkTab ct, Dims dm, float c_log2, int pool_r, int lse_natural,
+    const T *__restrict__ q, const T *__restrict__ K, const float *__restrict__ lse,
+    float2 *__restrict__ part, float *__restrict__ out) {
+  typedef RowBlock<T, D, 64 * NW> RB;
+  constexpr int KEYS = 32 * NW;
+  constexpr int P = RB::P;
+  constexpr int KW = D / (2 * P);                      // 16-byte words of a key row per lane
+  __shared__ __align__(16) float qs[2][32 * RB::STRIDE];
+  __shared__ float sh_a[2][NW][32], sh_b[2][NW][32];   // sweep 1: per-wavefront row statistics
+  __shared__ float sh_l2[2][32];                       // sweep 2: the row block's log-sum-exp
+  __shared__ float sh_raw[KEYS];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = find_seq(ct, st.batch, blockIdx.x);
   const int chunk = blockIdx.x - ct.off[b];
   const int c = blockIdx.y;
   const int n = st.n[b];
   const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
-  const int j = chunk * GEN_CHUNK + tid;
-  const bool valid = j < n;
-  float k[D];
-  if (valid) {
-    load_row<T, D>(K + (st.tok_off[b] + j) * dm.k_stride_tok + c * dm.k_stride_head, k);
-  } else {
-#pragma unroll
-    for (int e = 0; e < D; ++e) k[e] = 0.0f;
-  }
+  const int r = PASS == 2 && pool_r > 0 ? pool_r : 0;
+  const int own = KEYS - 2 * r;
+  const int k0 = chunk * own - r;                      // first key of the workgroup; keys outside [0, n) are masked
+  const int key = k0 + wv * 32 + l32;
   const T *qhead = q + ((size_t)b * RQ + (size_t)c * R) * D;
-  for (int r0 = 0; r0 < R; r0 += ROW_TILE) {
-    __syncthreads();
-    stage_q<T, D>(qhead, r0, R, qs);
-    __syncthreads();
-    const int rt = min(ROW_TILE, R - r0);
-    for (int r = 0; r < rt; ++r) {
-      const float s = valid ? logit<D>(qs[r], k, dm.scale) : -INFINITY;
-      float m = s;
+  const size_t lse0 = (size_t)b * RQ + (size_t)c * R;
+
+  RB rb;
+  rb.fetch(qhead, 0, R);
+  float kf[KW * P];
+  {
+    const T *src = K + (st.tok_off[b] + min(max(key, 0), n - 1)) * dm.k_stride_tok + c * dm.k_stride_head + half * P;
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-      float l = (valid && m > -INFINITY) ? expf(s - m) : 0.0f;
+    for (int s = 0; s < KW; ++s) Elem<T>::unpack(*reinterpret_cast<const uint4 *>(src + s * 2 * P), kf + s * P);
+  }
+  auto row_l2 = [&](int row) {                         // padding rows: +inf, their weights are exactly zero
+    const float v = lse[lse0 + min(row, R - 1)];
+    return row < R ? (lse_natural ? v * LOG2E : v) : INFINITY;
+  };
+  rb.store(qs[0]);
+  if (PASS == 2 && tid < 32) sh_l2[0][tid] = row_l2(tid);
+  __syncthreads();
+
+  float total = 0.0f;
+  const int blocks = (R + 31) / 32;
+  for (int ib = 0; ib < blocks; ++ib) {
+    const int cur = ib & 1;
+    const bool more = ib + 1 < blocks;
+    float next_l2 = 0.0f;
+    if (more) {
+      rb.fetch(qhead, (ib + 1) * 32, R);
+      if (PASS == 2 && tid < 32) next_l2 = row_l2((ib + 1) * 32 + tid);
+    }
+    // two chains of d/2 multiply-adds instead of one of d: the rounding of a logit follows the longest
+    floatx16 acc = {0}, acc1 = {0};
+    const float *qrow = qs[cur] + l32 * RB::STRIDE + half * P;
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
-      if (lane == 0) { sm[wv][r] = m; sl[wv][r] = l; }
+    for (int s = 0; s < KW; ++s) {
+#pragma unroll
+      for (int e = 0; e < P; e += 4) {
+        const float4 v = *reinterpret_cast<const float4 *>(qrow + s * 2 * P + e);
+        const float qv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          floatx16 &a = (i & 1) ? acc1 : acc;
+          a = PASS == 1 ? __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s * P + e + i], qv[i], a, 0, 0, 0)
+                        : __builtin_amdgcn_mfma_f32_32x32x2f32(qv[i], kf[s * P + e + i], a, 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] += acc1[i];
+    if (PASS == 1) {
+      // acc[i]: key k0 + wv*32 + 8*(i/4) + 4*half + i%4, window row ib*32 + l32
+      float m = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        acc[i] = (k0 + wv * 32 + 8 * (i / 4) + 4 * half + i % 4 < n) ? acc[i] * c_log2 : -INFINITY;
+        m = fmaxf(m, acc[i]);
+      }
+      m = fmaxf(m, __shfl_xor(m, 32));
+      const float ref = (m == -INFINITY) ? 0.0f : m;
+      float l = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) l += fast_exp2(acc[i] - ref);
+      l += __shfl_xor(l, 32);
+      if (half == 0) { sh_a[cur][wv][l32] = m; sh_b[cur][wv][l32] = l; }
+    } else {
+      // acc[i]: window row ib*32 + 8*(i/4) + 4*half + i%4, key k0 + wv*32 + l32
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        total += fast_exp2(fmaf(acc[i], c_log2, -sh_l2[cur][8 * (i / 4) + 4 * half + i % 4]));
+    }
+    if (more) {
+      rb.store(qs[cur ^ 1]);
+      if (PASS == 2 && tid < 32) sh_l2[cur ^ 1][tid] = next_l2;
     }
     __syncthreads();
-    if (tid < rt) {
-      float M = fmaxf(fmaxf(sm[0][tid], sm[1][tid]), fmaxf(sm[2][tid], sm[3][tid]));
+    // (the buffers of this row block are written again two barriers from here)
+    if (PASS == 1 && tid < 32 && ib * 32 + tid < R) {
+      float M = sh_a[cur][0][tid];
+#pragma unroll
+      for (int i = 1; i < NW; ++i) M = fmaxf(M, sh_a[cur][i][tid]);
+      const float ref = (M == -INFINITY) ? 0.0f : M;
       float L = 0.0f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (sm[i][tid] > -INFINITY) L += sl[i][tid] * expf(sm[i][tid] - M);
-      const size_t o = (size_t)blockIdx.x * RQ + (size_t)c * R + r0 + tid;
-      part[o] = make_float2(M, L);
+      for (int i = 0; i < NW; ++i) L += sh_b[cur][i][tid] * fast_exp2(sh_a[cur][i][tid] - ref);
+      part[(size_t)blockIdx.x * RQ + (size_t)c * R + ib * 32 + tid] = make_float2(M, L);
     }
   }
-}
-
-// Sweep 2: normalised weights summed over the g*w rows of the head, divided by g*w.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void raw_generic_kernel(
-    SeqTab st, ChunkTab ct, Dims dm, const T *__restrict__ q, const T *__restrict__ K,
-    const float *__restrict__ lse, float *__restrict__ raw) {
-  __shared__ float qs[ROW_TILE][D];
-  __shared__ float sl[ROW_TILE];
-  const int tid = threadIdx.x;
-  const int b = find_seq(ct, st.batch, blockIdx.x);
-  const int chunk = blockIdx.x - ct.off[b];
-  const int c = blockIdx.y;
-  const int n = st.n[b];
-  const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
-  const int j = chunk * GEN_CHUNK + tid;
-  const bool valid = j < n;
-  float k[D];
-  if (valid) {
-    load_row<T, D>(K + (st.tok_off[b] + j) * dm.k_stride_tok + c * dm.k_stride_head, k);
-  } else {
-#pragma unroll
-    for (int e = 0; e < D; ++e) k[e] = 0.0f;
-  }
-  const T *qhead = q + ((size_t)b * RQ + (size_t)c * R) * D;
-  float acc = 0.0f;
-  for (int r0 = 0; r0 < R; r0 += ROW_TILE) {
+  if (PASS == 2) {
+    total += __shfl_xor(total, 32);
+    const float raw = total * (1.0f / (float)R);
+    float *dst = out + st.score_off[b] + (size_t)c * n;
+    if (pool_r < 0) {
+      if (half == 0 && key < n) dst[key] = raw;
+      return;
+    }
+    // a key outside the sequence counts as weight 0, which never wins: its window is clipped
+    if (half == 0) sh_raw[wv * 32 + l32] = (key >= 0 && key < n) ? raw : 0.0f;
     __syncthreads();
-    stage_q<T, D>(qhead, r0, R, qs);
-    if (tid < ROW_TILE) sl[tid] = (r0 + tid < R) ? lse[(size_t)b * RQ + (size_t)c * R + r0 + tid] : 0.0f;
-    __syncthreads();
-    const int rt = min(ROW_TILE, R - r0);
-    for (int r = 0; r < rt; ++r) acc += expf(logit<D>(qs[r], k, dm.scale) - sl[r]);
+    if (tid < own && k0 + r + tid < n) {
+      float m = sh_raw[tid];
+      for (int t = 1; t <= 2 * r; ++t) m = fmaxf(m, sh_raw[tid + t]);
+      dst[k0 + r + tid] = m;
+    }
   }
-  if (valid) raw[st.score_off[b] + (size_t)c * n + j] = acc * (1.0f / (float)R);
 }
 
 // The other order of Alg. 2 l.4 (as printed there): every window row is max-pooled along the keys
@@ -224,9 +331,13 @@ __global__ __launch_bounds__(256) void pooled_generic_kernel(
 // lse[b][row] = log of the sum over the sequence's chunks of l * exp(m).  One wavefront per row:
 // the lanes stride over the chunks (independent loads), then the 64 partial (max, sum) pairs are
 // merged with shuffles.
+// LOG2: the partials' references are in the base-2 domain (rounded once instead of once more on the
+// way to natural logarithms); the result then is too, unless natural_out asks for the other.
+template <bool LOG2>
 __global__ __launch_bounds__(256) void lse_combine_kernel(SeqTab st, ChunkTab ct, int RQ,
                                                           const float2 *__restrict__ part,
-                                                          float *__restrict__ lse) {
+                                                          float *__restrict__ lse, int natural_out) {
+  auto ex = [](float x) { return LOG2 ? exp2f(x) : expf(x); };
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int b = blockIdx.y;
@@ -236,17 +347,20 @@ __global__ __launch_bounds__(256) void lse_combine_kernel(SeqTab st, ChunkTab ct
     const float2 ml = part[(size_t)k * RQ + row];
     const float m = ml.x, l = ml.y;
     const float nm = fmaxf(M, m);
-    if (nm > -INFINITY) L = L * expf(M - nm) + l * expf(m - nm);
+    if (nm > -INFINITY) L = L * ex(M - nm) + l * ex(m - nm);
     M = nm;
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     const float m2 = __shfl_xor(M, off), l2 = __shfl_xor(L, off);
     const float nm = fmaxf(M, m2);
-    if (nm > -INFINITY) L = L * expf(M - nm) + l2 * expf(m2 - nm);
+    if (nm > -INFINITY) L = L * ex(M - nm) + l2 * ex(m2 - nm);
     M = nm;
   }
-  if (lane == 0) lse[(size_t)b * RQ + row] = M + logf(L);
+  if (lane == 0) {
+    const float v = M + (LOG2 ? log2f(L) : logf(L));
+    lse[(size_t)b * RQ + row] = LOG2 && natural_out ? v * LN2 : v;
+  }
 }
 
 // scores[j] = max of raw over [j - k/2, j + k/2] clipped to the head's row (stride 1, same length).
@@ -267,13 +381,10 @@ __global__ __launch_bounds__(256) void pool_kernel(SeqTab st, ChunkTab ct, int p
   scores[base + j] = m;
 }
 
-ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma) {
+static ScorePlan plan_score_chunk(const SeqTab &st, const Dims &dm, int part_chunk) {
   ScorePlan p;
-  // partial statistics: one (max, sum) pair per window row and chunk of keys; the plain-FMA
-  // kernels cut a sequence into GEN_CHUNK keys, the matrix-core kernels into longer chunks
-  const bool mfma = on_mfma;
-  (void)dtype;
-  p.part_chunk = mfma ? choose_mfma_variant(st, dm).chunk : GEN_CHUNK;
+  // partial statistics: one (max, sum) pair per window row and chunk of keys
+  p.part_chunk = part_chunk;
   const size_t chunks = make_chunks(st, p.part_chunk).off[st.batch];
   const size_t RQ = (size_t)dm.h_q * dm.w;
   size_t o = 0;
@@ -284,10 +395,22 @@ ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma) 
   return p;
 }
 
+ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma) {
+  (void)dtype;
+  if (on_mfma) return plan_score_chunk(st, dm, choose_mfma_variant(st, dm).chunk);
+  // The fp32 kernels' partials are per 128 keys (workgroups of four wavefronts spread best), or per
+  // 256 keys where the smaller ones would not fit into the built-in scratch array any more: half the
+  // partials, and a sequence that long fills the chip with either.
+  const ScorePlan p = plan_score_chunk(st, dm, F32_KEYS);
+  const size_t spare = 1024;                           // what the callers add for alignment
+  if (p.total + plan_topk_bytes(st, dm) + spare <= (size_t)ADAKV_STATIC_SCRATCH_BYTES) return p;
+  return plan_score_chunk(st, dm, 2 * F32_KEYS);
+}
+
 void launch_lse_combine(const SeqTab &st, const ChunkTab &ct, int RQ, const float2 *part,
                         float *lse, hipStream_t s) {
-  ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel, dim3((RQ + 3) / 4, st.batch),
-               dim3(256), s, st, ct, RQ, part, lse);
+  ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel<false>, dim3((RQ + 3) / 4, st.batch),
+               dim3(256), s, st, ct, RQ, part, lse, 1);
 }
 
 void launch_pool(const SeqTab &st, const Dims &dm, const float *raw, float *scores,
@@ -297,19 +420,42 @@ void launch_pool(const SeqTab &st, const Dims &dm, const float *raw, float *scor
                dm.pool_k, raw, scores);
 }
 
+// The pool inside sweep 2 scores 2r keys of every 128 twice; a kernel of its own takes 4 us.  A
+// compute unit works through its workgroups at the rate of its matrix cores, so what the overlap
+// costs is the workgroups that the fullest compute unit gets more, each 32 rows x 32 keys x d in
+// every wavefront (4096 cycles = 1.8 us at d = 128) per row block.  8191 keys x 8 heads, 128 rows:
+// 544 workgroups fused (three on some of the 256 compute units) 34.2 us, 512 and a pool kernel
+// 24.3 + 4.1 us.
+bool f32_pool_fused(const SeqTab &st, const Dims &dm) {
+  const int r = dm.pool_k / 2;
+  if (r == 0 || r > F32_POOL_MAX) return r == 0;
+  const int most = (make_chunks(st, F32_KEYS - 2 * r).off[st.batch] * dm.h_kv + 255) / 256;
+  const int most_apart = (make_chunks(st, F32_KEYS).off[st.batch] * dm.h_kv + 255) / 256;
+  const int row_blocks = (dm.g * dm.w + 31) / 32;
+  return (most - most_apart) * row_blocks * 1.8f * dm.d / 128 <= 4.0f;
+}
+
 template <typename T, int D>
 static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const void *K,
                         const float *row_lse, float *scores, char *ws, const ScorePlan &pl,
                         bool pool_first, hipStream_t s) {
-  const ChunkTab ct = make_chunks(st, GEN_CHUNK);
-  dim3 grid(ct.off[st.batch], dm.h_kv), block(256);
+  const float c_log2 = dm.scale * LOG2E;
+  const dim3 block(256);
   float2 *part = (float2 *)(ws + pl.part);
   float *lse = (float *)(ws + pl.lse), *raw = (float *)(ws + pl.raw);
   const float *use_lse = row_lse;
   if (!row_lse) {
-    ADAKV_LAUNCH("score_stats_fma", (stats_generic_kernel<T, D>), grid, block, s, st, ct, dm,
-                 (const T *)q, (const T *)K, part);
-    launch_lse_combine(st, ct, dm.h_q * dm.w, part, lse, s);
+    const ChunkTab ct = make_chunks(st, pl.part_chunk);
+    const dim3 grid(ct.off[st.batch], dm.h_kv);
+    if (pl.part_chunk == F32_KEYS)
+      ADAKV_LAUNCH("score_stats_fma", (score_f32_kernel<T, D, 1, 4>), grid, block, s, st, ct, dm, c_log2, -1,
+                   0, (const T *)q, (const T *)K, (const float *)nullptr, part, (float *)nullptr);
+    else
+      ADAKV_LAUNCH("score_stats_fma", (score_f32_kernel<T, D, 1, 8>), grid, dim3(512), s, st, ct, dm, c_log2,
+                   -1, 0, (const T *)q, (const T *)K, (const float *)nullptr, part, (float *)nullptr);
+    const int RQ = dm.h_q * dm.w;
+    ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel<true>, dim3((RQ + 3) / 4, st.batch), block, s,
+                 st, ct, RQ, (const float2 *)part, lse, pool_first ? 1 : 0);
     use_lse = lse;
   }
   if (pool_first) {
@@ -318,9 +464,13 @@ static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const v
                  block, s, st, co, dm, (const T *)q, (const T *)K, use_lse, scores);
     return;
   }
-  ADAKV_LAUNCH("score_weights_fma", (raw_generic_kernel<T, D>), grid, block, s, st, ct, dm,
-               (const T *)q, (const T *)K, use_lse, raw);
-  launch_pool(st, dm, raw, scores, s);
+  const int r = dm.pool_k / 2;
+  const bool fused = f32_pool_fused(st, dm);
+  const ChunkTab ct = make_chunks(st, fused ? F32_KEYS - 2 * r : F32_KEYS);
+  ADAKV_LAUNCH("score_weights_fma", (score_f32_kernel<T, D, 2, 4>), dim3(ct.off[st.batch], dm.h_kv), block, s,
+               st, ct, dm, c_log2, fused ? r : -1, row_lse ? 1 : 0, (const T *)q, (const T *)K, use_lse,
+               (float2 *)nullptr, fused ? scores : raw);
+  if (!fused) launch_pool(st, dm, raw, scores, s);
 }
 
 hipError_t launch_score_generic(const SeqTab &st, const Dims &dm, int dtype, const void *q,
