@@ -338,7 +338,7 @@ size_t adakv_decode_workspace_bytes(const adakv_layer *L, int32_t headroom) {
   SeqTab st; Dims dm;
   if (build_tables(L, st, dm) != ADAKV_OK || check_headroom(st, dm, headroom) != ADAKV_OK) return 0;
   if (!decode_supported(dm)) return 0;
-  return plan_decode(st, dm, headroom).total + 256;
+  return plan_decode(st, dm, L->dtype, headroom).total + 256;
 }
 
 int adakv_decode_attn(const adakv_layer *L, const void *q_new, const int32_t *cu_seqlens,
@@ -352,7 +352,7 @@ int adakv_decode_attn(const adakv_layer *L, const void *q_new, const int32_t *cu
   if (!q_new || !cu_seqlens || !K_cache || !V_cache || !seg_len || !out) return ADAKV_EINVAL;
   if (!decode_supported(dm)) return ADAKV_EUNSUPPORTED;
   if (!aligned16(q_new) || !aligned16(K_cache) || !aligned16(V_cache)) return ADAKV_EUNSUPPORTED;
-  if (!ws || ws_bytes < plan_decode(st, dm, headroom).total + 256) return ADAKV_EWORKSPACE;
+  if (!ws || ws_bytes < plan_decode(st, dm, L->dtype, headroom).total + 256) return ADAKV_EWORKSPACE;
   char *wsp = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
   hipError_t e = launch_decode_attn(st, dm, L->dtype, headroom, q_new, nullptr, nullptr,
                                     cu_seqlens, (void *)K_cache, (void *)V_cache,
@@ -375,7 +375,7 @@ int adakv_decode_step(const adakv_layer *L, const void *q_new, const void *k_new
   if (!aligned16(q_new) || !aligned16(k_new) || !aligned16(v_new) || !aligned16(K_cache) ||
       !aligned16(V_cache))
     return ADAKV_EUNSUPPORTED;
-  if (!ws || ws_bytes < plan_decode(st, dm, headroom).total + 256) return ADAKV_EWORKSPACE;
+  if (!ws || ws_bytes < plan_decode(st, dm, L->dtype, headroom).total + 256) return ADAKV_EWORKSPACE;
   char *wsp = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
   hipError_t e = launch_decode_attn(st, dm, L->dtype, headroom, q_new, k_new, v_new, cu_seqlens,
                                     K_cache, V_cache, seg_len, overflow, out, lse, wsp,

@@ -133,7 +133,7 @@ struct DecodePlan {
   size_t seg_tab, total;            // per segment: first partial, partials, rows, appended
 };
 bool decode_supported(const Dims &dm);
-DecodePlan plan_decode(const SeqTab &st, const Dims &dm, int headroom);
+DecodePlan plan_decode(const SeqTab &st, const Dims &dm, int dtype, int headroom);
 // k_new == nullptr: attention only (cache and lengths are only read)
 hipError_t launch_decode_attn(const SeqTab &st, const Dims &dm, int dtype, int headroom,
                               const void *q, const void *k_new, const void *v_new, const int *cu,

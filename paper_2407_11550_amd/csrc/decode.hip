@@ -4,15 +4,17 @@
 // Layout: segment s = b*h_kv + c starts at row cu[s] + s*headroom of K_cache / V_cache and holds
 // seg_len[s] rows of ROWB = d*sizeof(T) bytes, so a segment is one contiguous byte range.
 //
-// Attention: HBM-bound (every cached K and V row is read once, 2*ROWB bytes for 4*g*d flops),
-// and with g <= 8 query rows per segment far too thin for the matrix cores, so the products
-// run on the vector ALUs.  A row is read by LPR = ROWB/16 neighbouring lanes, 16 bytes each:
+// Attention: HBM-bound (every cached K and V row is read once, 2*ROWB bytes for 4*g*d flops).
+// 16-bit caches run both products on the matrix cores (decode_mfma_kernel), fp32 caches on the
+// vector ALUs (decode_attn_kernel): there a row is read by LPR = ROWB/16 neighbouring lanes, 16 bytes each:
 // every load instruction of a wavefront fetches 64/LPR whole rows = 1 KB of consecutive memory.
 // Segment lengths live on the device, so the host launches an upper bound of workgroups
 // (capacity / split + segments); each workgroup finds its (segment, split) from a prefix sum of
 // the lengths, writes partial (max, sum, weighted value sum) per query head, and a second kernel
 // merges the splits of each segment.
 #include <math.h>
+
+#include <type_traits>
 
 #include "common.h"
 
@@ -44,28 +46,8 @@ __device__ __forceinline__ float row_sum(float x) {
   return x;
 }
 
+struct f16_t { unsigned short bits; };        // IEEE half: tag type (bf16: unsigned short)
 template <typename T> struct Elem;
-template <> struct Elem<unsigned short> {     // bf16: 8 elements per 16 bytes
-  static constexpr int EPL = 8;
-  static __device__ __forceinline__ void widen(u32x4 v, float (&f)[8]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f[2 * i] = __builtin_bit_cast(float, v[i] << 16);
-      f[2 * i + 1] = __builtin_bit_cast(float, v[i] & 0xffff0000u);
-    }
-  }
-};
-struct f16_t { unsigned short bits; };        // IEEE half: tag type, same size as the bf16 tag
-template <> struct Elem<f16_t> {
-  static constexpr int EPL = 8;
-  static __device__ __forceinline__ void widen(u32x4 v, float (&f)[8]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f[2 * i] = (float)__builtin_bit_cast(_Float16, (unsigned short)(v[i] & 0xFFFFu));
-      f[2 * i + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(v[i] >> 16));
-    }
-  }
-};
 template <> struct Elem<float> {
   static constexpr int EPL = 4;
   static __device__ __forceinline__ void widen(u32x4 v, float (&f)[4]) {
@@ -119,6 +101,31 @@ __device__ __forceinline__ int scan_blocks(int nseg, int per, int split, int hea
   return before + inc - mine;
 }
 
+// The thread whose run holds this workgroup's segment writes it to sh[16..20] (segment, split, rows,
+// first row, 1 if the last row is the one the call appends).  The merge kernel finds a segment's
+// partial results through seg_tab; the launch has at least one workgroup per segment, and workgroup
+// s files the entry of segment s.
+__device__ __forceinline__ void find_block(int excl, int nseg, int per, int split, int headroom, int grow,
+                                           const int *cu, const int *seg_len, int *sh, int4 *seg_tab) {
+  int first = excl;
+  for (int i = 0; i < per; ++i) {
+    const int s = threadIdx.x * per + i;
+    if (s >= nseg) break;
+    const int now = rows_held(cu, seg_len, s, headroom, grow);
+    const int appended = now - rows_held(cu, seg_len, s, headroom, 0);
+    const int nb = (now + split - 1) / split;
+    if ((int)blockIdx.x >= first && (int)blockIdx.x < first + nb) {
+      sh[16] = s;
+      sh[17] = (int)blockIdx.x - first;
+      sh[18] = now;
+      sh[19] = cu[s];
+      sh[20] = appended;
+    }
+    if (s == (int)blockIdx.x) seg_tab[s] = make_int4(first, nb, now, appended);
+    first += nb;
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Query heads one wavefront carries: at most four (queries and accumulators take 2*GW*EPL
 // registers).  A larger group is split over NGRP sets of four wavefronts that read the
@@ -158,27 +165,7 @@ __global__ __launch_bounds__((256 * HeadSplit<T, G>::NGRP)) void decode_attn_ker
   const int grow = k_new != nullptr ? 1 : 0;
   int total;
   const int excl = scan_blocks<NW * NGRP>(nseg, per, split, headroom, grow, cu, seg_len, sh_scan, &total);
-  {
-    int first = excl;
-    for (int i = 0; i < per; ++i) {
-      const int s = tid * per + i;
-      if (s >= nseg) break;
-      const int now = rows_held(cu, seg_len, s, headroom, grow);
-      const int nb = (now + split - 1) / split;
-      if ((int)blockIdx.x >= first && (int)blockIdx.x < first + nb) {
-        sh_scan[16] = s;
-        sh_scan[17] = (int)blockIdx.x - first;
-        sh_scan[18] = now;
-        sh_scan[19] = cu[s];
-        sh_scan[20] = now - rows_held(cu, seg_len, s, headroom, 0);  // 1: the last row is the new one
-      }
-      // the merge kernel finds a segment's partial results through this table; the launch has at
-      // least one workgroup per segment, and workgroup s files the entry of segment s
-      if (s == (int)blockIdx.x)
-        seg_tab[s] = make_int4(first, nb, now, now - rows_held(cu, seg_len, s, headroom, 0));
-      first += nb;
-    }
-  }
+  find_block(excl, nseg, per, split, headroom, grow, cu, seg_len, sh_scan, seg_tab);
   if ((int)blockIdx.x >= total) return;        // uniform: the launch is an upper bound
   __syncthreads();
   const int s = sh_scan[16], j = sh_scan[17], len = sh_scan[18];
@@ -311,6 +298,265 @@ __global__ __launch_bounds__((256 * HeadSplit<T, G>::NGRP)) void decode_attn_ker
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// 16-bit caches: both products on the matrix cores (v_mfma_f32_16x16x32), one wavefront per tile of
+// 32 rows, nothing staged through LDS and no data crossing lanes between the two products.
+//
+//   logits   D[row][head] = K Q^T: a lane loads 16-byte words of row l%16 (twice: 32 rows), and
+//            ends up with head l%16 and the rows 4 (l/16) + i and 16 + 4 (l/16) + i, i < 4.  The
+//            columns past the group repeat its heads.
+//   values   D[head][column] += P V: what a lane holds is its part of the P operand if the rows are
+//            numbered that way, so V is loaded in that numbering: a lane takes 8 rows x D/16
+//            columns and turns its own 8 x (D/16) block with byte permutes.
+//
+// P stays in 32 bits: it is cut into three 16-bit parts whose sum is P to 2^-24 (bf16: truncated to
+// 8, 8 and 8 bits; fp16: of P 2^15, so that what is small beside the maximum keeps its bits), and the
+// 16 rows of the P operand hold the parts side by side (the repeated heads).  For g = 8 the third
+// part goes through a product of its own.  Products of 16-bit values and their sums are exact in
+// fp32 up to the accumulation, as they were on the vector units.
+//
+// The vector form before this one (16 lanes per row, a dot product and two fused multiply-adds
+// per element and head) issued 130 instructions per four rows at g = 4 and 240 at g = 8, which
+// made it the bound from g = 8 on: a 134 MB cache at g = 8 took 77.2 us, now 29.8 (a plain
+// read of as much: 25); 49 MB at g = 4 19.2, now 12.9 (kernel times, launch included).
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+
+template <bool F16>
+__device__ __forceinline__ floatx4 mfma16(u32x4 a, u32x4 b, floatx4 c) {
+  if constexpr (F16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+template <bool F16> constexpr float P_SCALE = F16 ? 32768.0f : 1.0f;
+
+// The 16-bit value that x is cut to, back in 32 bits, where `on`; 0 elsewhere.
+template <bool F16> __device__ __forceinline__ float cut(float x, bool on) {
+  if constexpr (F16) return on ? (float)(_Float16)x : 0.0f;
+  else return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) & (on ? 0xffff0000u : 0u));
+}
+// x0 and x1 cut to 16 bits, x0 in the lower half of the word.
+template <bool F16> __device__ __forceinline__ unsigned pack(float x0, float x1) {
+  if constexpr (F16)
+    return (unsigned)__builtin_bit_cast(unsigned short, (_Float16)x0) |
+           ((unsigned)__builtin_bit_cast(unsigned short, (_Float16)x1) << 16);
+  else
+    return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, x1), __builtin_bit_cast(unsigned, x0), 0x07060302u);
+}
+
+template <bool F16, int D, int G>
+__global__ __launch_bounds__(256) void decode_mfma_kernel(
+    int nseg, int h, int per, int split, int headroom, float c_log2, const unsigned short *__restrict__ q,
+    const char *__restrict__ k_new, const char *__restrict__ v_new, const int *__restrict__ cu,
+    const int *__restrict__ seg_len, char *Kc, char *Vc, float *__restrict__ part_acc,
+    float *__restrict__ part_ml, int4 *__restrict__ seg_tab) {
+  constexpr int NW = 4;                        // wavefronts that share the rows of a split
+  constexpr int ROWB = D * 2;
+  constexpr int KS = D / 32;                   // k-steps of the logits
+  constexpr int VC = D / 16;                   // columns of V per lane
+  constexpr int TR = 32;                       // rows per tile
+  constexpr int PARTS = G == 8 ? 2 : 3;        // parts of P held side by side
+  constexpr bool THIRD = G == 8;               // the last part has accumulators of its own
+  typedef unsigned int vword __attribute__((ext_vector_type(VC / 2)));
+
+  __shared__ int sh_scan[24];                  // [0..15] the prefix sum's wavefront totals, [16..20] results
+  __shared__ __align__(16) float sh_acc[NW][PARTS * G][D];
+  __shared__ __align__(16) float sh_third[THIRD ? NW : 1][THIRD ? G : 1][THIRD ? D : 1];
+  __shared__ float sh_m[NW][G], sh_l[NW][G];
+
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // ---- which (segment, split) is this workgroup?  (as in decode_attn_kernel) --------------------
+  const int grow = k_new != nullptr ? 1 : 0;
+  int total;
+  const int excl = scan_blocks<NW>(nseg, per, split, headroom, grow, cu, seg_len, sh_scan, &total);
+  find_block(excl, nseg, per, split, headroom, grow, cu, seg_len, sh_scan, seg_tab);
+  if ((int)blockIdx.x >= total) return;        // uniform: the launch is an upper bound
+  __syncthreads();
+  const int s = __builtin_amdgcn_readfirstlane(sh_scan[16]), j0 = __builtin_amdgcn_readfirstlane(sh_scan[17]);
+  const int len = __builtin_amdgcn_readfirstlane(sh_scan[18]), cu_s = __builtin_amdgcn_readfirstlane(sh_scan[19]);
+  const int new_row = __builtin_amdgcn_readfirstlane(sh_scan[20]) ? len - 1 : -1;
+  const int r0 = j0 * split, r1 = min(len, r0 + split);
+  const long long seg_byte = ((long long)cu_s + (long long)s * headroom) * ROWB;
+  char *Kb = Kc + seg_byte;
+  char *Vb = Vc + seg_byte;
+  const char *kn = k_new + (long long)s * ROWB, *vn = v_new + (long long)s * ROWB;
+
+  u32x4 qf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    qf[ks] = *reinterpret_cast<const u32x4 *>(q + ((long long)s * G + l16 % G) * D + (4 * ks + lg) * 8);
+
+  float m = M_INIT, l = 0.0f;                  // of head l16 % G; m the same in all lanes of a head
+  floatx4 acc[VC], acc3[THIRD ? VC : 1];
+#pragma unroll
+  for (int e = 0; e < VC; ++e) acc[e] = floatx4{0};
+  if (THIRD) {
+#pragma unroll
+    for (int e = 0; e < VC; ++e) acc3[e] = floatx4{0};
+  }
+  const int part = l16 / G;                    // which part of P this lane's operand rows hold
+
+  for (int t0 = r0 + wv * TR; t0 < r1; t0 += NW * TR) {
+    u32x4 kk[2][KS];
+    vword vv[8];
+    const bool edge = t0 + TR > r1 || (new_row >= t0 && new_row < t0 + TR);
+    const char *kt = Kb + (long long)t0 * ROWB, *vt = Vb + (long long)t0 * ROWB;
+    const unsigned vcol = l16 * (VC * 2);
+    if (!edge) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          kk[t][ks] = *reinterpret_cast<const u32x4 *>(kt + (unsigned)((16 * t + l16) * ROWB + (4 * ks + lg) * 16));
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        vv[j] = *reinterpret_cast<const vword *>(vt + (unsigned)((16 * (j / 4) + 4 * lg + j % 4) * ROWB + vcol));
+    } else {
+      // rows past the end repeat the block's last one (and are masked); the appended row comes from
+      // k_new / v_new, its place in the cache is not written yet, and the lanes it falls to store it
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int r = t0 + 16 * t + l16, rr = min(r, r1 - 1);
+        const char *src = rr == new_row ? kn : Kb + (long long)rr * ROWB;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          kk[t][ks] = *reinterpret_cast<const u32x4 *>(src + (4 * ks + lg) * 16);
+          if (r == new_row) *reinterpret_cast<u32x4 *>(Kb + (long long)r * ROWB + (4 * ks + lg) * 16) = kk[t][ks];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int r = t0 + 16 * (j / 4) + 4 * lg + j % 4, rr = min(r, r1 - 1);
+        const char *src = rr == new_row ? vn : Vb + (long long)rr * ROWB;
+        vv[j] = *reinterpret_cast<const vword *>(src + vcol);
+        if (r == new_row) *reinterpret_cast<vword *>(Vb + (long long)r * ROWB + vcol) = vv[j];
+      }
+    }
+    float sc[8];                               // row t0 + 16 (j/4) + 4 lg + j%4, not scaled yet
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      // a sum of its own per k-step, then a tree: the rounding of a logit is what the result's error
+      // against 64 bits consists of (one chain of KS products: 1.3 times as much)
+      floatx4 a[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) a[ks] = mfma16<F16>(kk[t][ks], qf[ks], floatx4{0});
+#pragma unroll
+      for (int o = KS / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int ks = 0; ks < o; ++ks) a[ks] += a[ks + o];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sc[4 * t + i] = a[0][i];
+    }
+    if (edge) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (t0 + 16 * (j / 4) + 4 * lg + j % 4 >= r1) sc[j] = -INFINITY;
+    }
+    float top = sc[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) top = fmaxf(top, sc[j]);
+    top *= c_log2;
+    if (__any(top > m)) {                      // a new running maximum somewhere in the wavefront
+      top = fmaxf(top, __shfl_xor(top, 16));
+      top = fmaxf(top, __shfl_xor(top, 32));
+      const float mn = fmaxf(m, top);
+      const float corr = fast_exp2(m - mn);
+      l *= corr;
+      m = mn;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float ci = __shfl(corr, 4 * lg + i);   // accumulator row 4 lg + i: that lane's head
+#pragma unroll
+        for (int e = 0; e < VC; ++e) {
+          acc[e][i] *= ci;
+          if (THIRD) acc3[e][i] *= ci;
+        }
+      }
+    }
+    float p[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      p[j] = fast_exp2(fmaf(sc[j], c_log2, -m));
+      l += p[j];
+      p[j] *= P_SCALE<F16>;
+    }
+    u32x4 pa, pc;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float x0 = p[2 * k], x1 = p[2 * k + 1];
+      x0 -= cut<F16>(x0, part >= 1);
+      x1 -= cut<F16>(x1, part >= 1);
+      if (!THIRD) {
+        x0 -= cut<F16>(x0, part >= 2);
+        x1 -= cut<F16>(x1, part >= 2);
+      }
+      pa[k] = pack<F16>(x0, x1);
+      if (THIRD) {
+        float y0 = p[2 * k], y1 = p[2 * k + 1];
+        y0 -= cut<F16>(y0, true); y1 -= cut<F16>(y1, true);
+        y0 -= cut<F16>(y0, true); y1 -= cut<F16>(y1, true);
+        pc[k] = pack<F16>(y0, y1);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < VC; ++e) {
+      u32x4 vb;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        vb[k] = __builtin_amdgcn_perm(vv[2 * k + 1][e / 2], vv[2 * k][e / 2], (e & 1) ? 0x07060302u : 0x05040100u);
+      acc[e] = mfma16<F16>(pa, vb, acc[e]);
+      if (THIRD) acc3[e] = mfma16<F16>(pc, vb, acc3[e]);
+    }
+  }
+
+  // ---- the wavefronts' results meet in LDS -------------------------------------------------------
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (lane < G) { sh_m[wv][lane] = m; sh_l[wv][lane] = l; }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = 4 * lg + i;                // part * G + head
+#pragma unroll
+    for (int e = 0; e < VC; e += 4) {
+      if (row < PARTS * G)
+        *reinterpret_cast<float4 *>(&sh_acc[wv][row][l16 * VC + e]) =
+            make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
+      if (THIRD && row < G)
+        *reinterpret_cast<float4 *>(&sh_third[wv][row][l16 * VC + e]) =
+            make_float4(acc3[e][i], acc3[e + 1][i], acc3[e + 2][i], acc3[e + 3][i]);
+    }
+  }
+  __syncthreads();
+  for (int t = tid; t < G * D; t += 64 * NW) {
+    const int gi = t / D, e = t % D;
+    float M = sh_m[0][gi];
+#pragma unroll
+    for (int w2 = 1; w2 < NW; ++w2) M = fmaxf(M, sh_m[w2][gi]);
+    float a = 0.0f, ll = 0.0f;
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2) {
+      const float f = fast_exp2(sh_m[w2][gi] - M);
+      // an infinite value row makes the first part's sum infinite and 0 * inf = NaN of the others
+      const float first = sh_acc[w2][gi][e];
+      float rest = sh_acc[w2][G + gi][e];
+      rest += THIRD ? sh_third[w2][gi][e] : sh_acc[w2][2 * G + gi][e];
+      const float x = first + (__builtin_fabsf(first) < INFINITY ? rest : 0.0f);
+      a = fmaf(x * (1.0f / P_SCALE<F16>), f, a);
+      ll = fmaf(sh_l[w2][gi], f, ll);
+    }
+    part_acc[((long long)blockIdx.x * G + gi) * D + e] = a;
+    if (e == 0) {
+      part_ml[((long long)blockIdx.x * G + gi) * 2] = M;
+      part_ml[((long long)blockIdx.x * G + gi) * 2 + 1] = ll;
+    }
+  }
+}
+
 // One workgroup per (segment, query head of its group) merges that segment's splits and
 // normalises.  A long segment has hundreds of splits, so they are merged NSLOT side by side
 // (each by D/4 lanes holding a float4 of the value sum), four loads deep, then across slots.
@@ -410,11 +656,17 @@ void run_decode(const SeqTab &st, const Dims &dm, int headroom, const DecodePlan
   float *part_acc = (float *)(ws + pl.part_acc);
   float *part_ml = (float *)(ws + pl.part_ml);
   int4 *seg_tab = (int4 *)(ws + pl.seg_tab);
-  ADAKV_LAUNCH("decode_attn", (decode_attn_kernel<T, D, G>), dim3(pl.nblk),
-               dim3(256 * HeadSplit<T, G>::NGRP), s, nseg,
-               dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E, (const T *)q,
-               (const char *)k_new, (const char *)v_new, cu, (const int *)seg_len, (char *)Kc,
-               (char *)Vc, part_acc, part_ml, seg_tab);
+  if constexpr (sizeof(T) == 4)
+    ADAKV_LAUNCH("decode_attn", (decode_attn_kernel<T, D, G>), dim3(pl.nblk),
+                 dim3(256 * HeadSplit<T, G>::NGRP), s, nseg,
+                 dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E, (const T *)q,
+                 (const char *)k_new, (const char *)v_new, cu, (const int *)seg_len, (char *)Kc,
+                 (char *)Vc, part_acc, part_ml, seg_tab);
+  else
+    ADAKV_LAUNCH("decode_attn", (decode_mfma_kernel<std::is_same<T, f16_t>::value, D, G>), dim3(pl.nblk),
+                 dim3(256), s, nseg, dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E,
+                 (const unsigned short *)q, (const char *)k_new, (const char *)v_new, cu,
+                 (const int *)seg_len, (char *)Kc, (char *)Vc, part_acc, part_ml, seg_tab);
   // only a call that appends hands the lengths to the merge kernel for updating
   ADAKV_LAUNCH("decode_combine", (decode_combine_kernel<D, G>), dim3(nseg, G), dim3(1024), s,
                (const int4 *)seg_tab, k_new ? seg_len : nullptr, overflow, (const float *)part_acc,
@@ -452,18 +704,24 @@ bool decode_supported(const Dims &dm) {
   return (dm.g == 1 || dm.g == 2 || dm.g == 4 || dm.g == 8) && (dm.d == 64 || dm.d == 128);
 }
 
-DecodePlan plan_decode(const SeqTab &st, const Dims &dm, int headroom) {
+DecodePlan plan_decode(const SeqTab &st, const Dims &dm, int dtype, int headroom) {
   DecodePlan pl;
   const long long nseg = (long long)st.batch * dm.h_kv;
   const long long cap = (long long)st.out_off[st.batch] + nseg * headroom;
-  // Rows per workgroup.  Three workgroups fit on a compute unit, 768 on the chip: the split is
-  // the multiple of 64 rows (one load round of a workgroup) that fills one such resident round,
-  // so that all workgroups start together and none is left for a thin second round.
-  constexpr long long ROUND_WGS = 752;                       // a little under the 768 resident at once
-  const long long room = ROUND_WGS - nseg;                   // the segments' last, partial splits
+  // Rows per workgroup: what fills one resident round, so that all workgroups start together and
+  // none is left for a thin second round.  Three workgroups fit on a compute unit (768 on the
+  // chip), two of the 16-bit kernel for g = 8 at d = 128, whose third part of P takes 32 more
+  // registers (134 MB cache: 35.2 us with 500 workgroups, 41.0 with 752, 39.7 with 1500; at g = 4,
+  // 49 MB: 17.6, 16.2, 18.2).  The split is a multiple of one round of the workgroup's loads: 128
+  // rows in the 16-bit kernels, four wavefronts of 32 (16.2 us against 17.2 with multiples of 64),
+  // 64 rows in the fp32 kernel and for caches so small that there are workgroups to spare.
+  const bool mfma = dtype != ADAKV_FP32;
+  const long long round_wgs = mfma && dm.g == 8 && dm.d == 128 ? 500 : 752;
+  const long long room = round_wgs - nseg;                   // the segments' last, partial splits
   long long want = room > 64 ? (cap + room - 1) / room : cap / 512;
   if (want < 64) want = 64;
-  const int split = (int)((want + 63) / 64 * 64);
+  const int unit = mfma && want > 64 ? 128 : 64;
+  const int split = (int)((want + unit - 1) / unit * unit);
   pl.split = split;
   pl.nblk = (int)(cap / split + nseg);          // >= sum over segments of ceil(len / split)
   pl.part_acc = 0;
@@ -477,7 +735,7 @@ hipError_t launch_decode_attn(const SeqTab &st, const Dims &dm, int dtype, int h
                               const void *q, const void *k_new, const void *v_new, const int *cu,
                               void *Kc, void *Vc, int *seg_len, int *overflow, float *out,
                               float *lse, char *ws, hipStream_t s) {
-  const DecodePlan pl = plan_decode(st, dm, headroom);
+  const DecodePlan pl = plan_decode(st, dm, dtype, headroom);
   const DecodeArgs a = {q, k_new, v_new, cu, Kc, Vc, seg_len, overflow, out, lse, ws};
   bool ok;
   if (dtype == ADAKV_BF16) {

@@ -1,0 +1,72 @@
+"""Decode attention on 16-bit caches at the edges of its split: tiles of 32 rows, four wavefronts of
+one tile each per round, workgroups of 64 rows or a multiple of 128, an appended row in the last
+place of a tile or the first of a new one; and values at the ends of the types' ranges."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_11550_amd as adakv
+from oracle import decode_oracle as D
+from paper_2407_11550_amd import synth
+
+from parity_util import to_f64
+from test_gpu_decode import _assert_decode_close
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+LENGTHS = [1, 2, 15, 16, 31, 32, 33, 63, 64, 65, 95, 127, 128, 129, 192, 193]
+
+
+def _cache(dt, d, g, lengths, headroom, seed):
+    h, w = len(lengths), 1
+    n = max(lengths) + 7
+    wl = synth.small_workload(g * h, h, d, w, 7, [n], [sum(lengths)], dtype=dt, seed=seed)
+    Kc, Vc, cu, lens = synth.ragged_cache(wl, [v - w for v in lengths], headroom, seed=seed, device=DEV)
+    for s in range(h):                                   # spare rows must never be read
+        a = int(cu[s + 1]) + s * headroom
+        Kc[a:a + headroom] = float("nan")
+        Vc[a:a + headroom] = float("nan")
+    return wl, adakv.Layer.from_workload(wl), Kc, Vc, cu, lens
+
+
+@pytest.mark.parametrize("g", [1, 2, 4, 8])
+@pytest.mark.parametrize("dt,d", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float16, 128), (torch.float16, 64)])
+@pytest.mark.parametrize("longer", [0, 9000], ids=["rows64", "rows128"])   # 9000 more rows per segment: longer splits
+def test_decode_step_at_tile_edges(dt, d, g, longer):
+    print("decode tiles", dt, d, g, longer, flush=True)
+    lengths = [v + longer for v in LENGTHS]
+    hr = 2
+    wl, layer, Kc, Vc, cu, lens = _cache(dt, d, g, lengths, hr, seed=40 + g)
+    q, kn, vn = synth.decode_inputs(wl, 2, seed=g, device=DEV)
+    oK, oV = to_f64(Kc), to_f64(Vc)
+    olen, cuh = lens.cpu().numpy().astype(np.int64), cu.cpu().numpy()
+    vmax = float(torch.nan_to_num(Vc.float(), nan=0.0).abs().max())
+    for t in range(2):
+        out, lse = adakv.decode_step(layer, q[t], kn[t], vn[t], cu, hr, Kc, Vc, lens, want_lse=True)
+        torch.cuda.synchronize()
+        D.append(oK, oV, cuh, hr, olen, to_f64(kn[t]).reshape(-1, d), to_f64(vn[t]).reshape(-1, d))
+        assert np.array_equal(lens.cpu().numpy(), olen)
+        ref_out, ref_lse = D.decode_attention(to_f64(q[t]), oK, oV, cuh, hr, olen, wl.g)
+        _assert_decode_close(out, lse, ref_out, ref_lse, vmax, f"step {t}")
+        assert np.array_equal(to_f64(Kc), oK, equal_nan=True) and np.array_equal(to_f64(Vc), oV, equal_nan=True)
+
+
+@pytest.mark.parametrize("g", [4, 8])
+@pytest.mark.parametrize("dt,tiny", [(torch.float16, 2.0 ** -18), (torch.bfloat16, 2.0 ** -100)], ids=["fp16", "bf16"])
+def test_decode_values_at_the_ends_of_the_range(dt, tiny, g):
+    """fp16 values below the normal range keep their bits, and an infinite value row gives the
+    infinity (not the NaN that 0 * inf of a cut weight would make)."""
+    print("decode range", dt, g, flush=True)
+    wl, layer, Kc, Vc, cu, lens = _cache(dt, 128, g, [300, 77], 1, seed=3)
+    q, _, _ = synth.decode_inputs(wl, 1, seed=3, device=DEV)
+    Vt = (Vc.float() * tiny).to(dt)
+    out = adakv.decode_attn(layer, q[0], cu, 1, Kc, Vt, lens)
+    ref, _ = D.decode_attention(to_f64(q[0]), to_f64(Kc), to_f64(Vt), cu.cpu().numpy(), 1, lens.cpu().numpy(), g)
+    _assert_decode_close(out / tiny, None, ref / tiny, None, float(torch.nan_to_num(Vc.float(), nan=0.0).abs().max()), "tiny")
+    Vi = Vc.clone()
+    Vi[5, 17] = float("inf")
+    Vi[6, 18] = float("-inf")
+    got = adakv.decode_attn(layer, q[0], cu, 1, Kc, Vi, lens)[0, :g].cpu()
+    assert torch.all(got[:, 17] == float("inf")) and torch.all(got[:, 18] == float("-inf"))
+    keep = [e for e in range(128) if e not in (17, 18)]
+    assert torch.isfinite(got[:, keep]).all()
