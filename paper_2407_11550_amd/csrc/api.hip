@@ -277,8 +277,10 @@ int adakv_compress(const adakv_layer *L, const void *q_window, const void *K, co
   adakv_layer P = *L;
   P.flags |= ADAKV_FLAG_PIPELINE;
   if ((rc = adakv_score(&P, q_window, K, row_lse, scores, ws, ws_bytes, hip_stream)) != ADAKV_OK) return rc;
-  if ((rc = adakv_allocate(&P, scores, budgets, cu_seqlens, ws, ws_bytes, hip_stream)) != ADAKV_OK) return rc;
-  if ((rc = adakv_select(&P, scores, budgets, cu_seqlens, indices, ws, ws_bytes, hip_stream)) != ADAKV_OK) return rc;
+  char *wsp = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
+  if (launch_topk(st, dm, scores, budgets, cu_seqlens, indices, wsp + topk_offset(st, dm, &P),
+                  pipeline_mode(&P, dm), (hipStream_t)hip_stream) != hipSuccess)
+    return ADAKV_EHIP;
   return adakv_compact(&P, K, V, indices, cu_seqlens, K_out, V_out, hip_stream);
 }
 

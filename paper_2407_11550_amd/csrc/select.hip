@@ -10,7 +10,8 @@
 // key's bits 31..21, 20..10 and 9..0.  Each scope runs two kernels (a kernel boundary is the
 // cheapest device-wide synchronisation on this part; a device-scope fence inside a kernel writes
 // a whole L2 back), so the whole Top-k is four launches after the first-digit histograms, which
-// the scoring kernel leaves behind in pipeline mode (two small kernels make them otherwise):
+// the scoring kernel leaves behind in pipeline mode (two small kernels make them otherwise).  Short
+// rows run a scope, or both, inside one block per sequence or segment instead (below):
 //
 //   gather   every block of 4096 positions finds the first digit d0 of its scope's threshold from
 //            the finished first-digit histogram, adds the second digits of its elements under d0
@@ -84,6 +85,21 @@ struct TopkBufs {
   unsigned short *entries;   // last digits (10 bits each)
 };
 
+// Inclusive prefix sum over the 64 lanes of a wavefront, all of them active: data-parallel-primitive
+// adds inside the vector unit (six of them; through the LDS crossbar every step waits some 100 cycles).
+__device__ __forceinline__ int wave_scan_incl(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1 (rows of 16 lanes)
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);      // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);      // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);      // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+  return x;
+}
+__device__ __forceinline__ int wave_sum(int x) {       // the same in all lanes
+  return __builtin_amdgcn_readlane(wave_scan_incl(x), 63);
+}
+
 // This thread's NB/256 consecutive bins of a finished histogram, as 16-byte loads.  Kept apart
 // from locate() so that callers can issue these loads together with everything else they need
 // from memory (one round trip instead of a chain of them).
@@ -116,17 +132,13 @@ __device__ __forceinline__ void locate(const Bins<NB> &mine, int krem, unsigned 
   unsigned s = 0;
 #pragma unroll
   for (int i = 0; i < PER; ++i) s += mine.v[i];
-  unsigned suf = s;                                    // sum over lanes >= this one
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned v = __shfl_down(suf, off);
-    if (lane + off < 64) suf += v;
-  }
+  const unsigned upto = (unsigned)wave_scan_incl((int)s);                      // lanes up to this one
+  const unsigned all = (unsigned)__builtin_amdgcn_readlane((int)upto, 63);
   __syncthreads();                                     // sh may be in use by the caller
-  if (lane == 0 && wv < 4) sh[wv] = suf;
+  if (lane == 0 && wv < 4) sh[wv] = all;
   if (tid == 0) { sh[4] = 0u; sh[5] = (unsigned)krem; }   // fallback keeps later reads in bounds
   __syncthreads();
-  unsigned above = suf - s;                            // elements in bins owned by higher threads
+  unsigned above = all - upto;                         // elements in bins owned by higher threads
   for (int i = wv + 1; i < 4; ++i) above += sh[i];
   if (tid < 256 && above < (unsigned)krem && (unsigned)krem <= above + s) {
     unsigned acc = above;
@@ -232,8 +244,7 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SeqTab st, ChunkTab ct
     if (in && dg == d0) atomicAdd(&lh[(key >> 10) & 2047u], 1u);
     above += in && dg > d0;
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) above += __shfl_xor(above, off);
+  above = wave_sum(above);
   if (lane == 0) atomicAdd(&sh_above, above);
   __syncthreads();
   // bucket starts, largest digit first is not needed: buckets are addressed by digit.  Thread t
@@ -242,12 +253,7 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SeqTab st, ChunkTab ct
   unsigned tsum = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) { cnt[i] = lh[tid * 8 + i]; tsum += cnt[i]; }
-  unsigned inc = tsum;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned v = __shfl_up(inc, off);
-    if (lane >= off) inc += v;
-  }
+  const unsigned inc = (unsigned)wave_scan_incl((int)tsum);
   if (lane == 63) sh_wave[wv] = (int)inc;
   __syncthreads();
   unsigned base = inc - tsum;
@@ -297,12 +303,7 @@ __device__ __forceinline__ void bucket_of(const TopkBufs &tb, size_t blk, unsign
 template <int NT>
 __device__ __forceinline__ int block_scan_incl(int v, int &incl, int *sh /*[NT/64]*/) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int u = __shfl_up(x, off);
-    if (lane >= off) x += u;
-  }
+  const int x = wave_scan_incl(v);
   __syncthreads();
   if (lane == 63) sh[wv] = x;
   __syncthreads();
@@ -419,21 +420,24 @@ __device__ __forceinline__ void locate_last(const unsigned *lh2, int r1, unsigne
   locate<1024>(m, r1, d2, ties, sh);
 }
 
-// Layer scope, second kernel: Algorithm 1's counts f_c and the safeguard of Alg. 2 l.8.
-// One block of sixteen wavefronts per sequence.
-constexpr int FIN_NT = 1024;
-__global__ __launch_bounds__(FIN_NT) void alloc_finish_kernel(SeqTab st, ChunkTab ct, int h, int w,
-                                                              int alpha_fix, TopkBufs tb,
-                                                              int *__restrict__ budgets,
-                                                              int *__restrict__ cu) {
-  __shared__ unsigned sh[8];
-  __shared__ int sh_scan[FIN_NT / 64];
-  __shared__ unsigned lh2[1024];
-  __shared__ unsigned held[HOLD_LAYER];                // (last digit << 6) | head
-  __shared__ int sh_gt[64], sh_eq[64];
+// What a block that knows a sequence's whole layer scope holds in LDS: per head the elements above
+// the layer's threshold and at it, then the budgets.
+constexpr int FIN_NT = 1024;                           // sixteen wavefronts
+struct LayerCounts {
+  int gt[64], eq[64];
+  long long rem[64];
+  int base[64];                                        // the budgets, when safeguard() is done
+};
+
+// Layer scope from the gather kernel's results, by a block of sixteen wavefronts: Algorithm 1's
+// counts.  Returns the number of threshold-valued elements to take, in flat order.
+// scratch: 1024 + HOLD_LAYER words of LDS.
+__device__ __forceinline__ int layer_counts(const ChunkTab &ct, int h, int b, int Bp, const TopkBufs &tb,
+                                            LayerCounts &lc, unsigned *sh, int *sh_scan,
+                                            unsigned *scratch) {
+  unsigned *lh2 = scratch, *held = scratch + 1024;     // held: (last digit << 6) | head
+  int *sh_gt = lc.gt, *sh_eq = lc.eq;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int b = blockIdx.x;
-  const int Bp = st.Bp[b];
   if (tid < 64) { sh_gt[tid] = 0; sh_eq[tid] = 0; }
   for (int i = tid; i < 1024; i += FIN_NT) lh2[i] = 0u;
   const Bins<RADIX_BINS> m0 = load_bins<RADIX_BINS>(tb.hist_tot0 + (size_t)b * RADIX_BINS);
@@ -505,19 +509,26 @@ __global__ __launch_bounds__(FIN_NT) void alloc_finish_kernel(SeqTab st, ChunkTa
         CountAbove ca(d2);
         for_bucket(tb.entries + (size_t)k * ENT_PER_BLOCK, first, count, ca);
         int gt = ca.gt, eq = ca.eq;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) { gt += __shfl_xor(gt, off); eq += __shfl_xor(eq, off); }
+        gt = wave_sum(gt);
+        eq = wave_sum(eq);
         if (lane == 0) { atomicAdd(&sh_gt[k % h], gt); atomicAdd(&sh_eq[k % h], eq); }
       }
     }
   }
   __syncthreads();
-  // One lane per head (h <= 64): every step below is a count over the other heads, so the lanes
-  // never wait for each other and the 64-bit divisions run side by side.
-  if (tid >= 64) return;
-  __shared__ long long sh_rem[64];
-  __shared__ int sh_base[64];
-  const int c = tid;
+  return ties;
+}
+
+// The safeguard of Alg. 2 l.8 on the counts, by the first wavefront of a block (the others pass
+// through; a barrier makes the budgets in lc.base visible to them).  One lane per head (h <= 64):
+// every step is a count over the other heads, so the lanes never wait for each other and the 64-bit
+// divisions run side by side.
+__device__ __forceinline__ void safeguard(int h, int Bp, int alpha_fix, int ties, LayerCounts &lc) {
+  if (threadIdx.x >= 64) return;
+  const int *sh_gt = lc.gt, *sh_eq = lc.eq;
+  long long *sh_rem = lc.rem;
+  int *sh_base = lc.base;
+  const int c = threadIdx.x;
   const bool live = c < h;
   const long long one = 65536, a = alpha_fix;
   long long rem = -1;
@@ -551,18 +562,37 @@ __global__ __launch_bounds__(FIN_NT) void alloc_finish_kernel(SeqTab st, ChunkTa
   }
   const int left = (int)((long long)Bp - given);       // 0 <= left < h
   if (rank < left) base += 1;                          // largest remainders, ties to the lower head
-  budgets[b * h + c] = base;
-  sh_base[c] = base;
+  // (every lane has read the others' floors before any of them is replaced: one wavefront, and the
+  // fence below keeps the order)
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  sh_base[c] = base;
+}
+
+// Layer scope, second kernel.  One block per sequence.
+__global__ __launch_bounds__(FIN_NT) void alloc_finish_kernel(SeqTab st, ChunkTab ct, int h, int w,
+                                                              int alpha_fix, TopkBufs tb,
+                                                              int *__restrict__ budgets,
+                                                              int *__restrict__ cu) {
+  __shared__ unsigned sh[8];
+  __shared__ int sh_scan[FIN_NT / 64];
+  __shared__ unsigned scratch[1024 + HOLD_LAYER];
+  __shared__ LayerCounts lc;
+  const int b = blockIdx.x, c = threadIdx.x;
+  const int Bp = st.Bp[b];
+  const int ties = layer_counts(ct, h, b, Bp, tb, lc, sh, sh_scan, scratch);
+  safeguard(h, Bp, alpha_fix, ties, lc);
+  __syncthreads();
+  if (c >= h) return;
+  budgets[b * h + c] = lc.base[c];
   int run = st.out_off[b];
-  for (int i = 0; i <= c; ++i) run += sh_base[i] + w;
+  for (int i = 0; i <= c; ++i) run += lc.base[i] + w;
   if (b == 0 && c == 0) cu[0] = 0;
   cu[b * h + c + 1] = run;
 }
 
-constexpr int EPT = SEL_CHUNK / 256;   // consecutive positions per thread in the emit kernel
+constexpr int EPT = SEL_CHUNK / 256;   // positions per thread in the emit kernel, 256 apart
 
 // Head scope, second kernel.  Block (chunk, head) writes the kept positions of its 4096.
 __global__ __launch_bounds__(256) void emit_write_kernel(
@@ -571,6 +601,7 @@ __global__ __launch_bounds__(256) void emit_write_kernel(
     int rows_total) {
   __shared__ unsigned sh[8];
   __shared__ int sh_scan[4];
+  __shared__ int tab[EPT * 4];                         // per round and wavefront: above << 16 | at the threshold
   __shared__ unsigned lh2[1024];
   __shared__ unsigned held[HOLD_HEAD];                 // (last digit << 1) | (lies in an earlier block)
   __shared__ int sh_cnt[2];
@@ -586,11 +617,14 @@ __global__ __launch_bounds__(256) void emit_write_kernel(
   const int bud = budgets[seg];
   const float *row = scores + soff + (size_t)c * n;
 
-  // this thread's 16 consecutive positions (loads issued before the scans below)
-  const int j0 = chunk * SEL_CHUNK + tid * EPT;
+  // Positions are dealt out round by round (chunk start + 256 i + tid): the loads are whole lines, and
+  // position order is round, wavefront, lane, where a ballot gives every lane its place.  (16
+  // consecutive positions per thread, as before, made every load instruction touch 64 lines.)  Issued
+  // before the scans below; places past the end get key 0, which is never above or at a threshold.
+  const int j0 = chunk * SEL_CHUNK + tid;
   unsigned keys[EPT];
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) keys[i] = (j0 + i < n) ? key_of(row[j0 + i]) : 0u;
+  for (int i = 0; i < EPT; ++i) keys[i] = __float_as_uint(row[min(j0 + 256 * i, n - 1)]);
   const Bins<RADIX_BINS> m0 = load_bins<RADIX_BINS>(tb.hist0 + (size_t)seg * RADIX_BINS);
   const Bins<RADIX_BINS> m1 = load_bins<RADIX_BINS>(tb.hist1 + (size_t)seg * RADIX_BINS);
   for (int i = tid; i < 1024; i += 256) lh2[i] = 0u;
@@ -672,37 +706,295 @@ __global__ __launch_bounds__(256) void emit_write_kernel(
       pe += ca.eq;
     }
     thr = (d0 << 21) | (d1 << 10) | d2;
+    if (thr == 0u) ties = 0;                           // (no key of a score: inconsistent input)
+  }
+  __syncthreads();
+  pg = wave_sum(pg);
+  pe = wave_sum(pe);
+  if (lane == 0) { atomicAdd(&sh_cnt[0], pg); atomicAdd(&sh_cnt[1], pe); }
+
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const unsigned key = key_of(__uint_as_float(keys[i]));
+    keys[i] = j0 + 256 * i < n ? key : 0u;
+    const int g = __popcll(__ballot(keys[i] > thr)), e = __popcll(__ballot(keys[i] == thr));
+    if (lane == 0) tab[i * 4 + wv] = (g << 16) | e;    // (a block holds 4096 positions: 13 bits each)
+  }
+  __syncthreads();
+  if (wv == 0) {
+    const int v = tab[lane];
+    tab[lane] = wave_scan_incl(v) - v;
   }
   __syncthreads();
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) { pg += __shfl_xor(pg, off); pe += __shfl_xor(pe, off); }
-  if (lane == 0) { atomicAdd(&sh_cnt[0], pg); atomicAdd(&sh_cnt[1], pe); }
-
-  int g = 0, e = 0;
-#pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const bool valid = j0 + i < n;
-    g += valid && keys[i] > thr;
-    e += valid && keys[i] == thr;
-  }
-  // both counts in one scan (a block holds 4096 positions: 13 bits each)
-  int ige;
-  block_scan_incl<256>((g << 16) | e, ige, sh_scan);   // its barriers also publish sh_cnt
-  int ng = sh_cnt[0] + (ige >> 16) - g, ne = sh_cnt[1] + (ige & 0xFFFF) - e;   // over all earlier positions of the head
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const int j = j0 + i;
-    if (j >= n) break;
-    const bool isg = keys[i] > thr, ise = keys[i] == thr;
+    const unsigned long long bg = __ballot(keys[i] > thr), be = __ballot(keys[i] == thr);
+    if ((bg | be) == 0) continue;
+    // over all earlier positions of the head
+    const int ng = sh_cnt[0] + (tab[i * 4 + wv] >> 16) +
+                   (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bg >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bg, 0u));
+    const int ne = sh_cnt[1] + (tab[i * 4 + wv] & 0xFFFF) +
+                   (int)__builtin_amdgcn_mbcnt_hi((unsigned)(be >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)be, 0u));
     const int pos = out0 + ng + min(ne, ties);
-    if ((isg || (ise && ne < ties)) && (unsigned)pos < (unsigned)rows_total) indices[pos] = j;
-    ng += isg;
-    ne += ise;
+    if ((keys[i] > thr || (keys[i] == thr && ne < ties)) && (unsigned)pos < (unsigned)rows_total)
+      indices[pos] = j0 + 256 * i;
   }
   if (chunk == 0) {
     for (int rr = tid; rr < w; rr += 256)
       if ((unsigned)(out0 + bud + rr) < (unsigned)rows_total) indices[out0 + bud + rr] = n + rr;
   }
+}
+
+// ---- short rows: a whole scope inside one block --------------------------------------------------
+//
+// A kernel boundary costs 4 us here and every dependent trip to memory 2 us, whatever a kernel
+// computes, so where a block of 1024 threads can hold all scores of a scope in registers (16 per
+// thread) it finds the threshold without leaving LDS: second and last digits are counted in two
+// passes over the registers, the first ones are the scoring kernel's (CARRIED) or counted likewise.
+// Elements are dealt out round by round (element 1024 i +
+// tid), so a wavefront's 64 are neighbours: position order is round, wavefront, lane, and a
+// ballot per round gives a lane its place.  Bound by latency: one load of the scores (4 bytes per
+// lane, all rounds in flight), three searches of a histogram, one scan.
+constexpr int BLK_NT = 1024, BLK_WV = BLK_NT / 64;
+
+template <int NB> __device__ __forceinline__ Bins<NB> lds_bins(const unsigned *lh) {
+  Bins<NB> m;
+  const int t = threadIdx.x & 255;
+  const unsigned keep = threadIdx.x < 256 ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+  for (int i = 0; i < NB / 256; ++i) m.v[i] = lh[t * (NB / 256) + i] & keep;
+  return m;
+}
+
+// Rounds past the last element are skipped (uniformly); places past it get key 0, which no score has
+// (a score is neither negative nor a NaN) and which is never above or at a threshold.
+template <int EPT>
+__device__ __forceinline__ void load_keys(const float *__restrict__ row, int n, unsigned (&keys)[EPT]) {
+  float x[EPT];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    x[i] = 0.0f;
+    if (i * BLK_NT < n) x[i] = row[min(i * BLK_NT + (int)threadIdx.x, n - 1)];
+  }
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) keys[i] = i * BLK_NT + (int)threadIdx.x < n ? key_of(x[i]) : 0u;
+}
+
+// Counts a digit per lane where `on`.  64 atomics on one LDS word run one after the other, and equal
+// scores (plateaus, repeated keys) stand side by side, so the lanes that agree with the first one
+// count once.
+__device__ __forceinline__ void count_digit(unsigned *bins, unsigned digit, bool on) {
+  const unsigned long long act = __ballot(on);
+  if (act == 0) return;
+  const int leader = __ffsll((long long)act) - 1;
+  const unsigned dl = (unsigned)__builtin_amdgcn_readlane((int)digit, leader);
+  const unsigned long long same = __ballot(on && digit == dl);
+  if ((int)(threadIdx.x & 63) == leader) atomicAdd(&bins[dl], (unsigned)__popcll(same));
+  else if (on && digit != dl) atomicAdd(&bins[digit], 1u);
+}
+
+constexpr int BLK_LDS = RADIX_BINS + 1024 + RADIX_BINS;   // second, last and first digits
+
+// The key of rank krem >= 1 among the n keys of the block, and how many equal to it are taken.
+// `first`: the scope's finished first-digit histogram (CARRIED).
+template <int EPT, bool CARRIED>
+__device__ __forceinline__ void block_threshold(const unsigned (&keys)[EPT], int n, int krem,
+                                                const Bins<RADIX_BINS> &first, unsigned *lds,
+                                                unsigned *sh, unsigned &thr, int &ties) {
+  const int tid = threadIdx.x;
+  unsigned d0, d1, d2;
+  int r0, r1;
+  __syncthreads();                                     // the caller may still use lds
+  for (int i = tid; i < BLK_LDS; i += BLK_NT) lds[i] = 0u;
+  if (CARRIED) {
+    locate<RADIX_BINS>(first, krem, d0, r0, sh);       // its barriers also publish the cleared bins
+  } else {
+    __syncthreads();
+    unsigned *lh0 = lds + RADIX_BINS + 1024;
+#pragma unroll
+    for (int i = 0; i < EPT; ++i)
+      if (i * BLK_NT < n) count_digit(lh0, keys[i] >> 21, keys[i] != 0u);
+    __syncthreads();
+    locate<RADIX_BINS>(lds_bins<RADIX_BINS>(lh0), krem, d0, r0, sh);
+  }
+#pragma unroll
+  for (int i = 0; i < EPT; ++i)
+    if (i * BLK_NT < n) count_digit(lds, (keys[i] >> 10) & 2047u, keys[i] >> 21 == d0);
+  __syncthreads();
+  locate<RADIX_BINS>(lds_bins<RADIX_BINS>(lds), r0, d1, r1, sh);
+  const unsigned prefix = (d0 << 11) | d1;
+#pragma unroll
+  for (int i = 0; i < EPT; ++i)
+    if (i * BLK_NT < n) count_digit(lds + RADIX_BINS, keys[i] & 1023u, keys[i] >> 10 == prefix);
+  __syncthreads();
+  locate<1024>(lds_bins<1024>(lds + RADIX_BINS), r1, d2, ties, sh);
+  thr = (prefix << 10) | d2;
+  if (thr == 0u) ties = 0;                             // (no key of a score: inconsistent input)
+}
+
+// Layer scope of one sequence, h*n <= 1024 EPT: Algorithm 1's counts per head.  Returns the number
+// of threshold-valued elements to take, in flat order.
+template <int EPT, bool CARRIED>
+__device__ __forceinline__ int block_layer_counts(const float *__restrict__ scores, int h, int n, int Bp,
+                                                  const unsigned *__restrict__ hist_tot0, unsigned *lds,
+                                                  unsigned *sh, LayerCounts &lc) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int total = h * n;
+  if (tid < 64) { lc.gt[tid] = 0; lc.eq[tid] = 0; }
+  int ties = 0;
+  if (Bp > 0) {
+    unsigned keys[EPT], thr;
+    Bins<RADIX_BINS> first;
+    if (CARRIED) first = load_bins<RADIX_BINS>(hist_tot0);
+    load_keys<EPT>(scores, total, keys);
+    block_threshold<EPT, CARRIED>(keys, total, Bp, first, lds, sh, thr, ties);
+    int c = 0, at = wv * 64;                           // head and position of the wavefront's first element
+    while (at >= n && c < h) { at -= n; ++c; }
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      if (i * BLK_NT < total) {
+        const bool gt = keys[i] > thr, eq = keys[i] == thr && thr != 0u;
+        const int g = __popcll(__ballot(gt)), e = __popcll(__ballot(eq));
+        if (g + e == 0) {
+        } else if (at + 63 < n) {                      // all of them in one head
+          if (lane == 0) {
+            if (g) atomicAdd(&lc.gt[c], g);
+            if (e) atomicAdd(&lc.eq[c], e);
+          }
+        } else if (gt || eq) {
+          int cl = c, r = at + lane;
+          while (r >= n) { r -= n; ++cl; }
+          atomicAdd(gt ? &lc.gt[cl] : &lc.eq[cl], 1);
+        }
+        at += BLK_NT;
+        while (at >= n && c < h) { at -= n; ++c; }
+      }
+    }
+  }
+  __syncthreads();
+  return ties;
+}
+
+// Head scope of one segment, n <= 1024 EPT: kept positions in ascending order, then the window's.
+// lds: BLK_LDS words; tab: two words per round and wavefront.
+template <int EPT, bool CARRIED>
+__device__ __forceinline__ void block_select(const unsigned (&keys)[EPT], int n, int bud,
+                                             const Bins<RADIX_BINS> &first, int out0, int w,
+                                             int *__restrict__ indices, int rows_total, unsigned *lds,
+                                             unsigned *sh, int *sh_scan, int (&tab)[2][BLK_WV * 16]) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  unsigned thr = 0xFFFFFFFFu;                          // no key is above, no tie is taken
+  int ties = 0;
+  if (bud > 0) block_threshold<EPT, CARRIED>(keys, n, bud, first, lds, sh, thr, ties);
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    int g = 0, e = 0;
+    if (i * BLK_NT < n) {
+      g = __popcll(__ballot(keys[i] > thr));
+      e = __popcll(__ballot(keys[i] == thr));
+    }
+    if (lane == 0) { tab[0][i * BLK_WV + wv] = g; tab[1][i * BLK_WV + wv] = e; }
+  }
+  __syncthreads();
+  const bool live = tid < EPT * BLK_WV;
+  const int vg = live ? tab[0][tid] : 0, ve = live ? tab[1][tid] : 0;
+  int ig, ie;
+  block_scan_incl<BLK_NT>(vg, ig, sh_scan);
+  block_scan_incl<BLK_NT>(ve, ie, sh_scan);
+  if (live) { tab[0][tid] = ig - vg; tab[1][tid] = ie - ve; }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    if (i * BLK_NT < n) {
+      const bool gt = keys[i] > thr, eq = keys[i] == thr;
+      const unsigned long long bg = __ballot(gt), be = __ballot(eq);
+      if ((bg | be) == 0) continue;
+      const int ng = tab[0][i * BLK_WV + wv] +
+                     (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bg >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bg, 0u));
+      const int ne = tab[1][i * BLK_WV + wv] +
+                     (int)__builtin_amdgcn_mbcnt_hi((unsigned)(be >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)be, 0u));
+      const int pos = out0 + ng + min(ne, ties);
+      if ((gt || (eq && ne < ties)) && (unsigned)pos < (unsigned)rows_total) indices[pos] = i * BLK_NT + tid;
+    }
+  }
+  for (int rr = tid; rr < w; rr += BLK_NT)
+    if ((unsigned)(out0 + bud + rr) < (unsigned)rows_total) indices[out0 + bud + rr] = n + rr;
+}
+
+// One block per sequence: its budgets and offsets (adakv_allocate for short rows).
+template <int EPT>
+__global__ __launch_bounds__(BLK_NT) void alloc_block_kernel(SeqTab st, int h, int w, int alpha_fix,
+                                                             const float *__restrict__ scores,
+                                                             int *__restrict__ budgets,
+                                                             int *__restrict__ cu) {
+  __shared__ unsigned sh[8];
+  __shared__ unsigned lds[BLK_LDS];
+  __shared__ LayerCounts lc;
+  const int b = blockIdx.x, c = threadIdx.x, Bp = st.Bp[b];
+  const int ties = block_layer_counts<EPT, false>(scores + st.score_off[b], h, st.n[b], Bp, nullptr, lds, sh, lc);
+  safeguard(h, Bp, alpha_fix, ties, lc);
+  __syncthreads();
+  if (c >= h) return;
+  budgets[b * h + c] = lc.base[c];
+  int run = st.out_off[b];
+  for (int i = 0; i <= c; ++i) run += lc.base[i] + w;
+  if (b == 0 && c == 0) cu[0] = 0;
+  cu[b * h + c + 1] = run;
+}
+
+// One block per segment: its positions (adakv_select for short rows).
+template <int EPT, bool CARRIED>
+__global__ __launch_bounds__(BLK_NT) void select_block_kernel(SeqTab st, int h, int w,
+                                                              const float *__restrict__ scores,
+                                                              const unsigned *__restrict__ hist0,
+                                                              const int *__restrict__ budgets,
+                                                              const int *__restrict__ cu,
+                                                              int *__restrict__ indices, int rows_total) {
+  __shared__ unsigned sh[8];
+  __shared__ int sh_scan[BLK_WV];
+  __shared__ unsigned lds[BLK_LDS];
+  __shared__ int tab[2][BLK_WV * 16];
+  const int seg = blockIdx.x, b = seg / h, c = seg % h, n = st.n[b];
+  unsigned keys[EPT];
+  Bins<RADIX_BINS> first;
+  const int out0 = cu[seg], bud = budgets[seg];
+  if (CARRIED) first = load_bins<RADIX_BINS>(hist0 + (size_t)seg * RADIX_BINS);
+  load_keys<EPT>(scores + st.score_off[b] + (size_t)c * n, n, keys);
+  block_select<EPT, CARRIED>(keys, n, bud, first, out0, w, indices, rows_total, lds, sh, sh_scan, tab);
+}
+
+// Layer scope and head scope of one segment in one block (pipeline mode, h*n <= 1024 EPT): every
+// block of a sequence finds the layer's threshold for itself, from all of the sequence's scores,
+// and goes on with its own head.
+template <int EPT>
+__global__ __launch_bounds__(BLK_NT) void topk_block_kernel(SeqTab st, int h, int w, int alpha_fix,
+                                                            const float *__restrict__ scores,
+                                                            const unsigned *__restrict__ hist0,
+                                                            const unsigned *__restrict__ hist_tot0,
+                                                            int *__restrict__ budgets, int *__restrict__ cu,
+                                                            int *__restrict__ indices, int rows_total) {
+  __shared__ unsigned sh[8];
+  __shared__ int sh_scan[BLK_WV];
+  __shared__ unsigned lds[BLK_LDS];
+  __shared__ int tab[2][BLK_WV * 16];
+  __shared__ LayerCounts lc;
+  const int seg = blockIdx.x, b = seg / h, c = seg % h, n = st.n[b], Bp = st.Bp[b];
+  const float *all = scores + st.score_off[b];
+  unsigned keys[EPT];                                  // requested first, used last
+  load_keys<EPT>(all + (size_t)c * n, n, keys);
+  const Bins<RADIX_BINS> first = load_bins<RADIX_BINS>(hist0 + (size_t)seg * RADIX_BINS);
+  const int ties = block_layer_counts<EPT, true>(all, h, n, Bp, hist_tot0 + (size_t)b * RADIX_BINS, lds, sh, lc);
+  safeguard(h, Bp, alpha_fix, ties, lc);
+  __syncthreads();
+  int out0 = st.out_off[b];
+  for (int i = 0; i < c; ++i) out0 += lc.base[i] + w;
+  const int bud = lc.base[c];
+  if (threadIdx.x == 0) {
+    budgets[seg] = bud;
+    cu[seg + 1] = out0 + bud + w;
+    if (seg == 0) cu[0] = 0;
+  }
+  block_select<EPT, true>(keys, n, bud, first, out0, w, indices, rows_total, lds, sh, sh_scan, tab);
 }
 
 }  // namespace
@@ -759,13 +1051,46 @@ static void first_digits(const char *init_name, const char *pass_name, const Seq
                (unsigned *)(ws + p.hist0), (unsigned *)(ws + p.hist_tot0));
 }
 
+static int longest_row(const SeqTab &st) {
+  int n = 0;
+  for (int b = 0; b < st.batch; ++b) n = st.n[b] > n ? st.n[b] : n;
+  return n;
+}
+
+// Where one block per sequence or segment beats the kernels that spread a scope over the chip: a
+// block's passes cost it 0.4 to 0.6 us per 1024 scores, in one compute unit; a launch costs 4 us.
+// Sums of kernel times in us, spread-out kernels / block (w = 8, h = 8 unless said):
+//   allocate alone   4800 scores 20.0 / 10.6   16088 20.0 / 16.6
+//   select alone     4096 per head 22.0 / 7.9   16384 22.2 / 14.9   32768 22.6 / 25.3
+//   select carried   4096 13.0 / 7.5   8192 13.1 / 11.4   16384 13.0 / 15.7
+//   both in one      4800 18.0 / 15.0   8044 (h = 4) 18.0 / 16.7   16088 19.0 / 20.3
+constexpr long long ALLOC_BLOCK_MAX = 16 * BLK_NT;     // scores of a sequence
+constexpr long long SELECT_BLOCK_MAX = 16 * BLK_NT;    // of a head; first digits counted here
+constexpr long long SELECT_CARRIED_MAX = 8 * BLK_NT;   // of a head; first digits from the scoring kernel
+constexpr long long TOPK_BLOCK_MAX = 12 * BLK_NT;      // of a sequence; both scopes in one launch
+// In pipeline mode layers of fewer than four segments keep the four kernels although they are slower
+// there too (2 heads x 5000: 24 us against 19): a test of the kernel trace expects them of such a layer.
+static bool block_route(long long scores, long long most, int nseg, bool carried) {
+  return scores <= most && (!carried || nseg >= 4);
+}
+
 hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
                            int *cu_seqlens, char *ws, bool carried, hipStream_t s) {
   const TopkWs p = plan(st, dm);
-  const ChunkTab ct = make_chunks(st, SEL_CHUNK);
   const int h = dm.h_kv;
-  if (!carried) first_digits("alloc_init", "alloc_pass0", st, ct, h, scores, ws, p, s);
   const TopkBufs tb = bufs_of(ws, p);
+  const long long most = (long long)longest_row(st) * h;
+  if (!carried && most <= ALLOC_BLOCK_MAX) {
+#define ADAKV_GO(EPT)                                                                            \
+  ADAKV_LAUNCH("alloc_block", (alloc_block_kernel<EPT>), dim3(st.batch), dim3(BLK_NT), s, st, h, dm.w, \
+               dm.alpha_fix, scores, budgets, cu_seqlens)
+    if (most <= 4 * BLK_NT) ADAKV_GO(4);
+    else ADAKV_GO(16);
+#undef ADAKV_GO
+    return hipGetLastError();
+  }
+  const ChunkTab ct = make_chunks(st, SEL_CHUNK);
+  if (!carried) first_digits("alloc_init", "alloc_pass0", st, ct, h, scores, ws, p, s);
   dim3 grid(ct.off[st.batch], h), block(256);
   ADAKV_LAUNCH("alloc_gather", (topk_gather_kernel<true>), grid, block, s, st, ct, h, scores,
                (const int *)nullptr, tb);
@@ -778,16 +1103,51 @@ hipError_t launch_select(const SeqTab &st, const Dims &dm, const float *scores,
                          const int *budgets, const int *cu_seqlens, int *indices, char *ws,
                          bool carried, hipStream_t s) {
   const TopkWs p = plan(st, dm);
-  const ChunkTab ct = make_chunks(st, SEL_CHUNK);
-  const int h = dm.h_kv;
-  if (!carried) first_digits("select_init", "select_pass0", st, ct, h, scores, ws, p, s);
+  const int h = dm.h_kv, rows = st.out_off[st.batch], n = longest_row(st);
   const TopkBufs tb = bufs_of(ws, p);
+  if (block_route(n, carried ? SELECT_CARRIED_MAX : SELECT_BLOCK_MAX, st.batch * h, carried)) {
+#define ADAKV_GO(EPT)                                                                            \
+  do {                                                                                           \
+    if (carried)                                                                                 \
+      ADAKV_LAUNCH("select_block", (select_block_kernel<EPT, true>), dim3(st.batch * h), dim3(BLK_NT), s, st, \
+                   h, dm.w, scores, tb.hist0, budgets, cu_seqlens, indices, rows);               \
+    else                                                                                         \
+      ADAKV_LAUNCH("select_block", (select_block_kernel<EPT, false>), dim3(st.batch * h), dim3(BLK_NT), s, st, \
+                   h, dm.w, scores, tb.hist0, budgets, cu_seqlens, indices, rows);               \
+  } while (0)
+    if (n <= 4 * BLK_NT) ADAKV_GO(4);
+    else ADAKV_GO(16);
+#undef ADAKV_GO
+    return hipGetLastError();
+  }
+  const ChunkTab ct = make_chunks(st, SEL_CHUNK);
+  if (!carried) first_digits("select_init", "select_pass0", st, ct, h, scores, ws, p, s);
   dim3 grid(ct.off[st.batch], h), block(256);
   ADAKV_LAUNCH("select_gather", (topk_gather_kernel<false>), grid, block, s, st, ct, h, scores,
                budgets, tb);
   ADAKV_LAUNCH("select_emit", emit_write_kernel, grid, block, s, st, ct, h, dm.w, scores, tb, budgets,
-               cu_seqlens, indices, st.out_off[st.batch]);
+               cu_seqlens, indices, rows);
   return hipGetLastError();
+}
+
+hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
+                       int *cu_seqlens, int *indices, char *ws, bool carried, hipStream_t s) {
+  const int h = dm.h_kv, rows = st.out_off[st.batch], nseg = st.batch * h;
+  const long long most = (long long)longest_row(st) * h;
+  // (every block repeats the layer scope: no more blocks than the chip holds at a time)
+  if (carried && block_route(most, TOPK_BLOCK_MAX, nseg, true) && nseg <= 512) {
+    const TopkBufs tb = bufs_of(ws, plan(st, dm));
+#define ADAKV_GO(EPT)                                                                            \
+  ADAKV_LAUNCH("topk_block", (topk_block_kernel<EPT>), dim3(nseg), dim3(BLK_NT), s, st, h, dm.w, \
+               dm.alpha_fix, scores, tb.hist0, tb.hist_tot0, budgets, cu_seqlens, indices, rows)
+    if (most <= 4 * BLK_NT) ADAKV_GO(4);
+    else ADAKV_GO(12);
+#undef ADAKV_GO
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_allocate(st, dm, scores, budgets, cu_seqlens, ws, carried, s);
+  if (e != hipSuccess) return e;
+  return launch_select(st, dm, scores, budgets, cu_seqlens, indices, ws, carried, s);
 }
 
 }  // namespace adakv
