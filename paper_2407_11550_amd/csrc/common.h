@@ -59,7 +59,8 @@ struct TopkCarry;
 // Which instantiation of the MFMA scoring kernels a layer gets (score_mfma.hip).
 struct MfmaVariant {
   int mb, rs, kg;      // 32-row blocks per wavefront; wavefronts along window rows, along keys
-  int chunk;           // keys per workgroup
+  int chunk;           // keys per workgroup at most (what the instantiation has room for)
+  int len;             // keys per workgroup
   bool fuse_lse;       // sweep 2 combines sweep 1's partial statistics itself
   bool fuse_pool;      // sweep 2 applies the max-pool itself
 };
@@ -74,6 +75,7 @@ struct ScorePlan {                  // byte offsets into the workspace
   int part_chunk;                   // keys per partial-statistics chunk
 };
 ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma);
+size_t score_workspace(const SeqTab &st, const Dims &dm, int part_chunk);   // with partial statistics per part_chunk keys
 bool mfma_path_supported(const Dims &dm, int dtype);
 bool f32_pool_fused(const SeqTab &st, const Dims &dm);   // the fp32 weights sweep applies the max-pool itself
 

@@ -395,9 +395,13 @@ static ScorePlan plan_score_chunk(const SeqTab &st, const Dims &dm, int part_chu
   return p;
 }
 
+size_t score_workspace(const SeqTab &st, const Dims &dm, int part_chunk) {
+  return plan_score_chunk(st, dm, part_chunk).total;
+}
+
 ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma) {
   (void)dtype;
-  if (on_mfma) return plan_score_chunk(st, dm, choose_mfma_variant(st, dm).chunk);
+  if (on_mfma) return plan_score_chunk(st, dm, choose_mfma_variant(st, dm).len);
   // The fp32 kernels' partials are per 128 keys (workgroups of four wavefronts spread best), or per
   // 256 keys where the smaller ones would not fit into the built-in scratch array any more: half the
   // partials, and a sequence that long fills the chip with either.

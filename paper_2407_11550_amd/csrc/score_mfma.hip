@@ -8,7 +8,7 @@
 //   sweep 2 (PASS 2)  exp(logit - lse) summed over the g*w rows      -> pre-pool scores
 // A caller-supplied row_lse skips sweep 1.
 //
-// Work split.  In sweep 2 a workgroup owns CHUNK consecutive keys of one KV head (the fused
+// Work split.  In sweep 2 a workgroup owns chunk_len consecutive keys of one KV head (the fused
 // max-pool wants neighbours); in sweep 1 the workgroups of a head take the head's tile sets in
 // turn (set c, c + nch, ...), because a (max, sum) pair does not care which keys it saw and the
 // chip then streams one dense region of K at a time.  All g query heads of the group share
@@ -42,7 +42,6 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int TILE = 32;           // keys per MFMA tile
-constexpr long long CHUNK_SWITCH_WGS = 512;   // fewer workgroups than this: halve the chunk
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr int MFMA_POOL_ROWS_MAX_RADIUS = 7;
@@ -73,10 +72,10 @@ __device__ __forceinline__ floatx16 mfma16(bf16x8 a, bf16x8 b, floatx16 c) {
 // lane.  Tiles then overlap by the pool radius on either side: only the inner 32 - 2r
 // lanes of a tile have all their neighbours and produce a score.
 template <int D, int MB, int RS, int KG, int CHUNK, int PASS, bool F16, bool PR = false>
-__global__ __launch_bounds__(64 * RS * KG) void score_mfma_kernel(
+__global__ __launch_bounds__(64 * RS * KG, PR && RS == 2 ? 2 : 1) void score_mfma_kernel(
     SeqTab st, ChunkTab ct, Dims dm, float c_log2, const unsigned short *__restrict__ q,
     const unsigned short *__restrict__ K, const float *__restrict__ lse,
-    float2 *__restrict__ part, float *__restrict__ out, int halo,
+    float2 *__restrict__ part, float *__restrict__ out, int halo, int chunk_len,
     TopkCarry tc) {
   constexpr int NW = RS * KG;                // wavefronts per workgroup
   constexpr int NT = 64 * NW;
@@ -118,8 +117,9 @@ __global__ __launch_bounds__(64 * RS * KG) void score_mfma_kernel(
   const int chunk = cg - ct.off[b];
   const int n = st.n[b];
   const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
-  const int kc0 = chunk * CHUNK;             // first key of the chunk
-  const int kc1 = min(n, kc0 + CHUNK);
+  // (CHUNK is what the score array in LDS holds at most; a layer's chunks are chunk_len keys)
+  const int kc0 = chunk * chunk_len;         // first key of the chunk
+  const int kc1 = min(n, kc0 + chunk_len);
   // sweep 2 with the pool fused also scores the neighbours the pool looks at: a whole tile in
   // front of the chunk (tiles stay aligned), the pool radius behind it.  No tile may start past
   // the last key somebody needs: the row clamp in load_set counts rows from the tile set's
@@ -170,7 +170,8 @@ __global__ __launch_bounds__(64 * RS * KG) void score_mfma_kernel(
   }
   // (with overlapping tiles the wavefront groups' tiles start tstep rows apart in the buffer)
   const int rd_off = kg * (tstep * STRIDE16) + l32 * STRIDE16 + half;
-  // interleaved: ceil(n / CHUNK) workgroups share ceil(n / (KG*TILE)) >= nch sets, at least one each
+  // interleaved: ceil(n / chunk_len) workgroups share ceil(n / (KG*TILE)) >= nch sets, at least one each
+  // (chunk_len >= KG*TILE)
   const int sets_all = (ntiles + KG - 1) / KG;
   const int iters = INTER ? (sets_all - chunk + nch - 1) / nch : sets_all;
   // The workgroups of a head run side by side and their chunks lie a fixed power-of-two number
@@ -373,29 +374,36 @@ __global__ __launch_bounds__(64 * RS * KG) void score_mfma_kernel(
       // wins (the pool window is clipped to the sequence).
       const int j = tile * tstep - pool_r + l32;       // key, counted from k0
       const unsigned inseq = (k0 + j >= 0 && k0 + j < n) ? 0xFFFFFFFFu : 0u;
-      unsigned p[MB][16];
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          p[mb][r] = __float_as_uint(fast_exp2(fmaf(acc[mb][r], c_log2, -l2[mb][r]))) & inseq;
-      for (int t = 0; t < pool_r; ++t) {               // keys j .. j + pool_r
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) p[mb][r] = max(p[mb][r], wave_shift<0x130>(p[mb][r]));
-      }
-      for (int t = 0; t < pool_r; ++t) {               // keys j - pool_r .. j + pool_r
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) p[mb][r] = max(p[mb][r], wave_shift<0x138>(p[mb][r]));
-      }
+      // The 128-row kernels take one row block after the other: both at once need 276 registers, one
+      // wavefront per SIMD, 42.5 us for the sweep instead of 32.1 (32768 keys x 8 heads).  The others
+      // keep both in flight (256 rows, 131072 keys: 166 us against 171).
+      constexpr int PB = RS == 2 ? 1 : MB;
       float sum = 0.0f;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+      for (int m0 = 0; m0 < MB; m0 += PB) {
+        unsigned p[PB][16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum += __uint_as_float(p[mb][r]);
+        for (int mb = 0; mb < PB; ++mb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            p[mb][r] = __float_as_uint(fast_exp2(fmaf(acc[m0 + mb][r], c_log2, -l2[m0 + mb][r]))) & inseq;
+        for (int t = 0; t < pool_r; ++t) {             // keys j .. j + pool_r
+#pragma unroll
+          for (int mb = 0; mb < PB; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) p[mb][r] = max(p[mb][r], wave_shift<0x130>(p[mb][r]));
+        }
+        for (int t = 0; t < pool_r; ++t) {             // keys j - pool_r .. j + pool_r
+#pragma unroll
+          for (int mb = 0; mb < PB; ++mb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) p[mb][r] = max(p[mb][r], wave_shift<0x138>(p[mb][r]));
+        }
+#pragma unroll
+        for (int mb = 0; mb < PB; ++mb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum += __uint_as_float(p[mb][r]);
+      }
       sum += __shfl_xor(sum, 32);
       if (half == 0 && l32 >= pool_r && l32 < TILE - pool_r && j < k1 - k0) sh_part[rs][j] = sum;
     } else {
@@ -694,10 +702,20 @@ __global__ __launch_bounds__(64 * RS * KG) void score_mfma_kernel(
       pk[i] = min(kc0 + tid + i * NT, kc1 - 1);
       pooled[i] = -INFINITY;
     }
-    for (int t = -r; t <= r; ++t) {
+    if (2 * chunk_len > CHUNK) {
+      for (int t = -r; t <= r; ++t) {
 #pragma unroll
-      for (int i = 0; i < KPT; ++i)
-        pooled[i] = fmaxf(pooled[i], sh_part[0][min(max(pk[i] + t, 0), n - 1) - k0]);
+        for (int i = 0; i < KPT; ++i)
+          pooled[i] = fmaxf(pooled[i], sh_part[0][min(max(pk[i] + t, 0), n - 1) - k0]);
+      }
+    } else {
+      // a short chunk in a large instantiation: only the keys there are (kept apart, because the test
+      // between the reads of a full chunk cost the sweep 2 us of 51 at 131072 keys)
+      for (int t = -r; t <= r; ++t) {
+#pragma unroll
+        for (int i = 0; i < KPT; ++i)
+          if (i * NT < chunk_len) pooled[i] = fmaxf(pooled[i], sh_part[0][min(max(pk[i] + t, 0), n - 1) - k0]);
+      }
     }
 #pragma unroll
     for (int i = 0; i < KPT; ++i) {
@@ -725,7 +743,7 @@ template <bool F16, int D, int MB, int RS, int KG, int CHUNK>
 void run_mfma(const MfmaVariant &v, const SeqTab &st, const Dims &dm, const void *q, const void *K,
               const float *row_lse, float *scores, char *ws, const ScorePlan &pl,
               const TopkCarry &tc, bool pool_rows, hipStream_t s) {
-  const ChunkTab ct = make_chunks(st, CHUNK);
+  const ChunkTab ct = make_chunks(st, v.len);
   const int nblk = ct.off[st.batch] * dm.h_kv;
   const float c_log2 = dm.scale * LOG2E;
   float2 *part = (float2 *)(ws + pl.part);
@@ -737,7 +755,7 @@ void run_mfma(const MfmaVariant &v, const SeqTab &st, const Dims &dm, const void
     ADAKV_LAUNCH("score_stats_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 1, F16>), dim3(nblk),
                  block, s, st, ct, dm, c_log2, (const unsigned short *)q,
                  (const unsigned short *)K, (const float *)nullptr, part,
-                 (float *)nullptr, 0, tc);
+                 (float *)nullptr, 0, v.len, tc);
     if (!fuse_lse) {
       launch_lse_combine(st, ct, dm.h_q * dm.w, part, lse, s);
       use_lse = lse;
@@ -749,12 +767,12 @@ void run_mfma(const MfmaVariant &v, const SeqTab &st, const Dims &dm, const void
     // the printed order of Alg. 2 l.4: the sweep pools every row itself and writes final scores
     ADAKV_LAUNCH("score_weights_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16, true>),
                  dim3(nblk), block, s, st, ct, dm, c_log2, (const unsigned short *)q,
-                 (const unsigned short *)K, use_lse, part, scores, 0, tc);
+                 (const unsigned short *)K, use_lse, part, scores, 0, v.len, tc);
     return;
   }
   ADAKV_LAUNCH("score_weights_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16>), dim3(nblk),
                block, s, st, ct, dm, c_log2, (const unsigned short *)q, (const unsigned short *)K,
-               use_lse, part, fuse_pool ? scores : raw, fuse_pool ? 1 : 0, tc);
+               use_lse, part, fuse_pool ? scores : raw, fuse_pool ? 1 : 0, v.len, tc);
   if (!fuse_pool) launch_pool(st, dm, raw, scores, s);
 }
 
@@ -818,57 +836,75 @@ bool mfma_path_supported(const Dims &dm, int dtype) {
          dm.k_stride_tok * 2 < (1ll << 24);   // 24-bit multiplies address a row inside a tile set
 }
 
+// Workgroups that chunks of `len` keys make.
+static long long workgroups(const SeqTab &st, const Dims &dm, int len) {
+  long long chunks = 0;
+  for (int b = 0; b < st.batch; ++b) chunks += (st.n[b] + len - 1) / len;
+  return chunks * dm.h_kv;
+}
+
 // The one place that decides which instantiation scores a layer: rows per wavefront and the
 // split of a workgroup's wavefronts over window rows (RS) and keys (KG) follow the number of
 // window rows per KV head; the chunk length follows the number of workgroups.
 MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   MfmaVariant v;
   const int R = dm.g * dm.w;
-  if (R <= 32) v = {1, 1, 4, 2048, false, false};
-  else if (R <= 64) v = {2, 1, 4, 2048, false, false};
-  else if (R <= 128) {
-    // chunk length: long chunks amortise the per-workgroup set-up, but every compute unit wants
-    // a few workgroups to choose from
-    long long keys = 0;
-    for (int b = 0; b < st.batch; ++b) keys += st.n[b];
-    const long long wg2048 = (keys / 2048 + st.batch) * dm.h_kv;
-    // 4096 keys when that alone nearly fills the 512 workgroups the chip holds at a time (seven
-    // eighths of them): one round of long workgroups instead of almost two of short ones
-    // (`llama8b_ragged`: 904 workgroups of 2048 keys or 472 of 4096, 279 -> 271 us per layer)
-    long long wg4096 = 0;
-    for (int b = 0; b < st.batch; ++b) wg4096 += (st.n[b] + 4095) / 4096;
-    wg4096 *= dm.h_kv;
-    const int chunk = 8 * wg4096 >= 7 * CHUNK_SWITCH_WGS ? 4096
-                      : wg2048 >= CHUNK_SWITCH_WGS ? 2048 : 2 * wg2048 >= CHUNK_SWITCH_WGS ? 1024 : 512;
-    v = {2, 2, 2, chunk, false, false};
-  } else if (R <= 256) {
-    // (the same rule one chunk length down: these workgroups carry twice the rows)
-    long long wg2048 = 0;
-    for (int b = 0; b < st.batch; ++b) wg2048 += (st.n[b] + 2047) / 2048;
-    wg2048 *= dm.h_kv;
-    v = {2, 4, 1, 8 * wg2048 >= 7 * CHUNK_SWITCH_WGS ? 2048 : 1024, false, false};
-  }
+  int slots, most;                             // workgroups the chip holds at a time; longest chunk
+  if (R <= 64) { v = {R <= 32 ? 1 : 2, 1, 4, 2048, 0, false, false}; slots = 256; most = 2048; }
+  else if (R <= 128) { v = {2, 2, 2, 512, 0, false, false}; slots = 512; most = 4096; }
+  else if (R <= 256) { v = {2, 4, 1, 1024, 0, false, false}; slots = 512; most = 2048; }
   // 512 rows: eight wavefronts of 64 rows; with d = 64 a row block needs half the registers and
-  // a tile half the loads, so four wavefronts of 128 rows.  Eight wavefronts fill a compute unit,
-  // so nothing overlaps with a workgroup's set-up and epilogue (about 4 and 7 us in the two
-  // sweeps): chunks of 2048 keys halve their number (measured on 131072 keys: 157 -> 145 and
-  // 175 -> 155 us for the two sweeps).
-  else if (dm.d == 128) {
-    long long keys = 0;
-    for (int b = 0; b < st.batch; ++b) keys += st.n[b];
-    // 4096 keys when that still gives every compute unit a workgroup (one round instead of two)
-    const long long wg4096 = (keys / 4096 + st.batch) * dm.h_kv;
-    v = {2, 8, 1, wg4096 >= 256 ? 4096 : 2048, false, false};
+  // a tile half the loads, so four wavefronts of 128 rows.
+  else if (dm.d == 128) { v = {2, 8, 1, 2048, 0, false, false}; slots = 256; most = 4096; }
+  else { v = {4, 4, 1, 1024, 0, false, false}; slots = 256; most = 1024; }
+  // Chunk length.  A workgroup's set-up and epilogue (4 and 7 us) want long chunks, the chip wants
+  // to be full, and workgroups beyond what it holds at a time wait for a second round.  So: the
+  // shortest chunk that gives every compute unit at most one workgroup, down to 64 keys (128 where
+  // four wavefronts take a tile each); if that is longer than 256 keys, one resident round of
+  // `slots`, and as many rounds as the longest chunk makes necessary beyond that.  Both sweeps
+  // together, 8 KV heads of dimension 128, against fixed lengths of 512 to 4096 (us):
+  //   rows   700 keys       2011           8000           20000          50021          100000
+  //     32   20.1 -> 13.7   34.4 -> 13.2   35.3 -> 16.8   36.6 -> 23.2   42.3 -> 42.9   87.4 -> 82.6
+  //    128   23.0 -> 14.6   24.9 -> 15.8   26.2 -> 21.4   37.2 -> 32.6   68.6 -> 53.8  109.6 -> 87.6
+  //    256   39.3 -> 16.3   51.7 -> 17.8   53.8 -> 25.8   57.1 -> 44.0   84.2 -> 75.6  159.5 -> 130.9
+  //    512   55.8 -> 24.2  123.8 -> 25.6  128.4 -> 38.9  132.6 -> 63.1  137.7 -> 119.8 271.9 -> 216.8
+  // (two workgroups of 128 keys instead of one of 256 per compute unit: 23.2 against 21.4 at 128
+  // rows and 8000 keys, 30.1 against 25.8 at 256 rows).
+  const int unit = TILE * v.kg;
+  auto shortest = [&](int from, long long wgs) {       // chunk of at least `from` keys that makes `wgs` workgroups at most
+    int lo = from / unit, hi = most / unit;
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      if (workgroups(st, dm, mid * unit) <= wgs) hi = mid;
+      else lo = mid + 1;
+    }
+    return hi * unit;
+  };
+  v.len = shortest(unit > 64 ? unit : 64, 256);
+  if (v.len > 256) {
+    const long long rounds = (workgroups(st, dm, most) + slots - 1) / slots;
+    v.len = shortest(256, rounds * slots);
   }
-  else v = {4, 4, 1, 1024, false, false};
+  // More chunks are more partial statistics: a layer that fits into the built-in scratch array with
+  // the longest chunks gets no split that would take it past the array's end.
+  auto fits = [&](int len) {
+    return score_workspace(st, dm, len) + plan_topk_bytes(st, dm) + 1024 <= (size_t)ADAKV_STATIC_SCRATCH_BYTES;
+  };
+  if (!fits(v.len) && fits(most)) v.len = most;
+  // The instantiation: the smallest score array in LDS that holds a chunk; with 512 rows a compute
+  // unit holds one workgroup either way and long sequences take the larger.
+  while (v.chunk < v.len) v.chunk *= 2;
+  if (v.rs == 8 && workgroups(st, dm, 4096) >= 256) v.chunk = 4096;
   // Fused forms: sweep 2 combines sweep 1's partial statistics itself unless a head has so many
-  // (chunks x rows) that every workgroup re-reading them would cost more than a kernel, and it
+  // (chunks x rows) that every workgroup re-reading them would cost more than a kernel (one round of
+  // the combination's loads: 131072 keys x 512 rows 141.5 us fused, 4.1 + 138.9 apart), and it
   // applies the max-pool itself when the pool radius fits into the one-tile halo.
-  const ChunkTab ct = make_chunks(st, v.chunk);
   int max_chunks = 0;
-  for (int b = 0; b < st.batch; ++b)
-    max_chunks = ct.off[b + 1] - ct.off[b] > max_chunks ? ct.off[b + 1] - ct.off[b] : max_chunks;
-  v.fuse_lse = (long long)max_chunks * R <= 8192;
+  for (int b = 0; b < st.batch; ++b) {
+    const int k = (st.n[b] + v.len - 1) / v.len;
+    max_chunks = k > max_chunks ? k : max_chunks;
+  }
+  v.fuse_lse = (long long)max_chunks * R <= (v.rs == 8 ? 16384 : 8192);
   v.fuse_pool = dm.pool_k / 2 <= TILE;
   return v;
 }

@@ -1,0 +1,116 @@
+"""Chunk lengths of the 16-bit scoring kernels follow the number of workgroups (any multiple of the
+keys an iteration takes, 64 to 4096): the index arithmetic over such lengths on the CPU, what the
+choice makes of a layer, and GPU parity at lengths where a chunk is as short as its pool halo."""
+import random
+
+import pytest
+import torch
+
+import paper_2407_11550_amd as adakv
+from oracle import adakv_oracle as O
+from paper_2407_11550_amd import synth
+
+import test_index_model as model
+from parity_util import assert_exact_on_scores, assert_scores_close, to_f64
+
+DEV = "cuda:0"
+LENGTHS = [1, 31, 33, 63, 64, 65, 127, 129, 300, 513, 1000, 2047, 4099, 6145]
+
+
+@pytest.mark.parametrize("kg,chunk_len", [(1, 64), (1, 96), (1, 160), (1, 480), (2, 64), (2, 192), (2, 832), (4, 128), (4, 384)])
+def test_index_arithmetic_at_any_chunk_length(kg, chunk_len):
+    assert chunk_len % (32 * kg) == 0
+    for n in LENGTHS:
+        assert model.interleaved_violations(n, chunk_len, kg) == 0, n
+        for pool_r in [0, 1, 3, 16, 32]:
+            for halo, sweep in [(1, 2), (0, 2), (0, 1)]:
+                assert model.violations(n, chunk_len, kg, pool_r, halo, sweep) == 0, (n, pool_r, halo, sweep)
+
+
+def fused_pool_violations(n, chunk_len, room, nt, pool_r):
+    """The pool of a chunk of chunk_len keys in an instantiation with room for `room`: thread tid pools
+    keys kc0 + tid + i*nt for the i with i*nt < chunk_len; every key of the chunk exactly once, every
+    read inside the scores the chunk has."""
+    bad = 0
+    for chunk in range((n + chunk_len - 1) // chunk_len):
+        kc0 = chunk * chunk_len
+        kc1 = min(n, kc0 + chunk_len)
+        k0 = kc0 - model.HALO if kc0 > 0 else kc0
+        span = min(n, kc1 + pool_r) - k0
+        bad += span > room + 2 * model.HALO
+        written = []
+        for i in range(room // nt):
+            for tid in range(nt):
+                if kc0 + tid + i * nt < kc1:
+                    written.append(kc0 + tid + i * nt)
+                    bad += not i * nt < chunk_len          # its window was looked at
+                pk = min(kc0 + tid + i * nt, kc1 - 1)
+                if i * nt < chunk_len:
+                    for t in (-pool_r, 0, pool_r):
+                        bad += not 0 <= min(max(pk + t, 0), n - 1) - k0 < span
+        bad += written != list(range(kc0, kc1))
+    return bad
+
+
+@pytest.mark.parametrize("room,nt,chunk_len", [(512, 256, 64), (512, 256, 320), (1024, 256, 832), (2048, 512, 160), (2048, 256, 128)])
+def test_pool_of_a_short_chunk_in_a_large_instantiation(room, nt, chunk_len):
+    for n in LENGTHS:
+        for pool_r in [0, 3, 32]:
+            assert fused_pool_violations(n, chunk_len, room, nt, pool_r) == 0, (n, pool_r)
+
+
+def test_choice_stays_inside_its_instantiation_and_never_starves_the_chip(lib):
+    rng = random.Random(5)
+    for _ in range(3000):
+        h, g, w = rng.choice([1, 2, 8, 64]), rng.choice([1, 2, 4, 8]), rng.choice([1, 8, 32, 64])
+        n = [int(2 ** rng.uniform(0, 18)) for _ in range(rng.choice([1, 1, 3, 17]))]
+        layer = adakv.Layer(torch.bfloat16, h * g, h, rng.choice([64, 128]), w, 7, 0.2, n, [h * w] * len(n))
+        v = adakv.describe(layer)
+        keys, unit = int(v["keys"]), 32 * int(v["kg"])
+        assert keys % unit == 0 and unit <= keys <= int(v["chunk"]) and keys >= 64, (v, n)
+        wgs = h * sum(-(-nb // keys) for nb in n)
+        most = {1: 2048, 2: 4096, 4: 2048 if v["mb"] == "2" else 1024, 8: 4096}[int(v["rs"])]
+        if wgs < 128 and keys > max(64, unit):              # half the compute units idle: only at the shortest chunk,
+            assert h * sum(-(-nb // most) for nb in n) >= 128 or h * sum(-(-nb // (keys - unit)) for nb in n) > 256, (v, n)
+
+
+# h_q, h_kv, d, w, pool_k, n, dtype, keys per workgroup
+SHORT = [
+    (2, 2, 128, 32, 7, [1000, 129, 127], torch.bfloat16, 128),      # 32 rows
+    (4, 2, 64, 32, 65, [700, 128], torch.float16, 128),             # 64 rows, the largest fused pool radius
+    (8, 2, 128, 32, 7, [700, 65, 64, 63, 1], torch.bfloat16, 64),   # 128 rows
+    (8, 2, 64, 32, 65, [500, 65], torch.bfloat16, 64),              # halo 32 on either side of 64 keys
+    (8, 2, 128, 60, 13, [321], torch.float16, 64),                  # 240 rows
+    (16, 2, 128, 64, 65, [500, 97], torch.bfloat16, 64),            # 512 rows
+    (16, 2, 64, 64, 7, [333], torch.float16, 64),                   # 512 rows, d = 64
+    (512, 64, 128, 33, 5, [600], torch.bfloat16, 160),              # 264 rows, five tiles per chunk
+    (256, 64, 128, 32, 7, [7000], torch.bfloat16, 896),             # 128 rows, one round of 512 workgroups
+]
+IDS = ["hq%d_h%d_d%d_w%d_k%d_n%s_%s" % (c[:5] + ("-".join(map(str, c[5])), str(c[6])[6:])) for c in SHORT]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("order", ["mean_then_pool", "row_lse", "pool_then_mean"])
+@pytest.mark.parametrize("case", SHORT, ids=IDS)
+def test_short_and_odd_chunks_match_oracle(case, order):
+    h_q, h, d, w, k, n, dt, keys = case
+    if order == "pool_then_mean" and (k > 15 or n == [7000]):
+        pytest.skip("beyond the radius that is pooled on the matrix cores" if k > 15 else "covered by the shorter ones")
+    print("chunk lengths", case, order, flush=True)
+    wl = synth.small_workload(h_q, h, d, w, k, n, [h * (w + max(1, nb // 10)) for nb in n], dtype=dt, seed=29)
+    q, K, V = synth.generate(wl, device=DEV)
+    layer = adakv.Layer.from_workload(wl, flags=4 if order == "pool_then_mean" else 0)
+    v = adakv.describe(layer)
+    assert int(v["keys"]) == keys, v
+    lse = synth.prefill_row_lse(wl, q, K) if order == "row_lse" else None
+    out = adakv.compress(layer, q, K, V, row_lse=lse)
+    off, soff, row0 = wl.tok_off, 0, 0
+    for b in range(wl.batch):
+        ref = O.score(to_f64(q[b]), to_f64(K[off[b]:off[b + 1]]), n[b], w, k,
+                      row_lse=None if lse is None else to_f64(lse[b]),
+                      **({"order": "pool_then_mean"} if order == "pool_then_mean" else {}))
+        sc = out["scores"][soff:soff + h * n[b]].cpu().numpy()
+        assert_scores_close(sc, ref, f"{order} seq {b}")
+        assert_exact_on_scores(out, sc, wl, K, V, b, seg0=b * h, row0=row0)
+        soff += h * n[b]
+        row0 += wl.B[b]
