@@ -114,6 +114,7 @@ class Layer:
             for nb in self.n:
                 tok_off.append(tok_off[-1] + nb + w)
         self.tok_off = [int(v) for v in tok_off]
+        self._rows_out, self._segments = sum(self.B), self.batch * h_kv    # of the arrays handed to the library
         self._n = (ctypes.c_int32 * self.batch)(*self.n)
         self._B = (ctypes.c_int32 * len(self.B))(*self.B)
         self._off = (ctypes.c_int64 * len(self.tok_off))(*self.tok_off)
@@ -141,11 +142,11 @@ class Layer:
 
     @property
     def num_rows_out(self):
-        return sum(self.B)
+        return self._rows_out
 
     @property
     def num_segments(self):
-        return self.batch * self.h_kv
+        return self._segments
 
 
 def workspace_bytes(layer: Layer) -> int:
@@ -159,7 +160,7 @@ def _ptr(t, name, dtype=None):
         raise ValueError(f"{name} must be a device tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()                 # (an int: the argument types of the library's functions convert it)
 
 
 def _need(t, numel, name):
@@ -195,8 +196,11 @@ def _check_q(layer, q):
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """The handle of `stream`, or of the current device's current stream.  A decoding step is two short
+    kernels, and making a Stream object for its handle alone took 1.5 of 15 us per call."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _workspace(layer, ws):
@@ -204,7 +208,7 @@ def _workspace(layer, ws):
         ws = torch.empty(max(workspace_bytes(layer), 16), dtype=torch.uint8, device="cuda")
     if ws.dtype != torch.uint8:
         raise ValueError("ws must be a uint8 tensor (its size is taken in bytes)")
-    return ws, ctypes.c_void_p(ws.data_ptr()), ctypes.c_size_t(ws.numel())
+    return ws, ws.data_ptr(), ws.numel()
 
 
 def score(layer: Layer, q_window, K, row_lse=None, out=None, ws=None, stream=None):
@@ -328,8 +332,7 @@ def compress(layer: Layer, q_window, K, V, row_lse=None, ws=None, stream=None, b
                             _ptr(row_lse, "row_lse", torch.float32), _ptr(sc, "scores", torch.float32),
                             _ptr(bud, "budgets", torch.int32), _ptr(cu, "cu_seqlens", torch.int32),
                             _ptr(idx, "indices", torch.int32), _ptr(K_out, "K_out", layer.torch_dtype),
-                            _ptr(V_out, "V_out", layer.torch_dtype), ctypes.c_void_p(ws.data_ptr()),
-                            ctypes.c_size_t(ws.numel()), _stream(stream))
+                            _ptr(V_out, "V_out", layer.torch_dtype), ws.data_ptr(), ws.numel(), _stream(stream))
     if st != 0:
         raise AdaKVError(st, "adakv_compress")
     return dict(scores=sc, budgets=bud, cu_seqlens=cu, indices=idx, K_out=K_out, V_out=V_out)
@@ -401,7 +404,7 @@ def probe_read(src, sink=None, stream=None):
         sink = torch.empty(PROBE_SINK_BYTES, dtype=torch.uint8, device=src.device)
     if sink.numel() * sink.element_size() < PROBE_SINK_BYTES:
         raise ValueError("sink too small")
-    st = load_library().adakv_probe_read(_ptr(src, "src"), ctypes.c_size_t(src.numel() * src.element_size()),
+    st = load_library().adakv_probe_read(_ptr(src, "src"), src.numel() * src.element_size(),
                                          _ptr(sink, "sink"), _stream(stream))
     if st != 0:
         raise AdaKVError(st, "adakv_probe_read")
@@ -411,13 +414,13 @@ def probe_read(src, sink=None, stream=None):
 # ---- decode side of the flattened layout ---------------------------------------------------------
 def cache_rows(layer: Layer, headroom: int) -> int:
     """Rows of K_cache / V_cache: every segment's retained rows plus `headroom` spare rows each."""
-    return layer.num_rows_out + layer.num_segments * int(headroom)
+    return layer._rows_out + layer._segments * int(headroom)
 
 
 def _check_cache(layer, K_cache, V_cache):
     """The cache tensors are addressed as contiguous rows of d elements."""
     for t, name in ((K_cache, "K_cache"), (V_cache, "V_cache")):
-        if not t.is_contiguous() or t.shape[-1] != layer.d:
+        if not t.is_contiguous() or t.size(-1) != layer.d:
             raise ValueError(f"{name} must be a contiguous [rows, {layer.d}] tensor")
 
 
@@ -470,11 +473,12 @@ def append(layer: Layer, k_new, v_new, cu_seqlens, headroom, K_cache, V_cache, s
     """adakv_append: one new K/V row per (sequence, KV head) behind each segment; seg_len grows."""
     lib = load_library()
     want = (layer.batch, layer.h_kv, layer.d)
-    if tuple(k_new.shape) != want or tuple(v_new.shape) != want:
+    if k_new.shape != want or v_new.shape != want:
         raise ValueError(f"k_new and v_new must be {want}")
     if not (k_new.is_contiguous() and v_new.is_contiguous()):
         raise ValueError("k_new and v_new must be contiguous")
-    if K_cache.shape[0] < cache_rows(layer, headroom) or V_cache.shape[0] < cache_rows(layer, headroom):
+    rows = cache_rows(layer, headroom)
+    if K_cache.size(0) < rows or V_cache.size(0) < rows:
         raise ValueError("cache too small for this layer and head-room")
     _check_cache(layer, K_cache, V_cache)
     _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
@@ -497,9 +501,10 @@ def decode_attn(layer: Layer, q_new, cu_seqlens, headroom, K_cache, V_cache, seg
     """adakv_decode_attn: out [batch, h_q, d] fp32 (and lse [batch, h_q] if asked for)."""
     lib = load_library()
     want = (layer.batch, layer.h_q, layer.d)
-    if tuple(q_new.shape) != want or not q_new.is_contiguous():
+    if q_new.shape != want or not q_new.is_contiguous():
         raise ValueError(f"q_new must be contiguous {want}")
-    if K_cache.shape[0] < cache_rows(layer, headroom) or V_cache.shape[0] < cache_rows(layer, headroom):
+    rows = cache_rows(layer, headroom)
+    if K_cache.size(0) < rows or V_cache.size(0) < rows:
         raise ValueError("cache too small for this layer and head-room")
     if out is None:
         out = torch.empty(want, dtype=torch.float32, device=q_new.device)
@@ -515,8 +520,7 @@ def decode_attn(layer: Layer, q_new, cu_seqlens, headroom, K_cache, V_cache, seg
                                _ptr(V_cache, "V_cache", layer.torch_dtype),
                                _ptr(seg_len, "seg_len", torch.int32),
                                _ptr(out, "out", torch.float32), _ptr(lse, "lse", torch.float32),
-                               ctypes.c_void_p(ws.data_ptr()), ctypes.c_size_t(ws.numel()),
-                               _stream(stream))
+                               ws.data_ptr(), ws.numel(), _stream(stream))
     if st != 0:
         raise AdaKVError(st, "adakv_decode_attn")
     return (out, lse) if (want_lse or lse is not None) else out
@@ -528,11 +532,12 @@ def decode_step(layer: Layer, q_new, k_new, v_new, cu_seqlens, headroom, K_cache
     lib = load_library()
     want = (layer.batch, layer.h_q, layer.d)
     wkv = (layer.batch, layer.h_kv, layer.d)
-    if tuple(q_new.shape) != want or not q_new.is_contiguous():
+    if q_new.shape != want or not q_new.is_contiguous():
         raise ValueError(f"q_new must be contiguous {want}")
-    if tuple(k_new.shape) != wkv or tuple(v_new.shape) != wkv or not (k_new.is_contiguous() and v_new.is_contiguous()):
+    if k_new.shape != wkv or v_new.shape != wkv or not (k_new.is_contiguous() and v_new.is_contiguous()):
         raise ValueError(f"k_new and v_new must be contiguous {wkv}")
-    if K_cache.shape[0] < cache_rows(layer, headroom) or V_cache.shape[0] < cache_rows(layer, headroom):
+    rows = cache_rows(layer, headroom)
+    if K_cache.size(0) < rows or V_cache.size(0) < rows:
         raise ValueError("cache too small for this layer and head-room")
     if out is None:
         out = torch.empty(want, dtype=torch.float32, device=q_new.device)
@@ -552,8 +557,7 @@ def decode_step(layer: Layer, q_new, k_new, v_new, cu_seqlens, headroom, K_cache
                                _ptr(seg_len, "seg_len", torch.int32),
                                _ptr(overflow, "overflow", torch.int32),
                                _ptr(out, "out", torch.float32), _ptr(lse, "lse", torch.float32),
-                               ctypes.c_void_p(ws.data_ptr()), ctypes.c_size_t(ws.numel()),
-                               _stream(stream))
+                               ws.data_ptr(), ws.numel(), _stream(stream))
     if st != 0:
         raise AdaKVError(st, "adakv_decode_step")
     return (out, lse) if (want_lse or lse is not None) else out
