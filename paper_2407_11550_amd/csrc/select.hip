@@ -836,7 +836,7 @@ __device__ __forceinline__ void block_threshold(const unsigned (&keys)[EPT], int
 // of threshold-valued elements to take, in flat order.
 template <int EPT, bool CARRIED>
 __device__ __forceinline__ int block_layer_counts(const float *__restrict__ scores, int h, int n, int Bp,
-                                                  const unsigned *__restrict__ hist_tot0, unsigned *lds,
+                                                  const TopkBufs &tb, int b, unsigned *lds,
                                                   unsigned *sh, LayerCounts &lc) {
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int total = h * n;
@@ -845,7 +845,7 @@ __device__ __forceinline__ int block_layer_counts(const float *__restrict__ scor
   if (Bp > 0) {
     unsigned keys[EPT], thr;
     Bins<RADIX_BINS> first;
-    if (CARRIED) first = load_bins<RADIX_BINS>(hist_tot0);
+    if (CARRIED) first = load_bins<RADIX_BINS>(tb.hist_tot0 + (size_t)b * RADIX_BINS);
     load_keys<EPT>(scores, total, keys);
     block_threshold<EPT, CARRIED>(keys, total, Bp, first, lds, sh, thr, ties);
     int c = 0, at = wv * 64;                           // head and position of the wavefront's first element
@@ -931,7 +931,7 @@ __global__ __launch_bounds__(BLK_NT) void alloc_block_kernel(SeqTab st, int h, i
   __shared__ unsigned lds[BLK_LDS];
   __shared__ LayerCounts lc;
   const int b = blockIdx.x, c = threadIdx.x, Bp = st.Bp[b];
-  const int ties = block_layer_counts<EPT, false>(scores + st.score_off[b], h, st.n[b], Bp, nullptr, lds, sh, lc);
+  const int ties = block_layer_counts<EPT, false>(scores + st.score_off[b], h, st.n[b], Bp, TopkBufs(), b, lds, sh, lc);
   safeguard(h, Bp, alpha_fix, ties, lc);
   __syncthreads();
   if (c >= h) return;
@@ -963,27 +963,28 @@ __global__ __launch_bounds__(BLK_NT) void select_block_kernel(SeqTab st, int h, 
   block_select<EPT, CARRIED>(keys, n, bud, first, out0, w, indices, rows_total, lds, sh, sh_scan, tab);
 }
 
-// Layer scope and head scope of one segment in one block (pipeline mode, h*n <= 1024 EPT): every
-// block of a sequence finds the layer's threshold for itself, from all of the sequence's scores,
-// and goes on with its own head.
-template <int EPT>
-__global__ __launch_bounds__(BLK_NT) void topk_block_kernel(SeqTab st, int h, int w, int alpha_fix,
-                                                            const float *__restrict__ scores,
-                                                            const unsigned *__restrict__ hist0,
-                                                            const unsigned *__restrict__ hist_tot0,
+// Layer scope and head scope of one segment in one block (pipeline mode): every block of a sequence
+// finds the layer's threshold for itself, from all of the sequence's scores (SHORT, h*n <= 1024 EPT)
+// or from the gather kernel's results (n <= 1024 EPT), and goes on with its own head.
+template <int EPT, bool SHORT>
+__global__ __launch_bounds__(BLK_NT) void topk_block_kernel(SeqTab st, ChunkTab ct, int h, int w,
+                                                            int alpha_fix,
+                                                            const float *__restrict__ scores, TopkBufs tb,
                                                             int *__restrict__ budgets, int *__restrict__ cu,
                                                             int *__restrict__ indices, int rows_total) {
+  static_assert(1024 + HOLD_LAYER >= BLK_LDS, "the head scope's histograms take the layer scope's place");
   __shared__ unsigned sh[8];
   __shared__ int sh_scan[BLK_WV];
-  __shared__ unsigned lds[BLK_LDS];
+  __shared__ unsigned lds[SHORT ? BLK_LDS : 1024 + HOLD_LAYER];
   __shared__ int tab[2][BLK_WV * 16];
   __shared__ LayerCounts lc;
   const int seg = blockIdx.x, b = seg / h, c = seg % h, n = st.n[b], Bp = st.Bp[b];
   const float *all = scores + st.score_off[b];
   unsigned keys[EPT];                                  // requested first, used last
   load_keys<EPT>(all + (size_t)c * n, n, keys);
-  const Bins<RADIX_BINS> first = load_bins<RADIX_BINS>(hist0 + (size_t)seg * RADIX_BINS);
-  const int ties = block_layer_counts<EPT, true>(all, h, n, Bp, hist_tot0 + (size_t)b * RADIX_BINS, lds, sh, lc);
+  const Bins<RADIX_BINS> first = load_bins<RADIX_BINS>(tb.hist0 + (size_t)seg * RADIX_BINS);
+  const int ties = SHORT ? block_layer_counts<EPT, true>(all, h, n, Bp, tb, b, lds, sh, lc)
+                         : layer_counts(ct, h, b, Bp, tb, lc, sh, sh_scan, lds);
   safeguard(h, Bp, alpha_fix, ties, lc);
   __syncthreads();
   int out0 = st.out_off[b];
@@ -1068,6 +1069,7 @@ constexpr long long ALLOC_BLOCK_MAX = 16 * BLK_NT;     // scores of a sequence
 constexpr long long SELECT_BLOCK_MAX = 16 * BLK_NT;    // of a head; first digits counted here
 constexpr long long SELECT_CARRIED_MAX = 8 * BLK_NT;   // of a head; first digits from the scoring kernel
 constexpr long long TOPK_BLOCK_MAX = 12 * BLK_NT;      // of a sequence; both scopes in one launch
+constexpr long long TOPK_ROW_MAX = 4 * BLK_NT;         // of a head; gather and the rest in one launch (16088: 18.3 -> 16.3)
 // In pipeline mode layers of fewer than four segments keep the four kernels although they are slower
 // there too (2 heads x 5000: 24 us against 19): a test of the kernel trace expects them of such a layer.
 static bool block_route(long long scores, long long most, int nseg, bool carried) {
@@ -1135,13 +1137,19 @@ hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, in
   const int h = dm.h_kv, rows = st.out_off[st.batch], nseg = st.batch * h;
   const long long most = (long long)longest_row(st) * h;
   // (every block repeats the layer scope: no more blocks than the chip holds at a time)
-  if (carried && block_route(most, TOPK_BLOCK_MAX, nseg, true) && nseg <= 512) {
+  const bool in_block = most <= TOPK_BLOCK_MAX;
+  if (carried && nseg >= 4 && nseg <= 512 && (in_block || longest_row(st) <= TOPK_ROW_MAX)) {
     const TopkBufs tb = bufs_of(ws, plan(st, dm));
-#define ADAKV_GO(EPT)                                                                            \
-  ADAKV_LAUNCH("topk_block", (topk_block_kernel<EPT>), dim3(nseg), dim3(BLK_NT), s, st, h, dm.w, \
-               dm.alpha_fix, scores, tb.hist0, tb.hist_tot0, budgets, cu_seqlens, indices, rows)
-    if (most <= 4 * BLK_NT) ADAKV_GO(4);
-    else ADAKV_GO(12);
+    const ChunkTab ct = make_chunks(st, SEL_CHUNK);
+    if (!in_block)
+      ADAKV_LAUNCH("alloc_gather", (topk_gather_kernel<true>), dim3(ct.off[st.batch], h), dim3(256), s, st, ct, h,
+                   scores, (const int *)nullptr, tb);
+#define ADAKV_GO(EPT, SHORT)                                                                     \
+  ADAKV_LAUNCH("topk_block", (topk_block_kernel<EPT, SHORT>), dim3(nseg), dim3(BLK_NT), s, st, ct, h, dm.w, \
+               dm.alpha_fix, scores, tb, budgets, cu_seqlens, indices, rows)
+    if (!in_block) ADAKV_GO(4, false);
+    else if (most <= 4 * BLK_NT) ADAKV_GO(4, true);
+    else ADAKV_GO(12, true);
 #undef ADAKV_GO
     return hipGetLastError();
   }

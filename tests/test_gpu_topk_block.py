@@ -71,7 +71,9 @@ def test_allocate_and_select_alone(layer_no, kind):
 STEPS = [
     (8, 4, 128, 8, [700, 40]),
     (8, 8, 64, 4, [1536]),                     # 12288 scores: the most that run in one launch
-    (8, 8, 64, 4, [1537]),
+    (8, 8, 64, 4, [1537]),                     # gather and one launch
+    (4, 4, 64, 2, [4096, 4095]),               # the longest head of that form
+    (4, 4, 64, 2, [4097]),
     (4, 4, 64, 2, [8192, 5]),                  # the longest head of the one-launch head scope
     (4, 4, 64, 2, [8193]),
     (32, 32, 64, 2, [70] * 17),                # 544 segments: a block per sequence would be repeated too often
