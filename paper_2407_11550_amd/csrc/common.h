@@ -133,6 +133,7 @@ int probe_waves_per_block();
 
 // ---- decode side of the flattened layout (decode.hip) -----------------------------------------
 struct DecodePlan {
+  bool whole;                       // one workgroup per segment, results written directly
   int split;                        // rows of a segment per workgroup
   int nblk;                         // workgroups launched: an upper bound on what the lengths need
   size_t part_acc, part_ml;         // byte offsets of the per-workgroup partial results

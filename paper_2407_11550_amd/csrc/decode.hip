@@ -347,13 +347,21 @@ template <bool F16> __device__ __forceinline__ unsigned pack(float x0, float x1)
     return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, x1), __builtin_bit_cast(unsigned, x0), 0x07060302u);
 }
 
-template <bool F16, int D, int G>
-__global__ __launch_bounds__(256) void decode_mfma_kernel(
+// Where a workgroup's result goes: partial results for the merge kernel, or (WHOLE, one workgroup per
+// segment) straight to the caller.
+struct DecodeOut {
+  float *part_acc, *part_ml;
+  int4 *seg_tab;
+  float *out, *lse;
+  int *new_len, *overflow;                     // null unless the call appends
+};
+
+template <bool F16, int D, int G, bool WHOLE>
+__global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
     int nseg, int h, int per, int split, int headroom, float c_log2, const unsigned short *__restrict__ q,
     const char *__restrict__ k_new, const char *__restrict__ v_new, const int *__restrict__ cu,
-    const int *__restrict__ seg_len, char *Kc, char *Vc, float *__restrict__ part_acc,
-    float *__restrict__ part_ml, int4 *__restrict__ seg_tab) {
-  constexpr int NW = 4;                        // wavefronts that share the rows of a split
+    const int *__restrict__ seg_len, char *Kc, char *Vc, DecodeOut res) {
+  constexpr int NW = WHOLE ? 8 : 4;            // wavefronts that share the rows of a split
   constexpr int ROWB = D * 2;
   constexpr int KS = D / 32;                   // k-steps of the logits
   constexpr int VC = D / 16;                   // columns of V per lane
@@ -372,15 +380,27 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(
 
   // ---- which (segment, split) is this workgroup?  (as in decode_attn_kernel) --------------------
   const int grow = k_new != nullptr ? 1 : 0;
-  int total;
-  const int excl = scan_blocks<NW>(nseg, per, split, headroom, grow, cu, seg_len, sh_scan, &total);
-  find_block(excl, nseg, per, split, headroom, grow, cu, seg_len, sh_scan, seg_tab);
-  if ((int)blockIdx.x >= total) return;        // uniform: the launch is an upper bound
-  __syncthreads();
-  const int s = __builtin_amdgcn_readfirstlane(sh_scan[16]), j0 = __builtin_amdgcn_readfirstlane(sh_scan[17]);
-  const int len = __builtin_amdgcn_readfirstlane(sh_scan[18]), cu_s = __builtin_amdgcn_readfirstlane(sh_scan[19]);
-  const int new_row = __builtin_amdgcn_readfirstlane(sh_scan[20]) ? len - 1 : -1;
-  const int r0 = j0 * split, r1 = min(len, r0 + split);
+  int s, len, cu_s, new_row, r0, r1;
+  if constexpr (WHOLE) {
+    s = blockIdx.x;
+    cu_s = cu[s];
+    len = rows_held(cu, seg_len, s, headroom, grow);
+    new_row = len > rows_held(cu, seg_len, s, headroom, 0) ? len - 1 : -1;
+    r0 = 0;
+    r1 = len;
+  } else {
+    int total;
+    const int excl = scan_blocks<NW>(nseg, per, split, headroom, grow, cu, seg_len, sh_scan, &total);
+    find_block(excl, nseg, per, split, headroom, grow, cu, seg_len, sh_scan, res.seg_tab);
+    if ((int)blockIdx.x >= total) return;      // uniform: the launch is an upper bound
+    __syncthreads();
+    s = __builtin_amdgcn_readfirstlane(sh_scan[16]);
+    len = __builtin_amdgcn_readfirstlane(sh_scan[18]);
+    cu_s = __builtin_amdgcn_readfirstlane(sh_scan[19]);
+    new_row = __builtin_amdgcn_readfirstlane(sh_scan[20]) ? len - 1 : -1;
+    r0 = __builtin_amdgcn_readfirstlane(sh_scan[17]) * split;
+    r1 = min(len, r0 + split);
+  }
   const long long seg_byte = ((long long)cu_s + (long long)s * headroom) * ROWB;
   char *Kb = Kc + seg_byte;
   char *Vb = Vc + seg_byte;
@@ -549,11 +569,22 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(
       a = fmaf(x * (1.0f / P_SCALE<F16>), f, a);
       ll = fmaf(sh_l[w2][gi], f, ll);
     }
-    part_acc[((long long)blockIdx.x * G + gi) * D + e] = a;
-    if (e == 0) {
-      part_ml[((long long)blockIdx.x * G + gi) * 2] = M;
-      part_ml[((long long)blockIdx.x * G + gi) * 2 + 1] = ll;
+    if constexpr (WHOLE) {
+      const long long row = (long long)s * G + gi;
+      res.out[row * D + e] = ll > 0.0f ? a / ll : 0.0f;
+      if (res.lse && e == 0) res.lse[row] = ll > 0.0f ? (M + log2f(ll)) * LN2 : -INFINITY;
+    } else {
+      res.part_acc[((long long)blockIdx.x * G + gi) * D + e] = a;
+      if (e == 0) {
+        res.part_ml[((long long)blockIdx.x * G + gi) * 2] = M;
+        res.part_ml[((long long)blockIdx.x * G + gi) * 2 + 1] = ll;
+      }
     }
+  }
+  // (nobody but this workgroup reads the segment's length)
+  if (WHOLE && res.new_len && tid == 0) {
+    if (new_row >= 0) res.new_len[s] = len;
+    else if (res.overflow) *res.overflow = 1;  // the segment was full, its new row was dropped
   }
 }
 
@@ -656,17 +687,25 @@ void run_decode(const SeqTab &st, const Dims &dm, int headroom, const DecodePlan
   float *part_acc = (float *)(ws + pl.part_acc);
   float *part_ml = (float *)(ws + pl.part_ml);
   int4 *seg_tab = (int4 *)(ws + pl.seg_tab);
-  if constexpr (sizeof(T) == 4)
+  if constexpr (sizeof(T) == 4) {
     ADAKV_LAUNCH("decode_attn", (decode_attn_kernel<T, D, G>), dim3(pl.nblk),
                  dim3(256 * HeadSplit<T, G>::NGRP), s, nseg,
                  dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E, (const T *)q,
                  (const char *)k_new, (const char *)v_new, cu, (const int *)seg_len, (char *)Kc,
                  (char *)Vc, part_acc, part_ml, seg_tab);
-  else
-    ADAKV_LAUNCH("decode_attn", (decode_mfma_kernel<std::is_same<T, f16_t>::value, D, G>), dim3(pl.nblk),
-                 dim3(256), s, nseg, dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E,
-                 (const unsigned short *)q, (const char *)k_new, (const char *)v_new, cu,
-                 (const int *)seg_len, (char *)Kc, (char *)Vc, part_acc, part_ml, seg_tab);
+  } else {
+    constexpr bool F16 = std::is_same<T, f16_t>::value;
+    const DecodeOut res = {part_acc, part_ml, seg_tab, out, lse, k_new ? seg_len : nullptr, overflow};
+    if (pl.whole) {
+      ADAKV_LAUNCH("decode_attn", (decode_mfma_kernel<F16, D, G, true>), dim3(nseg), dim3(512), s, nseg, dm.h_kv,
+                   per, pl.split, headroom, dm.scale * LOG2E, (const unsigned short *)q, (const char *)k_new,
+                   (const char *)v_new, cu, (const int *)seg_len, (char *)Kc, (char *)Vc, res);
+      return;
+    }
+    ADAKV_LAUNCH("decode_attn", (decode_mfma_kernel<F16, D, G, false>), dim3(pl.nblk), dim3(256), s, nseg,
+                 dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E, (const unsigned short *)q,
+                 (const char *)k_new, (const char *)v_new, cu, (const int *)seg_len, (char *)Kc, (char *)Vc, res);
+  }
   // only a call that appends hands the lengths to the merge kernel for updating
   ADAKV_LAUNCH("decode_combine", (decode_combine_kernel<D, G>), dim3(nseg, G), dim3(1024), s,
                (const int4 *)seg_tab, k_new ? seg_len : nullptr, overflow, (const float *)part_acc,
@@ -722,6 +761,12 @@ DecodePlan plan_decode(const SeqTab &st, const Dims &dm, int dtype, int headroom
   if (want < 64) want = 64;
   const int unit = mfma && want > 64 ? 128 : 64;
   const int split = (int)((want + unit - 1) / unit * unit);
+  // One workgroup of eight wavefronts per segment, and no merge kernel, where segments are short: up
+  // to 384 rows on average with the head-room full.  us per step of a 256-row head-room (segments up
+  // to four times the average), split / whole: 48 rows 10.5 / 8.8, 128 rows 10.4 / 8.8, 256 rows
+  // 10.5 / 9.7 for one sequence and 10.5 / 12.7 for eight, 512 rows 10.5 / 14.4 (g = 4, d = 128; the
+  // kernels alone at 128 rows: 10.0 / 7.5).
+  pl.whole = mfma && cap <= nseg * 384;
   pl.split = split;
   pl.nblk = (int)(cap / split + nseg);          // >= sum over segments of ceil(len / split)
   pl.part_acc = 0;

@@ -1,5 +1,6 @@
 """Decode attention on 16-bit caches at the edges of its split: tiles of 32 rows, four wavefronts of
-one tile each per round, workgroups of 64 rows or a multiple of 128, an appended row in the last
+one tile each per round, workgroups of 64 rows or a multiple of 128, or of eight wavefronts over a
+whole short segment; an appended row in the last
 place of a tile or the first of a new one; and values at the ends of the types' ranges."""
 import numpy as np
 import pytest
@@ -31,7 +32,8 @@ def _cache(dt, d, g, lengths, headroom, seed):
 
 @pytest.mark.parametrize("g", [1, 2, 4, 8])
 @pytest.mark.parametrize("dt,d", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float16, 128), (torch.float16, 64)])
-@pytest.mark.parametrize("longer", [0, 9000], ids=["rows64", "rows128"])   # 9000 more rows per segment: longer splits
+# more rows per segment: one workgroup per segment, splits of 64 rows, splits of a multiple of 128
+@pytest.mark.parametrize("longer", [0, 400, 9000], ids=["whole", "rows64", "rows128"])
 def test_decode_step_at_tile_edges(dt, d, g, longer):
     print("decode tiles", dt, d, g, longer, flush=True)
     lengths = [v + longer for v in LENGTHS]
@@ -49,6 +51,13 @@ def test_decode_step_at_tile_edges(dt, d, g, longer):
         ref_out, ref_lse = D.decode_attention(to_f64(q[t]), oK, oV, cuh, hr, olen, wl.g)
         _assert_decode_close(out, lse, ref_out, ref_lse, vmax, f"step {t}")
         assert np.array_equal(to_f64(Kc), oK, equal_nan=True) and np.array_equal(to_f64(Vc), oV, equal_nan=True)
+    full = torch.zeros(1, dtype=torch.int32, device=DEV)                  # no room left: nothing appended, and said so
+    before = [t.clone() for t in (Kc, Vc, lens)]
+    out, lse = adakv.decode_step(layer, q[0], kn[0], vn[0], cu, hr, Kc, Vc, lens, overflow=full, want_lse=True)
+    ref_out, ref_lse = D.decode_attention(to_f64(q[0]), oK, oV, cuh, hr, olen, wl.g)
+    _assert_decode_close(out, lse, ref_out, ref_lse, vmax, "full")
+    assert int(full) == 1
+    assert all(torch.equal(torch.nan_to_num(a.float()), torch.nan_to_num(b.float())) for a, b in zip(before, (Kc, Vc, lens)))
 
 
 @pytest.mark.parametrize("g", [4, 8])
