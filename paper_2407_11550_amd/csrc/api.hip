@@ -405,7 +405,8 @@ int adakv_describe(const adakv_layer *L, int have_row_lse, char *out, size_t out
   } else {
     len = snprintf(out, out_bytes, "score=%s dtype=%s d=%d rows=%d stats=%s lse=%s pool=%s topk=%s",
                    pool_first(L) ? "fma-pool-first" : "fma", dt, dm.d, dm.g * dm.w, stats,
-                   have_row_lse ? "caller" : "kernel",
+                   have_row_lse ? "caller"
+                   : !pool_first(L) && f32_lse_fused(st, plan_score(st, dm, L->dtype, false).part_chunk) ? "fused" : "kernel",
                    !pool_first(L) && f32_pool_fused(st, dm) ? "fused" : "kernel", topk);
   }
   return (len < 0 || (size_t)len >= out_bytes) ? ADAKV_EINVAL : ADAKV_OK;

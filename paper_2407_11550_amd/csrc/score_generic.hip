@@ -104,6 +104,7 @@ constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr int F32_KEYS = 128;                          // keys per workgroup: four wavefronts of 32 (sweep 1 also: eight)
 constexpr int F32_POOL_MAX = 16;                       // largest pool radius that sweep 2 applies itself
+constexpr int F32_FUSE_CHUNKS = 32;                    // most partials of a row that sweep 2 combines itself
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -147,11 +148,11 @@ struct RowBlock {
 //
 // The operands' k index is permuted alike in both: of every two 16-byte words of a row the lower
 // half of the wavefront takes the first, the upper half the second.
-template <typename T, int D, int PASS, int NW>
+template <typename T, int D, int PASS, int NW, bool COMBINE>
 __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
     SeqTab st, ChunkTab ct, Dims dm, float c_log2, int pool_r, int lse_natural,
     const T *__restrict__ q, const T *__restrict__ K, const float *__restrict__ lse,
-    float2 *__restrict__ part, float *__restrict__ out) {
+    float2 *__restrict__ part, int part_chunk, float *__restrict__ out) {
   typedef RowBlock<T, D, 64 * NW> RB;
   constexpr int KEYS = 32 * NW;
   constexpr int P = RB::P;
@@ -159,6 +160,8 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
   __shared__ __align__(16) float qs[2][32 * RB::STRIDE];
   __shared__ float sh_a[2][NW][32], sh_b[2][NW][32];   // sweep 1: per-wavefront row statistics
   __shared__ float sh_l2[2][32];                       // sweep 2: the row block's log-sum-exp
+  constexpr int SL = 2 * NW;                           // threads that share a row of the statistics combination
+  __shared__ float sh_pm[COMBINE ? SL : 1][32], sh_pl[COMBINE ? SL : 1][32];
   __shared__ float sh_raw[KEYS];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -186,8 +189,43 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
     const float v = lse[lse0 + min(row, R - 1)];
     return row < R ? (lse_natural ? v * LOG2E : v) : INFINITY;
   };
+  // COMBINE: sweep 2 combines sweep 1's partials of a row block itself (at most
+  // F32_FUSE_CHUNKS of them per sequence): SL threads share a row, what they load for the next block
+  // travels while this one is multiplied, and 32 threads add the SL slices up.
+  static_assert(!COMBINE || PASS == 2, "the weights sweep combines");
+  const int prow = tid & 31, slice = tid >> 5;
+  constexpr int PB = F32_FUSE_CHUNKS / SL;             // partials per thread
+  float2 pml[COMBINE ? PB : 1];
+  int nch = 0;
+  size_t part0 = 0;
+  if (COMBINE) {
+    for (int i = 0; i < b; ++i) part0 += (st.n[i] + part_chunk - 1) / part_chunk;
+    nch = (n + part_chunk - 1) / part_chunk;
+  }
+  auto load_partials = [&](int r0) {
+#pragma unroll
+    for (int u = 0; u < (COMBINE ? PB : 0); ++u)
+      pml[u] = part[(part0 + min(slice + u * SL, nch - 1)) * RQ + (size_t)c * R + min(r0 + prow, R - 1)];
+  };
+  auto fold_partials = [&]() {
+    float M = -INFINITY, L = 0.0f;
+#pragma unroll
+    for (int u = 0; u < (COMBINE ? PB : 0); ++u)
+      if (slice + u * SL < nch) M = fmaxf(M, pml[u].x);
+    const float ref = (M == -INFINITY) ? 0.0f : M;
+#pragma unroll
+    for (int u = 0; u < (COMBINE ? PB : 0); ++u)
+      if (slice + u * SL < nch) L += pml[u].y * fast_exp2(pml[u].x - ref);
+    sh_pm[slice][prow] = M;
+    sh_pl[slice][prow] = L;
+  };
   rb.store(qs[0]);
-  if (PASS == 2 && tid < 32) sh_l2[0][tid] = row_l2(tid);
+  if (COMBINE) {
+    load_partials(0);
+    fold_partials();
+  } else if (PASS == 2 && tid < 32) {
+    sh_l2[0][tid] = row_l2(tid);
+  }
   __syncthreads();
 
   float total = 0.0f;
@@ -196,9 +234,20 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
     const int cur = ib & 1;
     const bool more = ib + 1 < blocks;
     float next_l2 = 0.0f;
+    if (COMBINE && tid < 32) {
+      float M = sh_pm[0][tid];
+#pragma unroll
+      for (int i = 1; i < SL; ++i) M = fmaxf(M, sh_pm[i][tid]);
+      const float ref = (M == -INFINITY) ? 0.0f : M;
+      float L = 0.0f;
+#pragma unroll
+      for (int i = 0; i < SL; ++i) L += sh_pl[i][tid] * fast_exp2(sh_pm[i][tid] - ref);
+      sh_l2[cur][tid] = ib * 32 + tid < R ? M + __builtin_amdgcn_logf(L) : INFINITY;
+    }
     if (more) {
       rb.fetch(qhead, (ib + 1) * 32, R);
-      if (PASS == 2 && tid < 32) next_l2 = row_l2((ib + 1) * 32 + tid);
+      if (COMBINE) load_partials((ib + 1) * 32);
+      else if (PASS == 2 && tid < 32) next_l2 = row_l2((ib + 1) * 32 + tid);
     }
     // two chains of d/2 multiply-adds instead of one of d: the rounding of a logit follows the longest
     floatx16 acc = {0}, acc1 = {0};
@@ -235,6 +284,7 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
       l += __shfl_xor(l, 32);
       if (half == 0) { sh_a[cur][wv][l32] = m; sh_b[cur][wv][l32] = l; }
     } else {
+      if (COMBINE) __syncthreads();                    // the log-sum-exp above; and the slices have been read
       // acc[i]: window row ib*32 + 8*(i/4) + 4*half + i%4, key k0 + wv*32 + l32
 #pragma unroll
       for (int i = 0; i < 16; ++i)
@@ -242,7 +292,8 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
     }
     if (more) {
       rb.store(qs[cur ^ 1]);
-      if (PASS == 2 && tid < 32) sh_l2[cur ^ 1][tid] = next_l2;
+      if (COMBINE) fold_partials();
+      else if (PASS == 2 && tid < 32) sh_l2[cur ^ 1][tid] = next_l2;
     }
     __syncthreads();
     // (the buffers of this row block are written again two barriers from here)
@@ -439,6 +490,12 @@ bool f32_pool_fused(const SeqTab &st, const Dims &dm) {
   return (most - most_apart) * row_blocks * 1.8f * dm.d / 128 <= 4.0f;
 }
 
+bool f32_lse_fused(const SeqTab &st, int part_chunk) {
+  for (int b = 0; b < st.batch; ++b)
+    if ((st.n[b] + part_chunk - 1) / part_chunk > F32_FUSE_CHUNKS) return false;
+  return true;
+}
+
 template <typename T, int D>
 static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const void *K,
                         const float *row_lse, float *scores, char *ws, const ScorePlan &pl,
@@ -452,15 +509,20 @@ static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const v
     const ChunkTab ct = make_chunks(st, pl.part_chunk);
     const dim3 grid(ct.off[st.batch], dm.h_kv);
     if (pl.part_chunk == F32_KEYS)
-      ADAKV_LAUNCH("score_stats_fma", (score_f32_kernel<T, D, 1, 4>), grid, block, s, st, ct, dm, c_log2, -1,
-                   0, (const T *)q, (const T *)K, (const float *)nullptr, part, (float *)nullptr);
+      ADAKV_LAUNCH("score_stats_fma", (score_f32_kernel<T, D, 1, 4, false>), grid, block, s, st, ct, dm, c_log2, -1,
+                   0, (const T *)q, (const T *)K, (const float *)nullptr, part, pl.part_chunk, (float *)nullptr);
     else
-      ADAKV_LAUNCH("score_stats_fma", (score_f32_kernel<T, D, 1, 8>), grid, dim3(512), s, st, ct, dm, c_log2,
-                   -1, 0, (const T *)q, (const T *)K, (const float *)nullptr, part, (float *)nullptr);
-    const int RQ = dm.h_q * dm.w;
-    ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel<true>, dim3((RQ + 3) / 4, st.batch), block, s,
-                 st, ct, RQ, (const float2 *)part, lse, pool_first ? 1 : 0);
-    use_lse = lse;
+      ADAKV_LAUNCH("score_stats_fma", (score_f32_kernel<T, D, 1, 8, false>), grid, dim3(512), s, st, ct, dm, c_log2,
+                   -1, 0, (const T *)q, (const T *)K, (const float *)nullptr, part, pl.part_chunk, (float *)nullptr);
+    // Up to 32 partials per row (4096 keys) sweep 2 combines them itself, a launch of 4 us less: 2011
+    // keys x 8 heads x 128 rows 33.0 -> 29.0 us for both sweeps, 4000 x 512 rows 100.1 -> 97.5; with 64
+    // partials its workgroups read more of those than of keys (8000 x 4 heads x 512 rows, d = 64: 65.6 -> 67.6).
+    if (pool_first || !f32_lse_fused(st, pl.part_chunk)) {
+      const int RQ = dm.h_q * dm.w;
+      ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel<true>, dim3((RQ + 3) / 4, st.batch), block, s,
+                   st, ct, RQ, (const float2 *)part, lse, pool_first ? 1 : 0);
+      use_lse = lse;
+    }
   }
   if (pool_first) {
     const ChunkTab co = make_chunks(st, 256 - 2 * (dm.pool_k / 2));
@@ -471,9 +533,14 @@ static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const v
   const int r = dm.pool_k / 2;
   const bool fused = f32_pool_fused(st, dm);
   const ChunkTab ct = make_chunks(st, fused ? F32_KEYS - 2 * r : F32_KEYS);
-  ADAKV_LAUNCH("score_weights_fma", (score_f32_kernel<T, D, 2, 4>), dim3(ct.off[st.batch], dm.h_kv), block, s,
-               st, ct, dm, c_log2, fused ? r : -1, row_lse ? 1 : 0, (const T *)q, (const T *)K, use_lse,
-               (float2 *)nullptr, fused ? scores : raw);
+  const dim3 grid(ct.off[st.batch], dm.h_kv);
+#define ADAKV_GO(COMBINE)                                                                         \
+  ADAKV_LAUNCH("score_weights_fma", (score_f32_kernel<T, D, 2, 4, COMBINE>), grid, block, s, st, ct, dm, \
+               c_log2, fused ? r : -1, row_lse ? 1 : 0, (const T *)q, (const T *)K, use_lse, part, \
+               pl.part_chunk, fused ? scores : raw)
+  if (use_lse) ADAKV_GO(false);
+  else ADAKV_GO(true);
+#undef ADAKV_GO
   if (!fused) launch_pool(st, dm, raw, scores, s);
 }
 

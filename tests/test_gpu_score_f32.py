@@ -19,6 +19,8 @@ CASES = [
     (4, 4, 64, 8, 7, [1, 31, 32, 33], torch.float32, "fused"),            # fewer keys than a wavefront holds; one row block
     (4, 2, 128, 16, 7, [121, 122, 123, 128, 129], torch.float32, "fused"),  # around the owned 122 and the held 128 keys
     (4, 4, 128, 1, 1, [127, 257], torch.float32, "fused"),                # one row, no pool: all 128 keys owned
+    (4, 2, 64, 20, 7, [4096, 5, 3000], torch.float32, "fused"),           # 32 partials per row: combined in sweep 2
+    (4, 2, 64, 20, 7, [5, 4097], torch.float32, "fused"),                 # 33: by a kernel
     (12, 4, 64, 11, 5, [500, 77], torch.float32, "fused"),                # 33 rows: a row block with one row
     (2, 1, 128, 32, 33, [97, 300], torch.float32, "fused"),               # radius 16: 96 owned keys
     (2, 1, 128, 32, 35, [300], torch.float32, "kernel"),                   # radius 17: the pool in its own kernel
