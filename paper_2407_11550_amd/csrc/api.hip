@@ -70,11 +70,17 @@ static bool pool_first(const adakv_layer *L) { return (L->flags & ADAKV_FLAG_POO
 static bool on_mfma(const Dims &dm, const adakv_layer *L) {
   return pool_first(L) ? mfma_pool_rows_supported(dm, L->dtype) : mfma_path_supported(dm, L->dtype);
 }
-static size_t topk_offset(const SeqTab &st, const Dims &dm, const adakv_layer *L) {
-  return align_up(plan_score(st, dm, L->dtype, on_mfma(dm, L)).total, 256);
-}
-static size_t workspace_for(const SeqTab &st, const Dims &dm, const adakv_layer *L) {
-  return topk_offset(st, dm, L) + plan_topk_bytes(st, dm) + 256;
+// (planning looks at every sequence a few times: once per call)
+struct Plan {
+  ScorePlan score;
+  size_t topk, bytes;       // start of the Top-k part; workspace size
+};
+static Plan make_plan(const SeqTab &st, const Dims &dm, const adakv_layer *L) {
+  Plan p;
+  p.score = plan_score(st, dm, L->dtype, on_mfma(dm, L));
+  p.topk = align_up(p.score.total, 256);
+  p.bytes = p.topk + plan_topk_bytes(st, dm) + 256;
+  return p;
 }
 static bool pipeline_mode(const adakv_layer *L, const Dims &dm) {
   return (L->flags & ADAKV_FLAG_PIPELINE) != 0 && carry_supported(dm, L->dtype) && on_mfma(dm, L);
@@ -130,7 +136,7 @@ extern "C" {
 size_t adakv_workspace_bytes(const adakv_layer *L) {
   SeqTab st; Dims dm;
   if (build_tables(L, st, dm) != ADAKV_OK) return 0;
-  return workspace_for(st, dm, L);
+  return make_plan(st, dm, L).bytes;
 }
 
 int adakv_pyramid_budgets(int32_t n_layers, int64_t avg_budget, double ratio, int64_t *out) {
@@ -200,18 +206,18 @@ int adakv_score(const adakv_layer *L, const void *q_window, const void *K, const
   if (rc != ADAKV_OK) return rc;
   if (!q_window || !K || !scores) return ADAKV_EINVAL;
   if (!aligned16(q_window) || !aligned16(K) || !aligned16(scores)) return ADAKV_EUNSUPPORTED;
-  if (!ws || ws_bytes < workspace_for(st, dm, L)) return ADAKV_EWORKSPACE;
+  const Plan plan = make_plan(st, dm, L);
+  if (!ws || ws_bytes < plan.bytes) return ADAKV_EWORKSPACE;
   char *wsp = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
-  ScorePlan pl = plan_score(st, dm, L->dtype, on_mfma(dm, L));
   hipStream_t s = (hipStream_t)hip_stream;
   if (pool_first(L) && dm.pool_k / 2 > 100) return ADAKV_EUNSUPPORTED;
   TopkCarry tc = {nullptr, 0u, nullptr, nullptr};
-  if (pipeline_mode(L, dm)) tc = plan_carry(st, dm, wsp + topk_offset(st, dm, L));
+  if (pipeline_mode(L, dm)) tc = plan_carry(st, dm, wsp + plan.topk);
   hipError_t e = on_mfma(dm, L)
-                     ? launch_score_mfma(st, dm, L->dtype, q_window, K, row_lse, scores, wsp, pl, tc,
+                     ? launch_score_mfma(st, dm, L->dtype, q_window, K, row_lse, scores, wsp, plan.score, tc,
                                          pool_first(L), s)
                      : launch_score_generic(st, dm, L->dtype, q_window, K, row_lse, scores, wsp,
-                                            pl, pool_first(L), s);
+                                            plan.score, pool_first(L), s);
   return e == hipSuccess ? ADAKV_OK : ADAKV_EHIP;
 }
 
@@ -222,10 +228,11 @@ int adakv_allocate(const adakv_layer *L, const float *scores, int32_t *budgets,
   if (rc != ADAKV_OK) return rc;
   if (!scores || !budgets || !cu_seqlens) return ADAKV_EINVAL;
   if (!aligned16(scores)) return ADAKV_EUNSUPPORTED;
-  if (!ws || ws_bytes < workspace_for(st, dm, L)) return ADAKV_EWORKSPACE;
+  const Plan plan = make_plan(st, dm, L);
+  if (!ws || ws_bytes < plan.bytes) return ADAKV_EWORKSPACE;
   char *wsp = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
   hipError_t e = launch_allocate(st, dm, scores, budgets, cu_seqlens,
-                                 wsp + topk_offset(st, dm, L), pipeline_mode(L, dm),
+                                 wsp + plan.topk, pipeline_mode(L, dm),
                                  (hipStream_t)hip_stream);
   return e == hipSuccess ? ADAKV_OK : ADAKV_EHIP;
 }
@@ -238,10 +245,11 @@ int adakv_select(const adakv_layer *L, const float *scores, const int32_t *budge
   if (rc != ADAKV_OK) return rc;
   if (!scores || !budgets || !cu_seqlens || !indices) return ADAKV_EINVAL;
   if (!aligned16(scores)) return ADAKV_EUNSUPPORTED;
-  if (!ws || ws_bytes < workspace_for(st, dm, L)) return ADAKV_EWORKSPACE;
+  const Plan plan = make_plan(st, dm, L);
+  if (!ws || ws_bytes < plan.bytes) return ADAKV_EWORKSPACE;
   char *wsp = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
   hipError_t e = launch_select(st, dm, scores, budgets, cu_seqlens, indices,
-                               wsp + topk_offset(st, dm, L), pipeline_mode(L, dm),
+                               wsp + plan.topk, pipeline_mode(L, dm),
                                (hipStream_t)hip_stream);
   return e == hipSuccess ? ADAKV_OK : ADAKV_EHIP;
 }
@@ -273,12 +281,13 @@ int adakv_compress(const adakv_layer *L, const void *q_window, const void *K, co
       !aligned16(K_out) || !aligned16(V_out))
     return ADAKV_EUNSUPPORTED;
   if (pool_first(L) && dm.pool_k / 2 > 100) return ADAKV_EUNSUPPORTED;
-  if (!ws || ws_bytes < workspace_for(st, dm, L)) return ADAKV_EWORKSPACE;
+  const Plan plan = make_plan(st, dm, L);
+  if (!ws || ws_bytes < plan.bytes) return ADAKV_EWORKSPACE;
   adakv_layer P = *L;
   P.flags |= ADAKV_FLAG_PIPELINE;
   if ((rc = adakv_score(&P, q_window, K, row_lse, scores, ws, ws_bytes, hip_stream)) != ADAKV_OK) return rc;
   char *wsp = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
-  if (launch_topk(st, dm, scores, budgets, cu_seqlens, indices, wsp + topk_offset(st, dm, &P),
+  if (launch_topk(st, dm, scores, budgets, cu_seqlens, indices, wsp + plan.topk,
                   pipeline_mode(&P, dm), (hipStream_t)hip_stream) != hipSuccess)
     return ADAKV_EHIP;
   return adakv_compact(&P, K, V, indices, cu_seqlens, K_out, V_out, hip_stream);
@@ -292,7 +301,7 @@ int adakv_compress_static(const adakv_layer *L, const void *q_window, const void
   SeqTab st; Dims dm;
   int rc = build_tables(L, st, dm);
   if (rc != ADAKV_OK) return rc;
-  if (workspace_for(st, dm, L) > (size_t)ADAKV_STATIC_SCRATCH_BYTES) return ADAKV_ESCRATCH;
+  if (make_plan(st, dm, L).bytes > (size_t)ADAKV_STATIC_SCRATCH_BYTES) return ADAKV_ESCRATCH;
   void *ws = static_scratch();
   if (!ws) return ADAKV_EHIP;
   return adakv_compress(L, q_window, K, V, row_lse, scores, budgets, cu_seqlens, indices, K_out,
