@@ -860,7 +860,7 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   // Chunk length.  A workgroup's set-up and epilogue (4 and 7 us) want long chunks, the chip wants
   // to be full, and workgroups beyond what it holds at a time wait for a second round.  So: the
   // shortest chunk that gives every compute unit at most one workgroup, down to 64 keys (128 where
-  // four wavefronts take a tile each); if that is longer than 256 keys, one resident round of
+  // four wavefronts take a tile each); if that is longer than `one`, one resident round of
   // `slots`, and as many rounds as the longest chunk makes necessary beyond that.  Both sweeps
   // together, 8 KV heads of dimension 128, against fixed lengths of 512 to 4096 (us):
   //   rows   700 keys       2011           8000           20000          50021          100000
@@ -868,8 +868,16 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   //    128   23.0 -> 14.6   24.9 -> 15.8   26.2 -> 21.4   37.2 -> 32.6   68.6 -> 53.8  109.6 -> 87.6
   //    256   39.3 -> 16.3   51.7 -> 17.8   53.8 -> 25.8   57.1 -> 44.0   84.2 -> 75.6  159.5 -> 130.9
   //    512   55.8 -> 24.2  123.8 -> 25.6  128.4 -> 38.9  132.6 -> 63.1  137.7 -> 119.8 271.9 -> 216.8
-  // (two workgroups of 128 keys instead of one of 256 per compute unit: 23.2 against 21.4 at 128
-  // rows and 8000 keys, 30.1 against 25.8 at 256 rows).
+  // `one` is 512 keys: two shorter workgroups on a compute unit instead of one pay the set-up
+  // twice and fill the chip unevenly (between 256 and 512 of them), while one workgroup of more
+  // than 512 keys hides too little latency.  One against two (us, both sweeps):
+  //   rows    8000 keys      9600           11000          12500          14400          15800
+  //    128   21.4 | 23.2   22.8 | 26.8    24.2 | 27.2    25.5 | 27.6    27.4 | 28.2    28.0 | 28.8
+  //    256   25.8 | 30.1   28.8 | 36.0    30.4 | 36.5    33.2 | 36.9    36.0 | 38.2    37.8 | 39.0
+  // 4.1 us of two at 256 rows is the kernel that combines their statistics.  Without it sweep 1
+  // gains up to 12500 keys (15.4 -> 14.8) and sweep 2 only up to 11000 (17.2 -> 16.9; 17.4 -> 18.4
+  // at 12500), so where a sequence is short enough that sweep 2 combines either way the line is 384
+  // (eight sequences of 3200 to 484 keys, whole call, in two runs: 34.8 | 34.1).
   const int unit = TILE * v.kg;
   auto shortest = [&](int from, long long wgs) {       // chunk of at least `from` keys that makes `wgs` workgroups at most
     int lo = from / unit, hi = most / unit;
@@ -880,17 +888,19 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
     }
     return hi * unit;
   };
+  int longest = 0;
+  for (int b = 0; b < st.batch; ++b) longest = st.n[b] > longest ? st.n[b] : longest;
+  const int one = v.rs == 4 && (longest + 255ll) / 256 * R <= 8192 ? 384 : 512;
   v.len = shortest(unit > 64 ? unit : 64, 256);
-  if (v.len > 256) {
+  if (v.len > one) {
     const long long rounds = (workgroups(st, dm, most) + slots - 1) / slots;
     v.len = shortest(256, rounds * slots);
   }
   // More chunks are more partial statistics: a layer that fits into the built-in scratch array with
-  // the longest chunks gets no split that would take it past the array's end.
-  auto fits = [&](int len) {
-    return score_workspace(st, dm, len) + plan_topk_bytes(st, dm) + 1024 <= (size_t)ADAKV_STATIC_SCRATCH_BYTES;
-  };
-  if (!fits(v.len) && fits(most)) v.len = most;
+  // the longest chunks gets no split that would take it past the array's end (1 KiB for the
+  // alignment of the parts, asked of the split alone, so that a layer that just fits keeps fitting).
+  auto need = [&](int len) { return score_workspace(st, dm, len) + plan_topk_bytes(st, dm); };
+  if (need(v.len) + 1024 > (size_t)ADAKV_STATIC_SCRATCH_BYTES && need(most) <= (size_t)ADAKV_STATIC_SCRATCH_BYTES) v.len = most;
   // The instantiation: the smallest score array in LDS that holds a chunk; with 512 rows a compute
   // unit holds one workgroup either way and long sequences take the larger.
   while (v.chunk < v.len) v.chunk *= 2;

@@ -84,6 +84,7 @@ SHORT = [
     (16, 2, 128, 64, 65, [500, 97], torch.bfloat16, 64),            # 512 rows
     (16, 2, 64, 64, 7, [333], torch.float16, 64),                   # 512 rows, d = 64
     (512, 64, 128, 33, 5, [600], torch.bfloat16, 160),              # 264 rows, five tiles per chunk
+    (256, 64, 128, 32, 7, [1700], torch.bfloat16, 448),             # 128 rows, one workgroup per compute unit
     (256, 64, 128, 32, 7, [7000], torch.bfloat16, 896),             # 128 rows, one round of 512 workgroups
 ]
 IDS = ["hq%d_h%d_d%d_w%d_k%d_n%s_%s" % (c[:5] + ("-".join(map(str, c[5])), str(c[6])[6:])) for c in SHORT]
