@@ -309,11 +309,14 @@ __global__ __launch_bounds__((256 * HeadSplit<T, G>::NGRP)) void decode_attn_ker
 //            numbered that way, so V is loaded in that numbering: a lane takes 8 rows x D/16
 //            columns and turns its own 8 x (D/16) block with byte permutes.
 //
-// P stays in 32 bits: it is cut into three 16-bit parts whose sum is P to 2^-24 (bf16: truncated to
-// 8, 8 and 8 bits; fp16: of P 2^15, so that what is small beside the maximum keeps its bits), and the
-// 16 rows of the P operand hold the parts side by side (the repeated heads).  For g = 8 the third
-// part goes through a product of its own.  Products of 16-bit values and their sums are exact in
-// fp32 up to the accumulation, as they were on the vector units.
+// P stays in 32 bits: it is cut into three bf16 parts whose sum is P to 2^-24 (truncated to 8, 8 and 8
+// bits), and the 16 rows of the P operand hold the parts side by side (the repeated heads).  For g = 8
+// the third part goes through a product of its own.  Products of 16-bit values and their sums are exact
+// in fp32 up to the accumulation, as they were on the vector units.  The parts are bf16 for fp16 caches
+// too: fp16 parts run out of exponent 2^-39 below the maximum, so that a weight of 2^-28 kept 11 bits
+// and an infinite value row behind a smaller one gave 0 * inf.  An fp16 value is exactly the sum of a
+// bf16 value of its upper 8 bits and one of the lower 3, so its product takes two instructions, and P
+// travels multiplied by 2^64, which leaves the parts of the smallest weight above the bf16 range's end.
 //
 // The vector form before this one (16 lanes per row, a dot product and two fused multiply-adds
 // per element and head) issued 130 instructions per four rows at g = 4 and 240 at g = 8, which
@@ -331,21 +334,24 @@ __device__ __forceinline__ floatx4 mfma16(u32x4 a, u32x4 b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-template <bool F16> constexpr float P_SCALE = F16 ? 32768.0f : 1.0f;
+template <bool F16> constexpr float P_SCALE = F16 ? 0x1p64f : 1.0f;    // (|V| < 2^16, 2^31 rows: below the fp32 range's end)
+constexpr float LOW_MAX = 1024.0f;             // above the lower 3 bits of any finite fp16 value
 
-// The 16-bit value that x is cut to, back in 32 bits, where `on`; 0 elsewhere.
-template <bool F16> __device__ __forceinline__ float cut(float x, bool on) {
-  if constexpr (F16) return on ? (float)(_Float16)x : 0.0f;
-  else return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) & (on ? 0xffff0000u : 0u));
+// The bf16 value that x is cut to, back in 32 bits, where `on`; 0 elsewhere.
+__device__ __forceinline__ float cut(float x, bool on) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) & (on ? 0xffff0000u : 0u));
 }
-// x0 and x1 cut to 16 bits, x0 in the lower half of the word.
-template <bool F16> __device__ __forceinline__ unsigned pack(float x0, float x1) {
-  if constexpr (F16)
-    return (unsigned)__builtin_bit_cast(unsigned short, (_Float16)x0) |
-           ((unsigned)__builtin_bit_cast(unsigned short, (_Float16)x1) << 16);
-  else
-    return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, x1), __builtin_bit_cast(unsigned, x0), 0x07060302u);
+// x0 and x1 cut to bf16, x0 in the lower half of the word.
+__device__ __forceinline__ unsigned pack(float x0, float x1) {
+  return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, x1), __builtin_bit_cast(unsigned, x0), 0x07060302u);
 }
+// The upper (odd) or lower half of a word of two fp16 values.
+__device__ __forceinline__ float half_of(unsigned w, bool odd) {
+  return (float)__builtin_bit_cast(_Float16, (unsigned short)(odd ? w >> 16 : w & 0xffffu));
+}
+// What the cut leaves of an fp16 value in 32 bits.  Of an infinity (whose difference is a NaN) some
+// finite number: the upper part alone makes the product infinite.
+__device__ __forceinline__ float low_part(float x) { return fminf(x - cut(x, true), LOW_MAX); }
 
 // Where a workgroup's result goes: partial results for the merge kernel, or (WHOLE, one workgroup per
 // segment) straight to the caller.
@@ -509,28 +515,40 @@ __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       float x0 = p[2 * k], x1 = p[2 * k + 1];
-      x0 -= cut<F16>(x0, part >= 1);
-      x1 -= cut<F16>(x1, part >= 1);
+      x0 -= cut(x0, part >= 1);
+      x1 -= cut(x1, part >= 1);
       if (!THIRD) {
-        x0 -= cut<F16>(x0, part >= 2);
-        x1 -= cut<F16>(x1, part >= 2);
+        x0 -= cut(x0, part >= 2);
+        x1 -= cut(x1, part >= 2);
       }
-      pa[k] = pack<F16>(x0, x1);
+      pa[k] = pack(x0, x1);
       if (THIRD) {
         float y0 = p[2 * k], y1 = p[2 * k + 1];
-        y0 -= cut<F16>(y0, true); y1 -= cut<F16>(y1, true);
-        y0 -= cut<F16>(y0, true); y1 -= cut<F16>(y1, true);
-        pc[k] = pack<F16>(y0, y1);
+        y0 -= cut(y0, true); y1 -= cut(y1, true);
+        y0 -= cut(y0, true); y1 -= cut(y1, true);
+        pc[k] = pack(y0, y1);
       }
     }
 #pragma unroll
     for (int e = 0; e < VC; ++e) {
-      u32x4 vb;
+      u32x4 vb, vl;
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        vb[k] = __builtin_amdgcn_perm(vv[2 * k + 1][e / 2], vv[2 * k][e / 2], (e & 1) ? 0x07060302u : 0x05040100u);
-      acc[e] = mfma16<F16>(pa, vb, acc[e]);
-      if (THIRD) acc3[e] = mfma16<F16>(pc, vb, acc3[e]);
+      for (int k = 0; k < 4; ++k) {
+        const unsigned w0 = vv[2 * k][e / 2], w1 = vv[2 * k + 1][e / 2];
+        if constexpr (F16) {
+          const float x0 = half_of(w0, e & 1), x1 = half_of(w1, e & 1);
+          vb[k] = pack(x0, x1);
+          vl[k] = pack(low_part(x0), low_part(x1));
+        } else {
+          vb[k] = __builtin_amdgcn_perm(w1, w0, (e & 1) ? 0x07060302u : 0x05040100u);
+        }
+      }
+      acc[e] = mfma16<false>(pa, vb, acc[e]);
+      if (THIRD) acc3[e] = mfma16<false>(pc, vb, acc3[e]);
+      if constexpr (F16) {
+        acc[e] = mfma16<false>(pa, vl, acc[e]);
+        if (THIRD) acc3[e] = mfma16<false>(pc, vl, acc3[e]);
+      }
     }
   }
 

@@ -79,3 +79,40 @@ def test_decode_values_at_the_ends_of_the_range(dt, tiny, g):
     assert torch.all(got[:, 17] == float("inf")) and torch.all(got[:, 18] == float("-inf"))
     keep = [e for e in range(128) if e not in (17, 18)]
     assert torch.isfinite(got[:, keep]).all()
+
+
+@pytest.mark.parametrize("longer", [0, 900], ids=["whole", "split"])
+@pytest.mark.parametrize("g", [1, 4, 8])
+@pytest.mark.parametrize("dt,d", [(torch.float16, 64), (torch.float16, 128), (torch.bfloat16, 128)])
+def test_decode_small_weights_keep_their_bits(dt, d, g, longer):
+    """Rows far below the maximum of their tile (2^-11 to 2^-109 of it) decide the result where the rows
+    at the maximum hold zeros: every weight has 24 bits, and an infinite value behind a small one still
+    gives the infinity.  Bound: a weight is exp2 of an exponent of up to 110 that was rounded to 2^-24 of
+    itself three times (logit, scaling, maximum), 110 ln 2 * 3 * 2^-24 = 1.4e-5 of it, and some 2^-22 for
+    the sums; stated against the sum of |weight * value|."""
+    levels = [8.0, 14.0, 20.0, 30.0, 45.0, 70.0]
+    print("decode small weights", dt, d, g, longer, flush=True)
+    wl, _, Kc, Vc, cu, lens = _cache(dt, d, g, [97 + longer + 5 * i for i in range(len(levels))], 1, seed=9)
+    layer = adakv.Layer(dt, wl.h_q, wl.h_kv, d, wl.w, 7, 0.2, wl.n, wl.B, scale=1.0)
+    q = torch.zeros((1, wl.h_q, d), dtype=dt, device=DEV)
+    q[:, :, 0] = 1.0
+    q[:, 1::2, 0] = 0.75
+    for s, level in enumerate(levels):
+        a, L = int(cu[s]) + s, int(lens[s])
+        r = torch.arange(L, device=DEV)
+        Kc[a:a + L, 0] = torch.where(r % 16 == 0, 0.0, -(level + 0.25 * (r % 7))).to(dt)
+        Vc[a:a + L] = torch.where((r % 16 == 0)[:, None], 0.0, 100.0 * Vc[a:a + L].float()).to(dt)
+    out, lse = adakv.decode_attn(layer, q, cu, 1, Kc, Vc, lens, want_lse=True)
+    args = (cu.cpu().numpy(), 1, lens.cpu().numpy(), g)
+    ref, ref_lse = D.decode_attention(to_f64(q), to_f64(Kc), to_f64(Vc), *args, scale=1.0)
+    mass, _ = D.decode_attention(to_f64(q), to_f64(Kc), np.abs(to_f64(Vc)), *args, scale=1.0)
+    err = np.abs(to_f64(out) - ref) / mass
+    print("  worst error", err.max(), flush=True)
+    assert err.max() <= 2e-5
+    assert np.abs(to_f64(lse) - ref_lse).max() <= 2e-5
+    s = levels.index(30.0)
+    a = int(cu[s]) + s
+    Vc[a + 5, 7], Vc[a + 38, 8] = float("inf"), float("-inf")
+    got = adakv.decode_attn(layer, q, cu, 1, Kc, Vc, lens)[0, s * g:(s + 1) * g].cpu()
+    assert torch.all(got[:, 7] == float("inf")) and torch.all(got[:, 8] == float("-inf"))
+    assert torch.isfinite(got[:, [e for e in range(d) if e not in (7, 8)]]).all()
