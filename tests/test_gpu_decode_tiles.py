@@ -116,3 +116,28 @@ def test_decode_small_weights_keep_their_bits(dt, d, g, longer):
     got = adakv.decode_attn(layer, q, cu, 1, Kc, Vc, lens)[0, s * g:(s + 1) * g].cpu()
     assert torch.all(got[:, 7] == float("inf")) and torch.all(got[:, 8] == float("-inf"))
     assert torch.isfinite(got[:, [e for e in range(d) if e not in (7, 8)]]).all()
+
+
+@pytest.mark.parametrize("longer", [0, 900], ids=["whole", "split"])
+@pytest.mark.parametrize("g", [2, 8])
+@pytest.mark.parametrize("dt,d", [(torch.float16, 64), (torch.bfloat16, 128)])
+def test_decode_infinite_value_in_the_last_row(dt, d, g, longer):
+    """The last row of a segment, held or appended by the call, is repeated in the places behind it when a
+    tile is not full; an infinite value there gives the infinity in its column and touches no other."""
+    print("decode last row", dt, d, g, longer, flush=True)
+    lengths = [longer + v for v in (1, 2, 17, 31, 33, 45, 64, 96)]
+    _, layer, Kc, Vc, cu, lens = _cache(dt, d, g, lengths, 1, seed=21)
+    q, kn, vn = synth.decode_inputs(synth.small_workload(g * len(lengths), len(lengths), d, 1, 7, [8], [len(lengths)], dtype=dt, seed=21),
+                                    1, seed=21, device=DEV)
+    rest = [e for e in range(d) if e not in (3, 4)]
+    for s in range(len(lengths)):
+        a = int(cu[s]) + s + lengths[s] - 1
+        Vc[a, 3], Vc[a, 4] = float("inf"), float("-inf")
+    out = adakv.decode_attn(layer, q[0], cu, 1, Kc, Vc, lens).cpu()
+    assert torch.all(out[..., 3] == float("inf")) and torch.all(out[..., 4] == float("-inf"))
+    assert torch.isfinite(out[..., rest]).all()
+    Vc[torch.isinf(Vc)] = 0.0
+    vn[0, ..., 3], vn[0, ..., 4] = float("inf"), float("-inf")
+    out = adakv.decode_step(layer, q[0], kn[0], vn[0], cu, 1, Kc, Vc, lens).cpu()
+    assert torch.all(out[..., 3] == float("inf")) and torch.all(out[..., 4] == float("-inf"))
+    assert torch.isfinite(out[..., rest]).all()
