@@ -141,3 +141,32 @@ def test_decode_infinite_value_in_the_last_row(dt, d, g, longer):
     out = adakv.decode_step(layer, q[0], kn[0], vn[0], cu, 1, Kc, Vc, lens).cpu()
     assert torch.all(out[..., 3] == float("inf")) and torch.all(out[..., 4] == float("-inf"))
     assert torch.isfinite(out[..., rest]).all()
+
+
+# per sequence the rows of its heads; head-room; head dimension; one workgroup per segment
+ROUTES = [
+    ([[64] * 4], 256, 128, True),
+    ([[2040, 8, 8, 8]] + [[50] * 4] * 7, 16, 128, False),     # short on average, one long segment
+    ([[500] * 4] + [[20] * 4] * 7, 16, 128, False),           # one sequence whose heads may be long
+    ([[464, 100, 100, 100]], 16, 128, True),                  # 748 + 4 + 16 rows at most
+    ([[465, 100, 100, 100]], 16, 128, False),                 # one more
+    ([[465, 100, 100, 100]], 16, 64, True),                   # half the bytes
+    ([[128] * 4], 256, 128, True),
+    ([[129] * 4], 256, 128, False),                           # more than 384 rows of capacity on average
+]
+
+
+@pytest.mark.parametrize("rows,hr,d,whole", ROUTES)
+def test_one_workgroup_per_segment_only_where_no_segment_can_be_long(rows, hr, d, whole):
+    h, g, w = 4, 2, 4
+    print("decode routes", rows[0], len(rows), hr, d, flush=True)
+    wl = synth.small_workload(g * h, h, d, w, 7, [4000] * len(rows), [sum(r) for r in rows], dtype=torch.bfloat16, seed=5)
+    layer = adakv.Layer.from_workload(wl)
+    Kc, Vc, cu, lens = synth.ragged_cache(wl, [v - w for r in rows for v in r], hr, seed=5, device=DEV)
+    q, kn, vn = synth.decode_inputs(wl, 1, seed=5, device=DEV)
+    with adakv.KernelTrace(16) as tr:
+        out, lse = adakv.decode_step(layer, q[0], kn[0], vn[0], cu, hr, Kc, Vc, lens, want_lse=True)
+    torch.cuda.synchronize()
+    assert [n for n, _ in tr.durations_us()] == ["decode_attn"] + ([] if whole else ["decode_combine"])
+    ref_out, ref_lse = D.decode_attention(to_f64(q[0]), to_f64(Kc), to_f64(Vc), cu.cpu().numpy(), hr, lens.cpu().numpy(), g)
+    _assert_decode_close(out, lse, ref_out, ref_lse, float(Vc.float().abs().max()), f"{rows[0]}")
