@@ -443,8 +443,7 @@ __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
       for (int j = 0; j < 8; ++j)
         vv[j] = *reinterpret_cast<const vword *>(vt + (unsigned)((16 * (j / 4) + 4 * lg + j % 4) * ROWB + vcol));
     } else {
-      // rows past the end repeat the block's last one and are masked: their logits below, their values
-      // here, since a weight of 0 times an infinite value would be a NaN; the appended row comes from
+      // rows past the end repeat the block's last one (and are masked below); the appended row comes from
       // k_new / v_new, its place in the cache is not written yet, and the lanes it falls to store it
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -461,7 +460,6 @@ __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
         const int r = t0 + 16 * (j / 4) + 4 * lg + j % 4, rr = min(r, r1 - 1);
         const char *src = rr == new_row ? vn : Vb + (long long)rr * ROWB;
         vv[j] = *reinterpret_cast<const vword *>(src + vcol);
-        if (r >= r1) vv[j] = vword{0};
         if (r == new_row) *reinterpret_cast<vword *>(Vb + (long long)r * ROWB + vcol) = vv[j];
       }
     }
@@ -481,9 +479,11 @@ __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
       for (int i = 0; i < 4; ++i) sc[4 * t + i] = a[0][i];
     }
     if (edge) {
+      // the values too: a weight of 0 times an infinite one would be a NaN (here and not between the
+      // loads, where every one of them would be waited for: 64 segments of 1500 rows 15.7 -> 17.7 us)
 #pragma unroll
       for (int j = 0; j < 8; ++j)
-        if (t0 + 16 * (j / 4) + 4 * lg + j % 4 >= r1) sc[j] = -INFINITY;
+        if (t0 + 16 * (j / 4) + 4 * lg + j % 4 >= r1) { sc[j] = -INFINITY; vv[j] = vword{0}; }
     }
     float top = sc[0];
 #pragma unroll
