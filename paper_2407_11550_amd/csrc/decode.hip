@@ -101,8 +101,8 @@ __device__ __forceinline__ int scan_blocks(int nseg, int per, int split, int hea
   return before + inc - mine;
 }
 
-// The thread whose run holds this workgroup's segment writes it to sh[16..20] (segment, split, rows,
-// first row, 1 if the last row is the one the call appends).  The merge kernel finds a segment's
+// The thread whose run holds this workgroup's segment writes it to sh[16..21] (segment, split, rows,
+// first row, 1 if the last row is the one the call appends, splits of the segment).  The merge kernel finds a segment's
 // partial results through seg_tab; the launch has at least one workgroup per segment, and workgroup
 // s files the entry of segment s.
 __device__ __forceinline__ void find_block(int excl, int nseg, int per, int split, int headroom, int grow,
@@ -120,6 +120,7 @@ __device__ __forceinline__ void find_block(int excl, int nseg, int per, int spli
       sh[18] = now;
       sh[19] = cu[s];
       sh[20] = appended;
+      sh[21] = nb;
     }
     if (s == (int)blockIdx.x) seg_tab[s] = make_int4(first, nb, now, appended);
     first += nb;
@@ -376,7 +377,7 @@ __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
   constexpr bool THIRD = G == 8;               // the last part has accumulators of its own
   typedef unsigned int vword __attribute__((ext_vector_type(VC / 2)));
 
-  __shared__ int sh_scan[24];                  // [0..15] the prefix sum's wavefront totals, [16..20] results
+  __shared__ int sh_scan[24];                  // [0..15] the prefix sum's wavefront totals, [16..21] results
   __shared__ __align__(16) float sh_acc[NW][PARTS * G][D];
   __shared__ __align__(16) float sh_third[THIRD ? NW : 1][THIRD ? G : 1][THIRD ? D : 1];
   __shared__ float sh_m[NW][G], sh_l[NW][G];
@@ -404,8 +405,14 @@ __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
     len = __builtin_amdgcn_readfirstlane(sh_scan[18]);
     cu_s = __builtin_amdgcn_readfirstlane(sh_scan[19]);
     new_row = __builtin_amdgcn_readfirstlane(sh_scan[20]) ? len - 1 : -1;
-    r0 = __builtin_amdgcn_readfirstlane(sh_scan[17]) * split;
-    r1 = min(len, r0 + split);
+    // The segment's rows in equal parts, in whole tiles: the call lasts as long as its longest workgroup,
+    // and with `split` rows for all but the last one 1024 rows were cut into 896 + 128 (40 sequences x 8
+    // heads of as many rows, d = 128, g = 4: 42.9 us, now 34.7; the vector kernel's 832 + 192 at g = 1: 37.4,
+    // 40.4 with this one, now 33.0).  A part is `split` at most, and none is empty.
+    const int parts = __builtin_amdgcn_readfirstlane(sh_scan[21]);
+    const int rows = __builtin_amdgcn_readfirstlane(((len + parts - 1) / parts + TR - 1) / TR * TR);
+    r0 = __builtin_amdgcn_readfirstlane(sh_scan[17]) * rows;
+    r1 = min(len, r0 + rows);
   }
   const long long seg_byte = ((long long)cu_s + (long long)s * headroom) * ROWB;
   char *Kb = Kc + seg_byte;
@@ -772,14 +779,16 @@ DecodePlan plan_decode(const SeqTab &st, const Dims &dm, int dtype, int headroom
   // chip), two of the 16-bit kernel for g = 8 at d = 128, whose third part of P takes 32 more
   // registers (134 MB cache: 35.2 us with 500 workgroups, 41.0 with 752, 39.7 with 1500; at g = 4,
   // 49 MB: 17.6, 16.2, 18.2).  The split is a multiple of one round of the workgroup's loads: 128
-  // rows in the 16-bit kernels, four wavefronts of 32 (16.2 us against 17.2 with multiples of 64),
-  // 64 rows in the fp32 kernel and for caches so small that there are workgroups to spare.
+  // rows in the 16-bit kernels, four wavefronts of 32 (16.2 us against 17.2 with multiples of 64), but of
+  // half a round beyond two (segments of 4096 rows on average, uneven, 448 against 512: d = 128, g = 4
+  // 28.3 | 30.2, d = 64 18.9 | 20.0; all of them 4096: 27.7 | 27.7, 18.6 | 17.4); 64 rows in the fp32
+  // kernel and for caches so small that there are workgroups to spare.
   const bool mfma = dtype != ADAKV_FP32;
   const long long round_wgs = mfma && dm.g == 8 && dm.d == 128 ? 500 : 752;
   const long long room = round_wgs - nseg;                   // the segments' last, partial splits
   long long want = room > 64 ? (cap + room - 1) / room : cap / 512;
   if (want < 64) want = 64;
-  const int unit = mfma && want > 64 ? 128 : 64;
+  const int unit = mfma && want > 64 && want <= 256 ? 128 : 64;
   const int split = (int)((want + unit - 1) / unit * unit);
   // One workgroup of eight wavefronts per segment, and no merge kernel, where no segment can be long.
   // Heads are budgeted unevenly, so the line is drawn at the longest segment that the layer allows (one
