@@ -59,6 +59,29 @@ template <> struct Elem<float> {
   }
 };
 
+template <> struct Elem<unsigned short> {     // bf16
+  static constexpr int EPL = 8;
+  static __device__ __forceinline__ void widen(u32x4 v, float (&f)[8]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned int word = v[i];
+      f[2 * i] = __builtin_bit_cast(float, word << 16);
+      f[2 * i + 1] = __builtin_bit_cast(float, word & 0xffff0000u);
+    }
+  }
+};
+template <> struct Elem<f16_t> {
+  static constexpr int EPL = 8;
+  static __device__ __forceinline__ void widen(u32x4 v, float (&f)[8]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned int word = v[i];
+      f[2 * i] = (float)__builtin_bit_cast(_Float16, (unsigned short)(word & 0xffffu));
+      f[2 * i + 1] = (float)__builtin_bit_cast(_Float16, (unsigned short)(word >> 16));
+    }
+  }
+};
+
 // Rows of segment s this call works on: the rows held, plus the row the call itself appends
 // (`grow` = 1) if the segment has room for it.
 __device__ __forceinline__ int rows_held(const int *cu, const int *seg_len, int s, int headroom,
@@ -151,7 +174,7 @@ __global__ __launch_bounds__((256 * HeadSplit<T, G>::NGRP)) void decode_attn_ker
   constexpr int NT = 256 * NGRP;
   constexpr int U = 4;                         // row loads in flight per lane, for K and for V
 
-  __shared__ int sh_scan[24];                  // [0..15] the prefix sum's wavefront totals, [16..20] results
+  __shared__ int sh_scan[24];                  // [0..15] the prefix sum's wavefront totals, [16..21] results
   __shared__ float sh_acc[NW][G][D];
   __shared__ float sh_m[NW][G], sh_l[NW][G];
 
@@ -171,7 +194,10 @@ __global__ __launch_bounds__((256 * HeadSplit<T, G>::NGRP)) void decode_attn_ker
   __syncthreads();
   const int s = sh_scan[16], j = sh_scan[17], len = sh_scan[18];
   const int b = s / h, c = s % h;
-  const int r0 = j * split, r1 = min(len, r0 + split);
+  // (equal parts of the segment, as in decode_mfma_kernel, in the 64 rows of a split's unit)
+  const int parts = __builtin_amdgcn_readfirstlane(sh_scan[21]);
+  const int part = ((__builtin_amdgcn_readfirstlane(len) + parts - 1) / parts + 63) / 64 * 64;
+  const int r0 = j * part, r1 = min(len, r0 + part);
   const int new_row = sh_scan[20] ? len - 1 : -1;
   const long long seg_byte = ((long long)sh_scan[19] + (long long)s * headroom) * ROWB + col * 16;
   char *Kb = Kc + seg_byte;
@@ -243,6 +269,7 @@ __global__ __launch_bounds__((256 * HeadSplit<T, G>::NGRP)) void decode_attn_ker
         }
       }
       float vf[EPL];
+      if (it == iters - 1 && !ok[u]) vv[u] = u32x4{0};         // (a weight of 0 times an infinite value would be a NaN)
       Elem<T>::widen(vv[u], vf);
 #pragma unroll
       for (int gi = 0; gi < GW; ++gi) {
@@ -714,14 +741,15 @@ void run_decode(const SeqTab &st, const Dims &dm, int headroom, const DecodePlan
   float *part_acc = (float *)(ws + pl.part_acc);
   float *part_ml = (float *)(ws + pl.part_ml);
   int4 *seg_tab = (int4 *)(ws + pl.seg_tab);
-  if constexpr (sizeof(T) == 4) {
-    ADAKV_LAUNCH("decode_attn", (decode_attn_kernel<T, D, G>), dim3(pl.nblk),
-                 dim3(256 * HeadSplit<T, G>::NGRP), s, nseg,
-                 dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E, (const T *)q,
-                 (const char *)k_new, (const char *)v_new, cu, (const int *)seg_len, (char *)Kc,
-                 (char *)Vc, part_acc, part_ml, seg_tab);
-  } else {
-    constexpr bool F16 = std::is_same<T, f16_t>::value;
+  constexpr bool F16 = std::is_same<T, f16_t>::value;
+  // The matrix kernel multiplies 16 operand rows whatever the group, so with one head per KV head, and for
+  // fp16 (two products per value) with two of 128 columns, the vector kernel is the faster one.  us per
+  // step, vector | matrix, d = 128: 64 uneven segments of 4096 rows on average, 64 of 1500, 320 of 1024:
+  //   bf16, g = 1   26.8 | 27.2   14.0 | 15.2   31.6 | 33.1      g = 2   30.6 | 29.9   15.0 | 15.0   33.6 | 33.2
+  //   fp16, g = 1   26.4 | 29.2   13.7 | 14.9   31.2 | 35.5      g = 2   28.7 | 29.6   15.2 | 15.0   33.5 | 35.9
+  // fp16, g = 2, d = 64: 20.1 | 19.5   11.7 | 11.3   22.5 | 22.2.
+  constexpr bool VECTOR = sizeof(T) == 4 || G == 1 || (F16 && G == 2 && D == 128);
+  if constexpr (sizeof(T) == 2) {
     const DecodeOut res = {part_acc, part_ml, seg_tab, out, lse, k_new ? seg_len : nullptr, overflow};
     if (pl.whole) {
       ADAKV_LAUNCH("decode_attn", (decode_mfma_kernel<F16, D, G, true>), dim3(nseg), dim3(512), s, nseg, dm.h_kv,
@@ -729,10 +757,15 @@ void run_decode(const SeqTab &st, const Dims &dm, int headroom, const DecodePlan
                    (const char *)v_new, cu, (const int *)seg_len, (char *)Kc, (char *)Vc, res);
       return;
     }
-    ADAKV_LAUNCH("decode_attn", (decode_mfma_kernel<F16, D, G, false>), dim3(pl.nblk), dim3(256), s, nseg,
-                 dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E, (const unsigned short *)q,
-                 (const char *)k_new, (const char *)v_new, cu, (const int *)seg_len, (char *)Kc, (char *)Vc, res);
+    if constexpr (!VECTOR)
+      ADAKV_LAUNCH("decode_attn", (decode_mfma_kernel<F16, D, G, false>), dim3(pl.nblk), dim3(256), s, nseg,
+                   dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E, (const unsigned short *)q, (const char *)k_new,
+                   (const char *)v_new, cu, (const int *)seg_len, (char *)Kc, (char *)Vc, res);
   }
+  if constexpr (VECTOR)
+    ADAKV_LAUNCH("decode_attn", (decode_attn_kernel<T, D, G>), dim3(pl.nblk), dim3(256 * HeadSplit<T, G>::NGRP), s,
+                 nseg, dm.h_kv, per, pl.split, headroom, dm.scale * LOG2E, (const T *)q, (const char *)k_new,
+                 (const char *)v_new, cu, (const int *)seg_len, (char *)Kc, (char *)Vc, part_acc, part_ml, seg_tab);
   // only a call that appends hands the lengths to the merge kernel for updating
   ADAKV_LAUNCH("decode_combine", (decode_combine_kernel<D, G>), dim3(nseg, G), dim3(1024), s,
                (const int4 *)seg_tab, k_new ? seg_len : nullptr, overflow, (const float *)part_acc,

@@ -119,8 +119,8 @@ def test_decode_small_weights_keep_their_bits(dt, d, g, longer):
 
 
 @pytest.mark.parametrize("longer", [0, 900], ids=["whole", "split"])
-@pytest.mark.parametrize("g", [2, 8])
-@pytest.mark.parametrize("dt,d", [(torch.float16, 64), (torch.bfloat16, 128)])
+@pytest.mark.parametrize("g", [1, 2, 8])
+@pytest.mark.parametrize("dt,d", [(torch.float16, 64), (torch.bfloat16, 128), (torch.float32, 128)])
 def test_decode_infinite_value_in_the_last_row(dt, d, g, longer):
     """The last row of a segment, held or appended by the call, is repeated in the places behind it when a
     tile is not full; an infinite value there gives the infinity in its column and touches no other."""
