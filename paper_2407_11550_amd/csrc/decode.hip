@@ -390,11 +390,12 @@ struct DecodeOut {
   int *new_len, *overflow;                     // null unless the call appends
 };
 
+// (seg_len is also written, through res.new_len: after the barrier, by the one workgroup that read it)
 template <bool F16, int D, int G, bool WHOLE>
 __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
     int nseg, int h, int per, int split, int headroom, float c_log2, const unsigned short *__restrict__ q,
     const char *__restrict__ k_new, const char *__restrict__ v_new, const int *__restrict__ cu,
-    const int *__restrict__ seg_len, char *Kc, char *Vc, DecodeOut res) {
+    const int *seg_len, char *Kc, char *Vc, DecodeOut res) {
   constexpr int NW = WHOLE ? 8 : 4;            // wavefronts that share the rows of a split
   constexpr int ROWB = D * 2;
   constexpr int KS = D / 32;                   // k-steps of the logits
