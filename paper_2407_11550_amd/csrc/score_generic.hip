@@ -107,6 +107,14 @@ constexpr int F32_POOL_MAX = 16;                       // largest pool radius th
 constexpr int F32_FUSE_CHUNKS = 32;                    // most partials of a row that sweep 2 combines itself
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+// The instruction gives 0 below 2^-126; this one goes down to the last subnormal (keys with weights that
+// small are still ordered by them).
+constexpr float EXP2_LOW = -126.0f;
+__device__ __forceinline__ float exp2_small(float x) {
+  const bool small = x < EXP2_LOW;
+  const float y = fast_exp2(small ? x + 24.0f : x);
+  return small ? y * 0x1p-24f : y;
+}
 
 // The 32 window rows r0 .. r0+31 travel memory -> registers (fetch) -> LDS as fp32 (store).  Rows
 // past R are fetched from row R-1; their products are never used.
@@ -286,9 +294,19 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
     } else {
       if (COMBINE) __syncthreads();                    // the log-sum-exp above; and the slices have been read
       // acc[i]: window row ib*32 + 8*(i/4) + 4*half + i%4, key k0 + wv*32 + l32
+      float low = 0.0f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        total += fast_exp2(fmaf(acc[i], c_log2, -sh_l2[cur][8 * (i / 4) + 4 * half + i % 4]));
+      for (int i = 0; i < 16; ++i) {
+        acc[i] = fmaf(acc[i], c_log2, -sh_l2[cur][8 * (i / 4) + 4 * half + i % 4]);
+        low = fminf(low, acc[i]);
+      }
+      if (__any(low < EXP2_LOW)) {                     // weights below the normal range (or padding rows)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) total += exp2_small(acc[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) total += fast_exp2(acc[i]);
+      }
     }
     if (more) {
       rb.store(qs[cur ^ 1]);

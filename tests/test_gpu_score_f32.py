@@ -70,3 +70,27 @@ def test_fp32_scoring_at_the_edges_of_its_split(case, given_lse):
     assert tol < 2e-3 and np.all(got[layer.num_scores:] == -7.0)
     err = np.abs(got[:layer.num_scores] - want) / want
     assert err.max() <= tol, (err.max(), tol)
+
+
+@pytest.mark.parametrize("given_lse", [False, True], ids=["sweep", "row_lse"])
+@pytest.mark.parametrize("w,n", [(16, 300), (5, 300), (16, 5000)])       # 32 rows; 10; statistics combined by a kernel
+def test_weights_below_the_normal_range_keep_their_order(w, n, given_lse):
+    """One key takes all of the softmax, the others' weights are exp(-87.5) to exp(-102.5), 2^-126 to 2^-148:
+    scores of subnormal weights, not ties at zero.  A weight's exponent of up to 148 is rounded to 2^-24 of
+    itself in the logit, the scaling and the log-sum-exp, 148 ln 2 * 3 * 2^-24 = 1.8e-5 of the weight, and
+    a subnormal sum, mean and conversion to half a unit of 2^-149 each."""
+    print("fp32 small weights", w, n, given_lse, flush=True)
+    h, g, d = 2, 2, 64
+    rng = np.random.default_rng(n + w)
+    K = torch.zeros((n + w, h, d), device=DEV)
+    K[:, :, 0] = torch.from_numpy(-(87.5 + 15 * rng.random((n + w, h))).astype(np.float32)).to(DEV)
+    K[n // 2, :, 0] = 0.0
+    q = torch.zeros((1, g * h, w, d), device=DEV)
+    q[..., 0] = 1.0
+    layer = adakv.Layer(torch.float32, g * h, h, d, w, 1, 0.2, [n], [h * w], scale=1.0)
+    lse = torch.zeros((1, g * h, w), device=DEV) if given_lse else None      # (the dominant key's logit is 0)
+    got = adakv.score(layer, q, K, row_lse=lse).cpu().numpy().astype(np.float64).reshape(h, n)
+    x = K[:n, :, 0].double().cpu().numpy().T
+    want = np.exp(x) if given_lse else np.exp(x) / np.exp(x).sum(axis=1, keepdims=True)
+    assert np.all(np.abs(got - want) <= 3e-5 * want + 2 * 2.0 ** -149)
+    assert np.all(got[want > 3 * 2.0 ** -149] > 0)
