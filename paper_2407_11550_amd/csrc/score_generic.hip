@@ -117,7 +117,7 @@ __device__ __forceinline__ float exp2_small(float x) {
 }
 
 // The 32 window rows r0 .. r0+31 travel memory -> registers (fetch) -> LDS as fp32 (store).  Rows
-// past R are fetched from row R-1; their products are never used.
+// past R are fetched from row R-1; their products are left out of every result.
 template <typename T, int D, int NT>
 struct RowBlock {
   static constexpr int P = Elem<T>::PER16;
@@ -300,9 +300,12 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
         acc[i] = fmaf(acc[i], c_log2, -sh_l2[cur][8 * (i / 4) + 4 * half + i % 4]);
         low = fminf(low, acc[i]);
       }
-      if (__any(low < EXP2_LOW)) {                     // weights below the normal range (or padding rows)
+      if (ib * 32 + 32 > R || __any(low < EXP2_LOW)) {
+        // padding rows (row R-1 once more, and an infinite logit against their infinite log-sum-exp would
+        // be a NaN), or weights below the normal range
 #pragma unroll
-        for (int i = 0; i < 16; ++i) total += exp2_small(acc[i]);
+        for (int i = 0; i < 16; ++i)
+          total += ib * 32 + 8 * (i / 4) + 4 * half + i % 4 < R ? exp2_small(acc[i]) : 0.0f;
       } else {
 #pragma unroll
         for (int i = 0; i < 16; ++i) total += fast_exp2(acc[i]);

@@ -94,3 +94,22 @@ def test_weights_below_the_normal_range_keep_their_order(w, n, given_lse):
     want = np.exp(x) if given_lse else np.exp(x) / np.exp(x).sum(axis=1, keepdims=True)
     assert np.all(np.abs(got - want) <= 3e-5 * want + 2 * 2.0 ** -149)
     assert np.all(got[want > 3 * 2.0 ** -149] > 0)
+
+
+@pytest.mark.parametrize("w", [5, 16, 33])             # 10, 32 and 66 window rows
+def test_an_infinite_logit_gives_an_infinite_score(w):
+    """With the caller's log-sum-exp one infinite key is its own affair: an infinite weight in every row,
+    whether or not the rows fill their blocks of 32, and finite scores elsewhere."""
+    print("fp32 infinite logit", w, flush=True)
+    h, g, d, n = 2, 2, 64, 200
+    wl = synth.small_workload(g * h, h, d, w, 1, [n], [h * w], dtype=torch.float32, seed=3, temps=(0.25, 1.0))
+    q, K, _ = synth.generate(wl, device=DEV)
+    q[..., 0] = q[..., 0].abs() + 0.1
+    lse = synth.prefill_row_lse(wl, q, K)
+    layer = adakv.Layer.from_workload(wl)
+    clean = adakv.score(layer, q, K, row_lse=lse).reshape(h, n)
+    K[77, :, 0] = float("inf")
+    got = adakv.score(layer, q, K, row_lse=lse).reshape(h, n)
+    assert torch.all(got[:, 77] == float("inf"))
+    got[:, 77] = clean[:, 77]
+    assert torch.equal(got, clean)
