@@ -347,12 +347,14 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
       if (half == 0 && key < n) dst[key] = raw;
       return;
     }
-    // a key outside the sequence counts as weight 0, which never wins: its window is clipped
-    if (half == 0) sh_raw[wv * 32 + l32] = (key >= 0 && key < n) ? raw : 0.0f;
+    // (a window that leaves the sequence takes the key at its end more than once: the same maximum, and
+    // scores that are NaN stay so)
+    if (half == 0) sh_raw[wv * 32 + l32] = raw;
     __syncthreads();
+    const int lo = max(-k0, 0), hi = min(KEYS, n - k0) - 1;
     if (tid < own && k0 + r + tid < n) {
-      float m = sh_raw[tid];
-      for (int t = 1; t <= 2 * r; ++t) m = fmaxf(m, sh_raw[tid + t]);
+      float m = sh_raw[min(max(tid, lo), hi)];
+      for (int t = 1; t <= 2 * r; ++t) m = fmaxf(m, sh_raw[min(max(tid + t, lo), hi)]);
       dst[k0 + r + tid] = m;
     }
   }

@@ -113,3 +113,22 @@ def test_an_infinite_logit_gives_an_infinite_score(w):
     assert torch.all(got[:, 77] == float("inf"))
     got[:, 77] = clean[:, 77]
     assert torch.equal(got, clean)
+
+
+@pytest.mark.parametrize("k", [1, 7, 33, 35])          # no pool; in the sweep (radius 3, 16); in a kernel of its own
+@pytest.mark.parametrize("n", [[3, 40], [122, 129, 300]])
+def test_a_key_that_is_not_a_number_shows_in_every_score(k, n):
+    """A NaN key makes every row's log-sum-exp, and so every weight of its head, a NaN; the scores say so up
+    to the ends of the sequence, and the other heads are left alone."""
+    print("fp32 nan key", k, n, flush=True)
+    wl = synth.small_workload(4, 2, 64, 8, k, n, [2 * 8] * len(n), dtype=torch.float32, seed=5)
+    q, K, _ = synth.generate(wl, device=DEV)
+    layer = adakv.Layer.from_workload(wl)
+    clean = adakv.score(layer, q, K)
+    for b, nb in enumerate(n):
+        K[wl.tok_off[b] + nb // 2, 1, 5] = float("nan")
+    got, at = adakv.score(layer, q, K), 0
+    for nb in n:
+        assert torch.equal(got[at:at + nb], clean[at:at + nb])
+        assert torch.isnan(got[at + nb:at + 2 * nb]).all(), nb
+        at += 2 * nb
