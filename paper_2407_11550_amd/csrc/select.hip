@@ -1136,9 +1136,13 @@ hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, in
                        int *cu_seqlens, int *indices, char *ws, bool carried, hipStream_t s) {
   const int h = dm.h_kv, rows = st.out_off[st.batch], nseg = st.batch * h;
   const long long most = (long long)longest_row(st) * h;
-  // (every block repeats the layer scope: no more blocks than the chip holds at a time)
+  // Every block repeats the layer scope with a compute unit's whole issue rate (sixteen wavefronts), so there
+  // are no more of them than compute units; two on one take turns.  The whole step, us, block / the kernels
+  // that spread a scope over the chip, d = 64, 8 rows: 4 x 64 heads x 4096 88 / 88, on plateaus (scores in one
+  // 22-bit prefix, which every block streams) 160 / 160; 5 x 64 120 / 109, 262 / 188; 8 x 64 166 / 154, 311 / 234;
+  // 8 x 64 heads x 190 72 / 46; 32 x 8 x 1500 55 / 56; 64 x 8 x 1500 89 / 78.
   const bool in_block = most <= TOPK_BLOCK_MAX;
-  if (carried && nseg >= 4 && nseg <= 512 && (in_block || longest_row(st) <= TOPK_ROW_MAX)) {
+  if (carried && nseg >= 4 && nseg <= 256 && (in_block || longest_row(st) <= TOPK_ROW_MAX)) {
     const TopkBufs tb = bufs_of(ws, plan(st, dm));
     const ChunkTab ct = make_chunks(st, SEL_CHUNK);
     if (!in_block)

@@ -37,7 +37,7 @@ LAYERS = [
     (5, [16385]),                              # and one past it
     (2, [40000]),                              # beyond a block in either scope
     (64, [700, 1024]),
-    (64, [80] * 9),                            # 576 segments: more than one block per segment is given in adakv_compress
+    (64, [80] * 9),                            # 576 segments
 ]
 
 
@@ -76,7 +76,7 @@ STEPS = [
     (4, 4, 64, 2, [4097]),
     (4, 4, 64, 2, [8192, 5]),                  # the longest head of the one-launch head scope
     (4, 4, 64, 2, [8193]),
-    (32, 32, 64, 2, [70] * 17),                # 544 segments: a block per sequence would be repeated too often
+    (32, 32, 64, 2, [70] * 17),                # 544 segments: more blocks than compute units would repeat the layer scope
     (2, 2, 64, 2, [900]),                      # two segments
 ]
 
@@ -97,3 +97,30 @@ def test_whole_step(step, keep):
         assert_exact_on_scores(out, sc[soff:soff + h * n[b]], wl, K, V, b, seg0=b * h, row0=row0)
         row0 += B[b]
         soff += h * n[b]
+
+
+# 32 KV heads; prefix length, sequences, the Top-k kernels of the step
+MANY = [
+    (70, 8, ["topk_block"]),                                  # 256 segments: one block per compute unit
+    (70, 9, ["alloc_gather", "alloc_finish", "select_block"]),
+    (400, 8, ["alloc_gather", "topk_block"]),                 # 12 800 scores per sequence
+    (400, 9, ["alloc_gather", "alloc_finish", "select_block"]),
+]
+
+
+@pytest.mark.parametrize("n,nseq,kernels", MANY)
+def test_no_more_repeated_layer_scopes_than_compute_units(n, nseq, kernels):
+    """A block per segment that repeats the layer scope for itself only while there is a compute unit for each."""
+    print("topk many segments", n, nseq, flush=True)
+    h, w = 32, 2
+    B = [h * w + h * n // 20] * nseq
+    wl = synth.small_workload(h, h, 64, w, 7, [n] * nseq, B, seed=19)
+    q, K, V = synth.generate(wl, device=DEV)
+    layer = adakv.Layer.from_workload(wl)
+    with adakv.KernelTrace(64) as tr:
+        out = adakv.compress(layer, q, K, V)
+    torch.cuda.synchronize()
+    assert [k for k, _ in tr.durations_us() if k.split("_")[0] in ("topk", "alloc", "select")] == kernels
+    sc = out["scores"].cpu().numpy()
+    for b in range(nseq):
+        assert_exact_on_scores(out, sc[b * h * n:(b + 1) * h * n], wl, K, V, b, seg0=b * h, row0=b * B[0])
