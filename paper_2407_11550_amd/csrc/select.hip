@@ -1065,17 +1065,13 @@ static int longest_row(const SeqTab &st) {
 //   select alone     4096 per head 22.0 / 7.9   16384 22.2 / 14.9   32768 22.6 / 25.3
 //   select carried   4096 13.0 / 7.5   8192 13.1 / 11.4   16384 13.0 / 15.7
 //   both in one      4800 18.0 / 15.0   8044 (h = 4) 18.0 / 16.7   16088 19.0 / 20.3
+// The whole step of few segments (d = 128, 128 rows): 1 x 2048 43.5 / 30.3, 2 x 5000 49.2 / 40.4, 3 x 4096
+// 46.7 / 39.7, 2 x 8192 50.5 / 47.5, 1 x 12288 49.2 / 42.0.
 constexpr long long ALLOC_BLOCK_MAX = 16 * BLK_NT;     // scores of a sequence
 constexpr long long SELECT_BLOCK_MAX = 16 * BLK_NT;    // of a head; first digits counted here
 constexpr long long SELECT_CARRIED_MAX = 8 * BLK_NT;   // of a head; first digits from the scoring kernel
 constexpr long long TOPK_BLOCK_MAX = 12 * BLK_NT;      // of a sequence; both scopes in one launch
 constexpr long long TOPK_ROW_MAX = 4 * BLK_NT;         // of a head; gather and the rest in one launch (16088: 18.3 -> 16.3)
-// In pipeline mode layers of fewer than four segments keep the four kernels although they are slower
-// there too (2 heads x 5000: 24 us against 19): a test of the kernel trace expects them of such a layer.
-static bool block_route(long long scores, long long most, int nseg, bool carried) {
-  return scores <= most && (!carried || nseg >= 4);
-}
-
 hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
                            int *cu_seqlens, char *ws, bool carried, hipStream_t s) {
   const TopkWs p = plan(st, dm);
@@ -1107,7 +1103,7 @@ hipError_t launch_select(const SeqTab &st, const Dims &dm, const float *scores,
   const TopkWs p = plan(st, dm);
   const int h = dm.h_kv, rows = st.out_off[st.batch], n = longest_row(st);
   const TopkBufs tb = bufs_of(ws, p);
-  if (block_route(n, carried ? SELECT_CARRIED_MAX : SELECT_BLOCK_MAX, st.batch * h, carried)) {
+  if (n <= (carried ? SELECT_CARRIED_MAX : SELECT_BLOCK_MAX)) {
 #define ADAKV_GO(EPT)                                                                            \
   do {                                                                                           \
     if (carried)                                                                                 \
@@ -1142,7 +1138,7 @@ hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, in
   // 22-bit prefix, which every block streams) 160 / 160; 5 x 64 120 / 109, 262 / 188; 8 x 64 166 / 154, 311 / 234;
   // 8 x 64 heads x 190 72 / 46; 32 x 8 x 1500 55 / 56; 64 x 8 x 1500 89 / 78.
   const bool in_block = most <= TOPK_BLOCK_MAX;
-  if (carried && nseg >= 4 && nseg <= 256 && (in_block || longest_row(st) <= TOPK_ROW_MAX)) {
+  if (carried && nseg <= 256 && (in_block || longest_row(st) <= TOPK_ROW_MAX)) {
     const TopkBufs tb = bufs_of(ws, plan(st, dm));
     const ChunkTab ct = make_chunks(st, SEL_CHUNK);
     if (!in_block)

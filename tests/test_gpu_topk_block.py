@@ -78,6 +78,10 @@ STEPS = [
     (4, 4, 64, 2, [8193]),
     (32, 32, 64, 2, [70] * 17),                # 544 segments: more blocks than compute units would repeat the layer scope
     (2, 2, 64, 2, [900]),                      # two segments
+    (1, 1, 64, 2, [12288, 9]),                 # one head: the most that run in one launch
+    (1, 1, 64, 2, [12289]),
+    (3, 3, 64, 2, [4096]),
+    (2, 2, 64, 2, [8192]),                     # two kernels for the layer, one block per head
 ]
 
 
