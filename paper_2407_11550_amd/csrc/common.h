@@ -92,10 +92,11 @@ bool mfma_pool_rows_supported(const Dims &dm, int dtype);   // ADAKV_FLAG_POOL_T
 // ---- allocation and selection (select.hip) --------------------------------------------------
 // A score becomes a 32-bit key whose unsigned order is the float order (+0.0f turns -0 into +0;
 // non-negative floats order like their bit patterns, the general transform keeps the order for
-// negative inputs too).  The first radix digit is the key's top 11 bits.
+// negative inputs too).  The first radix digit is the key's top 11 bits.  Key 0 marks places past the end
+// of a row: no number has it, and the one pattern of a NaN that would (all bits set) shares key 1.
 __device__ __forceinline__ unsigned key_of(float x) {
   const unsigned u = __float_as_uint(x + 0.0f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return (u & 0x80000000u) ? max(~u, 1u) : (u | 0x80000000u);
 }
 
 // Pipeline mode (ADAKV_FLAG_PIPELINE): the scoring call clears the Top-k histograms and files

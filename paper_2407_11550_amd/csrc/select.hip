@@ -767,7 +767,7 @@ template <int NB> __device__ __forceinline__ Bins<NB> lds_bins(const unsigned *l
 }
 
 // Rounds past the last element are skipped (uniformly); places past it get key 0, which no score has
-// (a score is neither negative nor a NaN) and which is never above or at a threshold.
+// and which is never above or at a threshold.
 template <int EPT>
 __device__ __forceinline__ void load_keys(const float *__restrict__ row, int n, unsigned (&keys)[EPT]) {
   float x[EPT];

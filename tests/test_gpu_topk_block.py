@@ -128,3 +128,23 @@ def test_no_more_repeated_layer_scopes_than_compute_units(n, nseq, kernels):
     sc = out["scores"].cpu().numpy()
     for b in range(nseq):
         assert_exact_on_scores(out, sc[b * h * n:(b + 1) * h * n], wl, K, V, b, seg0=b * h, row0=b * B[0])
+
+
+@pytest.mark.parametrize("n", [600, 5000, 20000])      # both scopes in a block, the head scope, neither
+def test_scores_with_all_bits_set_are_positions_like_others(n):
+    """Memory that was filled with ones (a NaN, outside the contract) comes last, by position, and a budget
+    that takes everything still lists every position once."""
+    print("topk all bits set", n, flush=True)
+    h, w = 2, 3
+    bits = np.random.default_rng(n).random((h, n)).astype(np.float32).view(np.int32)
+    bits[:, ::3] = -1
+    flat = torch.from_numpy(bits.reshape(-1).copy()).to(DEV).view(torch.float32)
+    for keep in (n, n - n // 6):
+        layer = adakv.Layer(torch.bfloat16, h, h, 64, w, 7, 1.0, [n], [h * (w + keep)])
+        bud, cu = adakv.allocate(layer, flat)
+        assert bud.tolist() == [keep] * h
+        idx = torch.full((layer.num_rows_out,), -5, dtype=torch.int32, device=DEV)
+        adakv.select(layer, flat, bud, cu, indices=idx)
+        numbers = [j for j in range(n) if j % 3]
+        want = sorted(numbers + list(range(0, n, 3))[:keep - len(numbers)]) + list(range(n, n + w))
+        assert idx.cpu().tolist() == want * h
