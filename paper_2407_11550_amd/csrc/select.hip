@@ -1061,13 +1061,17 @@ static int longest_row(const SeqTab &st) {
 // Where one block per sequence or segment beats the kernels that spread a scope over the chip: a
 // block's passes cost it 0.4 to 0.6 us per 1024 scores, in one compute unit; a launch costs 4 us.
 // Sums of kernel times in us, spread-out kernels / block (w = 8, h = 8 unless said):
-//   allocate alone   4800 scores 20.0 / 10.6   16088 20.0 / 16.6
+//   allocate alone   4800 scores 20.0 / 10.6   16088 20.0 / 16.6; the counts per head make more heads dearer in
+//                    a block (us per call): h = 32 8192 scores 18.1 / 16.1, 12 288 17.8 / 18.3, 16 384 17.5 / 20.3,
+//                    h = 64 8192 19.9 / 20.2, 12 288 19.9 / 22.4 (with eight sequences 23.1 / 20.8, 23.2 / 23.3)
 //   select alone     4096 per head 22.0 / 7.9   16384 22.2 / 14.9   32768 22.6 / 25.3
 //   select carried   4096 13.0 / 7.5   8192 13.1 / 11.4   16384 13.0 / 15.7
 //   both in one      4800 18.0 / 15.0   8044 (h = 4) 18.0 / 16.7   16088 19.0 / 20.3
 // The whole step of few segments (d = 128, 128 rows): 1 x 2048 43.5 / 30.3, 2 x 5000 49.2 / 40.4, 3 x 4096
 // 46.7 / 39.7, 2 x 8192 50.5 / 47.5, 1 x 12288 49.2 / 42.0.
-constexpr long long ALLOC_BLOCK_MAX = 16 * BLK_NT;     // scores of a sequence
+constexpr long long alloc_block_max(int h) {           // scores of a sequence
+  return (h <= 8 ? 16 : h <= 32 ? 12 : 8) * BLK_NT;
+}
 constexpr long long SELECT_BLOCK_MAX = 16 * BLK_NT;    // of a head; first digits counted here
 constexpr long long SELECT_CARRIED_MAX = 8 * BLK_NT;   // of a head; first digits from the scoring kernel
 constexpr long long TOPK_BLOCK_MAX = 12 * BLK_NT;      // of a sequence; both scopes in one launch
@@ -1078,7 +1082,7 @@ hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores
   const int h = dm.h_kv;
   const TopkBufs tb = bufs_of(ws, p);
   const long long most = (long long)longest_row(st) * h;
-  if (!carried && most <= ALLOC_BLOCK_MAX) {
+  if (!carried && most <= alloc_block_max(h)) {
 #define ADAKV_GO(EPT)                                                                            \
   ADAKV_LAUNCH("alloc_block", (alloc_block_kernel<EPT>), dim3(st.batch), dim3(BLK_NT), s, st, h, dm.w, \
                dm.alpha_fix, scores, budgets, cu_seqlens)

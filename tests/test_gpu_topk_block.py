@@ -37,6 +37,8 @@ LAYERS = [
     (5, [16385]),                              # and one past it
     (2, [40000]),                              # beyond a block in either scope
     (64, [700, 1024]),
+    (16, [768]), (16, [769]),                  # 12 288 scores of more than eight heads in a block, and past it
+    (64, [128, 7]), (64, [129]),               # 8192 of more than 32
     (64, [80] * 9),                            # 576 segments
 ]
 
@@ -148,3 +150,18 @@ def test_scores_with_all_bits_set_are_positions_like_others(n):
         numbers = [j for j in range(n) if j % 3]
         want = sorted(numbers + list(range(0, n, 3))[:keep - len(numbers)]) + list(range(n, n + w))
         assert idx.cpu().tolist() == want * h
+
+
+@pytest.mark.parametrize("h,n,block", [(8, 2048, True), (8, 2049, False), (9, 1365, True), (9, 1366, False),
+                                       (32, 384, True), (32, 385, False), (33, 248, True), (33, 249, False)])
+def test_one_block_allocates_fewer_scores_the_more_heads_there_are(h, n, block):
+    print("alloc route", h, n, flush=True)
+    layer = adakv.Layer(torch.bfloat16, h, h, 64, 3, 7, 0.2, [n], [h * (3 + n // 9)])
+    scores = torch.rand(h * n, device=DEV)
+    with adakv.KernelTrace(16) as tr:
+        bud, _ = adakv.allocate(layer, scores)
+    torch.cuda.synchronize()
+    assert [k for k, _ in tr.durations_us()] == (["alloc_block"] if block else
+                                                 ["alloc_init", "alloc_pass0", "alloc_gather", "alloc_finish"])
+    want, _ = O.allocate(scores.cpu().numpy().reshape(h, n), layer.B[0], 3, 0.2)
+    assert np.array_equal(bud.cpu().numpy(), want)
