@@ -195,12 +195,18 @@ def _check_q(layer, q):
     _need(q, layer.batch * layer.h_q * layer.w * layer.d, "q_window")
 
 
+# torch's own functions for the current stream's handle: not part of its public interface, so they may be
+# missing in another version
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     """The handle of `stream`, or of the current device's current stream.  A decoding step is two short
     kernels, and making a Stream object for its handle alone took 1.5 of 15 us per call."""
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if stream is None and _current_raw_stream is not None and _current_device is not None:
+        return _current_raw_stream(_current_device())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _workspace(layer, ws):

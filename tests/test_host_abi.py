@@ -235,3 +235,22 @@ def test_binding_rejects_buffers_that_do_not_fit_the_layer(lib):
     with pytest.raises(ValueError, match="ws must be"):
         adakv.decode_attn(L, torch.zeros(1, 32, 128, dtype=bf), i32(9), 0, torch.zeros(320, 128, dtype=bf),
                           torch.zeros(320, 128, dtype=bf), i32(8), ws=torch.zeros(1 << 18, dtype=torch.int32))
+
+
+def test_current_stream_without_torch_private_functions(monkeypatch):
+    """The handle of the current stream comes from functions that torch does not promise; without them it
+    comes from the public Stream object."""
+    import types
+
+    import paper_2407_11550_amd.binding as B
+    asked = []
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: asked.append(1) or types.SimpleNamespace(cuda_stream=77))
+    for missing in ("_current_raw_stream", "_current_device"):
+        with monkeypatch.context() as m:
+            m.setattr(B, missing, None)
+            assert B._stream(None) == 77
+    assert len(asked) == 2
+    monkeypatch.setattr(B, "_current_raw_stream", lambda dev: 1000 + dev)
+    monkeypatch.setattr(B, "_current_device", lambda: 3)
+    assert B._stream(None) == 1003 and B._stream(types.SimpleNamespace(cuda_stream=5)) == 5
+    assert len(asked) == 2
