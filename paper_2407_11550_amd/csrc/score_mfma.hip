@@ -874,10 +874,12 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   //   rows    8000 keys      9600           11000          12500          14400          15800
   //    128   21.4 | 23.2   22.8 | 26.8    24.2 | 27.2    25.5 | 27.6    27.4 | 28.2    28.0 | 28.8
   //    256   25.8 | 30.1   28.8 | 36.0    30.4 | 36.5    33.2 | 36.9    36.0 | 38.2    37.8 | 39.0
-  // 4.1 us of two at 256 rows is the kernel that combines their statistics.  Without it sweep 1
-  // gains up to 12500 keys (15.4 -> 14.8) and sweep 2 only up to 11000 (17.2 -> 16.9; 17.4 -> 18.4
-  // at 12500), so where a sequence is short enough that sweep 2 combines either way the line is 384
-  // (eight sequences of 3200 to 484 keys, whole call, in two runs: 34.8 | 34.1).
+  // 4.1 us of two at 256 rows is the kernel that combines their statistics, so where a sequence is short
+  // enough that sweep 2 combines either way the two come closer, and at d = 64, where a workgroup's
+  // stream is half as long, they win: line at 384 there.  256 rows, 8 heads, 512 | 384:
+  //   keys        14000         16000       3200 .. 484    5000 4000 3000    7000 5000    6 x 2000
+  //   d = 64    27.5 | 26.7   29.5 | 28.6   27.6 | 26.2     25.9 | 25.4    25.9 | 25.2   26.0 | 25.4
+  //   d = 128   31.1 | 31.3   34.0 | 34.0   34.3 | 34.1     30.4 | 32.1    30.3 | 31.8   30.4 | 31.7
   const int unit = TILE * v.kg;
   auto shortest = [&](int from, long long wgs) {       // chunk of at least `from` keys that makes `wgs` workgroups at most
     int lo = from / unit, hi = most / unit;
@@ -890,7 +892,7 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   };
   int longest = 0;
   for (int b = 0; b < st.batch; ++b) longest = st.n[b] > longest ? st.n[b] : longest;
-  const int one = v.rs == 4 && (longest + 255ll) / 256 * R <= 8192 ? 384 : 512;
+  const int one = v.rs == 4 && dm.d == 64 && (longest + 255ll) / 256 * R <= 8192 ? 384 : 512;
   v.len = shortest(unit > 64 ? unit : 64, 256);
   if (v.len > one) {
     const long long rounds = (workgroups(st, dm, most) + slots - 1) / slots;
