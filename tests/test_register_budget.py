@@ -68,19 +68,20 @@ def score_kernels(lib):
 
 def test_two_wavefronts_per_simd_where_the_layout_counts_on_them(score_kernels):
     """The 128-row kernels (four wavefronts, two workgroups per compute unit) and the 256- and
-    512-row kernels, in both sweeps and both 16-bit types: at most 256 registers (vector plus
-    accumulation registers).  The row-pooling form of the weights sweep is known to need more on
-    d = 128 and is left out; so are the 32- and 64-row forms with four key groups, which are bound
-    by memory with one wavefront per SIMD as well."""
+    512-row kernels, in both sweeps and both 16-bit types, and the row-pooling form of the 128-row
+    weights sweep (which takes one row block at a time for it): at most 256 registers (vector plus
+    accumulation registers).  The row-pooling form of the 256- and 512-row kernels keeps both row
+    blocks in flight, needs more on d = 128 and is left out; so are the 32- and 64-row forms with
+    four key groups, which are bound by memory with one wavefront per SIMD as well."""
     checked = 0
     for (d, mb, rs, kg, chunk, sweep, f16, pool_rows), md in score_kernels.items():
-        if pool_rows or (mb, rs, kg) not in ((2, 2, 2), (2, 4, 1), (2, 8, 1)):
+        if (mb, rs, kg) not in (((2, 2, 2),) if pool_rows else ((2, 2, 2), (2, 4, 1), (2, 8, 1))):
             continue
-        assert md["vgpr"] + md["agpr"] <= 256, ((d, mb, rs, kg, chunk, sweep, f16), md)
+        assert md["vgpr"] + md["agpr"] <= 256, ((d, mb, rs, kg, chunk, sweep, f16, pool_rows), md)
         checked += 1
     # types x sweeps x (d = 128: four chunk lengths, 256 rows and 512 rows with two each;
-    # d = 64: the first six)
-    assert checked == 2 * 2 * (8 + 6)
+    # d = 64: the first six), and types x d x four chunk lengths of the row-pooling sweep
+    assert checked == 2 * 2 * (8 + 6) + 2 * 2 * 4
 
 
 def test_no_scoring_kernel_spills(score_kernels):
