@@ -194,7 +194,7 @@ __global__ __launch_bounds__((256 * HeadSplit<T, G>::NGRP)) void decode_attn_ker
   __syncthreads();
   const int s = sh_scan[16], j = sh_scan[17], len = sh_scan[18];
   const int b = s / h, c = s % h;
-  // (equal parts of the segment, as in decode_mfma_kernel, in the 64 rows of a split's unit)
+  // (equal parts of the segment, as in decode_mfma_kernel, in multiples of the split's own unit)
   const int parts = __builtin_amdgcn_readfirstlane(sh_scan[21]);
   const int part = ((__builtin_amdgcn_readfirstlane(len) + parts - 1) / parts + 63) / 64 * 64;
   const int r0 = j * part, r1 = min(len, r0 + part);
@@ -433,12 +433,13 @@ __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
     len = __builtin_amdgcn_readfirstlane(sh_scan[18]);
     cu_s = __builtin_amdgcn_readfirstlane(sh_scan[19]);
     new_row = __builtin_amdgcn_readfirstlane(sh_scan[20]) ? len - 1 : -1;
-    // The segment's rows in equal parts, in whole tiles: the call lasts as long as its longest workgroup,
-    // and with `split` rows for all but the last one 1024 rows were cut into 896 + 128 (40 sequences x 8
-    // heads of as many rows, d = 128, g = 4: 42.9 us, now 34.7; the vector kernel's 832 + 192 at g = 1: 37.4,
-    // 40.4 with this one, now 33.0).  A part is `split` at most, and none is empty.
+    // The segment's rows in equal parts, in whole rounds of the workgroup: the call lasts as long as its
+    // longest workgroup, and with `split` rows for all but the last one 1024 rows were cut into 896 + 128
+    // (40 sequences x 8 heads of as many rows, d = 128, g = 4: 42.9 us, now 34.7; the vector kernel's 832 + 192
+    // at g = 1: 37.4, 40.4 with this one, then 33.0).  None is empty.  (Whole tiles instead of rounds: 40 uneven
+    // segments of 900 rows 11.8 instead of 11.3 us, 320 of 400 rows 21.7 instead of 22.0.)
     const int parts = __builtin_amdgcn_readfirstlane(sh_scan[21]);
-    const int rows = __builtin_amdgcn_readfirstlane(((len + parts - 1) / parts + TR - 1) / TR * TR);
+    const int rows = min(split, __builtin_amdgcn_readfirstlane(((len + parts - 1) / parts + NW * TR - 1) / (NW * TR) * (NW * TR)));
     r0 = __builtin_amdgcn_readfirstlane(sh_scan[17]) * rows;
     r1 = min(len, r0 + rows);
   }

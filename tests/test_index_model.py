@@ -111,20 +111,21 @@ def test_interleaved_sets_of_sweep_one_cover_every_key_once(chunk_len, kg):
         assert interleaved_violations(n, chunk_len, kg) == 0, n
 
 
-def equal_parts(length, split):
+def equal_parts(length, split, unit):
     """The parts of a decode segment: as many as splits of `split` rows (a multiple of 64) would be, each
-    of the same number of 32-row tiles."""
+    of the same number of rows up to a multiple of `unit`, and no more than `split`."""
     parts = (length + split - 1) // split
-    rows = ((length + parts - 1) // parts + 31) // 32 * 32
+    rows = min(split, ((length + parts - 1) // parts + unit - 1) // unit * unit)
     return [(j * rows, min(length, j * rows + rows)) for j in range(parts)]
 
 
-@pytest.mark.parametrize("split", [64, 128, 192, 256, 512, 576, 1088, 4096])
-def test_parts_of_a_decode_segment_are_equal_and_cover_it(split):
+@pytest.mark.parametrize("unit", [64, 128])            # the vector kernel's, the matrix kernel's
+@pytest.mark.parametrize("split", [64, 128, 192, 256, 448, 512, 576, 1088, 4096])
+def test_parts_of_a_decode_segment_are_equal_and_cover_it(split, unit):
     for length in list(range(1, 700)) + [split * k + e for k in (1, 2, 3, 17, 100) for e in (-1, 0, 1, 31, 32, 33)]:
-        parts = equal_parts(length, split)
+        parts = equal_parts(length, split, unit)
         assert parts[0][0] == 0 and parts[-1][1] == length
         assert all(a < b for a, b in parts), (length, parts)                       # none is empty
         assert all(x[1] == y[0] for x, y in zip(parts, parts[1:]))
         longest = max(b - a for a, b in parts)
-        assert longest <= split and longest <= -(-length // len(parts)) + 31
+        assert longest <= split and longest <= -(-length // len(parts)) + unit - 1
