@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
       if (COMBINE) __syncthreads();                    // the log-sum-exp above; and the slices have been read
       // acc[i]: window row ib*32 + 8*(i/4) + 4*half + i%4, key k0 + wv*32 + l32
       const float *l2 = sh_l2[cur] + 4 * half;
-      float sum = 0.0f;
+      const float before = total;
       bool careful = ib * 32 + 32 > R;                 // padding rows (row R-1 once more, and an infinite logit
       if (!careful) {                                  // against their infinite log-sum-exp would be a NaN)
         float low = 0.0f;
@@ -303,23 +303,22 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
         for (int i = 0; i < 16; ++i) {
           const float x = fmaf(acc[i], c_log2, -l2[8 * (i / 4) + i % 4]);
           low = fminf(low, x);
-          sum += fast_exp2(x);
+          total += fast_exp2(x);
         }
         careful = __any(low < EXP2_LOW);               // weights below the normal range
       }
       if (careful) {
-        sum = 0.0f;
+        total = before;
 #pragma unroll
         for (int j = 0; j < 16; j += 4) {
           if (ib * 32 + 2 * j >= R) break;
 #pragma unroll
           for (int i = j; i < j + 4; ++i) {
             const float w = exp2_small(fmaf(acc[i], c_log2, -l2[8 * (i / 4) + i % 4]));
-            sum += ib * 32 + 8 * (i / 4) + 4 * half + i % 4 < R ? w : 0.0f;
+            total += ib * 32 + 8 * (i / 4) + 4 * half + i % 4 < R ? w : 0.0f;
           }
         }
       }
-      total += sum;
     }
     if (more) {
       rb.store(qs[cur ^ 1]);
