@@ -825,19 +825,22 @@ DecodePlan plan_decode(const SeqTab &st, const Dims &dm, int dtype, int headroom
   if (want < 64) want = 64;
   const int unit = mfma && want > 64 && want <= 256 ? 128 : 64;
   const int split = (int)((want + unit - 1) / unit * unit);
-  // One workgroup of eight wavefronts per segment, and no merge kernel, where no segment can be long.
-  // Heads are budgeted unevenly, so the line is drawn at the longest segment that the layer allows (one
-  // head with all of its sequence's prefix budget, head-room full): a compute unit walks it alone, and
-  // what that takes follows its bytes.  us per step, split / whole, d = 128, g = 4, by rows of the longest
-  // segment: 256 10.2 / 7.1, 512 10.8 / 8.7, 768 11.0 / 11.6, 1024 10.6 / 13.1, 2048 10.7 / 21.8, 4096
-  // 10.6 / 38.9; d = 64: 512 10.5 / 7.3, 1024 10.7 / 8.9.  And at 384 rows of capacity on average.
-  long long longest = 0;
+  // One workgroup of eight wavefronts per segment, and no merge kernel, where no segment can be long: a
+  // compute unit walks it alone, and what that takes follows its bytes.  us per step, split / whole, d = 128,
+  // g = 4, by rows of the longest segment: 256 10.2 / 7.1, 512 10.8 / 8.7, 768 11.0 / 11.6, 1024 10.6 / 13.1,
+  // 2048 10.7 / 21.8, 4096 10.6 / 38.9; d = 64: 512 10.5 / 7.3, 1024 10.7 / 8.9.  Heads are budgeted unevenly
+  // (the longest of a layer holds three to four times the average), so, head-room full, four times the
+  // average may reach 768 rows of 256 bytes, where both take the same, and the most that the layer allows,
+  // one head with all of its sequence's prefix budget, 1024.  And 384 rows of capacity on average.
+  long long likely = 0, longest = 0;
   for (int b = 0; b < st.batch; ++b) {
     const long long most = st.Bp[b] < st.n[b] ? st.Bp[b] : st.n[b];
+    const long long four = 4ll * ((st.Bp[b] + dm.h_kv - 1) / dm.h_kv);
     longest = most > longest ? most : longest;
+    likely = (four < most ? four : most) > likely ? (four < most ? four : most) : likely;
   }
-  longest += dm.w + headroom;
-  pl.whole = mfma && cap <= nseg * 384 && longest * dm.d <= 768 * 128;
+  const long long fixed = dm.w + headroom;
+  pl.whole = mfma && cap <= nseg * 384 && (likely + fixed) * dm.d <= 768 * 128 && (longest + fixed) * dm.d <= 1024 * 128;
   pl.split = split;
   pl.nblk = (int)(cap / split + nseg);          // >= sum over segments of ceil(len / split)
   pl.part_acc = 0;

@@ -149,8 +149,11 @@ ROUTES = [
     ([[2040, 8, 8, 8]] + [[50] * 4] * 7, 16, 128, False),     # short on average, one long segment
     ([[500] * 4] + [[20] * 4] * 7, 16, 128, False),           # one sequence whose heads may be long
     ([[464, 100, 100, 100]], 16, 128, True),                  # 748 + 4 + 16 rows at most
-    ([[465, 100, 100, 100]], 16, 128, False),                 # one more
+    ([[465, 100, 100, 100]], 16, 128, False),                 # four times the average: one more
     ([[465, 100, 100, 100]], 16, 64, True),                   # half the bytes
+    ([[460, 71] + [72] * 6], 89, 128, True),                  # eight heads: four times the average 561, at most 931 + 4 + 89 rows
+    ([[460] + [72] * 7], 89, 128, False),                     # one more
+    ([[460] + [72] * 7], 89, 64, True),
     ([[128] * 4], 256, 128, True),
     ([[129] * 4], 256, 128, False),                           # more than 384 rows of capacity on average
 ]
@@ -158,7 +161,7 @@ ROUTES = [
 
 @pytest.mark.parametrize("rows,hr,d,whole", ROUTES)
 def test_one_workgroup_per_segment_only_where_no_segment_can_be_long(rows, hr, d, whole):
-    h, g, w = 4, 2, 4
+    h, g, w = len(rows[0]), 2, 4
     print("decode routes", rows[0], len(rows), hr, d, flush=True)
     wl = synth.small_workload(g * h, h, d, w, 7, [4000] * len(rows), [sum(r) for r in rows], dtype=torch.bfloat16, seed=5)
     layer = adakv.Layer.from_workload(wl)
