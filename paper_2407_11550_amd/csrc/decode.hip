@@ -5,13 +5,15 @@
 // seg_len[s] rows of ROWB = d*sizeof(T) bytes, so a segment is one contiguous byte range.
 //
 // Attention: HBM-bound (every cached K and V row is read once, 2*ROWB bytes for 4*g*d flops).
-// 16-bit caches run both products on the matrix cores (decode_mfma_kernel), fp32 caches on the
-// vector ALUs (decode_attn_kernel): there a row is read by LPR = ROWB/16 neighbouring lanes, 16 bytes each:
-// every load instruction of a wavefront fetches 64/LPR whole rows = 1 KB of consecutive memory.
+// 16-bit caches run both products on the matrix cores (decode_mfma_kernel); fp32 caches, and 16-bit ones
+// with so few query heads per KV head that the matrix instructions stay empty, run on the vector ALUs
+// (decode_attn_kernel): there a row is read by LPR = ROWB/16 neighbouring lanes, 16 bytes each: every load
+// instruction of a wavefront fetches 64/LPR whole rows = 1 KB of consecutive memory.
 // Segment lengths live on the device, so the host launches an upper bound of workgroups
-// (capacity / split + segments); each workgroup finds its (segment, split) from a prefix sum of
-// the lengths, writes partial (max, sum, weighted value sum) per query head, and a second kernel
-// merges the splits of each segment.
+// (capacity / split + segments); each workgroup finds its segment and its part of it from a prefix sum
+// of the lengths, writes partial (max, sum, weighted value sum) per query head, and a second kernel
+// merges the parts of each segment.  Where no segment of a layer can be long, one workgroup takes each
+// segment (decode_mfma_kernel, WHOLE) and writes the result itself: no prefix sum, no merge.
 #include <math.h>
 
 #include <type_traits>

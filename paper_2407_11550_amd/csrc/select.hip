@@ -24,8 +24,9 @@
 //            found through the bucket starts without touching the scores again.  The last digit
 //            and the number of ties to take come from them inside the block.  The layer scope
 //            then counts per head and applies the safeguard; the head scope places every kept
-//            position by prefix counts (earlier blocks' counts from the bucket starts, then a
-//            block scan over 16 consecutive positions per thread).
+//            position by prefix counts (earlier blocks' counts from the bucket starts; inside the
+//            block positions go round by round, wavefront by wavefront, lane by lane, and a ballot
+//            gives every lane its place).
 //
 // When more elements share a 22-bit prefix than a block can hold at once (plateaus: equal or
 // almost equal scores), the finishing kernels stream the buckets instead of holding them.
