@@ -752,6 +752,8 @@ void run_decode(const SeqTab &st, const Dims &dm, int headroom, const DecodePlan
   //   bf16, g = 1   26.8 | 27.2   14.0 | 15.2   31.6 | 33.1      g = 2   30.6 | 29.9   15.0 | 15.0   33.6 | 33.2
   //   fp16, g = 1   26.4 | 29.2   13.7 | 14.9   31.2 | 35.5      g = 2   28.7 | 29.6   15.2 | 15.0   33.5 | 35.9
   // fp16, g = 2, d = 64: 20.1 | 19.5   11.7 | 11.3   22.5 | 22.2.
+  // bf16, g = 1, d = 64 (kernels alone): 64 segments of 1500 rows 11.6 | 12.1, 256 of 6000 81.4 | 87.9, but 256
+  // of 1500 26.0 | 23.8, the one shape measured that the matrix kernel does faster.
   constexpr bool VECTOR = sizeof(T) == 4 || G == 1 || (F16 && G == 2 && D == 128);
   if constexpr (sizeof(T) == 2) {
     const DecodeOut res = {part_acc, part_ml, seg_tab, out, lse, k_new ? seg_len : nullptr, overflow};
