@@ -61,6 +61,7 @@ struct MfmaVariant {
   int mb, rs, kg;      // 32-row blocks per wavefront; wavefronts along window rows, along keys
   int chunk;           // keys per workgroup at most (what the instantiation has room for)
   int len;             // keys per workgroup
+  int part_len;        // keys per workgroup of sweep 1 (never fewer)
   bool fuse_lse;       // sweep 2 combines sweep 1's partial statistics itself
   bool fuse_pool;      // sweep 2 applies the max-pool itself
 };

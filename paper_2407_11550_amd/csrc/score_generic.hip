@@ -411,16 +411,14 @@ __global__ __launch_bounds__(256) void pooled_generic_kernel(
 
 }  // namespace
 
-// lse[b][row] = log of the sum over the sequence's chunks of l * exp(m).  One wavefront per row:
+// lse[b][row] = log of the sum over the sequence's chunks of l * 2^m.  One wavefront per row:
 // the lanes stride over the chunks (independent loads), then the 64 partial (max, sum) pairs are
 // merged with shuffles.
-// LOG2: the partials' references are in the base-2 domain (rounded once instead of once more on the
-// way to natural logarithms); the result then is too, unless natural_out asks for the other.
-template <bool LOG2>
+// The partials' references are in the base-2 domain (rounded once instead of once more on the
+// way to natural logarithms); the result is too, unless natural_out asks for the other.
 __global__ __launch_bounds__(256) void lse_combine_kernel(SeqTab st, ChunkTab ct, int RQ,
                                                           const float2 *__restrict__ part,
                                                           float *__restrict__ lse, int natural_out) {
-  auto ex = [](float x) { return LOG2 ? exp2f(x) : expf(x); };
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int b = blockIdx.y;
@@ -430,19 +428,19 @@ __global__ __launch_bounds__(256) void lse_combine_kernel(SeqTab st, ChunkTab ct
     const float2 ml = part[(size_t)k * RQ + row];
     const float m = ml.x, l = ml.y;
     const float nm = fmaxf(M, m);
-    if (nm > -INFINITY) L = L * ex(M - nm) + l * ex(m - nm);
+    if (nm > -INFINITY) L = L * exp2f(M - nm) + l * exp2f(m - nm);
     M = nm;
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     const float m2 = __shfl_xor(M, off), l2 = __shfl_xor(L, off);
     const float nm = fmaxf(M, m2);
-    if (nm > -INFINITY) L = L * ex(M - nm) + l2 * ex(m2 - nm);
+    if (nm > -INFINITY) L = L * exp2f(M - nm) + l2 * exp2f(m2 - nm);
     M = nm;
   }
   if (lane == 0) {
-    const float v = M + (LOG2 ? log2f(L) : logf(L));
-    lse[(size_t)b * RQ + row] = LOG2 && natural_out ? v * LN2 : v;
+    const float v = M + log2f(L);
+    lse[(size_t)b * RQ + row] = natural_out ? v * LN2 : v;
   }
 }
 
@@ -496,8 +494,8 @@ ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma) 
 
 void launch_lse_combine(const SeqTab &st, const ChunkTab &ct, int RQ, const float2 *part,
                         float *lse, hipStream_t s) {
-  ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel<false>, dim3((RQ + 3) / 4, st.batch),
-               dim3(256), s, st, ct, RQ, part, lse, 1);
+  ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel, dim3((RQ + 3) / 4, st.batch),
+               dim3(256), s, st, ct, RQ, part, lse, 0);
 }
 
 void launch_pool(const SeqTab &st, const Dims &dm, const float *raw, float *scores,
@@ -551,7 +549,7 @@ static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const v
     // partials its workgroups read more of those than of keys (8000 x 4 heads x 512 rows, d = 64: 65.6 -> 67.6).
     if (pool_first || !f32_lse_fused(st, pl.part_chunk)) {
       const int RQ = dm.h_q * dm.w;
-      ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel<true>, dim3((RQ + 3) / 4, st.batch), block, s,
+      ADAKV_LAUNCH("score_lse_combine", lse_combine_kernel, dim3((RQ + 3) / 4, st.batch), block, s,
                    st, ct, RQ, (const float2 *)part, lse, pool_first ? 1 : 0);
       use_lse = lse;
     }

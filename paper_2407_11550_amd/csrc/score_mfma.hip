@@ -9,24 +9,23 @@
 // A caller-supplied row_lse skips sweep 1.
 //
 // Work split.  In sweep 2 a workgroup owns chunk_len consecutive keys of one KV head (the fused
-// max-pool wants neighbours); in sweep 1 the workgroups of a head take the head's tile sets in
-// turn (set c, c + nch, ...), because a (max, sum) pair does not care which keys it saw and the
-// chip then streams one dense region of K at a time.  All g query heads of the group share
-// every K tile.  A wavefront keeps at most 64 window rows of Q in registers as MFMA
-// operands for the whole chunk (MB blocks of 32 rows), which leaves room for two wavefronts per
-// SIMD, so one wavefront's exponentials overlap the other's matrix work.  RS wavefronts split
-// the rows of a head, and the KG = NW/RS groups of wavefronts take the 32-key tiles of the
-// chunk in turn.  A K tile travels HBM -> registers (coalesced 16-byte loads of whole rows,
-// issued by the whole workgroup, two iterations ahead) -> LDS (padded rows, shared by the
-// wavefronts that need the tile) -> registers in operand layout.
+// max-pool wants neighbours); in sweep 1 the workgroups of a head take the head's tiles in turn,
+// because a (max, sum) pair does not care which keys it saw and the chip then streams one dense
+// region of K at a time.  All g query heads of the group share every K tile of 32 keys, and the
+// window queries stay in registers as MFMA operands for a workgroup's whole life.  Up to 128 rows
+// every wavefront holds all of them and works on tiles of its own (stats_own, weights_own); beyond,
+// RS wavefronts of at most 64 rows (two per SIMD) share a tile: HBM -> registers (coalesced
+// 16-byte loads of whole rows, issued by the whole workgroup, two iterations ahead) -> LDS (padded
+// rows) -> registers in operand layout (sweep_shared).
 //
 // Operand roles differ between the sweeps because of what the accumulator layout makes cheap
 // (D[i][j]: lane = column j, 16 rows i per lane):
 //   sweep 1: D = K_tile Q^T, a lane owns ONE window row and 16 keys: running (max, sum) per
 //            lane, nothing crosses lanes until the chunk is done;
 //   sweep 2: D = Q K_tile^T, a lane owns ONE key and 16 window rows: the sum over rows is
-//            lane-local adds plus one cross-half add; partial sums of the RS row groups meet
-//            in LDS when the chunk is done and are added in a fixed order.
+//            lane-local adds plus one cross-half add (partial sums of RS row groups meet
+//            in LDS when the chunk is done and are added in a fixed order).
+// Sweep 1 hands its (max, sum) pairs to sweep 2 with the maximum in the base-2 domain.
 #include <math.h>
 
 #include <type_traits>
@@ -43,8 +42,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int TILE = 32;           // keys per MFMA tile
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr float LN2 = 0.6931471805599453f;
 constexpr int MFMA_POOL_ROWS_MAX_RADIUS = 7;
+constexpr int OWN_MOST = 3840;     // keys of a chunk at 128 rows, d = 128: beside 64 KiB of tiles in half of a compute unit's LDS
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // The value of the neighbouring lane: CTRL 0x130 = wave_shl:1 (lane i reads lane i+1), 0x138 =
@@ -66,17 +65,74 @@ __device__ __forceinline__ floatx16 mfma16(bf16x8 a, bf16x8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// The end of a weights sweep: the max-pool (radius r, stride 1, same length, window clipped to the sequence;
+// Section 4.1: kernel 7) of the chunk [kc0, kc1) whose scores lie in sh_part from key k0 on, and, in pipeline
+// mode, the first radix digits of what is written, counted in sh_hist (cleared; a barrier has passed since).
+template <int NT, int CHUNK>
+__device__ __forceinline__ void pool_and_file(const float *sh_part, unsigned *sh_hist, float *__restrict__ dst,
+                                              int kc0, int kc1, int k0, int n, int chunk_len, int r,
+                                              const TopkCarry &tc, int b, int seg) {
+  const int tid = threadIdx.x;
+  // A thread pools KPT keys at once, one window offset at a time, so that KPT independent LDS
+  // reads are in flight instead of one chain per key.  Offsets that leave the sequence are
+  // clamped onto its ends (taking an element of the window twice does not change a maximum);
+  // a thread's keys past the chunk end repeat the last key and are not written.
+  constexpr int KPT = CHUNK / NT;
+  static_assert(CHUNK % NT == 0, "every thread pools the same number of keys");
+  float pooled[KPT];
+  int pk[KPT];
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) {
+    pk[i] = min(kc0 + tid + i * NT, kc1 - 1);
+    pooled[i] = -INFINITY;
+  }
+  if (2 * chunk_len > CHUNK) {
+    for (int t = -r; t <= r; ++t) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i)
+        pooled[i] = fmaxf(pooled[i], sh_part[min(max(pk[i] + t, 0), n - 1) - k0]);
+    }
+  } else {
+    // a short chunk in a large instantiation: only the keys there are (kept apart, because the test
+    // between the reads of a full chunk cost the sweep 2 us of 51 at 131072 keys)
+    for (int t = -r; t <= r; ++t) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i)
+        if (i * NT < chunk_len) pooled[i] = fmaxf(pooled[i], sh_part[min(max(pk[i] + t, 0), n - 1) - k0]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) {
+    if (kc0 + tid + i * NT < kc1) {
+      dst[pk[i]] = pooled[i];
+      if (tc.hist0) atomicAdd(&sh_hist[key_of(pooled[i]) >> 21], 1u);
+    }
+  }
+  if (tc.hist0) {
+    __syncthreads();
+    unsigned *gh = tc.hist0 + (size_t)seg * RADIX_BINS;
+    unsigned *gt = tc.hist_tot0 + (size_t)b * RADIX_BINS;
+    for (int i = tid; i < RADIX_BINS; i += NT) {
+      const unsigned v = sh_hist[i];
+      if (v) {
+        atomicAdd(&gh[i], v);
+        atomicAdd(&gt[i], v);
+      }
+    }
+  }
+}
+
 // PR (sweep 2 only): the printed order of Alg. 2 l.4, max-pool along the keys in every window row
 // first, mean over the rows afterwards.  A lane of sweep 2 owns one key and 16 rows per row block,
 // so the pool is a sliding maximum across neighbouring lanes, with whole-wavefront shifts by one
 // lane.  Tiles then overlap by the pool radius on either side: only the inner 32 - 2r
 // lanes of a tile have all their neighbours and produce a score.
-template <int D, int MB, int RS, int KG, int CHUNK, int PASS, bool F16, bool PR = false>
-__global__ __launch_bounds__(64 * RS * KG, PR && RS == 2 ? 2 : 1) void score_mfma_kernel(
-    SeqTab st, ChunkTab ct, Dims dm, float c_log2, const unsigned short *__restrict__ q,
-    const unsigned short *__restrict__ K, const float *__restrict__ lse,
+template <int D, int MB, int RS, int KG, int CHUNK, int PASS, bool F16, bool PR>
+__device__ __forceinline__ void sweep_shared(
+    const SeqTab &st, const ChunkTab &ct, const ChunkTab &cp, const Dims &dm, float c_log2, const unsigned short *__restrict__ q,
+    const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
     float2 *__restrict__ part, float *__restrict__ out, int halo, int chunk_len,
-    TopkCarry tc) {
+    const TopkCarry &tc) {
   constexpr int NW = RS * KG;                // wavefronts per workgroup
   constexpr int NT = 64 * NW;
   constexpr int KS = D / 16;                 // MFMA k-steps per tile
@@ -234,7 +290,7 @@ __global__ __launch_bounds__(64 * RS * KG, PR && RS == 2 ? 2 : 1) void score_mfm
   constexpr int RSTEP = RPAD / RPT;            // rows combined side by side
   static_assert(SL * RSTEP == NT && RPT * RSTEP == RPAD, "threads and rows must tile each other");
   const int qi = tid % RSTEP, sl = tid / RSTEP;
-  const int kend = ct.off[b + 1];
+  const int kend = cp.off[b + 1];
   float2 pml[PASS == 2 ? CB : 1];              // (max, sum) of CB chunks
   auto load_parts = [&](int k0c, int row) {
 #pragma unroll
@@ -244,7 +300,7 @@ __global__ __launch_bounds__(64 * RS * KG, PR && RS == 2 ? 2 : 1) void score_mfm
       pml[u] = part[o];
     }
   };
-  if (PASS == 2 && !lse) load_parts(ct.off[b] + sl, qi);
+  if (PASS == 2 && !lse) load_parts(cp.off[b] + sl, qi);
 
   // The first two tile sets are requested next; the combination and the loads of the query
   // fragments (further down, so that they do not hold registers while the partials do) happen
@@ -259,7 +315,7 @@ __global__ __launch_bounds__(64 * RS * KG, PR && RS == 2 ? 2 : 1) void score_mfm
   if (PASS == 2) {
     float *sh_lse = &sh_rows[0][0][0];       // RPAD floats
     if (lse) {
-      for (int i = tid; i < RPAD; i += NT) sh_lse[i] = (i < R) ? lse[head_row0 + i] * LOG2E : INFINITY;
+      for (int i = tid; i < RPAD; i += NT) sh_lse[i] = (i < R) ? lse[head_row0 + i] * lse_mul : INFINITY;
     } else {
       // fold the partials in: first the largest maximum of a batch, then every sum scaled to it
       // (independent exponentials instead of a chain of rescalings)
@@ -267,18 +323,18 @@ __global__ __launch_bounds__(64 * RS * KG, PR && RS == 2 ? 2 : 1) void score_mfm
       for (int rr = 0; rr < RPT; ++rr) {
         const int row = qi + rr * RSTEP;
         float M = -INFINITY, L = 0.0f;
-        for (int k0c = ct.off[b] + sl; k0c < kend; k0c += CB * SL) {
-          if (rr > 0 || k0c != ct.off[b] + sl) load_parts(k0c, row);
+        for (int k0c = cp.off[b] + sl; k0c < kend; k0c += CB * SL) {
+          if (rr > 0 || k0c != cp.off[b] + sl) load_parts(k0c, row);
           float bm = -INFINITY;
 #pragma unroll
           for (int u = 0; u < CB; ++u)
-            if (k0c + u * SL < kend) bm = fmaxf(bm, pml[u].x * LOG2E);
+            if (k0c + u * SL < kend) bm = fmaxf(bm, pml[u].x);
           const float nm = fmaxf(M, bm);
           const float ref = (nm == -INFINITY) ? 0.0f : nm;
           float acc = L * fast_exp2(M - ref);
 #pragma unroll
           for (int u = 0; u < CB; ++u)
-            if (k0c + u * SL < kend) acc += pml[u].y * fast_exp2(pml[u].x * LOG2E - ref);
+            if (k0c + u * SL < kend) acc += pml[u].y * fast_exp2(pml[u].x - ref);
           L = acc;
           M = nm;
         }
@@ -668,7 +724,7 @@ __global__ __launch_bounds__(64 * RS * KG, PR && RS == 2 ? 2 : 1) void score_mfm
         L += sh_rows[1][k * RS + rsi][wi] * fast_exp2(sh_rows[0][k * RS + rsi][wi] - ref);
       if (qi < R) {
         const size_t o = (size_t)cg * RQ + (size_t)c * R + qi;
-        part[o] = make_float2(M * LN2, L);         // the maximum back in the natural-log domain
+        part[o] = make_float2(M, L);               // (base 2, as the weights sweep wants it)
       }
     }
   } else {
@@ -688,55 +744,630 @@ __global__ __launch_bounds__(64 * RS * KG, PR && RS == 2 ? 2 : 1) void score_mfm
     }
     __syncthreads();
     float *dst = out + st.score_off[b] + (size_t)c * n;
-    const int r = halo ? dm.pool_k / 2 : 0;
-    // A thread pools KPT keys at once, one window offset at a time, so that KPT independent LDS
-    // reads are in flight instead of one chain per key.  Offsets that leave the sequence are
-    // clamped onto its ends (taking an element of the window twice does not change a maximum);
-    // a thread's keys past the chunk end repeat the last key and are not written.
-    constexpr int KPT = CHUNK / NT;
-    static_assert(CHUNK % NT == 0, "every thread pools the same number of keys");
-    float pooled[KPT];
-    int pk[KPT];
+    pool_and_file<NT, CHUNK>(sh_part[0], sh_hist, dst, kc0, kc1, k0, n, chunk_len, halo ? dm.pool_k / 2 : 0, tc, b, b * h + c);
+  }
+}
+
+// ---- up to 128 window rows: every wavefront on its own ------------------------------------------
+//
+// The wavefronts of a workgroup share nothing but the window queries: each takes tiles of 32 keys in turn,
+// keeps all RB = MB * RS row blocks of Q in registers as operands, and has its own tiles on their way, straight
+// into its own part of LDS.  No barrier in the loop, no registers for loads in flight, every tile read from
+// LDS once.  A row block's products (a chain of D / 16 matrix instructions) are issued with the vector work on
+// the row block before it in between.
+//
+// Bound by reading K (what a kernel with these addresses and no arithmetic reaches: 44 us for 256 MiB, 13.4 us for
+// 64 MiB) and close behind by the vector work (27 us of a sweep at 128 rows x 131072 keys x 8 heads, 16 of them
+// exponentials at a quarter of the rate).  Against the form before, in which two wavefronts shared a tile that
+// came through registers, with a barrier per tile; us a call, d = 128, 8 KV heads, 128 rows:
+//   whole step, 2011 keys 39.0 -> 37.6, 32768 keys 70.3 -> 66.5, 131072 keys 151.6 -> 142.0;
+//   scores alone, six sequences (217 000 keys) 206 -> 186; with the caller's log-sum-exp, 50021 keys 27.3 -> 26.0.
+// The window queries come through LDS as well: read from memory as operand words every load touches 32 lines,
+// which kept the first tile waiting for 7 us (32768 keys: 22.0 + 25.0 us for the sweeps, 18.2 + 20.3 through LDS).
+template <int N> __device__ __forceinline__ void wait_vmem() {
+  static_assert(N < 64, "the counter's range");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));   // at most N loads on their way (they return in order)
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// A barrier for what the workgroup exchanges through LDS; loads on their way stay there.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// 64 x 16 bytes from base + at + the lane's off, straight into 1 KB of LDS.
+__device__ __forceinline__ void load_to_lds(const char *base, unsigned off, unsigned at, u32x4 *dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, 0x7fffffff, 0x00027000),
+      (__attribute__((address_space(3))) void *)dst, 16, off, at, 0, 0);
+}
+// The same behind the compiler's back, for loops that wait with wait_vmem alone: where buffers take turns,
+// the compiler would wait for every load before it reads any.  (In front of the load stand the wait states
+// that follow a write of m0, one, and a scalar register's write by the vector unit, five.)
+__device__ __forceinline__ void load_to_lds_untracked(const char *base, unsigned off, unsigned at, u32x4 *dst) {
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, 0x7fffffff, 0x00027000);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(
+                   (unsigned)(size_t)(__attribute__((address_space(3))) void *)dst),
+               "v"(off), "s"(rs), "s"(at)
+               : "memory", "m0");
+}
+// Lower half of the wavefront + upper half, in every lane.
+__device__ __forceinline__ float sum_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// A sum taken against a reference that was not its maximum may be a large one; where it is later scaled to a
+// larger reference, the factor would fall out of the range of fp32 before the product does.
+__device__ __forceinline__ void settle(float &m, float &l) {
+  const int e = l > 0x1p16f ? __builtin_amdgcn_frexp_expf(l) : 0;
+  m += (float)e;
+  l = ldexpf(l, -e);
+}
+
+// A wavefront's view of rows of D 16-bit elements in LDS: 32 rows at a time, 16-byte words swizzled so that
+// neighbouring lanes' operand reads (row l32, word 2s + half) fall on different banks.
+template <int D> struct RowTile {
+  static constexpr int KS = D / 16;                    // matrix instructions per row block
+  static constexpr int ROW16 = D / 8;                  // 16-byte words per row
+  static constexpr int WORDS = TILE * ROW16;
+  static constexpr int RPI = 64 / ROW16;               // rows per load instruction
+  static constexpr int LD = WORDS / 64;                // load instructions per tile
+  static constexpr int NV = D == 128 ? 4 : 2;          // load instructions until the swizzle repeats
+  static __device__ __forceinline__ unsigned swz(unsigned row) { return D == 128 ? row & 15u : (row >> 1) & 7u; }
+  // byte offset inside its row of the word that lane `ln` of load instruction i loads
+  static __device__ __forceinline__ unsigned col(unsigned ln, int i) {
+    return ((ln % ROW16) ^ swz((i % NV) * RPI + ln / ROW16)) * 16u;
+  }
+  // word of LDS that operand word s of this lane's row lies in
+  static __device__ __forceinline__ unsigned operand(unsigned l32, unsigned half, int s) {
+    return l32 * ROW16 + ((2 * s + half) ^ swz(l32));
+  }
+  // all rows of a tile are there: off[v] = the lane's row * tok_bytes + col
+  template <class Load>
+  static __device__ __forceinline__ void whole(const char *sb, unsigned tok_bytes, const unsigned (&off)[NV], Load &&load) {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      pk[i] = min(kc0 + tid + i * NT, kc1 - 1);
-      pooled[i] = -INFINITY;
+    for (int i = 0; i < LD; ++i) load(sb, off[i % NV], (unsigned)(i * RPI) * tok_bytes, i * 64);
+  }
+  // rows clamped to [lo, lim], counted from the tile's first
+  template <class Load>
+  static __device__ __forceinline__ void clamped(const char *sb, unsigned tok_bytes, int lo, int lim, unsigned lane, Load &&load) {
+    asm volatile("" : "+v"(lane));                     // (computed here, not kept in registers for the rare tile)
+#pragma unroll
+    for (int i = 0; i < LD; ++i) {
+      const unsigned row = (unsigned)max(min((int)(i * RPI + lane / ROW16), lim), lo);
+      load(sb, __umul24(row, tok_bytes) + col(lane, i), 0u, i * 64);
     }
-    if (2 * chunk_len > CHUNK) {
-      for (int t = -r; t <= r; ++t) {
+  }
+};
+
+// Sweep 1.  Tiles of a sequence are dealt out over all wavefronts of the head (the workgroups that the sequence
+// has in cp, four wavefronts each), so at any moment the chip reads one dense region of K.  One workgroup per
+// compute unit, one wavefront per SIMD with three tiles on their way: of two wavefronts the older one runs ahead
+// and leaves the younger one to stream alone (131072 keys: 57.4 us with two of two tiles each, 52 with one).
+template <int D, int RB, bool F16>
+__device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, const Dims &dm, float c_log2,
+                                          const unsigned short *__restrict__ q, const unsigned short *__restrict__ K,
+                                          float2 *__restrict__ part, const TopkCarry &tc) {
+  typedef RowTile<D> T;
+  constexpr int NW = 4, NT = 64 * NW, KS = T::KS, LD = T::LD;
+  constexpr int RPAD = 32 * RB;
+  constexpr int NBUF = 3;                             // tiles a wavefront has room for
+  constexpr int UN = RB % 2 && NBUF % 2 ? 2 * NBUF : NBUF;
+  __shared__ u32x4 kt[NW][NBUF][T::WORDS];
+  __shared__ u32x4 qs[RB * T::WORDS];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  // pipeline mode: the Top-k histograms, which the kernel after this one is the first to touch
+  if (tc.zero_begin)
+    for (unsigned i = blockIdx.x * NT + tid; i < tc.zero_words; i += gridDim.x * NT) tc.zero_begin[i] = 0u;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+  const int h = dm.h_kv;
+  const int c = blockIdx.x % h, cg = blockIdx.x / h;
+  const int b = find_seq(cp, st.batch, cg);
+  const int first = (cg - cp.off[b]) * NW + wv, stride = (cp.off[b + 1] - cp.off[b]) * NW;
+  const int n = st.n[b];
+  const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
+  const size_t head_row0 = (size_t)b * RQ + (size_t)c * R;
+  const int ntiles = (n + TILE - 1) / TILE;
+  const int iters = first < ntiles ? (ntiles - 1 - first) / stride + 1 : 0;
+  const char *kbase = reinterpret_cast<const char *>(K) +
+                      ((size_t)st.tok_off[b] * dm.k_stride_tok + (size_t)c * dm.k_stride_head) * 2;
+  const unsigned tok_bytes = (unsigned)dm.k_stride_tok * 2u;
+  unsigned ld_off[T::NV];
 #pragma unroll
-        for (int i = 0; i < KPT; ++i)
-          pooled[i] = fmaxf(pooled[i], sh_part[0][min(max(pk[i] + t, 0), n - 1) - k0]);
-      }
+  for (int v = 0; v < T::NV; ++v) ld_off[v] = __umul24(lane / T::ROW16, tok_bytes) + T::col(lane, v);
+  auto issue = [&](int it, int buf) {
+    const int key0 = (first + it * stride) * TILE;
+    const char *sb = kbase + (long long)key0 * tok_bytes;
+    auto load = [&](const char *base, unsigned off, unsigned at, int word) { load_to_lds_untracked(base, off, at, &kt[wv][buf][word]); };
+    if (key0 + TILE <= n) T::whole(sb, tok_bytes, ld_off, load);
+    else T::clamped(sb, tok_bytes, 0, n - 1 - key0, lane, load);
+  };
+  auto start = [&]() {
+#pragma unroll
+    for (int j = 0; j < NBUF; ++j)
+      if (j < iters) issue(j, j);
+  };
+  // tile `it` has arrived; those asked for behind it, at most NBUF - 1, may be on their way
+  auto await = [&](int it) {
+    const int behind = min(iters - 1 - it, NBUF - 1);
+    if (behind == NBUF - 1) wait_vmem<(NBUF - 1) * LD>();
+    else if (NBUF > 2 && behind == NBUF - 2) wait_vmem<(NBUF > 2 ? NBUF - 2 : 0) * LD>();
+    else if (NBUF > 3 && behind == NBUF - 3) wait_vmem<(NBUF > 3 ? NBUF - 3 : 0) * LD>();
+    else wait_vmem<0>();
+  };
+
+  // the window queries, through LDS: as operand words straight from memory every load would touch 32 lines
+  constexpr int QI = RPAD / T::RPI / NW;               // load instructions per wavefront
+  static_assert(QI * T::RPI * NW == RPAD, "");
+#pragma unroll
+  for (int i = 0; i < QI; ++i) {
+    const unsigned row = (unsigned)(wv * QI + i) * T::RPI + lane / T::ROW16;     // (rows past R are row R-1, zeroed below)
+    load_to_lds_untracked(reinterpret_cast<const char *>(q) + head_row0 * (D * 2),
+                          min(row, (unsigned)R - 1u) * (D * 2) + ((lane % T::ROW16) ^ T::swz(row)) * 16u, 0u,
+                          &qs[(wv * QI + i) * 64]);
+  }
+  start();
+  {
+    const int asked = min(iters, NBUF);
+    if (asked == NBUF) wait_vmem<NBUF * LD>();
+    else if (NBUF > 3 && asked == 3) wait_vmem<3 * LD>();
+    else if (NBUF > 2 && asked == 2) wait_vmem<2 * LD>();
+    else if (asked == 1) wait_vmem<LD>();
+    else wait_vmem<0>();
+  }
+  lds_barrier();
+  unsigned rd[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) rd[s] = T::operand(l32, half, s);
+  bf16x8 qf[RB][KS];
+#pragma unroll
+  for (int mb = 0; mb < RB; ++mb) {
+    const unsigned keep = mb * 32 + l32 < R ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) qf[mb][s] = as_bf16(qs[mb * T::WORDS + rd[s]] & keep);
+  }
+
+  bf16x8 kf[KS];
+  floatx16 acc[2];                                     // products of the current row block and of the one before
+  float rm[RB], rl[RB];                                // running maximum (or reference) and sum of the row this lane owns
+  auto read_first = [&]() {
+    await(0);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[wv][0][rd[s]]);
+  };
+  // the vector work on one row block's products, in KS shares
+  float ref = 0.0f, nmx = 0.0f, usum = 0.0f;
+  auto share = [&](auto lazy_tag, floatx16 &a, int mb, int s) {
+    if constexpr (decltype(lazy_tag)::value) {
+      if (s == 0) usum = 0.0f;
+#pragma unroll
+      for (int v = s * 16 / KS; v < (s + 1) * 16 / KS; ++v) usum += fast_exp2(fmaf(a[v], c_log2, -rm[mb]));
+      if (s == KS - 1) rl[mb] += usum;
     } else {
-      // a short chunk in a large instantiation: only the keys there are (kept apart, because the test
-      // between the reads of a full chunk cost the sweep 2 us of 51 at 131072 keys)
-      for (int t = -r; t <= r; ++t) {
+      if (s == 0) {
+        float tm = a[0];
 #pragma unroll
-        for (int i = 0; i < KPT; ++i)
-          if (i * NT < chunk_len) pooled[i] = fmaxf(pooled[i], sh_part[0][min(max(pk[i] + t, 0), n - 1) - k0]);
+        for (int r = 1; r < 16; ++r) tm = fmaxf(tm, a[r]);
+        nmx = fmaxf(rm[mb], tm * c_log2);
+        ref = (nmx == -INFINITY) ? 0.0f : nmx;
+        usum = 0.0f;
+      } else {
+#pragma unroll
+        for (int v = (s - 1) * 16 / (KS - 1); v < s * 16 / (KS - 1); ++v) usum += fast_exp2(fmaf(a[v], c_log2, -ref));
+      }
+      if (s == KS - 1) {
+        rl[mb] = rl[mb] * fast_exp2(rm[mb] - ref) + usum;
+        rm[mb] = nmx;
       }
     }
+  };
+  // the sequence's last tile, if it is not full, is the last of its wavefront and comes after the loop
+  const int plain = iters > 0 && (first + (iters - 1) * stride) * TILE + TILE > n ? iters - 1 : iters;
+  // All full tiles, the first of them in kf; behind it kf holds the tile after them, if there is one.
+  auto loop = [&](auto lazy_tag) {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      if (kc0 + tid + i * NT < kc1) {
-        dst[pk[i]] = pooled[i];
-        if (tc.hist0) atomicAdd(&sh_hist[key_of(pooled[i]) >> 21], 1u);
-      }
-    }
-    if (tc.hist0) {
-      __syncthreads();
-      unsigned *gh = tc.hist0 + (size_t)(b * h + c) * RADIX_BINS;
-      unsigned *gt = tc.hist_tot0 + (size_t)b * RADIX_BINS;
-      for (int i = tid; i < RADIX_BINS; i += NT) {
-        const unsigned v = sh_hist[i];
-        if (v) {
-          atomicAdd(&gh[i], v);
-          atomicAdd(&gt[i], v);
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = -INFINITY;    // (nothing before the first: no weight)
+    for (int it0 = 0; it0 < plain; it0 += UN) {
+#pragma unroll
+      for (int j = 0; j < UN; ++j) {
+        const int it = it0 + j;
+        if (it < plain) {
+          wait_lds();                                  // the tile is in registers: its place is free
+          if (it + NBUF < iters) issue(it + NBUF, j % NBUF);
+#pragma unroll
+          for (int mb = 0; mb < RB; ++mb) {
+            const int cur = (j * RB + mb) & 1, pmb = mb == 0 ? RB - 1 : mb - 1;
+            if (mb == RB - 1) await(it + 1);
+            floatx16 a = {0};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+              a = mfma16<F16>(kf[s], qf[mb][s], a);
+              if (mb == RB - 1) kf[s] = as_bf16(kt[wv][(j + 1) % NBUF][rd[s]]);   // (whatever lies there behind the last)
+              share(lazy_tag, acc[1 - cur], pmb, s);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            acc[cur] = a;
+            asm volatile("" : "+v"(rl[pmb]), "+v"(rm[pmb]));   // the vector work stays in front of this point
+          }
         }
       }
     }
+    if (plain > 0) {
+      floatx16 last = acc[1];
+      if (RB % 2 == 1 && (plain & 1)) last = acc[0];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) share(lazy_tag, last, RB - 1, s);
+    }
+  };
+  auto reset = [&]() {
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb) { rm[mb] = -INFINITY; rl[mb] = 0.0f; }
+  };
+  reset();
+  if (iters > 0) read_first();
+  // A sum of exp2(x - ref) is as accurate for one reference as for another unless it overflows, and what
+  // underflows is negligible beside the term that set the reference.  So with several tiles to come the
+  // first one's maxima serve all of them, without a search in every tile (50 instead of 70 vector
+  // instructions per row block: 18.2 -> 16.9 us at 32768 keys, 61.5 -> 58.6 at 131072); if a sum is not finite in the end, all is done again the careful way.
+  bool careful = plain < 4;
+  if (!careful) {
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb) {
+      floatx16 a = {0};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a = mfma16<F16>(kf[s], qf[mb][s], a);
+      float tm = a[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) tm = fmaxf(tm, a[r]);
+      rm[mb] = tm * c_log2;
+      asm volatile("" : "+v"(rm[mb]));                 // (one row block's products at a time)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    loop(std::true_type{});
+    bool bad = false;
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb) bad |= !(rl[mb] < INFINITY);
+    if (__any(bad)) {
+      careful = true;
+      wait_vmem<0>();
+      wait_lds();
+      reset();
+      start();
+      read_first();
+    } else {
+#pragma unroll
+      for (int mb = 0; mb < RB; ++mb) settle(rm[mb], rl[mb]);
+    }
   }
+  if (careful) loop(std::false_type{});
+  if (plain < iters) {
+    const int base = (first + plain * stride) * TILE;
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb) {
+      floatx16 a = {0};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a = mfma16<F16>(kf[s], qf[mb][s], a);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)                     // key base + 8 (r/4) + 4 half + r%4
+        if (base + 8 * (r / 4) + 4 * half + (r % 4) >= n) a[r] = -INFINITY;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) share(std::false_type{}, a, mb, s);
+      asm volatile("" : "+v"(rl[mb]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // merge the two lane halves (same window row, different keys), then the wavefronts
+  wait_vmem<0>();
+  wait_lds();
+  float *own = reinterpret_cast<float *>(&kt[wv][0][0]);
+  static_assert(T::WORDS * 16 >= 2 * RPAD * 4, "");
+#pragma unroll
+  for (int mb = 0; mb < RB; ++mb) {
+    const float m2 = __shfl_xor(rm[mb], 32), s2 = __shfl_xor(rl[mb], 32);
+    const float M = fmaxf(rm[mb], m2);
+    const float rf = (M == -INFINITY) ? 0.0f : M;
+    const float L = rl[mb] * fast_exp2(rm[mb] - rf) + s2 * fast_exp2(m2 - rf);
+    if (half == 0) { own[mb * 32 + l32] = M; own[RPAD + mb * 32 + l32] = L; }
+  }
+  __syncthreads();
+  if (tid < R) {
+    const float *o[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) o[k] = reinterpret_cast<const float *>(&kt[k][0][0]) + tid;
+    float M = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) M = fmaxf(M, o[k][0]);
+    const float rf = (M == -INFINITY) ? 0.0f : M;
+    float L = 0.0f;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) L += o[k][RPAD] * fast_exp2(o[k][0] - rf);
+    part[(size_t)cg * RQ + (size_t)c * R + tid] = make_float2(M, L);            // (base 2, as the weights sweep wants it)
+  }
+}
+
+// Sweep 2.  A workgroup owns chunk_len consecutive keys (the pool wants neighbours); its wavefronts take the
+// chunk's tiles in turn, backwards from a point that differs from workgroup to workgroup: concurrently running
+// workgroups then do not ask for addresses that are equal modulo the distance of their chunks.
+template <int D, int MB, int RS, int CHUNK, bool F16>
+__device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct, const ChunkTab &cp, const Dims &dm,
+                                            float c_log2, const unsigned short *__restrict__ q,
+                                            const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
+                                            const float2 *__restrict__ part, float *__restrict__ out, int halo,
+                                            int chunk_len, const TopkCarry &tc) {
+  typedef RowTile<D> T;
+  constexpr int NW = 4, NT = 64 * NW, KS = T::KS, LD = T::LD;
+  constexpr int RB = MB * RS, RPAD = 32 * RB;
+  constexpr int HALO = TILE;                           // keys scored in front of the chunk for the pool
+  constexpr int SPAN = (D == 128 && CHUNK == 4096 ? OWN_MOST : CHUNK) + 2 * HALO;
+  // (two arrays, so that the compiler sees that reading one does not wait for loads into the other)
+  __shared__ u32x4 kt0[NW][T::WORDS], kt1[NW][T::WORDS];
+  __shared__ __align__(16) float sh_lse[RPAD];
+  __shared__ __align__(16) float sh_part[SPAN > 4 * NT ? SPAN : 4 * NT];
+  constexpr int SL = 2 * NT / RPAD;                    // threads that share two rows in the statistics combination
+  float *sh_cm = sh_part, *sh_cl = sh_part + 2 * NT;   // (the prologue's, before any score is there)
+  static_assert(sizeof(kt0) >= RADIX_BINS * sizeof(unsigned), "the digit histogram takes the tiles' place");
+  unsigned *sh_hist = reinterpret_cast<unsigned *>(&kt0[0][0]);
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+  const int h = dm.h_kv;
+  const int c = blockIdx.x % h, cg = ct.off[st.batch] - 1 - (int)blockIdx.x / h;
+  const int b = find_seq(ct, st.batch, cg);
+  const int chunk = cg - ct.off[b], nch = ct.off[b + 1] - ct.off[b];
+  const int n = st.n[b];
+  const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
+  const int kc0 = chunk * chunk_len, kc1 = min(n, kc0 + chunk_len);
+  const int pool_r = halo ? dm.pool_k / 2 : 0;
+  // with the pool fused: a whole tile in front of the chunk, the pool radius behind it (no tile starts past the
+  // last key somebody needs)
+  const int k0 = halo && kc0 > 0 ? kc0 - HALO : kc0;
+  const int k1 = halo ? min(n, kc1 + pool_r) : kc1;
+  const int ntiles = (k1 - k0 + TILE - 1) / TILE;
+  const size_t head_row0 = (size_t)b * RQ + (size_t)c * R;
+
+  const int iters = wv < ntiles ? (ntiles - 1 - wv) / NW + 1 : 0;
+  const int rot = (int)(((long long)chunk * iters) / nch);
+  auto tile_of = [&](int it) {
+    const int p = rot - 1 - it;
+    return wv + (p < 0 ? p + iters : p) * NW;
+  };
+  const char *kbase = reinterpret_cast<const char *>(K) +
+                      ((size_t)st.tok_off[b] * dm.k_stride_tok + (size_t)c * dm.k_stride_head) * 2;
+  const unsigned tok_bytes = (unsigned)dm.k_stride_tok * 2u;
+  // rows nobody needs (in front of the pool radius, behind the sequence or the radius) repeat the nearest needed one
+  const int need_lo = max(kc0 - pool_r, 0), need_hi = min(kc1 - 1 + pool_r, n - 1);
+  unsigned ld_off[T::NV];
+#pragma unroll
+  for (int v = 0; v < T::NV; ++v) ld_off[v] = __umul24(lane / T::ROW16, tok_bytes) + T::col(lane, v);
+  auto issue_clamped = [&](int tile, auto &&load) {
+    const int key0 = min(k0 + tile * TILE, need_hi);
+    T::clamped(kbase + (long long)key0 * tok_bytes, tok_bytes, max(need_lo - key0, 0), need_hi - key0, lane, load);
+  };
+  auto issue = [&](int tile, int buf) {
+    const int key0 = k0 + tile * TILE;
+    u32x4 *dst = buf ? &kt1[wv][0] : &kt0[wv][0];
+    auto load = [&](const char *base, unsigned off, unsigned at, int word) { load_to_lds_untracked(base, off, at, dst + word); };
+    if (key0 >= need_lo && key0 + TILE - 1 <= need_hi) T::whole(kbase + (long long)key0 * tok_bytes, tok_bytes, ld_off, load);
+    else issue_clamped(tile, load);
+  };
+  // The first tile and, through LDS (the second tile's place), the window queries.  Unconditionally, and counted
+  // by the compiler, so that its wait for what was asked before them does not stop at them as well.
+  constexpr int QI = RPAD / T::RPI / NW;
+  static_assert(QI * T::RPI * NW == RPAD && RB * T::WORDS <= NW * T::WORDS, "");
+  u32x4 *qs = &kt1[0][0];
+  auto request = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    issue_clamped(iters > 0 ? tile_of(0) : 0, [&](const char *base, unsigned off, unsigned at, int word) { load_to_lds(base, off, at, &kt0[wv][word]); });
+#pragma unroll
+    for (int i = 0; i < QI; ++i) {
+      const unsigned row = (unsigned)(wv * QI + i) * T::RPI + lane / T::ROW16;   // (rows past R are row R-1, zeroed below)
+      load_to_lds(reinterpret_cast<const char *>(q) + head_row0 * (D * 2),
+                  min(row, (unsigned)R - 1u) * (D * 2) + ((lane % T::ROW16) ^ T::swz(row)) * 16u, 0u, qs + (wv * QI + i) * 64);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  unsigned rd[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) rd[s] = T::operand(l32, half, s);
+  bf16x8 qf[RB][KS];                                   // kept for the whole chunk
+  auto queries = [&]() {
+    wait_vmem<0>();
+    lds_barrier();
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb) {
+      const unsigned keep = mb * 32 + l32 < R ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) qf[mb][s] = as_bf16(qs[mb * T::WORDS + rd[s]] & keep);
+    }
+  };
+  // the rows' log-sum-exp in the base-2 domain; +inf on the padding rows makes their weights zero
+  if (lse) {
+    request();
+    for (int i = tid; i < RPAD; i += NT) sh_lse[i] = (i < R) ? lse[head_row0 + i] * lse_mul : INFINITY;
+    queries();
+  } else {
+    // Sweep 1's partials (max, sum) of this head's rows: SL threads take two rows, every SL-th partial each, CB of
+    // them at a time; they come from the cache and are asked for before anything else.  (The few partials that
+    // are combined here leave their offsets far inside 32 bits.)
+    constexpr int CB = 16;
+    const int q2 = tid % (RPAD / 2), sl = tid / (RPAD / 2);
+    const int row = min(2 * q2, max(R - 2, 0)), np = cp.off[b + 1] - cp.off[b];
+    struct __attribute__((packed, aligned(8))) Pair { float m0, l0, m1, l1; };
+    const float2 *pp = part + ((size_t)cp.off[b] * RQ + (size_t)c * R);
+    Pair pml[CB];
+    auto load_parts = [&](int p0) {
+#pragma unroll
+      for (int u = 0; u < CB; ++u) pml[u] = *reinterpret_cast<const Pair *>(pp + (unsigned)(min(p0 + u * SL, np - 1) * RQ + row));
+    };
+    float M0 = -INFINITY, L0 = 0.0f, M1 = -INFINITY, L1 = 0.0f;
+    // first the largest maximum of a batch, then every sum scaled to it (independent exponentials)
+    auto fold = [&](int p0) {
+      float n0 = M0, n1 = M1;
+#pragma unroll
+      for (int u = 0; u < CB; ++u)
+        if (p0 + u * SL < np) { n0 = fmaxf(n0, pml[u].m0); n1 = fmaxf(n1, pml[u].m1); }
+      const float r0 = (n0 == -INFINITY) ? 0.0f : n0, r1 = (n1 == -INFINITY) ? 0.0f : n1;
+      L0 *= fast_exp2(M0 - r0);
+      L1 *= fast_exp2(M1 - r1);
+#pragma unroll
+      for (int u = 0; u < CB; ++u)
+        if (p0 + u * SL < np) {
+          L0 += pml[u].l0 * fast_exp2(pml[u].m0 - r0);
+          L1 += pml[u].l1 * fast_exp2(pml[u].m1 - r1);
+        }
+      M0 = n0;
+      M1 = n1;
+    };
+    load_parts(sl);
+    request();
+    fold(sl);
+    for (int p0 = sl + CB * SL; p0 < np; p0 += CB * SL) {
+      load_parts(p0);
+      fold(p0);
+    }
+    if (2 * q2 == R - 1 && R > 1) { M0 = M1; L0 = L1; }        // (an odd number of rows: the last came as the second of its pair)
+    *reinterpret_cast<float2 *>(&sh_cm[sl * RPAD + 2 * q2]) = make_float2(M0, M1);
+    *reinterpret_cast<float2 *>(&sh_cl[sl * RPAD + 2 * q2]) = make_float2(L0, L1);
+    queries();                                         // (its barrier also shows the above)
+    if (tid < RPAD) {
+      float Mt = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < SL; ++i) Mt = fmaxf(Mt, sh_cm[i * RPAD + tid]);
+      const float ref = (Mt == -INFINITY) ? 0.0f : Mt;
+      float Lt = 0.0f;
+#pragma unroll
+      for (int i = 0; i < SL; ++i) Lt += sh_cl[i * RPAD + tid] * fast_exp2(sh_cm[i * RPAD + tid] - ref);
+      sh_lse[tid] = (tid < R) ? Mt + __builtin_amdgcn_logf(Lt) : INFINITY;
+    }
+  }
+  lds_barrier();                                       // everybody has its queries, and the log-sum-exp is there
+  if (iters > 1) issue(tile_of(1), 1);
+
+  bf16x8 kf[KS];
+  floatx16 acc[2];                                     // products of the current row block and of the one before
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = -INFINITY;
+  float sum[RS];
+#pragma unroll
+  for (int i = 0; i < RS; ++i) sum[i] = 0.0f;
+  const float inv = 1.0f / (float)R;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  // The 16 rows a lane sees of a row block: their log-sum-exp in registers, or, where the queries take 128 of
+  // them, four at a time from LDS, two groups ahead of their use.
+  constexpr bool L2_REGS = RB <= 2;
+  float l2[L2_REGS ? RB : 1][16];
+  if (L2_REGS) {
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) l2[mb][r] = sh_lse[mb * 32 + 8 * (r / 4) + 4 * half + (r % 4)];
+  }
+  f32x4 lq[4];
+  auto read_lq = [&](int mb, int q4) { return *reinterpret_cast<const f32x4 *>(&sh_lse[mb * 32 + 8 * q4 + 4 * half]); };
+  if (!L2_REGS) {
+    lq[0] = read_lq(RB - 1, 0);
+    lq[1] = read_lq(RB - 1, 1);
+  }
+  // share s of KS of the vector work on a row block's products; a[r]: window row mb*32 + 8*(r/4) + 4*half + r%4
+  auto share = [&](floatx16 &a, int mb, int next_mb, int s) {
+    constexpr int V = 16 / KS;
+#pragma unroll
+    for (int v = s * V; v < (s + 1) * V; ++v) {
+      float l;
+      if constexpr (L2_REGS) {
+        l = l2[mb][v];
+      } else {
+        if (v % 4 == 0) lq[(v / 4 + 2) % 4] = v / 4 < 2 ? read_lq(mb, v / 4 + 2) : read_lq(next_mb, v / 4 - 2);
+        l = lq[v / 4][v % 4];
+      }
+      sum[mb / MB] += fast_exp2(fmaf(a[v], c_log2, -l));
+    }
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < RS; ++i) sum[i] = 0.0f;
+  };
+  auto file = [&](int tile) {                          // a finished tile's mean weights (a key per lane; past n: never read)
+    float tot = sum_halves(sum[0]);
+#pragma unroll
+    for (int i = 1; i < RS; ++i) tot += sum_halves(sum[i]);
+    sh_part[tile * TILE + l32] = tot * inv;
+    clear();
+  };
+  if (iters > 0) {
+    if (iters > 1) wait_vmem<LD>(); else wait_vmem<0>();
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt0[wv][rd[s]]);
+  }
+  int prev = 0;                                        // tile before the current one
+  for (int it0 = 0; it0 < iters; it0 += 2) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int it = it0 + j;
+      if (it < iters) {
+        const int tile = tile_of(it);
+        wait_lds();                                    // the tile is in registers: its place is free
+        if (it + 2 < iters) issue(tile_of(it + 2), j);
+#pragma unroll
+        for (int mb = 0; mb < RB; ++mb) {
+          const int cur = (j * RB + mb) & 1, pmb = mb == 0 ? RB - 1 : mb - 1;
+          if (mb == RB - 1) {                          // the next tile, for the reads below
+            if (it + 2 < iters) wait_vmem<LD>(); else wait_vmem<0>();
+          }
+          floatx16 a = {0};
+#pragma unroll
+          for (int s = 0; s < KS; ++s) {
+            a = mfma16<F16>(qf[mb][s], kf[s], a);
+            if (mb == RB - 1) kf[s] = as_bf16(j == 0 ? kt1[wv][rd[s]] : kt0[wv][rd[s]]);   // (whatever lies there behind the last)
+            share(acc[1 - cur], pmb, mb, s);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          acc[cur] = a;
+          asm volatile("" : "+v"(sum[pmb / MB]));      // the vector work stays in front of this point
+          if (mb == 0) {
+            if (it > 0) file(prev);
+            else clear();
+          }
+        }
+        prev = tile;
+      }
+    }
+  }
+  if (iters > 0) {
+    floatx16 last = acc[1];
+    if (RB % 2 == 1 && (iters & 1)) last = acc[0];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) share(last, RB - 1, RB - 1, s);
+    file(prev);
+  }
+  wait_vmem<0>();                                      // (a wavefront without tiles has asked for one as well)
+  __syncthreads();
+  if (tc.hist0) {
+    for (int i = tid; i < RADIX_BINS; i += NT) sh_hist[i] = 0u;
+    __syncthreads();
+  }
+  pool_and_file<NT, CHUNK>(sh_part, sh_hist, out + st.score_off[b] + (size_t)c * n, kc0, kc1, k0, n, chunk_len,
+                           halo ? dm.pool_k / 2 : 0, tc, b, b * h + c);
+}
+
+// MB row blocks of 32 window rows times RS are a workgroup's rows, RS * KG its wavefronts.  Up to 128 rows a
+// wavefront takes all of them and the wavefronts split the keys; beyond, RS wavefronts share a tile.  CHUNK: what
+// a workgroup has room for (sweep 1 of up to 128 rows does not depend on it).
+template <int D, int MB, int RS, int KG, int CHUNK, int PASS, bool F16, bool PR = false>
+__global__ __launch_bounds__(64 * RS * KG, MB * RS <= 4 ? 2 : 1) void score_mfma_kernel(
+    SeqTab st, ChunkTab ct, ChunkTab cp, Dims dm, float c_log2, const unsigned short *__restrict__ q,
+    const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
+    float2 *__restrict__ part, float *__restrict__ out, int halo, int chunk_len,
+    TopkCarry tc) {
+  if constexpr (MB * RS <= 4 && PASS == 1)
+    stats_own<D, MB * RS, F16>(st, cp, dm, c_log2, q, K, part, tc);
+  else if constexpr (MB * RS <= 4 && !PR)
+    weights_own<D, MB, RS, CHUNK, F16>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
+  else
+    sweep_shared<D, MB, RS, KG, CHUNK, PASS, F16, PR>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
 }
 
 template <bool F16, int D, int MB, int RS, int KG, int CHUNK>
@@ -744,20 +1375,22 @@ void run_mfma(const MfmaVariant &v, const SeqTab &st, const Dims &dm, const void
               const float *row_lse, float *scores, char *ws, const ScorePlan &pl,
               const TopkCarry &tc, bool pool_rows, hipStream_t s) {
   const ChunkTab ct = make_chunks(st, v.len);
+  const ChunkTab cp = make_chunks(st, v.part_len);     // sweep 1's workgroups
   const int nblk = ct.off[st.batch] * dm.h_kv;
   const float c_log2 = dm.scale * LOG2E;
   float2 *part = (float2 *)(ws + pl.part);
   float *lse = (float *)(ws + pl.lse), *raw = (float *)(ws + pl.raw);
   const dim3 block(64 * RS * KG);
   const bool fuse_lse = v.fuse_lse, fuse_pool = v.fuse_pool;
-  const float *use_lse = row_lse;
+  const float *use_lse = row_lse;              // the caller's in the natural-log domain, the combined one in base 2
+  const float lse_mul = row_lse ? LOG2E : 1.0f;
   if (!row_lse) {
-    ADAKV_LAUNCH("score_stats_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 1, F16>), dim3(nblk),
-                 block, s, st, ct, dm, c_log2, (const unsigned short *)q,
-                 (const unsigned short *)K, (const float *)nullptr, part,
-                 (float *)nullptr, 0, v.len, tc);
+    ADAKV_LAUNCH("score_stats_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 1, F16>), dim3(cp.off[st.batch] * dm.h_kv),
+                 block, s, st, cp, cp, dm, c_log2, (const unsigned short *)q,
+                 (const unsigned short *)K, (const float *)nullptr, 1.0f, part,
+                 (float *)nullptr, 0, v.part_len, tc);
     if (!fuse_lse) {
-      launch_lse_combine(st, ct, dm.h_q * dm.w, part, lse, s);
+      launch_lse_combine(st, cp, dm.h_q * dm.w, part, lse, s);
       use_lse = lse;
     }
   } else if (tc.zero_begin) {
@@ -766,13 +1399,13 @@ void run_mfma(const MfmaVariant &v, const SeqTab &st, const Dims &dm, const void
   if (pool_rows) {
     // the printed order of Alg. 2 l.4: the sweep pools every row itself and writes final scores
     ADAKV_LAUNCH("score_weights_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16, true>),
-                 dim3(nblk), block, s, st, ct, dm, c_log2, (const unsigned short *)q,
-                 (const unsigned short *)K, use_lse, part, scores, 0, v.len, tc);
+                 dim3(nblk), block, s, st, ct, cp, dm, c_log2, (const unsigned short *)q,
+                 (const unsigned short *)K, use_lse, lse_mul, part, scores, 0, v.len, tc);
     return;
   }
   ADAKV_LAUNCH("score_weights_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16>), dim3(nblk),
-               block, s, st, ct, dm, c_log2, (const unsigned short *)q, (const unsigned short *)K,
-               use_lse, part, fuse_pool ? scores : raw, fuse_pool ? 1 : 0, v.len, tc);
+               block, s, st, ct, cp, dm, c_log2, (const unsigned short *)q, (const unsigned short *)K,
+               use_lse, lse_mul, part, fuse_pool ? scores : raw, fuse_pool ? 1 : 0, v.len, tc);
   if (!fuse_pool) launch_pool(st, dm, raw, scores, s);
 }
 
@@ -850,13 +1483,14 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   MfmaVariant v;
   const int R = dm.g * dm.w;
   int slots, most;                             // workgroups the chip holds at a time; longest chunk
-  if (R <= 64) { v = {R <= 32 ? 1 : 2, 1, 4, 2048, 0, false, false}; slots = 256; most = 2048; }
-  else if (R <= 128) { v = {2, 2, 2, 512, 0, false, false}; slots = 512; most = 4096; }
-  else if (R <= 256) { v = {2, 4, 1, 1024, 0, false, false}; slots = 512; most = 2048; }
+  // (most: at 128 rows and d = 128 what half of a compute unit's LDS holds beside four wavefronts' tiles)
+  if (R <= 64) { v = {R <= 32 ? 1 : 2, 1, 4, 2048, 0, 0, false, false}; slots = 256; most = 2048; }
+  else if (R <= 128) { v = {2, 2, 2, 512, 0, 0, false, false}; slots = 512; most = dm.d == 128 ? OWN_MOST : 4096; }
+  else if (R <= 256) { v = {2, 4, 1, 1024, 0, 0, false, false}; slots = 512; most = 2048; }
   // 512 rows: eight wavefronts of 64 rows; with d = 64 a row block needs half the registers and
   // a tile half the loads, so four wavefronts of 128 rows.
-  else if (dm.d == 128) { v = {2, 8, 1, 2048, 0, false, false}; slots = 256; most = 4096; }
-  else { v = {4, 4, 1, 1024, 0, false, false}; slots = 256; most = 1024; }
+  else if (dm.d == 128) { v = {2, 8, 1, 2048, 0, 0, false, false}; slots = 256; most = 4096; }
+  else { v = {4, 4, 1, 1024, 0, 0, false, false}; slots = 256; most = 1024; }
   // Chunk length.  A workgroup's set-up and epilogue (4 and 7 us) want long chunks, the chip wants
   // to be full, and workgroups beyond what it holds at a time wait for a second round.  So: the
   // shortest chunk that gives every compute unit at most one workgroup, down to 64 keys (128 where
@@ -903,6 +1537,21 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   // alignment of the parts, asked of the split alone, so that a layer that just fits keeps fitting).
   auto need = [&](int len) { return score_workspace(st, dm, len) + plan_topk_bytes(st, dm); };
   if (need(v.len) + 1024 > (size_t)ADAKV_STATIC_SCRATCH_BYTES && need(most) <= (size_t)ADAKV_STATIC_SCRATCH_BYTES) v.len = most;
+  // Sweep 1 of up to 128 rows is not bound to the chunks: one resident round of workgroups (of 128 KiB of LDS
+  // each at d = 128, half of that at d = 64) over all sequences, as many rounds as there are heads for beyond
+  // that, and never more workgroups than sweep 2's chunks (the partials have a place for each of those).
+  v.part_len = v.len;
+  if (R <= 128) {
+    const long long room = dm.d == 128 ? 256 : 512, heads = (long long)st.batch * dm.h_kv;
+    const long long wgs = (heads + room - 1) / room * room;
+    int lo = v.len / TILE, hi = longest / TILE + 1 > lo ? longest / TILE + 1 : lo;
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      if (workgroups(st, dm, mid * TILE) <= wgs) hi = mid;
+      else lo = mid + 1;
+    }
+    v.part_len = hi * TILE;
+  }
   // The instantiation: the smallest score array in LDS that holds a chunk; with 512 rows a compute
   // unit holds one workgroup either way and long sequences take the larger.
   while (v.chunk < v.len) v.chunk *= 2;
