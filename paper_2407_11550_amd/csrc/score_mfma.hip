@@ -14,9 +14,9 @@
 // region of K at a time.  All g query heads of the group share every K tile of 32 keys, and the
 // window queries stay in registers as MFMA operands for a workgroup's whole life.  Up to 128 rows
 // every wavefront holds all of them and works on tiles of its own (stats_own, weights_own); beyond,
-// RS wavefronts of at most 64 rows (two per SIMD) share a tile: HBM -> registers (coalesced
-// 16-byte loads of whole rows, issued by the whole workgroup, two iterations ahead) -> LDS (padded
-// rows) -> registers in operand layout (sweep_shared).
+// RS wavefronts of at most 64 rows (128 at d = 64) share the tiles (stats_group, weights_group).  A
+// K tile travels straight from HBM into LDS (rows of whole lines, 16 bytes a lane) and from there into
+// registers in operand layout.
 //
 // Operand roles differ between the sweeps because of what the accumulator layout makes cheap
 // (D[i][j]: lane = column j, 16 rows i per lane):
@@ -24,7 +24,9 @@
 //            lane, nothing crosses lanes until the chunk is done;
 //   sweep 2: D = Q K_tile^T, a lane owns ONE key and 16 window rows: the sum over rows is
 //            lane-local adds plus one cross-half add (partial sums of RS row groups meet
-//            in LDS when the chunk is done and are added in a fixed order).
+//            in LDS and are added in a fixed order);
+//   sweep 2 with the pool in front of the sum over rows: as sweep 1, the pool runs along a
+//            lane's registers, and the sum over rows crosses lanes once per tile.
 // Sweep 1 hands its (max, sum) pairs to sweep 2 with the maximum in the base-2 domain.
 #include <math.h>
 
@@ -46,11 +48,6 @@ constexpr int MFMA_POOL_ROWS_MAX_RADIUS = 7;
 constexpr int OWN_MOST = 3840;     // keys of a chunk at 128 rows, d = 128: beside 64 KiB of tiles in half of a compute unit's LDS
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-// The value of the neighbouring lane: CTRL 0x130 = wave_shl:1 (lane i reads lane i+1), 0x138 =
-// wave_shr:1 (lane i reads lane i-1); the last / first lane of the wavefront reads 0.
-template <int CTRL> __device__ __forceinline__ unsigned wave_shift(unsigned x) {
-  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
-}
 __device__ __forceinline__ bf16x8 as_bf16(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // One 32x32x16 product-accumulate on eight 16-bit elements per lane and operand; the fragments are
@@ -122,632 +119,6 @@ __device__ __forceinline__ void pool_and_file(const float *sh_part, unsigned *sh
   }
 }
 
-// PR (sweep 2 only): the printed order of Alg. 2 l.4, max-pool along the keys in every window row
-// first, mean over the rows afterwards.  A lane of sweep 2 owns one key and 16 rows per row block,
-// so the pool is a sliding maximum across neighbouring lanes, with whole-wavefront shifts by one
-// lane.  Tiles then overlap by the pool radius on either side: only the inner 32 - 2r
-// lanes of a tile have all their neighbours and produce a score.
-template <int D, int MB, int RS, int KG, int CHUNK, int PASS, bool F16, bool PR>
-__device__ __forceinline__ void sweep_shared(
-    const SeqTab &st, const ChunkTab &ct, const ChunkTab &cp, const Dims &dm, float c_log2, const unsigned short *__restrict__ q,
-    const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
-    float2 *__restrict__ part, float *__restrict__ out, int halo, int chunk_len,
-    const TopkCarry &tc) {
-  constexpr int NW = RS * KG;                // wavefronts per workgroup
-  constexpr int NT = 64 * NW;
-  constexpr int KS = D / 16;                 // MFMA k-steps per tile
-  constexpr int ROW16 = D * 2 / 16;          // 16-byte words per K row
-  constexpr int STRIDE16 = ROW16 + 1;        // padded LDS row, in 16-byte words
-  constexpr int RW = 32 * MB;                // window rows per wavefront
-  constexpr int RPAD = RW * RS;              // window rows per workgroup (padded)
-
-  __shared__ u32x4 kt[2][KG * TILE * STRIDE16];  // two buffers of one iteration's KG tiles
-  __shared__ float sh_rows[2][NW][RW];       // sweep 1: per-wave row (max, sum); sweep 2: [0][0] lse
-  constexpr int HALO = TILE;                 // keys scored on either side of the chunk for the pool
-  __shared__ float sh_part[PASS == 2 ? RS : 1][PASS == 2 ? CHUNK + 2 * HALO : 1];
-  constexpr int NCOMB = NT > RPAD ? NT : RPAD;   // (thread slices) x (rows) of the statistics combination
-  __shared__ float sh_cm[PASS == 2 ? NCOMB : 1], sh_cl[PASS == 2 ? NCOMB : 1];
-  // first radix digits of the chunk's scores: only needed once the tile loop is over, in the
-  // place of the K tiles (which leaves room for 4096-key chunks of eight row groups)
-  static_assert(sizeof(kt) >= RADIX_BINS * sizeof(unsigned), "the digit histogram must fit into the tile buffers");
-  unsigned *sh_hist = reinterpret_cast<unsigned *>(&kt[0][0]);
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  // Pipeline mode: the statistics sweep clears the Top-k histograms (they are first touched by
-  // the kernel after it), the weights sweep counts the first digit of every score it writes.
-  if (PASS == 1 && tc.zero_begin) {
-    for (unsigned i = blockIdx.x * NT + tid; i < tc.zero_words; i += gridDim.x * NT)
-      tc.zero_begin[i] = 0u;
-  }
-
-  // the wavefront index is the same in all lanes: telling the compiler keeps everything derived
-  // from it (tile numbers, K addresses, loop conditions) in scalar registers
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int half = lane >> 5, l32 = lane & 31;
-  const int kg = wv / RS, rs = wv % RS;
-  const int h = dm.h_kv;
-  const int c = blockIdx.x % h;
-  int cg = blockIdx.x / h;
-  if (PASS == 2) cg = ct.off[st.batch] - 1 - cg;
-  const int b = find_seq(ct, st.batch, cg);
-  const int chunk = cg - ct.off[b];
-  const int n = st.n[b];
-  const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
-  // (CHUNK is what the score array in LDS holds at most; a layer's chunks are chunk_len keys)
-  const int kc0 = chunk * chunk_len;         // first key of the chunk
-  const int kc1 = min(n, kc0 + chunk_len);
-  // sweep 2 with the pool fused also scores the neighbours the pool looks at: a whole tile in
-  // front of the chunk (tiles stay aligned), the pool radius behind it.  No tile may start past
-  // the last key somebody needs: the row clamp in load_set counts rows from the tile set's
-  // first key and must never go below it.
-  const int pool_r = (PASS == 2 && (halo || PR)) ? dm.pool_k / 2 : 0;
-  const int tstep = PR ? TILE - 2 * pool_r : TILE;     // keys a tile advances by
-  // Sweep 1 does not need a workgroup's keys to be neighbours (its result is a (max, sum) pair
-  // per row over whatever keys it saw), so there the tile sets of a head's workgroups are
-  // interleaved: workgroup `chunk` of the sequence's nch takes sets chunk, chunk + nch, ...
-  // of the whole sequence.  At any moment the workgroups of a head then read neighbouring sets,
-  // i.e. the chip streams one dense region of K instead of 64 regions 4 MiB apart (measured
-  // with a plain-read kernel of the same shape: 6.2 against 5.5 TB/s).
-  constexpr bool INTER = PASS == 1;
-  const int nch = ct.off[b + 1] - ct.off[b];
-  const int k0 = INTER ? 0 : (PASS == 2 && halo && kc0 > 0) ? kc0 - HALO : kc0;
-  const int k1 = INTER ? n : (PASS == 2 && halo) ? min(n, kc1 + pool_r) : kc1;
-  const int ntiles = (k1 - k0 + tstep - 1) / tstep;
-  const int row0 = rs * RW;                  // first window row of this wavefront
-  const size_t head_row0 = (size_t)b * RQ + (size_t)c * R;
-
-  // ---- K path ---------------------------------------------------------------------------------
-  // An iteration covers KG consecutive tiles (one per wavefront group).  All threads of the
-  // workgroup load the iteration's rows together: 16 lanes per 256-byte row, every byte read
-  // once per workgroup, addressed as a wave-uniform 64-bit base (scalar registers) plus a
-  // 32-bit per-lane offset.  The loads of iterations it+1 .. it+DEPTH are in flight while
-  // iteration it is computed (DEPTH register sets, two LDS buffers, one barrier per iteration).
-  // register sets = iterations of loads in flight (a third set fits the statistics sweep's
-  // registers and was measured: no faster; nor are four or six sets on the 512-row shape,
-  // where a set is a single word per thread)
-  constexpr int DEPTH = 2;
-  constexpr int TW = TILE * ROW16;                     // 16-byte words per tile
-  constexpr int LDPT = KG * TW / NT;                   // loads per thread per iteration
-  static_assert(KG * TW % NT == 0 && LDPT >= 1, "tile set must split evenly over the threads");
-  const char *kbase = reinterpret_cast<const char *>(K) +
-                      ((size_t)st.tok_off[b] * dm.k_stride_tok + (size_t)c * dm.k_stride_head) * 2;
-  const size_t tok_bytes = (size_t)dm.k_stride_tok * 2;
-  // word tid + i*NT of the iteration's KG*TW words: row (relative to the iteration's first key)
-  // and 16-byte column
-  int ld_rel[LDPT];
-  int wr_off[LDPT];                                    // word offset in an LDS buffer
-  const unsigned col_bytes = (unsigned)(tid % ROW16) * 16u;
-#pragma unroll
-  for (int i = 0; i < LDPT; ++i) {
-    const int wi = tid + i * NT;
-    const int tl = wi / TW, row = (wi % TW) / ROW16;
-    ld_rel[i] = tl * TILE + row;
-    wr_off[i] = tl * (TILE * STRIDE16) + row * STRIDE16 + tid % ROW16;
-  }
-  // (with overlapping tiles the wavefront groups' tiles start tstep rows apart in the buffer)
-  const int rd_off = kg * (tstep * STRIDE16) + l32 * STRIDE16 + half;
-  // interleaved: ceil(n / chunk_len) workgroups share ceil(n / (KG*TILE)) >= nch sets, at least one each
-  // (chunk_len >= KG*TILE)
-  const int sets_all = (ntiles + KG - 1) / KG;
-  const int iters = INTER ? (sets_all - chunk + nch - 1) / nch : sets_all;
-  // The workgroups of a head run side by side and their chunks lie a fixed power-of-two number
-  // of bytes apart; if all of them walked their chunk from its first row, they would ask for
-  // addresses that are equal modulo that distance at the same time, i.e. the same memory
-  // channels.  Each workgroup therefore starts at a different point of its chunk and wraps
-  // around (neither sweep depends on the order of the tiles).
-  const int rot = (int)(((long long)chunk * iters) / nch);
-  // Sweep 1 walks its chunk forwards from the rotated start; sweep 2 walks it backwards from
-  // there, i.e. it begins with what sweep 1 read last.  Both sweeps have every chunk in flight
-  // at once, so this, and not the order of the chunks, decides what the memory-side cache still
-  // holds: reading a set slightly larger than a cache twice in the same direction hits nothing,
-  // reading it back hits most of it.
-  auto phys = [&](int it) {
-    if (INTER) return chunk + it * nch;                // a set of the whole sequence
-    if (PASS == 2) {
-      const int p = rot - 1 - it;
-      return p < 0 ? p + iters : p;
-    }
-    const int p = it + rot;
-    return p >= iters ? p - iters : p;
-  };
-
-  // Branch-free on purpose (the compiler can only keep older loads in flight across a wait if
-  // the loads in between are issued on every path).  Rows are clamped into the range somebody
-  // reads: past the end of the sequence they re-read row n-1 (masked out later), and of the two
-  // halo tiles only the pool radius next to the chunk is fetched, the other rows repeat the
-  // nearest needed one (a cache hit) and their results are never looked at.
-  // tok_bytes < 2^24 is checked on the host.
-  const int need_lo = INTER ? 0 : max(kc0 - pool_r, 0);
-  const int need_hi = INTER ? n - 1 : min(kc1 - 1 + pool_r, n - 1);
-  auto load_set = [&](u32x4 (&g)[LDPT], int it) {
-    const int key0 = k0 + it * KG * tstep - (PR ? pool_r : 0);   // first key of the iteration
-    // both bounds are kept at or above zero, so the clamped row is never negative (it goes
-    // through an unsigned 24-bit multiply); key0 <= need_hi holds by the choice of k1 above
-    const int lim = max(need_hi - key0, 0), lo = max(need_lo - key0, 0);
-    const char *sb = kbase + (size_t)key0 * tok_bytes;
-#pragma unroll
-    for (int i = 0; i < LDPT; ++i) {
-      const unsigned off =
-          __umul24((unsigned)max(min(ld_rel[i], lim), lo), (unsigned)tok_bytes) + col_bytes;
-      g[i] = *reinterpret_cast<const u32x4 *>(sb + off);
-    }
-  };
-  auto store_set = [&](const u32x4 (&g)[LDPT], int buf) {
-#pragma unroll
-    for (int i = 0; i < LDPT; ++i) kt[buf][wr_off[i]] = g[i];
-  };
-
-  // Sweep 2 without a caller's log-sum-exp combines sweep 1's partial (max, sum) of this head's
-  // rows over the sequence's chunks.  With at least as many threads as (padded) rows, SL
-  // threads share a row and each takes every SL-th chunk; with fewer, a thread combines RPT
-  // rows one after the other.  CB chunks are loaded at a time, and the first CB of the first
-  // row are requested before anything else: loads return in order, and these come from the
-  // cache while the K rows below come from memory, so the combination runs in the shadow of
-  // the first K round trip instead of after it.
-  constexpr int CB = 32;
-  constexpr int SL = NT >= RPAD ? NT / RPAD : 1;
-  constexpr int RPT = NT >= RPAD ? 1 : RPAD / NT;
-  constexpr int RSTEP = RPAD / RPT;            // rows combined side by side
-  static_assert(SL * RSTEP == NT && RPT * RSTEP == RPAD, "threads and rows must tile each other");
-  const int qi = tid % RSTEP, sl = tid / RSTEP;
-  const int kend = cp.off[b + 1];
-  float2 pml[PASS == 2 ? CB : 1];              // (max, sum) of CB chunks
-  auto load_parts = [&](int k0c, int row) {
-#pragma unroll
-    for (int u = 0; u < CB; ++u) {
-      const int k = min(k0c + u * SL, kend - 1);
-      const size_t o = (size_t)k * RQ + (size_t)c * R + min(row, R - 1);
-      pml[u] = part[o];
-    }
-  };
-  if (PASS == 2 && !lse) load_parts(cp.off[b] + sl, qi);
-
-  // The first two tile sets are requested next; the combination and the loads of the query
-  // fragments (further down, so that they do not hold registers while the partials do) happen
-  // in the shadow of that round trip.
-  u32x4 g[DEPTH][LDPT];
-#pragma unroll
-  for (int j = 0; j < DEPTH; ++j) load_set(g[j], phys(min(j, iters - 1)));
-
-  // sweep 2: log2-domain log-sum-exp of the 16 rows a lane sees in each row block; +inf on the
-  // padding rows makes their weights exactly zero
-  float l2[PASS == 2 ? MB : 1][16];
-  if (PASS == 2) {
-    float *sh_lse = &sh_rows[0][0][0];       // RPAD floats
-    if (lse) {
-      for (int i = tid; i < RPAD; i += NT) sh_lse[i] = (i < R) ? lse[head_row0 + i] * lse_mul : INFINITY;
-    } else {
-      // fold the partials in: first the largest maximum of a batch, then every sum scaled to it
-      // (independent exponentials instead of a chain of rescalings)
-#pragma unroll
-      for (int rr = 0; rr < RPT; ++rr) {
-        const int row = qi + rr * RSTEP;
-        float M = -INFINITY, L = 0.0f;
-        for (int k0c = cp.off[b] + sl; k0c < kend; k0c += CB * SL) {
-          if (rr > 0 || k0c != cp.off[b] + sl) load_parts(k0c, row);
-          float bm = -INFINITY;
-#pragma unroll
-          for (int u = 0; u < CB; ++u)
-            if (k0c + u * SL < kend) bm = fmaxf(bm, pml[u].x);
-          const float nm = fmaxf(M, bm);
-          const float ref = (nm == -INFINITY) ? 0.0f : nm;
-          float acc = L * fast_exp2(M - ref);
-#pragma unroll
-          for (int u = 0; u < CB; ++u)
-            if (k0c + u * SL < kend) acc += pml[u].y * fast_exp2(pml[u].x - ref);
-          L = acc;
-          M = nm;
-        }
-        sh_cm[sl * RPAD + row] = M;
-        sh_cl[sl * RPAD + row] = L;
-      }
-      __syncthreads();
-      for (int row = tid; row < RPAD; row += NT) {
-        float Mt = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < SL; ++i) Mt = fmaxf(Mt, sh_cm[i * RPAD + row]);
-        const float ref = (Mt == -INFINITY) ? 0.0f : Mt;
-        float Lt = 0.0f;
-#pragma unroll
-        for (int i = 0; i < SL; ++i) Lt += sh_cl[i * RPAD + row] * fast_exp2(sh_cm[i * RPAD + row] - ref);
-        sh_lse[row] = (row < R) ? Mt + __builtin_amdgcn_logf(Lt) : INFINITY;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        l2[mb][r] = sh_lse[row0 + mb * 32 + 8 * (r / 4) + 4 * half + (r % 4)];
-  }
-  // ---- window queries of this wavefront as MFMA operands, kept for the whole chunk ----------
-  // (rows past R are loaded from row R-1 and zeroed, so every load is unconditional)
-  bf16x8 qf[MB][KS];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int row = row0 + mb * 32 + l32;
-    const unsigned keep = row < R ? 0xFFFFFFFFu : 0u;
-    const unsigned short *src = q + (head_row0 + min(row, R - 1)) * D + half * 8;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      u32x4 v = *reinterpret_cast<const u32x4 *>(src + s * 16);
-      v &= keep;
-      qf[mb][s] = as_bf16(v);
-    }
-  }
-
-  // sweep 1: running statistics of the window row this lane owns in each row block
-  float rm[MB], rl[MB];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) { rm[mb] = -INFINITY; rl[mb] = 0.0f; }
-  bool have_ref = false;                       // (the same for all lanes) a first tile has set rm
-  constexpr bool LAZY_REF = RPAD > 128;
-
-
-  // The matrix products of a tile and the softmax arithmetic on the PREVIOUS tile's products are
-  // independent, so they are written back to back in one basic block: the scheduler interleaves
-  // them and the exponentials of tile t run in the shadow of the MFMAs of tile t+1 (within one
-  // wavefront, not only between the two wavefronts of a SIMD).
-  auto mma = [&](const bf16x8 (&kf)[KS], floatx16 (&acc)[MB]) {
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      floatx16 a = {0};
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-        a = PASS == 1 ? mfma16<F16>(kf[s], qf[mb][s], a) : mfma16<F16>(qf[mb][s], kf[s], a);
-      acc[mb] = a;
-    }
-  };
-  // softmax arithmetic of one finished tile; RAGGED masks keys at or past n
-  auto epilogue = [&](auto ragged_tag, floatx16 (&acc)[MB], int tile) {
-    constexpr bool RAGGED = decltype(ragged_tag)::value;
-    const int base = k0 + tile * TILE;
-    if (PASS == 1) {
-      // acc[mb][r]: key base + 8*(r/4) + 4*half + r%4, window row row0 + mb*32 + l32
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        if (RAGGED) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (base + 8 * (r / 4) + 4 * half + (r % 4) >= n) acc[mb][r] = -INFINITY;
-        }
-        float tm = acc[mb][0];
-#pragma unroll
-        for (int r = 1; r < 16; ++r) tm = fmaxf(tm, acc[mb][r]);
-        const float nm = fmaxf(rm[mb], tm * c_log2);
-        const float ref = (nm == -INFINITY) ? 0.0f : nm;
-        float sum = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(acc[mb][r], c_log2, -ref));
-        rl[mb] = rl[mb] * fast_exp2(rm[mb] - ref) + sum;
-        rm[mb] = nm;
-      }
-    } else if (PR) {
-      // acc[mb][r]: window row row0 + mb*32 + 8*(r/4) + 4*half + r%4, key k0 + tile*tstep - pool_r + l32.
-      // The weights themselves are pooled: they are non-negative floats, whose order is the order
-      // of their bit patterns, so one integer max with the neighbouring lane as its operand does a
-      // step of the sliding maximum.  Keys outside the sequence count as weight 0, which never
-      // wins (the pool window is clipped to the sequence).
-      const int j = tile * tstep - pool_r + l32;       // key, counted from k0
-      const unsigned inseq = (k0 + j >= 0 && k0 + j < n) ? 0xFFFFFFFFu : 0u;
-      // The 128-row kernels take one row block after the other: both at once need 276 registers, one
-      // wavefront per SIMD, 42.5 us for the sweep instead of 32.1 (32768 keys x 8 heads).  The others
-      // keep both in flight (256 rows, 131072 keys: 166 us against 171).
-      constexpr int PB = RS == 2 ? 1 : MB;
-      float sum = 0.0f;
-#pragma unroll
-      for (int m0 = 0; m0 < MB; m0 += PB) {
-        unsigned p[PB][16];
-#pragma unroll
-        for (int mb = 0; mb < PB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            p[mb][r] = __float_as_uint(fast_exp2(fmaf(acc[m0 + mb][r], c_log2, -l2[m0 + mb][r]))) & inseq;
-        for (int t = 0; t < pool_r; ++t) {             // keys j .. j + pool_r
-#pragma unroll
-          for (int mb = 0; mb < PB; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) p[mb][r] = max(p[mb][r], wave_shift<0x130>(p[mb][r]));
-        }
-        for (int t = 0; t < pool_r; ++t) {             // keys j - pool_r .. j + pool_r
-#pragma unroll
-          for (int mb = 0; mb < PB; ++mb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) p[mb][r] = max(p[mb][r], wave_shift<0x138>(p[mb][r]));
-        }
-#pragma unroll
-        for (int mb = 0; mb < PB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum += __uint_as_float(p[mb][r]);
-      }
-      sum += __shfl_xor(sum, 32);
-      if (half == 0 && l32 >= pool_r && l32 < TILE - pool_r && j < k1 - k0) sh_part[rs][j] = sum;
-    } else {
-      // acc[mb][r]: window row row0 + mb*32 + 8*(r/4) + 4*half + r%4, key base + l32
-      float sum = 0.0f;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(acc[mb][r], c_log2, -l2[mb][r]));
-      sum += __shfl_xor(sum, 32);
-      // keys past n in a ragged tile get a value nobody reads
-      if (half == 0) sh_part[rs][tile * TILE + l32] = sum;   // key k0 + tile*TILE + l32
-    }
-  };
-  // The common case of the loop below in one piece: the matrix instructions of the current tile
-  // with the vector arithmetic of the previous (full) tile dealt out between them, a share in
-  // front of every MFMA (the first share covers the wait for the tile's LDS operands), and a scheduling fence after every share so that the order survives: an MFMA
-  // runs for tens of cycles in the matrix core while the wavefront goes on issuing vector
-  // instructions, but only if vector instructions follow it in program order.
-  auto fused_tile = [&](const bf16x8 (&kf)[KS], floatx16 (&accn)[MB], floatx16 (&acc)[MB], int tile,
-                        auto &&between) {
-    constexpr int SLOTS = MB * KS;               // matrix instructions per tile
-    constexpr int BETWEEN_SLOT = 6;              // between() runs after this slot's matrix instruction
-    constexpr int VALS = MB * 16;                // products of the previous tile per lane
-    floatx16 a[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) a[mb] = floatx16{0};
-    if (PASS == 1 && LAZY_REF && have_ref) {
-      // (shapes with more than 128 window rows per KV head, which are bound by their arithmetic;
-      // on the 128-row shapes the sweep is bound by memory and the shorter code measured 2 us slower)
-      // Once a row has a reference, its tiles' exponentials are taken against that same reference
-      // without looking for the tile's maximum first: a sum of exp2(x - ref) is as accurate for one
-      // reference as for another as long as nothing overflows (x - ref < 128), and what underflows
-      // (x - ref < -126) is negligible beside the term that set the reference, which is 1.  An
-      // overflow shows as a sum that is not finite; the tile is then folded in again the careful way.
-      float sum[MB];
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) sum[mb] = 0.0f;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const int slot = s * MB + mb;
-#pragma unroll
-          for (int v = slot * VALS / SLOTS; v < (slot + 1) * VALS / SLOTS; ++v)
-            sum[v / 16] += fast_exp2(fmaf(acc[v / 16][v % 16], c_log2, -rm[v / 16]));
-          a[mb] = mfma16<F16>(kf[s], qf[mb][s], a[mb]);
-          __builtin_amdgcn_sched_barrier(0);
-          if (slot == BETWEEN_SLOT) { between(); __builtin_amdgcn_sched_barrier(0); }
-        }
-      }
-      bool bad = false;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) bad |= !(sum[mb] < INFINITY);
-      if (__any(bad)) {
-        epilogue(std::false_type{}, acc, tile);
-      } else {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) rl[mb] += sum[mb];
-      }
-    } else if (PASS == 1) {
-      // slots 0 .. MB-1 find the row blocks' tile maxima, the others share the exponentials
-      constexpr int ESLOTS = SLOTS - MB;
-      float ref[MB], nmx[MB], sum[MB];
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const int slot = s * MB + mb;
-          if (slot < MB) {
-            float tm = acc[slot][0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) tm = fmaxf(tm, acc[slot][r]);
-            nmx[slot] = fmaxf(rm[slot], tm * c_log2);
-            ref[slot] = (nmx[slot] == -INFINITY) ? 0.0f : nmx[slot];
-            sum[slot] = 0.0f;
-          } else {
-            const int e = slot - MB;
-#pragma unroll
-            for (int v = e * VALS / ESLOTS; v < (e + 1) * VALS / ESLOTS; ++v)
-              sum[v / 16] += fast_exp2(fmaf(acc[v / 16][v % 16], c_log2, -ref[v / 16]));
-          }
-          a[mb] = mfma16<F16>(kf[s], qf[mb][s], a[mb]);
-          __builtin_amdgcn_sched_barrier(0);
-          if (slot == BETWEEN_SLOT) { between(); __builtin_amdgcn_sched_barrier(0); }
-        }
-      }
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        rl[mb] = rl[mb] * fast_exp2(rm[mb] - ref[mb]) + sum[mb];
-        rm[mb] = nmx[mb];
-      }
-      have_ref = true;
-    } else {
-      // The exponentials end two slots early, so that the exchange between the lane halves
-      // travels through the LDS crossbar while the last two matrix instructions are issued.
-      constexpr int ESLOTS = SLOTS - 2;
-      float sum = 0.0f, other = 0.0f;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const int slot = s * MB + mb;
-          if (slot < ESLOTS) {
-#pragma unroll
-            for (int v = slot * VALS / ESLOTS; v < (slot + 1) * VALS / ESLOTS; ++v)
-              sum += fast_exp2(fmaf(acc[v / 16][v % 16], c_log2, -l2[v / 16][v % 16]));
-          } else if (slot == ESLOTS) {
-            other = __shfl_xor(sum, 32);
-          }
-          a[mb] = mfma16<F16>(qf[mb][s], kf[s], a[mb]);
-          __builtin_amdgcn_sched_barrier(0);
-          if (slot == BETWEEN_SLOT) { between(); __builtin_amdgcn_sched_barrier(0); }
-        }
-      }
-      sum += other;
-      // key k0 + tile*TILE + l32; both lane halves hold the same sum and store it (no branch)
-      sh_part[rs][tile * TILE + l32] = sum;
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) accn[mb] = a[mb];
-  };
-  auto is_full = [&](int tile) { return k0 + tile * TILE + TILE <= n; };
-
-  floatx16 accp[MB];                                   // products of the tile before the current one
-  int prev_tile = -1;                                  // -1: none pending
-
-  // iteration it: LDS buffer it%2 holds its tiles; register set gb is in flight with the loads of
-  // it+1; set ga is free and takes it+DEPTH's
-  auto step = [&](int it, u32x4 (&ga)[LDPT], u32x4 (&gb)[LDPT]) {
-    bf16x8 kf[KS];
-    const u32x4 *buf = kt[it & 1];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(buf[rd_off + s * 2]);
-    // always issued (the last iterations re-read the final set): a conditional load would make
-    // the compiler wait for every outstanding load before the stores below.  With eight
-    // wavefronts, all of a compute unit's wavefronts leave the barrier together and nothing
-    // overlaps with the scalar address arithmetic of the load at the top of a tile; the weights
-    // sweep issues it between the tile's matrix instructions instead (measured on the 512-row
-    // shape: 153.5 -> 150.2 us; the statistics sweep, which has less other work between its
-    // matrix instructions to hide a late load behind, lost 7 us and keeps it at the top).
-    constexpr bool LOAD_BETWEEN = NW == 8 && PASS == 2;
-    auto ask = [&]() { load_set(ga, phys(min(it + DEPTH, iters - 1))); };
-    auto between = [&]() {
-      if constexpr (LOAD_BETWEEN) ask();
-    };
-    if constexpr (!LOAD_BETWEEN) ask();
-    const int tile = phys(it) * KG + kg;
-    const bool have = tile < ntiles;
-    if (!PR && have && prev_tile >= 0 && is_full(prev_tile)) {
-      // the common case, straight-line: products of this tile, arithmetic of the previous one
-      floatx16 accn[MB];
-      fused_tile(kf, accn, accp, prev_tile, between);
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) accp[mb] = accn[mb];
-      prev_tile = tile;
-    } else {
-      if (prev_tile >= 0) {
-        if (is_full(prev_tile)) epilogue(std::false_type{}, accp, prev_tile);
-        else epilogue(std::true_type{}, accp, prev_tile);
-      }
-      prev_tile = -1;
-      between();
-      if (have) {
-        mma(kf, accp);
-        prev_tile = tile;
-      }
-    }
-    store_set(gb, (it + 1) & 1);               // (after the last iteration nobody reads it: no branch)
-    __syncthreads();
-  };
-  // Two iterations in one piece, for an even it (LDS buffers 0, 1 and register sets g[0], g[1] in
-  // this order) whose two tile sets are full and follow a full tile: no decisions inside, and
-  // the products alternate between two register sets instead of being copied.  Runs of such
-  // pairs form a loop of their own, so that what the general step needs (which tile is ragged,
-  // which is missing, whether anything is pending) is looked at once per run, not once per tile:
-  // in the 512-row shapes a wavefront issued 185 to 200 instructions per tile, 40 to 48 of them
-  // scalar and 6 to 9 branches, against the tile's own 16 + 96.
-  constexpr bool PAIRS = !PR && DEPTH == 2 && NW == 8;   // (the smaller shapes are bound by memory and would pay with registers)
-  const int plain_sets = min(ntiles / KG, (n - k0) / (KG * TILE));   // sets [0, plain_sets): every tile there and full
-  auto pair = [&](int it) {
-    constexpr bool LOAD_BETWEEN = NW == 8 && PASS == 2;
-    bf16x8 kf[KS];
-    floatx16 accq[MB];
-    const int t0 = phys(it) * KG + kg, t1 = phys(it + 1) * KG + kg;
-    auto ask0 = [&]() { load_set(g[0], phys(min(it + 2, iters - 1))); };
-    auto ask1 = [&]() { load_set(g[1], phys(min(it + 3, iters - 1))); };
-    auto nothing = [&]() {};
-#pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[0][rd_off + s * 2]);
-    if constexpr (LOAD_BETWEEN) {
-      fused_tile(kf, accq, accp, prev_tile, ask0);
-    } else {
-      ask0();
-      fused_tile(kf, accq, accp, prev_tile, nothing);
-    }
-    store_set(g[1], 1);
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[1][rd_off + s * 2]);
-    if constexpr (LOAD_BETWEEN) {
-      fused_tile(kf, accp, accq, t0, ask1);
-    } else {
-      ask1();
-      fused_tile(kf, accp, accq, t0, nothing);
-    }
-    store_set(g[0], 0);
-    __syncthreads();
-    prev_tile = t1;
-  };
-  {
-    store_set(g[0], 0);
-    __syncthreads();
-    if constexpr (PAIRS) {
-      int it = 0;
-      while (it < iters) {
-        if (!(it & 1) && it + 2 <= iters && prev_tile >= 0 && is_full(prev_tile) &&
-            phys(it) < plain_sets && phys(it + 1) < plain_sets) {
-          do {
-            pair(it);
-            it += 2;
-          } while (it + 2 <= iters && phys(it) < plain_sets && phys(it + 1) < plain_sets);
-        } else {
-          if (it & 1) step(it, g[1], g[0]);
-          else step(it, g[0], g[1]);
-          ++it;
-        }
-      }
-    } else {
-      for (int it = 0; it < iters; it += DEPTH) {
-#pragma unroll
-        for (int j = 0; j < DEPTH; ++j)
-          if (it + j < iters) step(it + j, g[j], g[(j + 1) % DEPTH]);
-      }
-    }
-    if (prev_tile >= 0) {
-      if (is_full(prev_tile)) epilogue(std::false_type{}, accp, prev_tile);
-      else epilogue(std::true_type{}, accp, prev_tile);
-    }
-  }
-
-  if (PASS == 1) {
-    // merge the two lane halves (same window row, different keys), then the KG wavefront groups
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const float m2 = __shfl_xor(rm[mb], 32), s2 = __shfl_xor(rl[mb], 32);
-      const float M = fmaxf(rm[mb], m2);
-      const float ref = (M == -INFINITY) ? 0.0f : M;
-      const float L = rl[mb] * fast_exp2(rm[mb] - ref) + s2 * fast_exp2(m2 - ref);
-      if (half == 0) { sh_rows[0][wv][mb * 32 + l32] = M; sh_rows[1][wv][mb * 32 + l32] = L; }
-    }
-    __syncthreads();
-    for (int qi = tid; qi < RPAD; qi += NT) {
-      const int rsi = qi / RW, wi = qi % RW;
-      float M = -INFINITY;
-#pragma unroll
-      for (int k = 0; k < KG; ++k) M = fmaxf(M, sh_rows[0][k * RS + rsi][wi]);
-      const float ref = (M == -INFINITY) ? 0.0f : M;
-      float L = 0.0f;
-#pragma unroll
-      for (int k = 0; k < KG; ++k)
-        L += sh_rows[1][k * RS + rsi][wi] * fast_exp2(sh_rows[0][k * RS + rsi][wi] - ref);
-      if (qi < R) {
-        const size_t o = (size_t)cg * RQ + (size_t)c * R + qi;
-        part[o] = make_float2(M, L);               // (base 2, as the weights sweep wants it)
-      }
-    }
-  } else {
-    __syncthreads();
-    // add the RS row groups in a fixed order, take the mean, then (halo != 0) the max-pool:
-    // stride 1, same length, window clipped to the sequence (Section 4.1: kernel 7)
-    const float inv = 1.0f / (float)R;
-    const int span = k1 - k0;
-    if (tc.hist0) {                              // (the barrier above was the last use of the K tiles)
-      for (int i = tid; i < RADIX_BINS; i += NT) sh_hist[i] = 0u;
-    }
-    for (int j = tid; j < span; j += NT) {
-      float tot = 0.0f;
-#pragma unroll
-      for (int i = 0; i < RS; ++i) tot += sh_part[i][j];
-      sh_part[0][j] = tot * inv;
-    }
-    __syncthreads();
-    float *dst = out + st.score_off[b] + (size_t)c * n;
-    pool_and_file<NT, CHUNK>(sh_part[0], sh_hist, dst, kc0, kc1, k0, n, chunk_len, halo ? dm.pool_k / 2 : 0, tc, b, b * h + c);
-  }
-}
-
 // ---- up to 128 window rows: every wavefront on its own ------------------------------------------
 //
 // The wavefronts of a workgroup share nothing but the window queries: each takes tiles of 32 keys in turn,
@@ -771,6 +142,12 @@ template <int N> __device__ __forceinline__ void wait_vmem() {
   asm volatile("" ::: "memory");
 }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// An address that is the same in all lanes, in scalar registers even where the compiler would not keep it there.
+__device__ __forceinline__ const char *scalar_address(const char *p) {
+  const unsigned long long a = (unsigned long long)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  return (const char *)((unsigned long long)hi << 32 | lo);
+}
 // A barrier for what the workgroup exchanges through LDS; loads on their way stay there.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 // 64 x 16 bytes from base + at + the lane's off, straight into 1 KB of LDS.
@@ -782,6 +159,8 @@ __device__ __forceinline__ void load_to_lds(const char *base, unsigned off, unsi
 // The same behind the compiler's back, for loops that wait with wait_vmem alone: where buffers take turns,
 // the compiler would wait for every load before it reads any.  (In front of the load stand the wait states
 // that follow a write of m0, one, and a scalar register's write by the vector unit, five.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"        // m0 among the clobbers
 __device__ __forceinline__ void load_to_lds_untracked(const char *base, unsigned off, unsigned at, u32x4 *dst) {
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, 0x7fffffff, 0x00027000);
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(
@@ -789,6 +168,7 @@ __device__ __forceinline__ void load_to_lds_untracked(const char *base, unsigned
                "v"(off), "s"(rs), "s"(at)
                : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Lower half of the wavefront + upper half, in every lane.
 __device__ __forceinline__ float sum_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -839,6 +219,58 @@ template <int D> struct RowTile {
   }
 };
 
+// The printed order of Alg. 2 l.4 (PR): max-pool along the keys in every window row first, mean over the rows
+// afterwards.  A lane then owns one window row and, with the operand rows numbered this way, 16 consecutive keys of
+// a tile: D[i][j] has lane j's row and the keys i = 8 (r/4) + 4 half + r%4, and operand row i is key pooled_row(i), so
+// that register r is key 16 half + r.  The sliding maximum is then a three-operand maximum per weight and
+// unit of radius, between registers; only what lies next to the other half crosses lanes.  (A lane with one key of
+// 16 rows, the form before, needed two operations per weight and unit of radius, with neighbouring lanes as
+// operands: 20000 keys x 8 heads, 128 rows, d = 128 35.9 us, now 30.8, 512 rows 84.2 and 74.7; kernel 13 over 32768
+// keys 62.0 and 51.7.)  Tiles overlap by the radius on either side: their inner
+// 32 - 2 radius keys have all their neighbours and produce a score.  Rows outside the sequence repeat its last (first)
+// one, which is in every window that reaches them.
+__device__ __forceinline__ unsigned pooled_row(unsigned i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
+
+// keysum += e, pooled over `radius` keys to either side, one at a time: three-operand maxima in place; what lies next
+// to the half's first and last key comes from the other half, at a tile's ends it is the key itself.
+__device__ __forceinline__ void pool_rows(floatx16 &e, int radius, float (&keysum)[16]) {
+  for (int t = 0; t < radius; ++t) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(e[0]), __float_as_uint(e[15]), false, false);
+    float left = __uint_as_float(sw[0]);               // lower half: its own e[0]; upper half: the lower one's e[15]
+    const float right = __uint_as_float(sw[1]);        // lower half: the upper one's e[0]; upper half: its own e[15]
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float own = e[i];
+      e[i] = fmaxf(fmaxf(left, own), i < 15 ? e[i < 15 ? i + 1 : 15] : right);
+      left = own;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) keysum[i] += e[i];
+}
+// The 16 keys' sums over the 32 lanes of a half, each step adding lanes and halving the registers: a lane ends up
+// with the sum of key summed_key(lane).
+__device__ __forceinline__ unsigned summed_key(unsigned lane) {
+  return 16 * (lane >> 5) + ((lane >> 4) & 1) + 2 * ((lane >> 3) & 1) + 4 * ((lane >> 2) & 1) + 8 * ((lane >> 1) & 1);
+}
+template <int CTRL> __device__ __forceinline__ float add_dpp(float x) {
+  return x + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float sum_rows(const float (&k)[16], unsigned lane) {
+  auto pick = [](bool second, float x, float y) { return second ? y : x; };    // (by value: an lvalue choice would put the arrays into memory)
+  float a[8], b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {                        // lanes 16 apart; odd rows of 16 lanes go on with key 2i + 1
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(k[2 * i]), __float_as_uint(k[2 * i + 1]), false, false);
+    a[i] = add_dpp<0x128>(__uint_as_float(sw[0]) + __uint_as_float(sw[1]));                       // and lanes 8 apart (row_ror:8)
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = add_dpp<0x141>(pick(lane & 8, a[2 * i], a[2 * i + 1]));      // row_half_mirror: lanes j and 7 - j
+#pragma unroll
+  for (int i = 0; i < 2; ++i) c[i] = add_dpp<0x4E>(pick(lane & 4, b[2 * i], b[2 * i + 1]));       // quad_perm [2,3,0,1]
+  return add_dpp<0xB1>(pick(lane & 2, c[0], c[1]));                                               // quad_perm [1,0,3,2]
+}
+
 // Sweep 1.  Tiles of a sequence are dealt out over all wavefronts of the head (the workgroups that the sequence
 // has in cp, four wavefronts each), so at any moment the chip reads one dense region of K.  One workgroup per
 // compute unit, one wavefront per SIMD with three tiles on their way: of two wavefronts the older one runs ahead
@@ -851,7 +283,7 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
   constexpr int NW = 4, NT = 64 * NW, KS = T::KS, LD = T::LD;
   constexpr int RPAD = 32 * RB;
   constexpr int NBUF = 3;                             // tiles a wavefront has room for
-  constexpr int UN = RB % 2 && NBUF % 2 ? 2 * NBUF : NBUF;
+  constexpr int UN = RB % 2 == 1 && NBUF % 2 == 1 ? 2 * NBUF : NBUF;     // (a row block's products alternate between two places)
   __shared__ u32x4 kt[NW][NBUF][T::WORDS];
   __shared__ u32x4 qs[RB * T::WORDS];
 
@@ -1090,7 +522,7 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
 // Sweep 2.  A workgroup owns chunk_len consecutive keys (the pool wants neighbours); its wavefronts take the
 // chunk's tiles in turn, backwards from a point that differs from workgroup to workgroup: concurrently running
 // workgroups then do not ask for addresses that are equal modulo the distance of their chunks.
-template <int D, int MB, int RS, int CHUNK, bool F16>
+template <int D, int MB, int RS, int CHUNK, bool F16, bool PR>
 __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct, const ChunkTab &cp, const Dims &dm,
                                             float c_log2, const unsigned short *__restrict__ q,
                                             const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
@@ -1120,12 +552,14 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
   const int n = st.n[b];
   const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
   const int kc0 = chunk * chunk_len, kc1 = min(n, kc0 + chunk_len);
-  const int pool_r = halo ? dm.pool_k / 2 : 0;
+  const int pool_r = halo || PR ? dm.pool_k / 2 : 0;
+  const int tstep = PR ? TILE - 2 * pool_r : TILE;     // keys a tile advances by
+  const int before = PR ? pool_r : 0;                  // keys of a tile in front of its first own
   // with the pool fused: a whole tile in front of the chunk, the pool radius behind it (no tile starts past the
   // last key somebody needs)
   const int k0 = halo && kc0 > 0 ? kc0 - HALO : kc0;
   const int k1 = halo ? min(n, kc1 + pool_r) : kc1;
-  const int ntiles = (k1 - k0 + TILE - 1) / TILE;
+  const int ntiles = (k1 - k0 + tstep - 1) / tstep;
   const size_t head_row0 = (size_t)b * RQ + (size_t)c * R;
 
   const int iters = wv < ntiles ? (ntiles - 1 - wv) / NW + 1 : 0;
@@ -1143,11 +577,11 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
 #pragma unroll
   for (int v = 0; v < T::NV; ++v) ld_off[v] = __umul24(lane / T::ROW16, tok_bytes) + T::col(lane, v);
   auto issue_clamped = [&](int tile, auto &&load) {
-    const int key0 = min(k0 + tile * TILE, need_hi);
+    const int key0 = min(k0 + tile * tstep - before, need_hi);
     T::clamped(kbase + (long long)key0 * tok_bytes, tok_bytes, max(need_lo - key0, 0), need_hi - key0, lane, load);
   };
   auto issue = [&](int tile, int buf) {
-    const int key0 = k0 + tile * TILE;
+    const int key0 = k0 + tile * tstep - before;
     u32x4 *dst = buf ? &kt1[wv][0] : &kt0[wv][0];
     auto load = [&](const char *base, unsigned off, unsigned at, int word) { load_to_lds_untracked(base, off, at, dst + word); };
     if (key0 >= need_lo && key0 + TILE - 1 <= need_hi) T::whole(kbase + (long long)key0 * tok_bytes, tok_bytes, ld_off, load);
@@ -1169,9 +603,12 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  unsigned rd[KS];
+  unsigned rd[KS], rk[KS];                             // operand words of the queries, of a tile
 #pragma unroll
-  for (int s = 0; s < KS; ++s) rd[s] = T::operand(l32, half, s);
+  for (int s = 0; s < KS; ++s) {
+    rd[s] = T::operand(l32, half, s);
+    rk[s] = PR ? T::operand(pooled_row(l32), half, s) : rd[s];
+  }
   bf16x8 qf[RB][KS];                                   // kept for the whole chunk
   auto queries = [&]() {
     wait_vmem<0>();
@@ -1257,7 +694,7 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   // The 16 rows a lane sees of a row block: their log-sum-exp in registers, or, where the queries take 128 of
   // them, four at a time from LDS, two groups ahead of their use.
-  constexpr bool L2_REGS = RB <= 2;
+  constexpr bool L2_REGS = RB <= 2 && !PR;
   float l2[L2_REGS ? RB : 1][16];
   if (L2_REGS) {
 #pragma unroll
@@ -1267,9 +704,14 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
   }
   f32x4 lq[4];
   auto read_lq = [&](int mb, int q4) { return *reinterpret_cast<const f32x4 *>(&sh_lse[mb * 32 + 8 * q4 + 4 * half]); };
-  if (!L2_REGS) {
+  if (!L2_REGS && !PR) {
     lq[0] = read_lq(RB - 1, 0);
     lq[1] = read_lq(RB - 1, 1);
+  }
+  float l2row[PR ? RB : 1], keysum[PR ? 16 : 1];       // PR: of the row this lane owns; over the tile's rows so far
+  if constexpr (PR) {
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb) l2row[mb] = sh_lse[mb * 32 + l32];
   }
   // share s of KS of the vector work on a row block's products; a[r]: window row mb*32 + 8*(r/4) + 4*half + r%4
   auto share = [&](floatx16 &a, int mb, int next_mb, int s) {
@@ -1277,7 +719,10 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
 #pragma unroll
     for (int v = s * V; v < (s + 1) * V; ++v) {
       float l;
-      if constexpr (L2_REGS) {
+      if constexpr (PR) {
+        a[v] = fast_exp2(fmaf(a[v], c_log2, -l2row[mb]));
+        continue;
+      } else if constexpr (L2_REGS) {
         l = l2[mb][v];
       } else {
         if (v % 4 == 0) lq[(v / 4 + 2) % 4] = v / 4 < 2 ? read_lq(mb, v / 4 + 2) : read_lq(next_mb, v / 4 - 2);
@@ -1289,18 +734,29 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
   auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < RS; ++i) sum[i] = 0.0f;
-  };
-  auto file = [&](int tile) {                          // a finished tile's mean weights (a key per lane; past n: never read)
-    float tot = sum_halves(sum[0]);
+    if constexpr (PR) {
 #pragma unroll
-    for (int i = 1; i < RS; ++i) tot += sum_halves(sum[i]);
-    sh_part[tile * TILE + l32] = tot * inv;
+      for (int i = 0; i < 16; ++i) keysum[i] = 0.0f;
+    }
+  };
+  clear();
+  auto file = [&](int tile) {                          // a finished tile's mean weights (a key per lane; past n: never read)
+    if constexpr (PR) {
+      const float tot = sum_rows(keysum, lane);
+      const int at = summed_key(lane), key = tile * tstep + at - before;
+      if (!(lane & 1) && at >= pool_r && at < TILE - pool_r && key < k1 - k0) sh_part[key] = tot * inv;
+    } else {
+      float tot = sum_halves(sum[0]);
+#pragma unroll
+      for (int i = 1; i < RS; ++i) tot += sum_halves(sum[i]);
+      sh_part[tile * TILE + l32] = tot * inv;
+    }
     clear();
   };
   if (iters > 0) {
     if (iters > 1) wait_vmem<LD>(); else wait_vmem<0>();
 #pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt0[wv][rd[s]]);
+    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt0[wv][rk[s]]);
   }
   int prev = 0;                                        // tile before the current one
   for (int it0 = 0; it0 < iters; it0 += 2) {
@@ -1320,13 +776,20 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
           floatx16 a = {0};
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
-            a = mfma16<F16>(qf[mb][s], kf[s], a);
-            if (mb == RB - 1) kf[s] = as_bf16(j == 0 ? kt1[wv][rd[s]] : kt0[wv][rd[s]]);   // (whatever lies there behind the last)
+            a = PR ? mfma16<F16>(kf[s], qf[mb][s], a) : mfma16<F16>(qf[mb][s], kf[s], a);
+            if (mb == RB - 1) kf[s] = as_bf16(j == 0 ? kt1[wv][rk[s]] : kt0[wv][rk[s]]);   // (whatever lies there behind the last)
             share(acc[1 - cur], pmb, mb, s);
             __builtin_amdgcn_sched_barrier(0);
           }
           acc[cur] = a;
-          asm volatile("" : "+v"(sum[pmb / MB]));      // the vector work stays in front of this point
+          if constexpr (PR) {
+            pool_rows(acc[1 - cur], pool_r, keysum);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(keysum[i]));
+            __builtin_amdgcn_sched_barrier(0);
+          } else {
+            asm volatile("" : "+v"(sum[pmb / MB]));    // the vector work stays in front of this point
+          }
           if (mb == 0) {
             if (it > 0) file(prev);
             else clear();
@@ -1341,6 +804,7 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
     if (RB % 2 == 1 && (iters & 1)) last = acc[0];
 #pragma unroll
     for (int s = 0; s < KS; ++s) share(last, RB - 1, RB - 1, s);
+    if constexpr (PR) pool_rows(last, pool_r, keysum);
     file(prev);
   }
   wait_vmem<0>();                                      // (a wavefront without tiles has asked for one as well)
@@ -1349,6 +813,494 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
     for (int i = tid; i < RADIX_BINS; i += NT) sh_hist[i] = 0u;
     __syncthreads();
   }
+  pool_and_file<NT, CHUNK>(sh_part, sh_hist, out + st.score_off[b] + (size_t)c * n, kc0, kc1, k0, n, chunk_len,
+                           halo ? dm.pool_k / 2 : 0, tc, b, b * h + c);
+}
+
+// ---- more than 128 window rows: RS wavefronts share the tiles ---------------------------------------
+//
+// Every wavefront keeps MB row blocks of Q in registers and works on every tile of the workgroup.  Tiles come in
+// sets of ST, straight into LDS, a set ahead of the one that is worked on, and a set is what the wavefronts wait
+// for each other for: one barrier per ST tiles, so that the two wavefronts of a SIMD drift apart and one's matrix
+// instructions run beside the other's vector work.
+//
+// The order of things around a barrier, in a set's last tile in front of its last row block's products: the
+// wavefront's share of the next set has arrived, its operand reads of this set are done - barrier - all of the next set is there and all of this set is free: the set after next is asked for.
+template <int D, int MB, int RS> struct Group {
+  typedef RowTile<D> T;
+  static constexpr int NT = 64 * RS, RPAD = 32 * MB * RS;
+  static constexpr int ST = 4;                         // tiles of a set
+  static constexpr int SETW = ST * T::WORDS;
+  static constexpr int LDW = ST * T::LD / RS;          // load instructions per wavefront and set
+  static_assert(LDW * RS == ST * T::LD, "a set must split evenly over the wavefronts");
+};
+
+// The queries of wavefront wv's row blocks as operands, straight from memory (behind the first sets, whose way
+// from HBM is longer than the 32 lines that each of these loads touches take).  Rows past R are row R-1, until ...
+template <int D, int MB>
+__device__ __forceinline__ void group_queries(const unsigned short *q, size_t head_row0, int R, int wv, int l32, int half,
+                                              u32x4 (&qw)[MB][RowTile<D>::KS]) {
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const unsigned short *src = q + (head_row0 + min((wv * MB + mb) * 32 + l32, R - 1)) * D + half * 8;
+#pragma unroll
+    for (int s = 0; s < RowTile<D>::KS; ++s) qw[mb][s] = *reinterpret_cast<const u32x4 *>(src + s * 16);
+  }
+}
+// ... they are zeroed.
+template <int MB, int KS>
+__device__ __forceinline__ void zero_padding(const u32x4 (&qw)[MB][KS], int R, int wv, int l32, bf16x8 (&qf)[MB][KS]) {
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const unsigned keep = (wv * MB + mb) * 32 + l32 < R ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) qf[mb][s] = as_bf16(qw[mb][s] & keep);
+  }
+}
+
+// Sweep 1: the sets of a sequence are dealt out over the workgroups of the head.
+template <int D, int MB, int RS, bool F16>
+__device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp, const Dims &dm, float c_log2,
+                                            const unsigned short *__restrict__ q, const unsigned short *__restrict__ K,
+                                            float2 *__restrict__ part, int part_len, const TopkCarry &tc) {
+  typedef Group<D, MB, RS> G;
+  typedef RowTile<D> T;
+  constexpr int KS = T::KS, ST = G::ST, NT = G::NT;
+  __shared__ u32x4 kt[2][G::SETW];
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tc.zero_begin)
+    for (unsigned i = blockIdx.x * NT + tid; i < tc.zero_words; i += gridDim.x * NT) tc.zero_begin[i] = 0u;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+  const int h = dm.h_kv;
+  const int c = blockIdx.x % h, cg = blockIdx.x / h;
+  const int b = find_seq(cp, st.batch, cg);
+  const int first = cg - cp.off[b], stride = cp.off[b + 1] - cp.off[b];
+  const int n = st.n[b];
+  const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
+  const size_t head_row0 = (size_t)b * RQ + (size_t)c * R;
+  // Sets of fewer tiles where whole ones would give some workgroups a sixteenth (two tiles instead of four) or a tenth
+  // (one) more than their part_len keys.  256 rows, 20000 keys x 8 heads, 63 workgroups of 320 keys a head: 157 sets of
+  // four are 12 tiles for some, 313 of two 10 for all.
+  const int ntiles = (n + TILE - 1) / TILE, share_of = part_len / TILE;
+  int stt = ST;
+  if ((-share_of & (ST - 1)) * 16 > share_of) stt = 2;
+  if (stt < ST && (share_of & 1) * 10 > share_of) stt = 1;
+  const int nsets = (ntiles + stt - 1) / stt;
+  const int iters = first < nsets ? (nsets - 1 - first) / stride + 1 : 0;
+  const char *kbase = reinterpret_cast<const char *>(K) +
+                      ((size_t)st.tok_off[b] * dm.k_stride_tok + (size_t)c * dm.k_stride_head) * 2;
+  const unsigned tok_bytes = (unsigned)dm.k_stride_tok * 2u;
+  // a wavefront loads every RS-th instruction's rows of a set; rows past the sequence are its last
+  auto issue = [&](int it) {
+    const int key0 = (first + it * stride) * (stt * TILE), lim = min(n - 1 - key0, stt * TILE - 1);
+    const char *sb = scalar_address(kbase + (long long)key0 * tok_bytes);
+#pragma unroll
+    for (int i = 0; i < G::LDW; ++i) {
+      const int at = i * RS + wv;                      // load instruction of the set
+      if (i < G::LDW * stt / ST) {
+        const unsigned row = (unsigned)min((int)(at * T::RPI + lane / T::ROW16), lim);
+        load_to_lds_untracked(sb, __umul24(row, tok_bytes) + T::col(lane, at), 0u, &kt[it & 1][at * 64]);
+      }
+    }
+  };
+  unsigned rd[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) rd[s] = T::operand(l32, half, s);
+  bf16x8 qf[MB][KS];
+  // (the second set is asked for when the first one and the queries are there: loads return in order, and a short
+  // sequence would wait for all of it before it starts; 256 rows, 2011 keys: 7.8 us, 7.1 so)
+  if (iters > 0) issue(0);
+  {
+    u32x4 qw[MB][KS];
+    group_queries<D, MB>(q, head_row0, R, wv, l32, half, qw);
+    zero_padding<MB, KS>(qw, R, wv, l32, qf);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(qf[mb][KS - 1]));
+  }
+  wait_vmem<0>();
+  if (iters > 1) issue(1);
+
+  bf16x8 kf[KS];
+  floatx16 acc[2];
+  float rm[MB], rl[MB];
+  float ref = 0.0f, nmx = 0.0f, usum = 0.0f;
+  auto share = [&](auto lazy_tag, floatx16 &a, int mb, int s) {          // (as in stats_own)
+    if constexpr (decltype(lazy_tag)::value) {
+      if (s == 0) usum = 0.0f;
+#pragma unroll
+      for (int v = s * 16 / KS; v < (s + 1) * 16 / KS; ++v) usum += fast_exp2(fmaf(a[v], c_log2, -rm[mb]));
+      if (s == KS - 1) rl[mb] += usum;
+    } else {
+      if (s == 0) {
+        float tm = a[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) tm = fmaxf(tm, a[r]);
+        nmx = fmaxf(rm[mb], tm * c_log2);
+        ref = (nmx == -INFINITY) ? 0.0f : nmx;
+        usum = 0.0f;
+      } else {
+#pragma unroll
+        for (int v = (s - 1) * 16 / (KS - 1); v < s * 16 / (KS - 1); ++v) usum += fast_exp2(fmaf(a[v], c_log2, -ref));
+      }
+      if (s == KS - 1) {
+        rl[mb] = rl[mb] * fast_exp2(rm[mb] - ref) + usum;
+        rm[mb] = nmx;
+      }
+    }
+  };
+  auto reset = [&]() {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) { rm[mb] = -INFINITY; rl[mb] = 0.0f; }
+  };
+  // the first two sets have been asked for: the first one is there for everybody
+  auto read_first = [&]() {
+    if (iters > 1 && stt == ST) wait_vmem<G::LDW>(); else wait_vmem<0>();
+    lds_barrier();
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[0][rd[s]]);
+  };
+  // the sequence's last tile, if it is not full, is the last of its workgroup and comes after the loop
+  const bool tail = iters > 0 && first + (iters - 1) * stride == nsets - 1 && n % TILE != 0;
+  auto tiles_of = [&](int it) { return min(stt, ntiles - (first + it * stride) * stt); };
+  const int plain = iters > 0 ? (iters - 1) * stt + tiles_of(iters - 1) - (tail ? 1 : 0) : 0;
+  auto loop = [&](auto lazy_tag) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = -INFINITY;      // (nothing before the first: no weight)
+    for (int it = 0; it < iters; ++it) {
+      const int nt = tiles_of(it), full = nt - (tail && it == iters - 1 ? 1 : 0);
+      for (int t = 0; t < full; ++t) {
+        const bool leave = t == nt - 1;                // the next tile is the next set's first (behind the last: whatever lies there)
+        const u32x4 *src = leave ? &kt[(it + 1) & 1][0] : &kt[it & 1][(t + 1) * T::WORDS];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+          const int pmb = mb == 0 ? MB - 1 : mb - 1, cur = mb & 1;
+          if (mb == MB - 1 && leave && it + 1 < iters) {
+            wait_vmem<0>();
+            lds_barrier();
+            if (it + 2 < iters) issue(it + 2);
+          }
+          floatx16 a = {0};
+#pragma unroll
+          for (int s = 0; s < KS; ++s) {
+            a = mfma16<F16>(kf[s], qf[mb][s], a);
+            if (mb == MB - 1) kf[s] = as_bf16(src[rd[s]]);
+            share(lazy_tag, acc[1 - cur], pmb, s);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          acc[cur] = a;
+          asm volatile("" : "+v"(rl[pmb]), "+v"(rm[pmb]));   // the vector work stays in front of this point
+        }
+      }
+    }
+    if (plain > 0) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) share(lazy_tag, acc[1], MB - 1, s);
+    }
+  };
+  static_assert(MB % 2 == 0, "a row block's products alternate between two places");
+  reset();
+  if (iters > 0) read_first();
+  // (the kept reference as in stats_own; all wavefronts go the same way, because they meet at barriers)
+  bool careful = plain < 4;
+  if (!careful) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      floatx16 a = {0};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a = mfma16<F16>(kf[s], qf[mb][s], a);
+      float tm = a[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) tm = fmaxf(tm, a[r]);
+      rm[mb] = tm * c_log2;
+      asm volatile("" : "+v"(rm[mb]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    loop(std::true_type{});
+    bool bad = false;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) bad |= !(rl[mb] < INFINITY);
+    wait_vmem<0>();
+    if (__syncthreads_or(bad)) {
+      careful = true;
+      reset();
+      issue(0);
+      if (iters > 1) issue(1);
+      read_first();
+    } else {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) settle(rm[mb], rl[mb]);
+    }
+  }
+  if (careful) loop(std::false_type{});
+  if (tail) {
+    const int base = (ntiles - 1) * TILE;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      floatx16 a = {0};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a = mfma16<F16>(kf[s], qf[mb][s], a);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)                     // key base + 8 (r/4) + 4 half + r%4
+        if (base + 8 * (r / 4) + 4 * half + (r % 4) >= n) a[r] = -INFINITY;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) share(std::false_type{}, a, mb, s);
+      asm volatile("" : "+v"(rl[mb]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // the two lane halves hold the same window row's statistics over different keys
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const float m2 = __shfl_xor(rm[mb], 32), s2 = __shfl_xor(rl[mb], 32);
+    const float M = fmaxf(rm[mb], m2);
+    const float rf = (M == -INFINITY) ? 0.0f : M;
+    const float L = rl[mb] * fast_exp2(rm[mb] - rf) + s2 * fast_exp2(m2 - rf);
+    const int row = (wv * MB + mb) * 32 + l32;
+    if (half == 0 && row < R) part[(size_t)cg * RQ + (size_t)c * R + row] = make_float2(M, L);     // (base 2)
+  }
+}
+
+// Sweep 2: a workgroup owns chunk_len consecutive keys, as in weights_own.
+template <int D, int MB, int RS, int CHUNK, bool F16, bool PR>
+__device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &ct, const ChunkTab &cp, const Dims &dm,
+                                              float c_log2, const unsigned short *__restrict__ q,
+                                              const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
+                                              const float2 *__restrict__ part, float *__restrict__ out, int halo,
+                                              int chunk_len, const TopkCarry &tc) {
+  typedef Group<D, MB, RS> G;
+  typedef RowTile<D> T;
+  constexpr int KS = T::KS, ST = G::ST, NT = G::NT, RPAD = G::RPAD;
+  constexpr int HALO = TILE, SPAN = CHUNK + 2 * HALO;
+  constexpr int SKEYS = ST * TILE;                     // keys of a set
+  __shared__ u32x4 kt[2][G::SETW];
+  __shared__ float sh_sum[3][RS][SKEYS];               // the row groups' sums over a set's keys, three sets in turn
+  __shared__ __align__(16) float sh_lse[RPAD];
+  __shared__ __align__(16) float sh_part[SPAN];
+  constexpr int SL = 2 * NT / RPAD > 0 ? 2 * NT / RPAD : 1;      // threads that share two rows in the statistics combination
+  static_assert(SL * RPAD == 2 * NT && 2 * SL * RPAD <= SPAN, "threads and rows must tile each other");
+  float *sh_cm = sh_part, *sh_cl = sh_part + SL * RPAD;          // (the prologue's, before any score is there)
+  static_assert(sizeof(kt) >= RADIX_BINS * sizeof(unsigned), "the digit histogram takes the tiles' place");
+  unsigned *sh_hist = reinterpret_cast<unsigned *>(&kt[0][0]);
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+  const int h = dm.h_kv;
+  const int c = blockIdx.x % h, cg = ct.off[st.batch] - 1 - (int)blockIdx.x / h;
+  const int b = find_seq(ct, st.batch, cg);
+  const int chunk = cg - ct.off[b], nch = ct.off[b + 1] - ct.off[b];
+  const int n = st.n[b];
+  const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
+  const int kc0 = chunk * chunk_len, kc1 = min(n, kc0 + chunk_len);
+  const int pool_r = halo || PR ? dm.pool_k / 2 : 0;
+  const int tstep = PR ? TILE - 2 * pool_r : TILE;     // keys a tile advances by
+  const int before = PR ? pool_r : 0;                  // keys of a tile in front of its first own
+  const int k0 = halo && kc0 > 0 ? kc0 - HALO : kc0;
+  const int k1 = halo ? min(n, kc1 + pool_r) : kc1;
+  const int ntiles = (k1 - k0 + tstep - 1) / tstep, nsets = (ntiles + ST - 1) / ST;
+  const size_t head_row0 = (size_t)b * RQ + (size_t)c * R;
+  const int rot = (int)(((long long)chunk * nsets) / nch);
+  auto set_of = [&](int it) {                          // backwards from a point that differs from workgroup to workgroup
+    const int p = rot - 1 - it;
+    return p < 0 ? p + nsets : p;
+  };
+  auto tiles_of = [&](int set) { return min(ST, ntiles - set * ST); };
+  const char *kbase = reinterpret_cast<const char *>(K) +
+                      ((size_t)st.tok_off[b] * dm.k_stride_tok + (size_t)c * dm.k_stride_head) * 2;
+  const unsigned tok_bytes = (unsigned)dm.k_stride_tok * 2u;
+  const int need_lo = max(kc0 - pool_r, 0), need_hi = min(kc1 - 1 + pool_r, n - 1);
+  auto ask = [&](int it, auto &&load) {
+    const int key0 = k0 + set_of(it) * (ST * tstep) - before, lim = need_hi - key0, lo = max(need_lo - key0, 0);     // (no set starts past need_hi)
+    const char *sb = scalar_address(kbase + (long long)key0 * tok_bytes);
+#pragma unroll
+    for (int i = 0; i < G::LDW; ++i) {
+      const int at = wv * G::LDW + i;
+      const int rel = PR ? at / T::LD * tstep + at % T::LD * T::RPI : at * T::RPI;     // (overlapping tiles have rows of their own)
+      const unsigned row = (unsigned)max(min(rel + (int)(lane / T::ROW16), lim), lo);
+      load(sb, __umul24(row, tok_bytes) + T::col(lane, at), at * 64);
+    }
+  };
+  auto issue = [&](int it) {
+    ask(it, [&](const char *sb, unsigned off, int word) { load_to_lds_untracked(sb, off, 0u, &kt[it & 1][word]); });
+  };
+  unsigned rd[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) rd[s] = T::operand(PR ? pooled_row(l32) : l32, half, s);
+  u32x4 qw[MB][KS];
+  // The first set and the queries, counted by the compiler, so that its wait for what was asked for before does not
+  // stop at them as well (loads return in order).
+  auto request = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    ask(0, [&](const char *sb, unsigned off, int word) { load_to_lds(sb, off, 0u, &kt[0][word]); });
+    __builtin_amdgcn_sched_barrier(0);
+    group_queries<D, MB>(q, head_row0, R, wv, l32, half, qw);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (lse) {
+    request();
+    for (int i = tid; i < RPAD; i += NT) sh_lse[i] = (i < R) ? lse[head_row0 + i] * lse_mul : INFINITY;
+  } else {
+    // sweep 1's partials of this head's rows, two rows and every SL-th partial a thread (as in weights_own)
+    constexpr int CB = 16;
+    const int q2 = tid % (RPAD / 2), sl = tid / (RPAD / 2);
+    const int row = min(2 * q2, max(R - 2, 0)), np = cp.off[b + 1] - cp.off[b];
+    struct __attribute__((packed, aligned(8))) Pair { float m0, l0, m1, l1; };
+    const float2 *pp = part + ((size_t)cp.off[b] * RQ + (size_t)c * R);
+    Pair pml[CB];
+    auto load_parts = [&](int p0) {
+#pragma unroll
+      for (int u = 0; u < CB; ++u) pml[u] = *reinterpret_cast<const Pair *>(pp + (unsigned)(min(p0 + u * SL, np - 1) * RQ + row));
+    };
+    float M0 = -INFINITY, L0 = 0.0f, M1 = -INFINITY, L1 = 0.0f;
+    auto fold = [&](int p0) {
+      float n0 = M0, n1 = M1;
+#pragma unroll
+      for (int u = 0; u < CB; ++u)
+        if (p0 + u * SL < np) { n0 = fmaxf(n0, pml[u].m0); n1 = fmaxf(n1, pml[u].m1); }
+      const float r0 = (n0 == -INFINITY) ? 0.0f : n0, r1 = (n1 == -INFINITY) ? 0.0f : n1;
+      L0 *= fast_exp2(M0 - r0);
+      L1 *= fast_exp2(M1 - r1);
+#pragma unroll
+      for (int u = 0; u < CB; ++u)
+        if (p0 + u * SL < np) {
+          L0 += pml[u].l0 * fast_exp2(pml[u].m0 - r0);
+          L1 += pml[u].l1 * fast_exp2(pml[u].m1 - r1);
+        }
+      M0 = n0;
+      M1 = n1;
+    };
+    load_parts(sl);
+    request();
+    fold(sl);
+    for (int p0 = sl + CB * SL; p0 < np; p0 += CB * SL) {
+      load_parts(p0);
+      fold(p0);
+    }
+    if (2 * q2 == R - 1 && R > 1) { M0 = M1; L0 = L1; }
+    *reinterpret_cast<float2 *>(&sh_cm[sl * RPAD + 2 * q2]) = make_float2(M0, M1);
+    *reinterpret_cast<float2 *>(&sh_cl[sl * RPAD + 2 * q2]) = make_float2(L0, L1);
+  }
+  lds_barrier();
+  if (!lse) {
+    for (int r = tid; r < RPAD; r += NT) {
+      float Mt = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < SL; ++i) Mt = fmaxf(Mt, sh_cm[i * RPAD + r]);
+      const float ref = (Mt == -INFINITY) ? 0.0f : Mt;
+      float Lt = 0.0f;
+#pragma unroll
+      for (int i = 0; i < SL; ++i) Lt += sh_cl[i * RPAD + r] * fast_exp2(sh_cm[i * RPAD + r] - ref);
+      sh_lse[r] = (r < R) ? Mt + __builtin_amdgcn_logf(Lt) : INFINITY;
+    }
+    lds_barrier();
+  }
+  float l2[MB][PR ? 1 : 16];                           // log-sum-exp of the 16 rows (PR: the row) a lane sees in each row block
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if constexpr (PR) l2[mb][0] = sh_lse[(wv * MB + mb) * 32 + l32];
+      else l2[mb][r] = sh_lse[(wv * MB + mb) * 32 + 8 * (r / 4) + 4 * half + (r % 4)];
+
+  bf16x8 kf[KS];
+  floatx16 acc[2];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = -INFINITY;
+  float sum = 0.0f, keysum[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) keysum[i] = 0.0f;
+  const float inv = 1.0f / (float)R;
+  auto share = [&](floatx16 &a, int mb, int s) {       // a[r]: window row (wv*MB + mb)*32 + 8*(r/4) + 4*half + r%4
+    constexpr int V = 16 / KS;
+#pragma unroll
+    for (int v = s * V; v < (s + 1) * V; ++v)
+      if constexpr (PR) a[v] = fast_exp2(fmaf(a[v], c_log2, -l2[mb][0]));
+      else sum += fast_exp2(fmaf(a[v], c_log2, -l2[mb][v]));
+  };
+  // the row groups' sums over the keys of the it-th set, added in a fixed order (all of them are there)
+  auto combine = [&](int it) {
+    const int set = set_of(it);
+    for (int j = tid; j < SKEYS; j += NT) {
+      float tot = 0.0f;
+#pragma unroll
+      for (int i = 0; i < RS; ++i) tot += sh_sum[it % 3][i][j];
+      if constexpr (PR) {
+        const int at = j % TILE, key = (set * ST + j / TILE) * tstep + at - pool_r;
+        if (at >= pool_r && at < TILE - pool_r && key < k1 - k0) sh_part[key] = tot * inv;
+      } else {
+        if (set * SKEYS + j < ntiles * TILE) sh_part[set * SKEYS + j] = tot * inv;
+      }
+    }
+  };
+  bf16x8 qf[MB][KS];
+  zero_padding<MB, KS>(qw, R, wv, l32, qf);
+  wait_vmem<0>();
+  lds_barrier();                                       // (the second set when the first one is there: as in stats_group)
+  if (nsets > 1) issue(1);
+#pragma unroll
+  for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[0][rd[s]]);
+  auto file = [&](int it, int t) {                     // a finished tile's sums over this wavefront's rows
+    float *dst = &sh_sum[it % 3][wv][t * TILE];
+    if constexpr (PR) {
+      const float tot = sum_rows(keysum, lane);
+      if (!(lane & 1)) dst[summed_key(lane)] = tot;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) keysum[i] = 0.0f;
+    } else {
+      dst[l32] = sum_halves(sum);
+      sum = 0.0f;
+    }
+  };
+  int prev_it = 0, prev_t = 0;                         // set (in order of work) and place of the tile before the current one
+  for (int it = 0; it < nsets; ++it) {
+    const int nt = tiles_of(set_of(it));
+    for (int t = 0; t < nt; ++t) {
+      const bool leave = t == nt - 1;                  // the next tile is the next set's first (behind the last: whatever lies there)
+      const u32x4 *src = leave ? &kt[(it + 1) & 1][0] : &kt[it & 1][(t + 1) * T::WORDS];
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const int pmb = mb == 0 ? MB - 1 : mb - 1, cur = mb & 1;
+        if (mb == MB - 1 && leave && it + 1 < nsets) {
+          wait_vmem<0>();
+          lds_barrier();
+          if (it + 2 < nsets) issue(it + 2);
+          if (it > 0) combine(it - 1);
+        }
+        floatx16 a = {0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          a = PR ? mfma16<F16>(kf[s], qf[mb][s], a) : mfma16<F16>(qf[mb][s], kf[s], a);
+          if (mb == MB - 1) kf[s] = as_bf16(src[rd[s]]);
+          share(acc[1 - cur], pmb, s);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        acc[cur] = a;
+        if constexpr (PR) {
+          pool_rows(acc[1 - cur], pool_r, keysum);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(keysum[i]));
+          __builtin_amdgcn_sched_barrier(0);
+        } else {
+          asm volatile("" : "+v"(sum));                // the vector work stays in front of this point
+        }
+        if (mb == 0) file(prev_it, prev_t);            // (in front of the first: the place is written again)
+      }
+      prev_it = it;
+      prev_t = t;
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < KS; ++s) share(acc[1], MB - 1, s);
+  if constexpr (PR) pool_rows(acc[1], pool_r, keysum);
+  file(prev_it, prev_t);
+  wait_vmem<0>();
+  __syncthreads();
+  if (nsets > 1) combine(nsets - 2);
+  combine(nsets - 1);
+  if (tc.hist0)
+    for (int i = tid; i < RADIX_BINS; i += NT) sh_hist[i] = 0u;
+  __syncthreads();
   pool_and_file<NT, CHUNK>(sh_part, sh_hist, out + st.score_off[b] + (size_t)c * n, kc0, kc1, k0, n, chunk_len,
                            halo ? dm.pool_k / 2 : 0, tc, b, b * h + c);
 }
@@ -1364,10 +1316,12 @@ __global__ __launch_bounds__(64 * RS * KG, MB * RS <= 4 ? 2 : 1) void score_mfma
     TopkCarry tc) {
   if constexpr (MB * RS <= 4 && PASS == 1)
     stats_own<D, MB * RS, F16>(st, cp, dm, c_log2, q, K, part, tc);
-  else if constexpr (MB * RS <= 4 && !PR)
-    weights_own<D, MB, RS, CHUNK, F16>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
+  else if constexpr (MB * RS <= 4)
+    weights_own<D, MB, RS, CHUNK, F16, PR>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
+  else if constexpr (PASS == 1)
+    stats_group<D, MB, RS, F16>(st, cp, dm, c_log2, q, K, part, chunk_len, tc);
   else
-    sweep_shared<D, MB, RS, KG, CHUNK, PASS, F16, PR>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
+    weights_group<D, MB, RS, CHUNK, F16, PR>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
 }
 
 template <bool F16, int D, int MB, int RS, int KG, int CHUNK>
@@ -1398,9 +1352,8 @@ void run_mfma(const MfmaVariant &v, const SeqTab &st, const Dims &dm, const void
   }
   if (pool_rows) {
     // the printed order of Alg. 2 l.4: the sweep pools every row itself and writes final scores
-    ADAKV_LAUNCH("score_weights_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16, true>),
-                 dim3(nblk), block, s, st, ct, cp, dm, c_log2, (const unsigned short *)q,
-                 (const unsigned short *)K, use_lse, lse_mul, part, scores, 0, v.len, tc);
+    ADAKV_LAUNCH("score_weights_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16, true>), dim3(nblk), block, s, st, ct, cp,
+                 dm, c_log2, (const unsigned short *)q, (const unsigned short *)K, use_lse, lse_mul, part, scores, 0, v.len, tc);
     return;
   }
   ADAKV_LAUNCH("score_weights_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16>), dim3(nblk),
@@ -1537,12 +1490,15 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   // alignment of the parts, asked of the split alone, so that a layer that just fits keeps fitting).
   auto need = [&](int len) { return score_workspace(st, dm, len) + plan_topk_bytes(st, dm); };
   if (need(v.len) + 1024 > (size_t)ADAKV_STATIC_SCRATCH_BYTES && need(most) <= (size_t)ADAKV_STATIC_SCRATCH_BYTES) v.len = most;
-  // Sweep 1 of up to 128 rows is not bound to the chunks: one resident round of workgroups (of 128 KiB of LDS
-  // each at d = 128, half of that at d = 64) over all sequences, as many rounds as there are heads for beyond
-  // that, and never more workgroups than sweep 2's chunks (the partials have a place for each of those).
+  // Sweep 1 of up to 256 rows is not bound to the chunks: one resident round of workgroups over all sequences, as many
+  // rounds as there are heads for beyond that, and never more workgroups than sweep 2's chunks (the partials have a
+  // place for each of those).  Up to 128 rows the tiles' place in LDS leaves one workgroup per compute unit at d = 128,
+  // two at d = 64.  Beyond 128 rows two would fit, but one halves the partials, so that sweep 2 can combine them
+  // itself: 20000 keys x 8 heads, 256 rows 41.3 -> 38.5 us, 50021 74.3 -> 73.3; with chunks of more than 1024 keys a
+  // wavefront alone on its SIMD loses more than that kernel takes (131072 keys: 168.7 | 170.2).
   v.part_len = v.len;
-  if (R <= 128) {
-    const long long room = dm.d == 128 ? 256 : 512, heads = (long long)st.batch * dm.h_kv;
+  if (R <= 128 || (R <= 256 && v.len <= 1024)) {
+    const long long room = dm.d == 128 || R > 128 ? 256 : 512, heads = (long long)st.batch * dm.h_kv;
     const long long wgs = (heads + room - 1) / room * room;
     int lo = v.len / TILE, hi = longest / TILE + 1 > lo ? longest / TILE + 1 : lo;
     while (lo < hi) {
@@ -1562,7 +1518,7 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
   // applies the max-pool itself when the pool radius fits into the one-tile halo.
   int max_chunks = 0;
   for (int b = 0; b < st.batch; ++b) {
-    const int k = (st.n[b] + v.len - 1) / v.len;
+    const int k = (st.n[b] + v.part_len - 1) / v.part_len;
     max_chunks = k > max_chunks ? k : max_chunks;
   }
   v.fuse_lse = (long long)max_chunks * R <= (v.rs == 8 ? 16384 : 8192);
