@@ -7,13 +7,17 @@ no fallback: if the library is missing, calls raise.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "lib", "libadakv.so")
+_MARSHAL_PATH = os.path.join(_HERE, "lib", "_marshal.so")
 _lib = None
+_decode_step_address = 0
 
 ADAKV_BF16, ADAKV_FP32, ADAKV_FP16 = 0, 1, 2
 ADAKV_FLAG_PIPELINE = 2
@@ -94,6 +98,8 @@ def load_library():
     lib.adakv_describe.argtypes = [P, ctypes.c_int, ctypes.c_char_p, Z]
     lib.adakv_probe_read.restype = ctypes.c_int
     lib.adakv_probe_read.argtypes = [V, Z, V, V]
+    global _decode_step_address
+    _decode_step_address = ctypes.cast(lib.adakv_decode_step, V).value
     _lib = lib
     return lib
 
@@ -151,6 +157,23 @@ class Layer:
 
 def workspace_bytes(layer: Layer) -> int:
     return int(load_library().adakv_workspace_bytes(ctypes.byref(layer.c)))
+
+
+def _load_marshal():
+    """The module with a decoding step's checks in native code, or None: where it is not built, or was built for
+    another torch, the checks here do the same at 5 us more per call."""
+    if not os.path.exists(_MARSHAL_PATH):
+        return None
+    loader = importlib.machinery.ExtensionFileLoader("_marshal", _MARSHAL_PATH)
+    try:
+        mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", _MARSHAL_PATH, loader=loader))
+        loader.exec_module(mod)
+    except ImportError:
+        return None
+    return mod if mod.TORCH_VERSION == torch.__version__.split("+")[0] else None
+
+
+_marshal = _load_marshal()
 
 
 def _ptr(t, name, dtype=None):
@@ -536,6 +559,14 @@ def decode_step(layer: Layer, q_new, k_new, v_new, cu_seqlens, headroom, K_cache
                 overflow=None, out=None, lse=None, ws=None, stream=None, want_lse=False):
     """adakv_decode_step: append k_new/v_new to every segment and attend, in one call."""
     lib = load_library()
+    if _marshal is not None and out is not None and ws is not None and (lse is not None or not want_lse):
+        st = _marshal.decode_step(_decode_step_address, ctypes.addressof(layer.c), q_new, k_new, v_new, cu_seqlens,
+                                  headroom, K_cache, V_cache, seg_len, overflow, out, lse, ws, _stream(stream))
+        if st == 0:
+            return out if lse is None else (out, lse)
+        if st is not None:
+            raise AdaKVError(st, "adakv_decode_step")
+        # something is not as it has to be: the checks below say what
     want = (layer.batch, layer.h_q, layer.d)
     wkv = (layer.batch, layer.h_kv, layer.d)
     if q_new.shape != want or not q_new.is_contiguous():

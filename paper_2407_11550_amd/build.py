@@ -1,4 +1,4 @@
-"""Builds libadakv.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Builds libadakv.so for gfx950 with hipcc (cross-compiles without a GPU), and what goes with it."""
 from __future__ import annotations
 
 import os
@@ -52,6 +52,28 @@ def build(verbose: bool = False, extra_flags=(), jobs: int = 6) -> str:
     return out
 
 
+def build_marshal(verbose: bool = False) -> str:
+    """lib/_marshal.so: a decoding step's argument checks in native code (host code only, against torch's headers)."""
+    import sysconfig
+
+    import torch
+    home = os.path.dirname(torch.__file__)
+    out = os.path.join(HERE, "lib", "_marshal.so")
+    os.makedirs(os.path.dirname(out), exist_ok=True)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(home, "include"),
+           "-isystem", os.path.join(home, "include", "torch", "csrc", "api", "include"),
+           os.path.join(HERE, "csrc", "marshal.cpp"), "-L", os.path.join(home, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out]
+    if verbose:
+        print(" ".join(cmd))
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n" + r.stdout + r.stderr)
+    return out
+
+
 def build_abi_driver(verbose: bool = False) -> str:
     """tests/abi_driver: a plain C++ caller of the C ABI (hipMalloc, default stream, no Python),
     linked against the library built above; used by one GPU test."""
@@ -70,3 +92,4 @@ def build_abi_driver(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_marshal(verbose=True))
