@@ -480,15 +480,31 @@ size_t score_workspace(const SeqTab &st, const Dims &dm, int part_chunk) {
   return plan_score_chunk(st, dm, part_chunk).total;
 }
 
+// Whether sweep 1 leaves a partial per 256 keys.  With 33 to 64 partials per 128 keys that makes them few enough for
+// sweep 2 to combine, which saves the kernel of 4 us and costs sweep 2 1 to 1.7 us.  A workgroup of eight wavefronts
+// takes as long as two of four, so the fullest compute unit may get more to do: 1.8 us per unit and row block as in
+// f32_pool_fused().  Whole call, us, 128 / 256 keys: 8191 keys x 8 heads, 128 rows 53.4 / 51.4, 5000 keys 49.8 / 46.2,
+// d = 64 37.4 / 34.9; 8000 x 8 heads, 8 rows 25.8 / 23.2; 8000 x 4 heads, 32 rows, d = 64 (half a compute unit's
+// share more) 17.0 / 14.1.  Refused: 5000 x 4 heads, 128 rows 31.8 / 36.4; five of up to 6000 keys 107.2 / 110.0.
+static bool f32_wide_stats(const SeqTab &st, const Dims &dm) {
+  int longest = 0;
+  for (int b = 0; b < st.batch; ++b) longest = st.n[b] > longest ? st.n[b] : longest;
+  if (longest <= F32_FUSE_CHUNKS * F32_KEYS || longest > F32_FUSE_CHUNKS * 2 * F32_KEYS) return false;
+  const int narrow = (make_chunks(st, F32_KEYS).off[st.batch] * dm.h_kv + 255) / 256;
+  const int wide = (make_chunks(st, 2 * F32_KEYS).off[st.batch] * dm.h_kv + 255) / 256;
+  const int row_blocks = (dm.g * dm.w + 31) / 32;
+  return (2 * wide - narrow) * row_blocks * 1.8f * dm.d / 128 <= 1.5f;
+}
+
 ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma) {
   (void)dtype;
   if (on_mfma) return plan_score_chunk(st, dm, choose_mfma_variant(st, dm).len);
   // The fp32 kernels' partials are per 128 keys (workgroups of four wavefronts spread best), or per
-  // 256 keys where the smaller ones would not fit into the built-in scratch array any more: half the
-  // partials, and a sequence that long fills the chip with either.
+  // 256 keys where that saves a kernel (f32_wide_stats) or the smaller ones would not fit into the built-in
+  // scratch array any more: half the partials, and a sequence that long fills the chip with either.
   const ScorePlan p = plan_score_chunk(st, dm, F32_KEYS);
   const size_t spare = 1024;                           // what the callers add for alignment
-  if (p.total + plan_topk_bytes(st, dm) + spare <= (size_t)ADAKV_STATIC_SCRATCH_BYTES) return p;
+  if (!f32_wide_stats(st, dm) && p.total + plan_topk_bytes(st, dm) + spare <= (size_t)ADAKV_STATIC_SCRATCH_BYTES) return p;
   return plan_score_chunk(st, dm, 2 * F32_KEYS);
 }
 
