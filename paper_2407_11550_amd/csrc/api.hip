@@ -288,7 +288,7 @@ int adakv_compress(const adakv_layer *L, const void *q_window, const void *K, co
   if ((rc = adakv_score(&P, q_window, K, row_lse, scores, ws, ws_bytes, hip_stream)) != ADAKV_OK) return rc;
   char *wsp = (char *)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
   if (launch_topk(st, dm, scores, budgets, cu_seqlens, indices, wsp + plan.topk,
-                  pipeline_mode(&P, dm), (hipStream_t)hip_stream) != hipSuccess)
+                  pipeline_mode(&P, dm), wsp, plan.topk, (hipStream_t)hip_stream) != hipSuccess)
     return ADAKV_EHIP;
   return adakv_compact(&P, K, V, indices, cu_seqlens, K_out, V_out, hip_stream);
 }

@@ -121,9 +121,10 @@ hipError_t launch_select(const SeqTab &st, const Dims &dm, const float *scores,
                          const int *budgets, const int *cu_seqlens, int *indices, char *ws,
                          bool carried, hipStream_t s);
 
-// both, for callers that want nothing in between (adakv_compress)
+// both, for callers that want nothing in between (adakv_compress); spare: memory that nothing else holds by now
 hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
-                       int *cu_seqlens, int *indices, char *ws, bool carried, hipStream_t s);
+                       int *cu_seqlens, int *indices, char *ws, bool carried, char *spare, size_t spare_bytes,
+                       hipStream_t s);
 
 // ---- compaction (compact.hip) ---------------------------------------------------------------
 hipError_t launch_compact(const SeqTab &st, const Dims &dm, int dtype, const void *K,

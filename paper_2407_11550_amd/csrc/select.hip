@@ -10,8 +10,9 @@
 // key's bits 31..21, 20..10 and 9..0.  Each scope runs two kernels (a kernel boundary is the
 // cheapest device-wide synchronisation on this part; a device-scope fence inside a kernel writes
 // a whole L2 back), so the whole Top-k is four launches after the first-digit histograms, which
-// the scoring kernel leaves behind in pipeline mode (two small kernels make them otherwise).  Short
-// rows run a scope, or both, inside one block per sequence or segment instead (below):
+// the scoring kernel leaves behind in pipeline mode (two small kernels make them otherwise), or three
+// where the layer's finish and the head's gather share one.  Short rows run a scope, or both, inside
+// one block per sequence or segment instead (below):
 //
 //   gather   every block of 4096 positions finds the first digit d0 of its scope's threshold from
 //            the finished first-digit histogram, adds the second digits of its elements under d0
@@ -193,6 +194,78 @@ __global__ __launch_bounds__(256) void topk_digit0_kernel(SeqTab st, ChunkTab ct
   }
 }
 
+// The gather step of a block of NT threads: `sc` holds its scores (position j0 + tid + NT i, clamped
+// to j1 - 1), `mine` this thread's part of the scope's first digits, krem > 0 the rank sought, gh the
+// scope's second digits.  The caller has cleared lh and *sh_above.
+template <int NT>
+__device__ __forceinline__ void gather_block(const float (&sc)[SEL_CHUNK / NT], int j0, int j1,
+                                             const Bins<RADIX_BINS> &mine, int krem, const TopkBufs &tb, size_t blk,
+                                             unsigned *gh, unsigned *lh /*[RADIX_BINS]: second-digit counts, then running bucket fill*/,
+                                             unsigned *sh /*[8]*/, int *sh_above, int *sh_wave /*[NT/64]*/) {
+  constexpr int EPB = SEL_CHUNK / NT, PER = RADIX_BINS / NT;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  unsigned d0;
+  int r0;
+  locate<RADIX_BINS>(mine, krem, d0, r0, sh);          // its barriers also publish the cleared lh
+  unsigned keys[EPB];
+  int above = 0;
+#pragma unroll
+  for (int i = 0; i < EPB; ++i) {
+    const bool in = j0 + tid + NT * i < j1;
+    const unsigned key = key_of(sc[i]);
+    keys[i] = key;
+    const unsigned dg = key >> 21;
+    if (in && dg == d0) atomicAdd(&lh[(key >> 10) & 2047u], 1u);
+    above += in && dg > d0;
+  }
+  above = wave_sum(above);
+  if (lane == 0) atomicAdd(sh_above, above);
+  __syncthreads();
+  // bucket starts, largest digit first is not needed: buckets are addressed by digit.  Thread t
+  // owns PER bins from PER t: exclusive scan over the block.
+  unsigned cnt[PER];
+  unsigned tsum = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) { cnt[i] = lh[tid * PER + i]; tsum += cnt[i]; }
+  const unsigned inc = (unsigned)wave_scan_incl((int)tsum);
+  if (lane == 63) sh_wave[wv] = (int)inc;
+  __syncthreads();
+  unsigned base = inc - tsum;
+  for (int i = 0; i < wv; ++i) base += (unsigned)sh_wave[i];
+  // starts to memory (one store), counts to the scope's histograms, starts into lh
+  unsigned stt[PER];
+  unsigned run = base;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) { stt[i] = run; run += cnt[i]; }
+  if constexpr (PER == 8) {
+    uint4 packed;
+    packed.x = stt[0] | (stt[1] << 16); packed.y = stt[2] | (stt[3] << 16);
+    packed.z = stt[4] | (stt[5] << 16); packed.w = stt[6] | (stt[7] << 16);
+    reinterpret_cast<uint4 *>(tb.starts + blk * RADIX_BINS)[tid] = packed;
+  } else {
+    static_assert(PER == 2, "two or eight bins per thread");
+    reinterpret_cast<unsigned *>(tb.starts + blk * RADIX_BINS)[tid] = stt[0] | (stt[1] << 16);
+  }
+  if (tid == NT - 1) { tb.note[blk].entries = (int)run; tb.note[blk].above = *sh_above; }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    if (cnt[i]) atomicAdd(&gh[tid * PER + i], cnt[i]);
+    lh[tid * PER + i] = stt[i];
+  }
+  __syncthreads();
+  // (the order inside a bucket follows the atomics, but only the multiset of a bucket's last
+  // digits is ever used)
+  unsigned short *ent = tb.entries + blk * ENT_PER_BLOCK;
+#pragma unroll
+  for (int i = 0; i < EPB; ++i) {
+    const bool in = j0 + tid + NT * i < j1;
+    if (in && (keys[i] >> 21) == d0) {
+      const unsigned slot = atomicAdd(&lh[(keys[i] >> 10) & 2047u], 1u);
+      if (slot < (unsigned)ENT_PER_BLOCK) ent[slot] = (unsigned short)(keys[i] & 1023u);
+    }
+  }
+}
+
 // The gather kernel of either scope.  grid as above.  LAYER: the threshold is sought over all
 // heads of a sequence (rank B'), else inside the block's own head (rank budgets[segment]).
 template <bool LAYER>
@@ -200,10 +273,10 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SeqTab st, ChunkTab ct
                                                           const float *__restrict__ scores,
                                                           const int *__restrict__ budgets,
                                                           TopkBufs tb) {
-  __shared__ unsigned lh[RADIX_BINS];                  // second-digit counts, then running bucket fill
+  __shared__ unsigned lh[RADIX_BINS];
   __shared__ unsigned sh[8];
   __shared__ int sh_above, sh_wave[4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x;
   const int b = find_seq(ct, st.batch, blockIdx.x);
   // the first sequence's facts sit at fixed places of the kernel arguments and arrive with the
   // first scalar fetch; only later sequences of a batch cost a dependent one
@@ -231,62 +304,8 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SeqTab st, ChunkTab ct
     if (tid == 0) { tb.note[blk].entries = 0; tb.note[blk].above = 0; }
     return;
   }
-  unsigned d0;
-  int r0;
-  locate<RADIX_BINS>(mine, krem, d0, r0, sh);          // its barriers also publish the cleared lh
-  unsigned keys[EPB];
-  int above = 0;
-#pragma unroll
-  for (int i = 0; i < EPB; ++i) {
-    const bool in = j0 + tid + 256 * i < j1;
-    const unsigned key = key_of(sc[i]);
-    keys[i] = key;
-    const unsigned dg = key >> 21;
-    if (in && dg == d0) atomicAdd(&lh[(key >> 10) & 2047u], 1u);
-    above += in && dg > d0;
-  }
-  above = wave_sum(above);
-  if (lane == 0) atomicAdd(&sh_above, above);
-  __syncthreads();
-  // bucket starts, largest digit first is not needed: buckets are addressed by digit.  Thread t
-  // owns bins 8t .. 8t+7: exclusive scan over the block.
-  unsigned cnt[8];
-  unsigned tsum = 0;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) { cnt[i] = lh[tid * 8 + i]; tsum += cnt[i]; }
-  const unsigned inc = (unsigned)wave_scan_incl((int)tsum);
-  if (lane == 63) sh_wave[wv] = (int)inc;
-  __syncthreads();
-  unsigned base = inc - tsum;
-  for (int i = 0; i < wv; ++i) base += (unsigned)sh_wave[i];
-  // starts to memory (one 16-byte store), counts to the scope's histograms, starts into lh
-  unsigned stt[8];
-  unsigned run = base;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) { stt[i] = run; run += cnt[i]; }
-  uint4 packed;
-  packed.x = stt[0] | (stt[1] << 16); packed.y = stt[2] | (stt[3] << 16);
-  packed.z = stt[4] | (stt[5] << 16); packed.w = stt[6] | (stt[7] << 16);
-  reinterpret_cast<uint4 *>(tb.starts + blk * RADIX_BINS)[tid] = packed;
-  if (tid == 255) { tb.note[blk].entries = (int)run; tb.note[blk].above = sh_above; }
   unsigned *gh = LAYER ? tb.hist1_tot + (size_t)b * RADIX_BINS : tb.hist1 + (size_t)seg * RADIX_BINS;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    if (cnt[i]) atomicAdd(&gh[tid * 8 + i], cnt[i]);
-    lh[tid * 8 + i] = stt[i];
-  }
-  __syncthreads();
-  // (the order inside a bucket follows the atomics, but only the multiset of a bucket's last
-  // digits is ever used)
-  unsigned short *ent = tb.entries + blk * ENT_PER_BLOCK;
-#pragma unroll
-  for (int i = 0; i < EPB; ++i) {
-    const bool in = j0 + tid + 256 * i < j1;
-    if (in && (keys[i] >> 21) == d0) {
-      const unsigned slot = atomicAdd(&lh[(keys[i] >> 10) & 2047u], 1u);
-      if (slot < (unsigned)ENT_PER_BLOCK) ent[slot] = (unsigned short)(keys[i] & 1023u);
-    }
-  }
+  gather_block<256>(sc, j0, j1, mine, krem, tb, blk, gh, lh, sh, &sh_above, sh_wave);
 }
 
 // Bucket d1 of one gather block: [first, first + count) in its entries.
@@ -591,6 +610,57 @@ __global__ __launch_bounds__(FIN_NT) void alloc_finish_kernel(SeqTab st, ChunkTa
   for (int i = 0; i <= c; ++i) run += lc.base[i] + w;
   if (b == 0 && c == 0) cu[0] = 0;
   cu[b * h + c + 1] = run;
+}
+
+// Layer scope, second kernel, and head scope, first kernel, in one launch: every block (chunk, head) works the
+// layer scope of its sequence out for itself, then gathers for its own head.  `layer` is what the layer's gather
+// left behind; the head's lists go to memory of their own (`head`), since other blocks still read the layer's.
+// A chain of dependent trips to memory bounds it, so that sixteen wavefronts repeat the layer scope in every
+// block in the time in which one block does it.  What it saves is a launch: finish + gather / this kernel, us,
+// 32768 keys x 8 heads 12.5 / 10.0 (the whole step 67.3 / 65.2), 131072 x 8 14.6 / 11.0 (135.1 / 131.2), four of up
+// to 30000 x 8 29.6 / 25.8 (86.4 / 82.3).
+__global__ __launch_bounds__(FIN_NT) void finish_gather_kernel(SeqTab st, ChunkTab ct, int h, int w, int alpha_fix,
+                                                               const float *__restrict__ scores, TopkBufs layer,
+                                                               TopkBufs head, int *__restrict__ budgets,
+                                                               int *__restrict__ cu) {
+  __shared__ unsigned sh[8];
+  __shared__ int sh_scan[FIN_NT / 64], sh_above;
+  __shared__ unsigned scratch[1024 + HOLD_LAYER];      // the layer scope's, then the head's second digits
+  __shared__ LayerCounts lc;
+  static_assert(RADIX_BINS <= 1024 + HOLD_LAYER, "the digits fit into the scratch words");
+  const int tid = threadIdx.x;
+  const int b = find_seq(ct, st.batch, blockIdx.x);
+  const int n = st.n[b], Bp = st.Bp[b];
+  const int chunk = blockIdx.x - ct.off[b];
+  const int c = blockIdx.y;
+  const int seg = b * h + c;
+  const float *row = scores + st.score_off[b] + (size_t)c * n;
+  const int j0 = chunk * SEL_CHUNK;
+  const int j1 = min(n, j0 + SEL_CHUNK);
+  float sc[SEL_CHUNK / FIN_NT];
+#pragma unroll
+  for (int i = 0; i < SEL_CHUNK / FIN_NT; ++i) sc[i] = row[min(j0 + tid + FIN_NT * i, j1 - 1)];
+  const Bins<RADIX_BINS> mine = load_bins<RADIX_BINS>(head.hist0 + (size_t)seg * RADIX_BINS);
+  const int ties = layer_counts(ct, h, b, Bp, layer, lc, sh, sh_scan, scratch);
+  safeguard(h, Bp, alpha_fix, ties, lc);
+  __syncthreads();                                     // the budgets; and nobody reads the scratch words any more
+  const int bud = lc.base[c];
+  for (int i = tid; i < RADIX_BINS; i += FIN_NT) scratch[i] = 0u;
+  if (tid == 0) sh_above = 0;
+  if (chunk == 0 && tid == 0) {
+    int run = st.out_off[b] + bud + w;
+    for (int i = 0; i < c; ++i) run += lc.base[i] + w;
+    budgets[seg] = bud;
+    cu[seg + 1] = run;
+    if (seg == 0) cu[0] = 0;
+  }
+  const size_t blk = (size_t)blockIdx.x * h + c;
+  if (bud <= 0) {
+    if (tid == 0) { head.note[blk].entries = 0; head.note[blk].above = 0; }
+    return;
+  }
+  gather_block<FIN_NT>(sc, j0, j1, mine, bud, head, blk, head.hist1 + (size_t)seg * RADIX_BINS, scratch, sh, &sh_above,
+                       sh_scan);
 }
 
 constexpr int EPT = SEL_CHUNK / 256;   // positions per thread in the emit kernel, 256 apart
@@ -1030,6 +1100,17 @@ void launch_topk_clear(const TopkCarry &tc, hipStream_t s) {
   launch_clear("score_hist_clear", tc.zero_begin, tc.zero_words, s);
 }
 
+// The gather lists alone, in other memory: how much, and where.
+static size_t list_bytes(size_t blocks) {
+  return align_up(blocks * RADIX_BINS * 2, 256) + align_up(blocks * sizeof(BlockNote), 256) + blocks * ENT_PER_BLOCK * 2;
+}
+static TopkBufs lists_in(TopkBufs tb, char *spare, size_t blocks) {
+  tb.starts = (unsigned short *)spare; spare += align_up(blocks * RADIX_BINS * 2, 256);
+  tb.note = (BlockNote *)spare; spare += align_up(blocks * sizeof(BlockNote), 256);
+  tb.entries = (unsigned short *)spare;
+  return tb;
+}
+
 static TopkBufs bufs_of(char *ws, const TopkWs &p) {
   TopkBufs tb;
   tb.hist0 = (const unsigned *)(ws + p.hist0);
@@ -1077,6 +1158,12 @@ constexpr long long SELECT_BLOCK_MAX = 16 * BLK_NT;    // of a head; first digit
 constexpr long long SELECT_CARRIED_MAX = 8 * BLK_NT;   // of a head; first digits from the scoring kernel
 constexpr long long TOPK_BLOCK_MAX = 12 * BLK_NT;      // of a sequence; both scopes in one launch
 constexpr long long TOPK_ROW_MAX = 4 * BLK_NT;         // of a head; gather and the rest in one launch (16088: 18.3 -> 16.3)
+// Longer rows: finish and the head's gather in one launch where every block has a compute unit to itself (each
+// repeats the layer scope with a compute unit's whole issue rate, on plateaus too: scores all equal, 32768 x 8
+// 81.9 / 80.7 us a step with four kernels / three, 131072 x 8 181 / 177, 20000 x 32 122 / 119) and where the
+// head's lists fit into what the scoring sweeps have done with.  Below four segments a scope leaves most of the
+// chip idle either way and the kernels stay apart, each scope with a time of its own in a trace.
+constexpr int FUSED_BLOCKS = 256, FUSED_SEGMENTS = 4;
 hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
                            int *cu_seqlens, char *ws, bool carried, hipStream_t s) {
   const TopkWs p = plan(st, dm);
@@ -1134,7 +1221,8 @@ hipError_t launch_select(const SeqTab &st, const Dims &dm, const float *scores,
 }
 
 hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
-                       int *cu_seqlens, int *indices, char *ws, bool carried, hipStream_t s) {
+                       int *cu_seqlens, int *indices, char *ws, bool carried, char *spare, size_t spare_bytes,
+                       hipStream_t s) {
   const int h = dm.h_kv, rows = st.out_off[st.batch], nseg = st.batch * h;
   const long long most = (long long)longest_row(st) * h;
   // Every block repeats the layer scope with a compute unit's whole issue rate (sixteen wavefronts), so there
@@ -1156,6 +1244,19 @@ hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, in
     else if (most <= 4 * BLK_NT) ADAKV_GO(4, true);
     else ADAKV_GO(12, true);
 #undef ADAKV_GO
+    return hipGetLastError();
+  }
+  const ChunkTab ct = make_chunks(st, SEL_CHUNK);
+  const size_t blocks = (size_t)ct.off[st.batch] * h;
+  if (carried && longest_row(st) > SELECT_CARRIED_MAX && nseg >= FUSED_SEGMENTS && blocks <= FUSED_BLOCKS &&
+      list_bytes(blocks) <= spare_bytes) {
+    const TopkBufs tb = bufs_of(ws, plan(st, dm)), head = lists_in(tb, spare, blocks);
+    const dim3 grid(ct.off[st.batch], h), block(256);
+    ADAKV_LAUNCH("alloc_gather", (topk_gather_kernel<true>), grid, block, s, st, ct, h, scores, (const int *)nullptr, tb);
+    ADAKV_LAUNCH("topk_finish_gather", finish_gather_kernel, grid, dim3(FIN_NT), s, st, ct, h, dm.w, dm.alpha_fix,
+                 scores, tb, head, budgets, cu_seqlens);
+    ADAKV_LAUNCH("select_emit", emit_write_kernel, grid, block, s, st, ct, h, dm.w, scores, head, budgets, cu_seqlens,
+                 indices, rows);
     return hipGetLastError();
   }
   const hipError_t e = launch_allocate(st, dm, scores, budgets, cu_seqlens, ws, carried, s);
