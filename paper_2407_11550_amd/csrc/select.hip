@@ -179,9 +179,17 @@ __global__ __launch_bounds__(256) void topk_digit0_kernel(SeqTab st, ChunkTab ct
   const int c = blockIdx.y;
   const float *row = scores + st.score_off[b] + (size_t)c * n;
   const int j0 = chunk * SEL_CHUNK, j1 = min(n, j0 + SEL_CHUNK);
+  // all of a thread's scores are requested before the first is counted, one trip to memory and not sixteen (indices
+  // past the end are clamped): eight sequences of up to 30011 x 8 scores nobody read yet 9.9 -> 5.7 us
+  constexpr int EPB = SEL_CHUNK / 256;
+  float sc[EPB];
+#pragma unroll
+  for (int i = 0; i < EPB; ++i) sc[i] = row[min(j0 + tid + 256 * i, j1 - 1)];
   for (int i = tid; i < RADIX_BINS; i += 256) lh[i] = 0u;
   __syncthreads();
-  for (int j = j0 + tid; j < j1; j += 256) atomicAdd(&lh[key_of(row[j]) >> 21], 1u);
+#pragma unroll
+  for (int i = 0; i < EPB; ++i)
+    if (j0 + tid + 256 * i < j1) atomicAdd(&lh[key_of(sc[i]) >> 21], 1u);
   __syncthreads();
   unsigned *gh = hist0 + (size_t)(b * h + c) * RADIX_BINS;
   unsigned *gt = hist_tot0 + (size_t)b * RADIX_BINS;
