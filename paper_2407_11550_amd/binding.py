@@ -98,7 +98,9 @@ def load_library():
     lib.adakv_describe.argtypes = [P, ctypes.c_int, ctypes.c_char_p, Z]
     lib.adakv_probe_read.restype = ctypes.c_int
     lib.adakv_probe_read.argtypes = [V, Z, V, V]
-    global _decode_step_address
+    global _decode_step_address, _marshal
+    if _marshal is None:                # built since this module was imported
+        _marshal = _load_marshal()
     _decode_step_address = ctypes.cast(lib.adakv_decode_step, V).value
     _lib = lib
     return lib

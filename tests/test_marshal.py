@@ -53,7 +53,7 @@ SPOILED = {
 }
 
 
-def test_tensors_of_the_host_and_others_are_not_taken():
+def test_tensors_of_the_host_and_others_are_not_taken(lib):
     assert binding._marshal is not None, "lib/_marshal.so is not built"
     layer, a = arguments("cpu")
     calls = []
@@ -93,7 +93,7 @@ def test_a_spoiled_argument_raises_as_without_the_native_checks(name, monkeypatc
 
 
 @pytest.mark.gpu
-def test_a_refusal_of_the_library_and_the_results(monkeypatch):
+def test_a_refusal_of_the_library_and_the_results(lib, monkeypatch):
     got = []
     for module in (binding._marshal, None):
         monkeypatch.setattr(binding, "_marshal", module)
