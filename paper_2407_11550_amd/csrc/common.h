@@ -114,6 +114,7 @@ TopkCarry plan_carry(const SeqTab &st, const Dims &dm, char *ws_topk);
 void launch_topk_clear(const TopkCarry &tc, hipStream_t s);
 
 size_t plan_topk_bytes(const SeqTab &st, const Dims &dm);
+size_t topk_spare_bytes(const SeqTab &st, const Dims &dm);   // what launch_topk's shortest form puts into `spare`; 0: not its form
 // carried: the first-digit histograms are already in the workspace and the rest is cleared
 hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
                            int *cu_seqlens, char *ws, bool carried, hipStream_t s);

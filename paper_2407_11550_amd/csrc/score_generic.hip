@@ -498,7 +498,14 @@ static bool f32_wide_stats(const SeqTab &st, const Dims &dm) {
 
 ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma) {
   (void)dtype;
-  if (on_mfma) return plan_score_chunk(st, dm, choose_mfma_variant(st, dm).len);
+  if (on_mfma) {
+    const MfmaVariant v = choose_mfma_variant(st, dm);
+    ScorePlan p = plan_score_chunk(st, dm, v.part_len);
+    // (the Top-k's shortest form finds room here where partials of the weights sweep's chunks would have made it)
+    const size_t lists = topk_spare_bytes(st, dm);
+    if (lists <= score_workspace(st, dm, v.len) && lists > p.total) p.total = lists;
+    return p;
+  }
   // The fp32 kernels' partials are per 128 keys (workgroups of four wavefronts spread best), or per
   // 256 keys where that saves a kernel (f32_wide_stats) or the smaller ones would not fit into the built-in
   // scratch array any more: half the partials, and a sequence that long fills the chip with either.

@@ -1485,28 +1485,33 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
     const long long rounds = (workgroups(st, dm, most) + slots - 1) / slots;
     v.len = shortest(256, rounds * slots);
   }
-  // More chunks are more partial statistics: a layer that fits into the built-in scratch array with
-  // the longest chunks gets no split that would take it past the array's end (1 KiB for the
-  // alignment of the parts, asked of the split alone, so that a layer that just fits keeps fitting).
-  auto need = [&](int len) { return score_workspace(st, dm, len) + plan_topk_bytes(st, dm); };
-  if (need(v.len) + 1024 > (size_t)ADAKV_STATIC_SCRATCH_BYTES && need(most) <= (size_t)ADAKV_STATIC_SCRATCH_BYTES) v.len = most;
   // Sweep 1 of up to 256 rows is not bound to the chunks: one resident round of workgroups over all sequences, as many
-  // rounds as there are heads for beyond that, and never more workgroups than sweep 2's chunks (the partials have a
-  // place for each of those).  Up to 128 rows the tiles' place in LDS leaves one workgroup per compute unit at d = 128,
-  // two at d = 64.  Beyond 128 rows two would fit, but one halves the partials, so that sweep 2 can combine them
-  // itself: 20000 keys x 8 heads, 256 rows 41.3 -> 38.5 us, 50021 74.3 -> 73.3; with chunks of more than 1024 keys a
-  // wavefront alone on its SIMD loses more than that kernel takes (131072 keys: 168.7 | 170.2).
-  v.part_len = v.len;
-  if (R <= 128 || (R <= 256 && v.len <= 1024)) {
+  // rounds as there are heads for beyond that, and never more workgroups than sweep 2's chunks.  Up to 128 rows the
+  // tiles' place in LDS leaves one workgroup per compute unit at d = 128, two at d = 64.  Beyond 128 rows two would
+  // fit, but one halves the partials, so that sweep 2 can combine them itself: 20000 keys x 8 heads, 256 rows
+  // 41.3 -> 38.5 us, 50021 74.3 -> 73.3; with chunks of more than 1024 keys a wavefront alone on its SIMD loses more
+  // than that kernel takes (131072 keys: 168.7 | 170.2).
+  auto stats_len = [&](int len, int least) {           // sweep 1's keys per workgroup beside chunks of len, no fewer than least
+    if (!(R <= 128 || (R <= 256 && len <= 1024))) return len;
     const long long room = dm.d == 128 || R > 128 ? 256 : 512, heads = (long long)st.batch * dm.h_kv;
     const long long wgs = (heads + room - 1) / room * room;
-    int lo = v.len / TILE, hi = longest / TILE + 1 > lo ? longest / TILE + 1 : lo;
+    int lo = least / TILE, hi = longest / TILE + 1 > lo ? longest / TILE + 1 : lo;
     while (lo < hi) {
       const int mid = (lo + hi) / 2;
       if (workgroups(st, dm, mid * TILE) <= wgs) hi = mid;
       else lo = mid + 1;
     }
-    v.part_len = hi * TILE;
+    return hi * TILE;
+  };
+  v.part_len = stats_len(v.len, v.len);
+  // More workgroups of sweep 1 are more partial statistics: a layer that fits into the built-in scratch array with
+  // the longest chunks (at 65 to 128 rows, whose chunks end at OWN_MOST, with partials per 4096 keys) gets no split
+  // that would take it past the array's end (1 KiB for the alignment of the parts, asked of the split alone, so that
+  // a layer that just fits keeps fitting).
+  auto need = [&](int part_len) { return score_workspace(st, dm, part_len) + plan_topk_bytes(st, dm); };
+  if (need(v.part_len) + 1024 > (size_t)ADAKV_STATIC_SCRATCH_BYTES) {
+    const int fewest = stats_len(most, most == OWN_MOST ? 4096 : most);
+    if (need(fewest) <= (size_t)ADAKV_STATIC_SCRATCH_BYTES) { v.len = most; v.part_len = fewest; }
   }
   // The instantiation: the smallest score array in LDS that holds a chunk; with 512 rows a compute
   // unit holds one workgroup either way and long sequences take the larger.

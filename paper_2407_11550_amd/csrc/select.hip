@@ -1172,6 +1172,11 @@ constexpr long long TOPK_ROW_MAX = 4 * BLK_NT;         // of a head; gather and 
 // head's lists fit into what the scoring sweeps have done with.  Below four segments a scope leaves most of the
 // chip idle either way and the kernels stay apart, each scope with a time of its own in a trace.
 constexpr int FUSED_BLOCKS = 256, FUSED_SEGMENTS = 4;
+size_t topk_spare_bytes(const SeqTab &st, const Dims &dm) {
+  const size_t blocks = (size_t)make_chunks(st, SEL_CHUNK).off[st.batch] * dm.h_kv;
+  const bool fused = longest_row(st) > SELECT_CARRIED_MAX && st.batch * dm.h_kv >= FUSED_SEGMENTS && blocks <= FUSED_BLOCKS;
+  return fused ? list_bytes(blocks) : 0;
+}
 hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
                            int *cu_seqlens, char *ws, bool carried, hipStream_t s) {
   const TopkWs p = plan(st, dm);
@@ -1254,11 +1259,10 @@ hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, in
 #undef ADAKV_GO
     return hipGetLastError();
   }
-  const ChunkTab ct = make_chunks(st, SEL_CHUNK);
-  const size_t blocks = (size_t)ct.off[st.batch] * h;
-  if (carried && longest_row(st) > SELECT_CARRIED_MAX && nseg >= FUSED_SEGMENTS && blocks <= FUSED_BLOCKS &&
-      list_bytes(blocks) <= spare_bytes) {
-    const TopkBufs tb = bufs_of(ws, plan(st, dm)), head = lists_in(tb, spare, blocks);
+  const size_t lists = topk_spare_bytes(st, dm);
+  if (carried && lists && lists <= spare_bytes) {
+    const ChunkTab ct = make_chunks(st, SEL_CHUNK);
+    const TopkBufs tb = bufs_of(ws, plan(st, dm)), head = lists_in(tb, spare, (size_t)ct.off[st.batch] * h);
     const dim3 grid(ct.off[st.batch], h), block(256);
     ADAKV_LAUNCH("alloc_gather", (topk_gather_kernel<true>), grid, block, s, st, ct, h, scores, (const int *)nullptr, tb);
     ADAKV_LAUNCH("topk_finish_gather", finish_gather_kernel, grid, dim3(FIN_NT), s, st, ct, h, dm.w, dm.alpha_fix,

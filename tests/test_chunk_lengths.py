@@ -115,3 +115,31 @@ def test_short_and_odd_chunks_match_oracle(case, order):
         assert_exact_on_scores(out, sc, wl, K, V, b, seg0=b * h, row0=row0)
         soff += h * n[b]
         row0 += wl.B[b]
+
+
+def _bytes_with_partials_per(keys, h_q, h, w, n):
+    """Workspace of a 16-bit layer whose statistics are kept per `keys` keys: partials, log-sum-exp, scores before the
+    pool, and the Top-k's digit counts and lists."""
+    up = lambda v: -(-v // 256) * 256
+    blocks = h * sum(-(-nb // 4096) for nb in n)
+    score = up(sum(-(-nb // keys) for nb in n) * h_q * w * 8) + up(len(n) * h_q * w * 4) + up(h * sum(n) * 4)
+    return score + 2 * 2048 * 4 * (len(n) * h + len(n)) + up(blocks * 4096) + up(blocks * 8) + up(blocks * 8192) + 256
+
+
+def test_layers_that_fit_the_built_in_scratch_array_with_partials_per_4096_keys_do_fit(lib):
+    """128 rows, d = 128: a chunk ends at 3840 keys there, the statistics need not."""
+    rng, near = random.Random(17), 0
+    shapes = [(32, 8, 32, [230774, 196046]), (128, 32, 32, [105509])]
+    for _ in range(4000):
+        h, batch = rng.choice([1, 2, 4, 8, 16, 32, 64]), rng.choice([1, 1, 2, 5, 20, 64])
+        g, w = rng.choice([(4, 32), (2, 64), (8, 13), (1, 100)])
+        part = [2 ** rng.uniform(0, 6) for _ in range(batch)]
+        n = [max(1, int(p / sum(part) * rng.uniform(3.2e6, 3.6e6) / h)) for p in part]
+        shapes.append((h * g, h, w, n))
+    for h_q, h, w, n in shapes:
+        with_4096 = _bytes_with_partials_per(4096, h_q, h, w, n)
+        if 23 << 20 < with_4096 <= adakv.binding.STATIC_SCRATCH_BYTES:
+            near += 1
+            layer = adakv.Layer(torch.bfloat16, h_q, h, 128, w, 7, 0.2, n, [h * w] * len(n))
+            assert adakv.workspace_bytes(layer) <= adakv.binding.STATIC_SCRATCH_BYTES, (h_q, h, w, n)
+    assert near > 100, near
