@@ -189,10 +189,34 @@ def _ptr(t, name, dtype=None):
 
 
 def _need(t, numel, name):
-    """A caller-supplied buffer must hold at least `numel` elements (the kernels index it by the
-    layer's sizes and never look at the tensor)."""
-    if t is not None and t.numel() < numel:
+    """A caller-supplied buffer must hold at least `numel` elements, one behind the other (the kernels
+    index it by the layer's sizes and never look at the tensor)."""
+    if t is None:
+        return
+    if t.numel() < numel:
         raise ValueError(f"{name} holds {t.numel()} elements, the layer needs {numel}")
+    if not t.is_contiguous() and not _dense(t, numel):
+        raise ValueError(f"{name} must be contiguous")
+
+
+def _dense(t, numel):
+    """Whether a view's first `numel` elements (the last dimension runs fastest) lie one behind the other."""
+    run = 1
+    for size, stride in zip(reversed(t.shape), reversed(t.stride())):
+        if run >= numel:
+            break
+        if size != 1 and stride != run:
+            return False
+        run *= size
+    return True
+
+
+def _check_ws(ws):
+    """The workspace's size travels to the library, which checks it."""
+    if ws.dtype != torch.uint8:
+        raise ValueError("ws must be a uint8 tensor (its size is taken in bytes)")
+    if not ws.is_contiguous():
+        raise ValueError("ws must be contiguous")
 
 
 def _check_kv(layer, t, name, strides, given):
@@ -237,8 +261,7 @@ def _stream(stream):
 def _workspace(layer, ws):
     if ws is None:
         ws = torch.empty(max(workspace_bytes(layer), 16), dtype=torch.uint8, device="cuda")
-    if ws.dtype != torch.uint8:
-        raise ValueError("ws must be a uint8 tensor (its size is taken in bytes)")
+    _check_ws(ws)
     return ws, ws.data_ptr(), ws.numel()
 
 
@@ -356,8 +379,7 @@ def compress(layer: Layer, q_window, K, V, row_lse=None, ws=None, stream=None, b
                            (cu, layer.num_segments + 1, "cu_seqlens"), (idx, layer.num_rows_out, "indices"),
                            (K_out, layer.num_rows_out * layer.d, "K_out"), (V_out, layer.num_rows_out * layer.d, "V_out")):
         _need(t, numel, name)
-    if ws.dtype != torch.uint8:                    # its size travels to the library, which checks it
-        raise ValueError("ws must be a uint8 tensor (its size is taken in bytes)")
+    _check_ws(ws)
     st = lib.adakv_compress(ctypes.byref(layer.c), _ptr(q_window, "q_window", layer.torch_dtype),
                             _ptr(K, "K", layer.torch_dtype), _ptr(V, "V", layer.torch_dtype),
                             _ptr(row_lse, "row_lse", torch.float32), _ptr(sc, "scores", torch.float32),
@@ -433,7 +455,7 @@ def probe_read(src, sink=None, stream=None):
         raise ValueError("src must be contiguous")
     if sink is None:
         sink = torch.empty(PROBE_SINK_BYTES, dtype=torch.uint8, device=src.device)
-    if sink.numel() * sink.element_size() < PROBE_SINK_BYTES:
+    if sink.numel() * sink.element_size() < PROBE_SINK_BYTES or not sink.is_contiguous():
         raise ValueError("sink too small")
     st = load_library().adakv_probe_read(_ptr(src, "src"), src.numel() * src.element_size(),
                                          _ptr(sink, "sink"), _stream(stream))
@@ -448,21 +470,20 @@ def cache_rows(layer: Layer, headroom: int) -> int:
     return layer._rows_out + layer._segments * int(headroom)
 
 
-def _check_cache(layer, K_cache, V_cache):
-    """The cache tensors are addressed as contiguous rows of d elements."""
+def _check_cache(layer, headroom, K_cache, V_cache):
+    """The cache tensors are addressed as contiguous rows of d elements (a flat tensor of d elements is one row)."""
     for t, name in ((K_cache, "K_cache"), (V_cache, "V_cache")):
-        if not t.is_contiguous() or t.size(-1) != layer.d:
+        if not t.is_contiguous() or t.size(-1) != layer.d or t.numel() < cache_rows(layer, headroom) * layer.d:
             raise ValueError(f"{name} must be a contiguous [rows, {layer.d}] tensor")
 
 
 def _check_decode_bufs(layer, headroom, K_cache, V_cache, cu_seqlens, seg_len, out, lse, ws):
-    _check_cache(layer, K_cache, V_cache)
+    _check_cache(layer, headroom, K_cache, V_cache)
     _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
     _need(seg_len, layer.num_segments, "seg_len")
     _need(out, layer.batch * layer.h_q * layer.d, "out")
     _need(lse, layer.batch * layer.h_q, "lse")
-    if ws.dtype != torch.uint8:                    # its size travels to the library, which checks it
-        raise ValueError("ws must be a uint8 tensor (its size is taken in bytes)")
+    _check_ws(ws)
 
 
 def decode_workspace_bytes(layer: Layer, headroom: int) -> int:
@@ -487,7 +508,8 @@ def cache_build(layer: Layer, K, V, indices, cu_seqlens, headroom, K_cache=None,
     _check_kv(layer, V, "V", layer.v_strides, layer.strides_given[1])
     _need(indices, layer.num_rows_out, "indices")
     _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
-    _check_cache(layer, K_cache, V_cache)
+    _check_cache(layer, headroom, K_cache, V_cache)
+    _need(seg_len, layer.num_segments, "seg_len")
     st = lib.adakv_cache_build(ctypes.byref(layer.c), _ptr(K, "K", layer.torch_dtype),
                                _ptr(V, "V", layer.torch_dtype), _ptr(indices, "indices", torch.int32),
                                _ptr(cu_seqlens, "cu_seqlens", torch.int32), int(headroom),
@@ -511,7 +533,7 @@ def append(layer: Layer, k_new, v_new, cu_seqlens, headroom, K_cache, V_cache, s
     rows = cache_rows(layer, headroom)
     if K_cache.size(0) < rows or V_cache.size(0) < rows:
         raise ValueError("cache too small for this layer and head-room")
-    _check_cache(layer, K_cache, V_cache)
+    _check_cache(layer, headroom, K_cache, V_cache)
     _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
     _need(seg_len, layer.num_segments, "seg_len")
     _need(overflow, 1, "overflow")

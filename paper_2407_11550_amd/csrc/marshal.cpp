@@ -26,9 +26,9 @@ bool is_rows(const at::Tensor *t, int64_t batch, int64_t h, int64_t d) {
   return t && t->dim() == 3 && t->size(0) == batch && t->size(1) == h && t->size(2) == d && t->is_contiguous();
 }
 bool is_cache(const at::Tensor *t, int64_t rows, int64_t d) {
-  return t && t->dim() >= 1 && t->size(0) >= rows && t->size(-1) == d && t->is_contiguous();
+  return t && t->dim() >= 1 && t->size(0) >= rows && t->size(-1) == d && t->numel() >= rows * d && t->is_contiguous();
 }
-bool holds(const at::Tensor *t, int64_t numel) { return t && t->numel() >= numel; }
+bool holds(const at::Tensor *t, int64_t numel) { return t && t->numel() >= numel && t->is_contiguous(); }
 
 // decode_step(function, layer, q, k, v, cu_seqlens, headroom, K_cache, V_cache, seg_len, overflow, out, lse, ws, stream)
 // -> the library's status, or None where the arguments are for binding.py to look at
@@ -60,7 +60,7 @@ PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!is_rows(q, L->batch, L->h_q, L->d) || !is_rows(k, L->batch, L->h_kv, L->d) || !is_rows(v, L->batch, L->h_kv, L->d) ||
         !is_cache(Kc, rows, L->d) || !is_cache(Vc, rows, L->d) || !holds(cu, nseg + 1) || !holds(len, nseg) ||
         (a[10] != Py_None && !holds(over, 1)) || !holds(out, (int64_t)L->batch * L->h_q * L->d) ||
-        (a[12] != Py_None && !holds(lse, (int64_t)L->batch * L->h_q)) || !ws)
+        (a[12] != Py_None && !holds(lse, (int64_t)L->batch * L->h_q)) || !holds(ws, 0))
       Py_RETURN_NONE;
     void *p[12] = {q->data_ptr(), k->data_ptr(), v->data_ptr(), cu->data_ptr(), Kc->data_ptr(), Vc->data_ptr(), len->data_ptr(),
                    over ? over->data_ptr() : nullptr, out->data_ptr(), lse ? lse->data_ptr() : nullptr, ws->data_ptr(), stream};

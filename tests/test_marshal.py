@@ -31,6 +31,11 @@ def native(layer, a, fn, stream=7):
     return binding._marshal.decode_step(ctypes.cast(fn, P).value, ctypes.addressof(layer.c), *a.values(), stream)
 
 
+def strided(t):
+    """The same values, every other element of a tensor twice as long."""
+    return torch.stack([t, t], dim=-1)[..., 0]
+
+
 # what each argument may be spoiled by; the native checks leave all of them to the ones in Python
 SPOILED = {
     "q_shape": lambda a: a.update(q_new=a["q_new"][:, :-1].contiguous()),
@@ -44,6 +49,12 @@ SPOILED = {
     "cache_short": lambda a: a.update(K_cache=a["K_cache"][:-1]),
     "cache_order": lambda a: a.update(V_cache=a["V_cache"].t().contiguous().t()),
     "cache_width": lambda a: a.update(V_cache=a["V_cache"].view(-1, D // 2)),
+    "cache_without_rows": lambda a: a.update(K_cache=a["K_cache"].new_empty(a["K_cache"].shape[0], 0, D)),
+    "cu_strided": lambda a: a.update(cu_seqlens=strided(a["cu_seqlens"])),
+    "len_strided": lambda a: a.update(seg_len=strided(a["seg_len"])),
+    "out_strided": lambda a: a.update(out=strided(a["out"])),
+    "lse_strided": lambda a: a.update(lse=strided(a["lse"])),
+    "ws_strided": lambda a: a.update(ws=strided(a["ws"])),
     "len_short": lambda a: a.update(seg_len=a["seg_len"][:-1]),
     "overflow_empty": lambda a: a.update(overflow=a["overflow"][:0]),
     "out_short": lambda a: a.update(out=a["out"][:1]),
@@ -105,3 +116,41 @@ def test_a_refusal_of_the_library_and_the_results(lib, monkeypatch):
         assert adakv.decode_step(layer, **dict(a, lse=None)) is a["out"]
         got.append([a[k].cpu() for k in ("out", "lse", "K_cache", "V_cache", "seg_len", "overflow")])
     assert all(torch.equal(x, y) for x, y in zip(*got))
+
+
+# h_q, h_kv, d, w: at most d rows with the head-room, so that a flat tensor of d elements has as many "rows" as are asked for
+FLAT = adakv.Layer(torch.bfloat16, 2, 1, 128, 4, 3, 0.2, [50], [40])
+
+
+@pytest.mark.parametrize("name", ["K_cache", "V_cache", "cu_seqlens", "seg_len", "out", "lse", "ws"])
+def test_memory_the_kernels_would_miss_is_refused(name, lib):
+    """A cache of one row of d elements, and buffers whose elements do not lie one behind the other: the checks in
+    Python refuse them by name (here before they look at the device)."""
+    f, i = (lambda *s: torch.zeros(*s, dtype=torch.bfloat16)), (lambda *v: torch.tensor(v, dtype=torch.int32))
+    a = dict(K_cache=f(43, 128), V_cache=f(43, 128), cu_seqlens=i(0, 40), seg_len=i(40), out=torch.zeros(1, 2, 128),
+             lse=torch.zeros(1, 2), ws=torch.zeros(adakv.decode_workspace_bytes(FLAT, 3), dtype=torch.uint8))
+    if name == "seg_len":                       # (one segment's length is one element, strided or not)
+        with pytest.raises(ValueError, match="must be a device tensor"):
+            adakv.decode_attn(FLAT, f(1, 2, 128), headroom=3, **dict(a, seg_len=strided(a["seg_len"])))
+        return
+    a[name] = f(128) if "cache" in name else strided(a[name])
+    with pytest.raises(ValueError, match=name):
+        adakv.decode_attn(FLAT, f(1, 2, 128), headroom=3, **a)
+
+
+@pytest.mark.gpu
+def test_a_flat_cache_and_rows_further_on(lib):
+    """The native checks leave a flat cache to the ones in Python; a buffer that is dense as far as it is used is taken."""
+    calls = []
+    fn = STEP(lambda *given: calls.append(given) or 0)
+    f, i = (lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device="cuda:0")), (lambda *v: torch.tensor(v, dtype=torch.int32, device="cuda:0"))
+    a = dict(q_new=f(1, 2, 128), k_new=f(1, 1, 128), v_new=f(1, 1, 128), cu_seqlens=i(0, 40), headroom=3, K_cache=f(43, 128),
+             V_cache=f(43, 128), seg_len=i(40), overflow=None, out=torch.zeros(1, 2, 128, device="cuda:0"), lse=None,
+             ws=torch.zeros(adakv.decode_workspace_bytes(FLAT, 3), dtype=torch.uint8, device="cuda:0"))
+    assert native(FLAT, a, fn) == 0 and len(calls) == 1
+    for name in ("K_cache", "V_cache"):
+        assert native(FLAT, dict(a, **{name: f(128)}), fn) is None
+        with pytest.raises(ValueError, match=name):
+            adakv.decode_step(FLAT, **dict(a, **{name: f(128)}))
+    wide = torch.zeros(3, 4, 128, device="cuda:0")[:, :2]        # the first [2, 128] lie together
+    assert adakv.decode_step(FLAT, **dict(a, out=wide)) is wide and len(calls) == 1
