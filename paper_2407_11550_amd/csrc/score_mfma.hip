@@ -132,7 +132,8 @@ __device__ __forceinline__ void pool_and_file(const float *sh_part, unsigned *sh
 // exponentials at a quarter of the rate).  Against the form before, in which two wavefronts shared a tile that
 // came through registers, with a barrier per tile; us a call, d = 128, 8 KV heads, 128 rows:
 //   whole step, 2011 keys 39.0 -> 37.6, 32768 keys 70.3 -> 66.5, 131072 keys 151.6 -> 142.0;
-//   scores alone, six sequences (217 000 keys) 206 -> 186; with the caller's log-sum-exp, 50021 keys 27.3 -> 26.0.
+//   scores alone, six sequences (217 000 keys) 206 -> 186; with the caller's log-sum-exp, 20000 keys 17.2 -> 13.3,
+//   50021 29.3 -> 26.2 (and 58.3 -> 57.1 at 131072 where the form before took 56.5, within 5 us from run to run).
 // The window queries come through LDS as well: read from memory as operand words every load touches 32 lines,
 // which kept the first tile waiting for 7 us (32768 keys: 22.0 + 25.0 us for the sweeps, 18.2 + 20.3 through LDS).
 template <int N> __device__ __forceinline__ void wait_vmem() {
@@ -166,6 +167,14 @@ __device__ __forceinline__ void load_to_lds_untracked(const char *base, unsigned
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(
                    (unsigned)(size_t)(__attribute__((address_space(3))) void *)dst),
                "v"(off), "s"(rs), "s"(at)
+               : "memory", "m0");
+}
+// 64 x 4 bytes, the same way.
+__device__ __forceinline__ void load_words_to_lds_untracked(const char *base, unsigned off, float *dst) {
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, 0x7fffffff, 0x00027000);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(
+                   (unsigned)(size_t)(__attribute__((address_space(3))) void *)dst),
+               "v"(off), "s"(rs)
                : "memory", "m0");
 }
 #pragma clang diagnostic pop
@@ -535,7 +544,7 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
   constexpr int SPAN = (D == 128 && CHUNK == 4096 ? OWN_MOST : CHUNK) + 2 * HALO;
   // (two arrays, so that the compiler sees that reading one does not wait for loads into the other)
   __shared__ u32x4 kt0[NW][T::WORDS], kt1[NW][T::WORDS];
-  __shared__ __align__(16) float sh_lse[RPAD];
+  __shared__ __align__(16) float sh_lse[RPAD < 64 ? 64 : RPAD];
   __shared__ __align__(16) float sh_part[SPAN > 4 * NT ? SPAN : 4 * NT];
   constexpr int SL = 2 * NT / RPAD;                    // threads that share two rows in the statistics combination
   float *sh_cm = sh_part, *sh_cl = sh_part + 2 * NT;   // (the prologue's, before any score is there)
@@ -587,21 +596,20 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
     if (key0 >= need_lo && key0 + TILE - 1 <= need_hi) T::whole(kbase + (long long)key0 * tok_bytes, tok_bytes, ld_off, load);
     else issue_clamped(tile, load);
   };
-  // The first tile and, through LDS (the second tile's place), the window queries.  Unconditionally, and counted
-  // by the compiler, so that its wait for what was asked before them does not stop at them as well.
+  // The first tile and, through LDS (the second tile's place), the window queries.
   constexpr int QI = RPAD / T::RPI / NW;
   static_assert(QI * T::RPI * NW == RPAD && RB * T::WORDS <= NW * T::WORDS, "");
   u32x4 *qs = &kt1[0][0];
-  auto request = [&]() {
-    __builtin_amdgcn_sched_barrier(0);
-    issue_clamped(iters > 0 ? tile_of(0) : 0, [&](const char *base, unsigned off, unsigned at, int word) { load_to_lds(base, off, at, &kt0[wv][word]); });
+  auto first_tile = [&](auto &&load) {
+    issue_clamped(iters > 0 ? tile_of(0) : 0, [&](const char *base, unsigned off, unsigned at, int word) { load(base, off, at, &kt0[wv][word]); });
+  };
+  auto load_queries = [&](auto &&load) {
 #pragma unroll
     for (int i = 0; i < QI; ++i) {
       const unsigned row = (unsigned)(wv * QI + i) * T::RPI + lane / T::ROW16;   // (rows past R are row R-1, zeroed below)
-      load_to_lds(reinterpret_cast<const char *>(q) + head_row0 * (D * 2),
-                  min(row, (unsigned)R - 1u) * (D * 2) + ((lane % T::ROW16) ^ T::swz(row)) * 16u, 0u, qs + (wv * QI + i) * 64);
+      load(reinterpret_cast<const char *>(q) + head_row0 * (D * 2),
+           min(row, (unsigned)R - 1u) * (D * 2) + ((lane % T::ROW16) ^ T::swz(row)) * 16u, 0u, qs + (wv * QI + i) * 64);
     }
-    __builtin_amdgcn_sched_barrier(0);
   };
   unsigned rd[KS], rk[KS];                             // operand words of the queries, of a tile
 #pragma unroll
@@ -611,7 +619,6 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
   }
   bf16x8 qf[RB][KS];                                   // kept for the whole chunk
   auto queries = [&]() {
-    wait_vmem<0>();
     lds_barrier();
 #pragma unroll
     for (int mb = 0; mb < RB; ++mb) {
@@ -622,9 +629,17 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
   };
   // the rows' log-sum-exp in the base-2 domain; +inf on the padding rows makes their weights zero
   if (lse) {
-    request();
-    for (int i = tid; i < RPAD; i += NT) sh_lse[i] = (i < R) ? lse[head_row0 + i] * lse_mul : INFINITY;
+    // The queries first and the first tile behind them, so that the second one, which takes their place, is asked for
+    // while the first is on its way.  (All of it behind the compiler's back: it would wait for the first tile with
+    // whatever it waits for first.)  us a call, first tile and queries / queries and first tile, 128 rows, 8 heads:
+    // 20000 keys 14.6 / 13.3, 50021 27.0 / 26.2, 131072 58.3 / 57.1; 32 rows, 50021 keys 23.0 / 22.2.
+    load_queries(load_to_lds_untracked);
+    if (wv < (RPAD + 63) / 64)
+      load_words_to_lds_untracked(reinterpret_cast<const char *>(lse + head_row0), (unsigned)min(tid, R - 1) * 4u, sh_lse + wv * 64);
+    first_tile(load_to_lds_untracked);
+    wait_vmem<LD>();
     queries();
+    if (tid < RPAD) sh_lse[tid] = tid < R ? sh_lse[tid] * lse_mul : INFINITY;
   } else {
     // Sweep 1's partials (max, sum) of this head's rows: SL threads take two rows, every SL-th partial each, CB of
     // them at a time; they come from the cache and are asked for before anything else.  (The few partials that
@@ -659,7 +674,11 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
       M1 = n1;
     };
     load_parts(sl);
-    request();
+    // (unconditionally, and counted by the compiler, so that its wait for the partials does not stop at these as well)
+    __builtin_amdgcn_sched_barrier(0);
+    first_tile(load_to_lds);
+    load_queries(load_to_lds);
+    __builtin_amdgcn_sched_barrier(0);
     fold(sl);
     for (int p0 = sl + CB * SL; p0 < np; p0 += CB * SL) {
       load_parts(p0);
@@ -668,6 +687,7 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
     if (2 * q2 == R - 1 && R > 1) { M0 = M1; L0 = L1; }        // (an odd number of rows: the last came as the second of its pair)
     *reinterpret_cast<float2 *>(&sh_cm[sl * RPAD + 2 * q2]) = make_float2(M0, M1);
     *reinterpret_cast<float2 *>(&sh_cl[sl * RPAD + 2 * q2]) = make_float2(L0, L1);
+    wait_vmem<0>();
     queries();                                         // (its barrier also shows the above)
     if (tid < RPAD) {
       float Mt = -INFINITY;
