@@ -853,9 +853,24 @@ template <int D, int MB, int RS> struct Group {
   static constexpr int SETW = ST * T::WORDS;
   static constexpr int LDW = ST * T::LD / RS;          // load instructions per wavefront and set
   static_assert(LDW * RS == ST * T::LD, "a set must split evenly over the wavefronts");
+  // The queries come through LDS where a row block fits into a wavefront's share of a set and there are two of them:
+  // as operand words straight from memory every load touches 32 lines, which cost a workgroup of 256 rows some 2 us.
+  // us a call, straight / through LDS, 256 rows, d = 128, 8 heads: with the caller's log-sum-exp 20000 keys 22.2 / 20.9,
+  // 50021 41.4 / 39.6 (the form without sets: 21.7, 39.7); both sweeps 2011 keys 16.4 / 15.1, 20000 40.9 / 38.1,
+  // 50021 77.4 / 72.4 (42.1, 74.9 at the last two).
+  static constexpr bool Q_LDS = MB == 2 && T::WORDS <= SETW / RS;
 };
+// One row block of the queries of wavefront wv, straight into its share of a set's place (rows past R are row R-1).
+template <int D, class Load>
+__device__ __forceinline__ void load_query_block(const unsigned short *q, size_t head_row0, int R, int row0, int lane, Load &&load) {
+  typedef RowTile<D> T;
+#pragma unroll
+  for (int i = 0; i < T::LD; ++i)
+    load(reinterpret_cast<const char *>(q) + head_row0 * (D * 2),
+         (unsigned)min(row0 + i * T::RPI + lane / T::ROW16, R - 1) * (D * 2) + T::col(lane, i), 0u, i * 64);
+}
 
-// The queries of wavefront wv's row blocks as operands, straight from memory (behind the first sets, whose way
+// Elsewhere: the queries of wavefront wv's row blocks as operands, straight from memory (behind the first sets, whose way
 // from HBM is longer than the 32 lines that each of these loads touches take).  Rows past R are row R-1, until ...
 template <int D, int MB>
 __device__ __forceinline__ void group_queries(const unsigned short *q, size_t head_row0, int R, int wv, int l32, int half,
@@ -930,8 +945,27 @@ __device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp
   bf16x8 qf[MB][KS];
   // (the second set is asked for when the first one and the queries are there: loads return in order, and a short
   // sequence would wait for all of it before it starts; 256 rows, 2011 keys: 7.8 us, 7.1 so)
-  if (iters > 0) issue(0);
-  {
+  if constexpr (G::Q_LDS) {
+    u32x4 *qs = &kt[1][wv * (G::SETW / RS)], qw[MB][KS];
+    auto query_block = [&](int mb) {
+      load_query_block<D>(q, head_row0, R, (wv * MB + mb) * 32, lane, [&](const char *base, unsigned off, unsigned at, int word) { load_to_lds_untracked(base, off, at, qs + word); });
+    };
+    auto read_query_block = [&](int mb) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) qw[mb][s] = qs[rd[s]];
+    };
+    query_block(0);
+    if (iters > 0) issue(0);
+    if (iters > 0 && stt == ST) wait_vmem<G::LDW>(); else wait_vmem<0>();
+    read_query_block(0);
+    wait_lds();
+    query_block(1);
+    wait_vmem<0>();
+    read_query_block(1);
+    zero_padding<MB, KS>(qw, R, wv, l32, qf);
+    lds_barrier();                                     // (the second set takes the queries' place)
+  } else {
+    if (iters > 0) issue(0);
     u32x4 qw[MB][KS];
     group_queries<D, MB>(q, head_row0, R, wv, l32, half, qw);
     zero_padding<MB, KS>(qw, R, wv, l32, qf);
@@ -1093,15 +1127,16 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
   constexpr int KS = T::KS, ST = G::ST, NT = G::NT, RPAD = G::RPAD;
   constexpr int HALO = TILE, SPAN = CHUNK + 2 * HALO;
   constexpr int SKEYS = ST * TILE;                     // keys of a set
-  __shared__ u32x4 kt[2][G::SETW];
+  // (two arrays, so that the compiler sees that reading one does not wait for loads into the other)
+  __shared__ u32x4 kt0[G::SETW], kt1[G::SETW];
   __shared__ float sh_sum[3][RS][SKEYS];               // the row groups' sums over a set's keys, three sets in turn
   __shared__ __align__(16) float sh_lse[RPAD];
   __shared__ __align__(16) float sh_part[SPAN];
   constexpr int SL = 2 * NT / RPAD > 0 ? 2 * NT / RPAD : 1;      // threads that share two rows in the statistics combination
   static_assert(SL * RPAD == 2 * NT && 2 * SL * RPAD <= SPAN, "threads and rows must tile each other");
   float *sh_cm = sh_part, *sh_cl = sh_part + SL * RPAD;          // (the prologue's, before any score is there)
-  static_assert(sizeof(kt) >= RADIX_BINS * sizeof(unsigned), "the digit histogram takes the tiles' place");
-  unsigned *sh_hist = reinterpret_cast<unsigned *>(&kt[0][0]);
+  static_assert(sizeof(kt0) >= RADIX_BINS * sizeof(unsigned), "the digit histogram takes the tiles' place");
+  unsigned *sh_hist = reinterpret_cast<unsigned *>(kt0);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1142,24 +1177,49 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
     }
   };
   auto issue = [&](int it) {
-    ask(it, [&](const char *sb, unsigned off, int word) { load_to_lds_untracked(sb, off, 0u, &kt[it & 1][word]); });
+    ask(it, [&](const char *sb, unsigned off, int word) { load_to_lds_untracked(sb, off, 0u, (it & 1 ? kt1 : kt0) + word); });
   };
   unsigned rd[KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s) rd[s] = T::operand(PR ? pooled_row(l32) : l32, half, s);
   u32x4 qw[MB][KS];
+  u32x4 *qs = kt1 + wv * (G::SETW / RS);               // the queries' way: this wavefront's share of the second set's place
+  auto query_block = [&](int mb) {
+    load_query_block<D>(q, head_row0, R, (wv * MB + mb) * 32, lane, [&](const char *base, unsigned off, unsigned at, int word) { load_to_lds(base, off, at, qs + word); });
+  };
+  auto read_query_block = [&](int mb) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) qw[mb][s] = qs[T::operand(l32, half, s)];
+  };
   // The first set and the queries, counted by the compiler, so that its wait for what was asked for before does not
   // stop at them as well (loads return in order).
   auto request = [&]() {
     __builtin_amdgcn_sched_barrier(0);
-    ask(0, [&](const char *sb, unsigned off, int word) { load_to_lds(sb, off, 0u, &kt[0][word]); });
+    if constexpr (G::Q_LDS) query_block(0);
+    ask(0, [&](const char *sb, unsigned off, int word) { load_to_lds(sb, off, 0u, kt0 + word); });
     __builtin_amdgcn_sched_barrier(0);
-    group_queries<D, MB>(q, head_row0, R, wv, l32, half, qw);
+    if constexpr (!G::Q_LDS) group_queries<D, MB>(q, head_row0, R, wv, l32, half, qw);
     __builtin_amdgcn_sched_barrier(0);
   };
+  // (the first row block is there long before the first set, and the second one's way is hidden by it)
+  auto queries = [&]() {
+    if constexpr (G::Q_LDS) {
+      wait_vmem<G::LDW>();
+      read_query_block(0);
+      wait_lds();
+      query_block(1);
+      wait_vmem<0>();
+      read_query_block(1);
+    }
+  };
+  float own_lse[(RPAD + NT - 1) / NT];
   if (lse) {
+#pragma unroll
+    for (int i = 0; i < (RPAD + NT - 1) / NT; ++i) own_lse[i] = lse[head_row0 + min(tid + i * NT, R - 1)] * lse_mul;
     request();
-    for (int i = tid; i < RPAD; i += NT) sh_lse[i] = (i < R) ? lse[head_row0 + i] * lse_mul : INFINITY;
+#pragma unroll
+    for (int i = 0; i < (RPAD + NT - 1) / NT; ++i)
+      if (tid + i * NT < RPAD) sh_lse[tid + i * NT] = tid + i * NT < R ? own_lse[i] : INFINITY;
   } else {
     // sweep 1's partials of this head's rows, two rows and every SL-th partial a thread (as in weights_own)
     constexpr int CB = 16;
@@ -1201,6 +1261,7 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
     *reinterpret_cast<float2 *>(&sh_cm[sl * RPAD + 2 * q2]) = make_float2(M0, M1);
     *reinterpret_cast<float2 *>(&sh_cl[sl * RPAD + 2 * q2]) = make_float2(L0, L1);
   }
+  queries();
   lds_barrier();
   if (!lse) {
     for (int r = tid; r < RPAD; r += NT) {
@@ -1259,7 +1320,7 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
   lds_barrier();                                       // (the second set when the first one is there: as in stats_group)
   if (nsets > 1) issue(1);
 #pragma unroll
-  for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[0][rd[s]]);
+  for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt0[rd[s]]);
   auto file = [&](int it, int t) {                     // a finished tile's sums over this wavefront's rows
     float *dst = &sh_sum[it % 3][wv][t * TILE];
     if constexpr (PR) {
@@ -1277,7 +1338,7 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
     const int nt = tiles_of(set_of(it));
     for (int t = 0; t < nt; ++t) {
       const bool leave = t == nt - 1;                  // the next tile is the next set's first (behind the last: whatever lies there)
-      const u32x4 *src = leave ? &kt[(it + 1) & 1][0] : &kt[it & 1][(t + 1) * T::WORDS];
+      const u32x4 *src = leave ? (it & 1 ? kt0 : kt1) : (it & 1 ? kt1 : kt0) + (t + 1) * T::WORDS;
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
         const int pmb = mb == 0 ? MB - 1 : mb - 1, cur = mb & 1;

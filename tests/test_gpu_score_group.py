@@ -26,7 +26,7 @@ CASES = [
 ]
 
 
-def _reference(wl, q, K, pool_first):
+def _reference(wl, q, K, pool_first, lse=None):
     out, bound, scale = [], 0.0, 1.0 / np.sqrt(wl.d)
     pool = torch.nn.functional.max_pool1d
     for b, n in enumerate(wl.n):
@@ -34,7 +34,8 @@ def _reference(wl, q, K, pool_first):
         for c in range(wl.h_kv):
             rows, keys = qb[c * wl.g:(c + 1) * wl.g].reshape(-1, wl.d), Kb[:, c].t().contiguous()
             bound = max(bound, float((scale * rows.abs() @ keys.abs()).max()))
-            a = torch.softmax(scale * rows @ keys, dim=1)
+            logits = scale * rows @ keys
+            a = torch.softmax(logits, dim=1) if lse is None else torch.exp(logits - lse[b, c * wl.g:(c + 1) * wl.g].reshape(-1, 1).double())
             if pool_first:
                 out.append(pool(a[None], wl.pool_k, 1, wl.pool_k // 2)[0].mean(0))
             else:
@@ -45,21 +46,23 @@ def _reference(wl, q, K, pool_first):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("given_lse", [False, True], ids=["sweep", "row_lse"])
 @pytest.mark.parametrize("pool_first", [False, True], ids=["mean_first", "pool_first"])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "hq%d_h%d_d%d_w%d_n%s" % (c[:4] + ("-".join(map(str, c[4][:4])),)))
-def test_scores_at_the_edges(case, pool_first):
+def test_scores_at_the_edges(case, pool_first, given_lse):
     h_q, h, d, w, n, dt, pools = case
     for k in pools:
-        print("sets and overlapping tiles", case[:5], k, pool_first, flush=True)
+        print("sets and overlapping tiles", case[:5], k, pool_first, given_lse, flush=True)
         wl = synth.small_workload(h_q, h, d, w, k, n, [h * w] * len(n), dtype=dt, seed=43, temps=(0.25, 1.0))
         q, K, _ = synth.generate(wl, device=DEV)
         layer = adakv.Layer.from_workload(wl, flags=4 if pool_first else 0)
         assert adakv.describe(layer)["score"] == ("mfma-pool-first" if pool_first else "mfma")
         out = torch.full((layer.num_scores + 64,), -7.0, device=DEV)      # canaries behind the scores
         ws = torch.full((adakv.workspace_bytes(layer),), 0xFF, dtype=torch.uint8, device=DEV)
-        adakv.score(layer, q, K, out=out, ws=ws)
+        lse = synth.prefill_row_lse(wl, q, K) if given_lse else None
+        adakv.score(layer, q, K, row_lse=lse, out=out, ws=ws)
         got = out.cpu().numpy().astype(np.float64)
-        want, tol = _reference(wl, q, K, pool_first)
+        want, tol = _reference(wl, q, K, pool_first, lse)
         assert tol < 2e-3 and np.all(got[layer.num_scores:] == -7.0)
         err = np.abs(got[:layer.num_scores] - want) / want
         assert err.max() <= tol, (k, err.max(), tol)
