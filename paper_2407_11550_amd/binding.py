@@ -122,7 +122,9 @@ class Layer:
             for nb in self.n:
                 tok_off.append(tok_off[-1] + nb + w)
         self.tok_off = [int(v) for v in tok_off]
-        self._rows_out, self._segments = sum(self.B), self.batch * h_kv    # of the arrays handed to the library
+        # of the arrays handed to the library
+        self._rows_out, self._segments, self._scores = sum(self.B), self.batch * h_kv, h_kv * sum(self.n)
+        self._last_row = None
         self._n = (ctypes.c_int32 * self.batch)(*self.n)
         self._B = (ctypes.c_int32 * len(self.B))(*self.B)
         self._off = (ctypes.c_int64 * len(self.tok_off))(*self.tok_off)
@@ -142,11 +144,13 @@ class Layer:
     @property
     def last_token_row(self):
         """One past the last K/V row any sequence of the layer owns."""
-        return max(self.tok_off[b] + self.n[b] + self.w for b in range(self.batch))
+        if self._last_row is None:
+            self._last_row = max(self.tok_off[b] + self.n[b] + self.w for b in range(self.batch))
+        return self._last_row
 
     @property
     def num_scores(self):
-        return self.h_kv * sum(self.n)
+        return self._scores
 
     @property
     def num_rows_out(self):

@@ -35,6 +35,13 @@ inline ChunkTab make_chunks(const SeqTab &st, int chunk) {
   return ct;
 }
 
+// How many chunks that makes.
+inline int count_chunks(const SeqTab &st, int chunk) {
+  int k = 0;
+  for (int b = 0; b < st.batch; ++b) k += (st.n[b] + chunk - 1) / chunk;
+  return k;
+}
+
 __device__ __forceinline__ int find_seq(const ChunkTab &ct, int batch, int blk) {
   int b = 0;
   while (b + 1 < batch && blk >= ct.off[b + 1]) ++b;
@@ -74,6 +81,7 @@ struct ScorePlan {                  // byte offsets into the workspace
   size_t raw;                       // [num_scores] pre-pool scores
   size_t total;
   int part_chunk;                   // keys per partial-statistics chunk
+  MfmaVariant mfma;                 // on the matrix cores: the instantiation that the above belongs to
 };
 ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma);
 size_t score_workspace(const SeqTab &st, const Dims &dm, int part_chunk);   // with partial statistics per part_chunk keys

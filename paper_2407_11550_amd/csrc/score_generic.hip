@@ -466,7 +466,7 @@ static ScorePlan plan_score_chunk(const SeqTab &st, const Dims &dm, int part_chu
   ScorePlan p;
   // partial statistics: one (max, sum) pair per window row and chunk of keys
   p.part_chunk = part_chunk;
-  const size_t chunks = make_chunks(st, p.part_chunk).off[st.batch];
+  const size_t chunks = count_chunks(st, p.part_chunk);
   const size_t RQ = (size_t)dm.h_q * dm.w;
   size_t o = 0;
   p.part = o; o += align_up(chunks * RQ * 8, 256);
@@ -490,8 +490,8 @@ static bool f32_wide_stats(const SeqTab &st, const Dims &dm) {
   int longest = 0;
   for (int b = 0; b < st.batch; ++b) longest = st.n[b] > longest ? st.n[b] : longest;
   if (longest <= F32_FUSE_CHUNKS * F32_KEYS || longest > F32_FUSE_CHUNKS * 2 * F32_KEYS) return false;
-  const int narrow = (make_chunks(st, F32_KEYS).off[st.batch] * dm.h_kv + 255) / 256;
-  const int wide = (make_chunks(st, 2 * F32_KEYS).off[st.batch] * dm.h_kv + 255) / 256;
+  const int narrow = (count_chunks(st, F32_KEYS) * dm.h_kv + 255) / 256;
+  const int wide = (count_chunks(st, 2 * F32_KEYS) * dm.h_kv + 255) / 256;
   const int row_blocks = (dm.g * dm.w + 31) / 32;
   return (2 * wide - narrow) * row_blocks * 1.8f * dm.d / 128 <= 1.5f;
 }
@@ -501,9 +501,10 @@ ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma) 
   if (on_mfma) {
     const MfmaVariant v = choose_mfma_variant(st, dm);
     ScorePlan p = plan_score_chunk(st, dm, v.part_len);
+    p.mfma = v;
     // (the Top-k's shortest form finds room here where partials of the weights sweep's chunks would have made it)
     const size_t lists = topk_spare_bytes(st, dm);
-    if (lists <= score_workspace(st, dm, v.len) && lists > p.total) p.total = lists;
+    if (lists > p.total && lists <= score_workspace(st, dm, v.len)) p.total = lists;
     return p;
   }
   // The fp32 kernels' partials are per 128 keys (workgroups of four wavefronts spread best), or per
@@ -537,8 +538,8 @@ void launch_pool(const SeqTab &st, const Dims &dm, const float *raw, float *scor
 bool f32_pool_fused(const SeqTab &st, const Dims &dm) {
   const int r = dm.pool_k / 2;
   if (r == 0 || r > F32_POOL_MAX) return r == 0;
-  const int most = (make_chunks(st, F32_KEYS - 2 * r).off[st.batch] * dm.h_kv + 255) / 256;
-  const int most_apart = (make_chunks(st, F32_KEYS).off[st.batch] * dm.h_kv + 255) / 256;
+  const int most = (count_chunks(st, F32_KEYS - 2 * r) * dm.h_kv + 255) / 256;
+  const int most_apart = (count_chunks(st, F32_KEYS) * dm.h_kv + 255) / 256;
   const int row_blocks = (dm.g * dm.w + 31) / 32;
   return (most - most_apart) * row_blocks * 1.8f * dm.d / 128 <= 4.0f;
 }

@@ -1505,9 +1505,7 @@ bool mfma_path_supported(const Dims &dm, int dtype) {
 
 // Workgroups that chunks of `len` keys make.
 static long long workgroups(const SeqTab &st, const Dims &dm, int len) {
-  long long chunks = 0;
-  for (int b = 0; b < st.batch; ++b) chunks += (st.n[b] + len - 1) / len;
-  return chunks * dm.h_kv;
+  return (long long)count_chunks(st, len) * dm.h_kv;
 }
 
 // The one place that decides which instantiation scores a layer: rows per wavefront and the
@@ -1576,6 +1574,7 @@ MfmaVariant choose_mfma_variant(const SeqTab &st, const Dims &dm) {
     if (!(R <= 128 || (R <= 256 && len <= 1024))) return len;
     const long long room = dm.d == 128 || R > 128 ? 256 : 512, heads = (long long)st.batch * dm.h_kv;
     const long long wgs = (heads + room - 1) / room * room;
+    if (workgroups(st, dm, least) <= wgs) return least;
     int lo = least / TILE, hi = longest / TILE + 1 > lo ? longest / TILE + 1 : lo;
     while (lo < hi) {
       const int mid = (lo + hi) / 2;
@@ -1616,7 +1615,7 @@ hipError_t launch_score_mfma(const SeqTab &st, const Dims &dm, int dtype, const 
                              const void *K, const float *row_lse, float *scores, char *ws,
                              const ScorePlan &pl, const TopkCarry &tc, bool pool_rows,
                              hipStream_t s) {
-  const MfmaVariant v = choose_mfma_variant(st, dm);
+  const MfmaVariant &v = pl.mfma;
   if (dtype == ADAKV_FP16)
     return dm.d == 64 ? run_mfma_d64_fp16(v, st, dm, q, K, row_lse, scores, ws, pl, tc, pool_rows, s)
                       : run_mfma_d128_fp16(v, st, dm, q, K, row_lse, scores, ws, pl, tc, pool_rows, s);

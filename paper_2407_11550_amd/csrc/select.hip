@@ -68,7 +68,7 @@ TopkWs plan(const SeqTab &st, const Dims &dm) {
   p.hist1_tot = o; o += (size_t)st.batch * RADIX_BINS * 4;
   p.hist1 = o; o += nseg * RADIX_BINS * 4;
   p.zero_end = o;
-  const size_t blocks = (size_t)make_chunks(st, SEL_CHUNK).off[st.batch] * dm.h_kv;
+  const size_t blocks = (size_t)count_chunks(st, SEL_CHUNK) * dm.h_kv;
   p.starts = o; o += align_up(blocks * RADIX_BINS * 2, 256);
   p.note = o; o += align_up(blocks * sizeof(BlockNote), 256);
   p.entries = o; o += align_up(blocks * ENT_PER_BLOCK * 2, 256);
@@ -1173,9 +1173,9 @@ constexpr long long TOPK_ROW_MAX = 4 * BLK_NT;         // of a head; gather and 
 // chip idle either way and the kernels stay apart, each scope with a time of its own in a trace.
 constexpr int FUSED_BLOCKS = 256, FUSED_SEGMENTS = 4;
 size_t topk_spare_bytes(const SeqTab &st, const Dims &dm) {
-  const size_t blocks = (size_t)make_chunks(st, SEL_CHUNK).off[st.batch] * dm.h_kv;
-  const bool fused = longest_row(st) > SELECT_CARRIED_MAX && st.batch * dm.h_kv >= FUSED_SEGMENTS && blocks <= FUSED_BLOCKS;
-  return fused ? list_bytes(blocks) : 0;
+  if (longest_row(st) <= SELECT_CARRIED_MAX || st.batch * dm.h_kv < FUSED_SEGMENTS) return 0;
+  const size_t blocks = (size_t)count_chunks(st, SEL_CHUNK) * dm.h_kv;
+  return blocks <= FUSED_BLOCKS ? list_bytes(blocks) : 0;
 }
 hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
                            int *cu_seqlens, char *ws, bool carried, hipStream_t s) {
