@@ -276,8 +276,8 @@ def score(layer: Layer, q_window, K, row_lse=None, out=None, ws=None, stream=Non
     _check_kv(layer, K, "K", layer.k_strides, layer.strides_given[0])
     _need(row_lse, layer.batch * layer.h_q * layer.w, "row_lse")
     if out is None:
-        out = torch.empty(layer.num_scores, dtype=torch.float32, device=K.device)
-    _need(out, layer.num_scores, "scores")
+        out = torch.empty(layer._scores, dtype=torch.float32, device=K.device)
+    _need(out, layer._scores, "scores")
     ws, wp, wn = _workspace(layer, ws)
     st = lib.adakv_score(ctypes.byref(layer.c), _ptr(q_window, "q_window", layer.torch_dtype),
                          _ptr(K, "K", layer.torch_dtype), _ptr(row_lse, "row_lse", torch.float32),
@@ -291,12 +291,12 @@ def allocate(layer: Layer, scores, budgets=None, cu_seqlens=None, ws=None, strea
     """adakv_allocate: budgets [batch*h_kv] and cu_seqlens [batch*h_kv+1], int32."""
     lib = load_library()
     if budgets is None:
-        budgets = torch.empty(layer.num_segments, dtype=torch.int32, device=scores.device)
+        budgets = torch.empty(layer._segments, dtype=torch.int32, device=scores.device)
     if cu_seqlens is None:
-        cu_seqlens = torch.empty(layer.num_segments + 1, dtype=torch.int32, device=scores.device)
-    _need(scores, layer.num_scores, "scores")
-    _need(budgets, layer.num_segments, "budgets")
-    _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
+        cu_seqlens = torch.empty(layer._segments + 1, dtype=torch.int32, device=scores.device)
+    _need(scores, layer._scores, "scores")
+    _need(budgets, layer._segments, "budgets")
+    _need(cu_seqlens, layer._segments + 1, "cu_seqlens")
     ws, wp, wn = _workspace(layer, ws)
     st = lib.adakv_allocate(ctypes.byref(layer.c), _ptr(scores, "scores", torch.float32),
                             _ptr(budgets, "budgets", torch.int32),
@@ -310,11 +310,11 @@ def select(layer: Layer, scores, budgets, cu_seqlens, indices=None, ws=None, str
     """adakv_select: retained positions [sum_b B_b] int32, flattened by (sequence, head)."""
     lib = load_library()
     if indices is None:
-        indices = torch.empty(layer.num_rows_out, dtype=torch.int32, device=scores.device)
-    _need(scores, layer.num_scores, "scores")
-    _need(budgets, layer.num_segments, "budgets")
-    _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
-    _need(indices, layer.num_rows_out, "indices")
+        indices = torch.empty(layer._rows_out, dtype=torch.int32, device=scores.device)
+    _need(scores, layer._scores, "scores")
+    _need(budgets, layer._segments, "budgets")
+    _need(cu_seqlens, layer._segments + 1, "cu_seqlens")
+    _need(indices, layer._rows_out, "indices")
     ws, wp, wn = _workspace(layer, ws)
     st = lib.adakv_select(ctypes.byref(layer.c), _ptr(scores, "scores", torch.float32),
                           _ptr(budgets, "budgets", torch.int32),
@@ -329,15 +329,15 @@ def compact(layer: Layer, K, V, indices, cu_seqlens, K_out=None, V_out=None, str
     """adakv_compact: K_out, V_out [sum_b B_b, d] in the layer's dtype."""
     lib = load_library()
     if K_out is None:
-        K_out = torch.empty((layer.num_rows_out, layer.d), dtype=layer.torch_dtype, device=K.device)
+        K_out = torch.empty((layer._rows_out, layer.d), dtype=layer.torch_dtype, device=K.device)
     if V_out is None:
-        V_out = torch.empty((layer.num_rows_out, layer.d), dtype=layer.torch_dtype, device=K.device)
+        V_out = torch.empty((layer._rows_out, layer.d), dtype=layer.torch_dtype, device=K.device)
     _check_kv(layer, K, "K", layer.k_strides, layer.strides_given[0])
     _check_kv(layer, V, "V", layer.v_strides, layer.strides_given[1])
-    _need(indices, layer.num_rows_out, "indices")
-    _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
-    _need(K_out, layer.num_rows_out * layer.d, "K_out")
-    _need(V_out, layer.num_rows_out * layer.d, "V_out")
+    _need(indices, layer._rows_out, "indices")
+    _need(cu_seqlens, layer._segments + 1, "cu_seqlens")
+    _need(K_out, layer._rows_out * layer.d, "K_out")
+    _need(V_out, layer._rows_out * layer.d, "V_out")
     st = lib.adakv_compact(ctypes.byref(layer.c), _ptr(K, "K", layer.torch_dtype),
                            _ptr(V, "V", layer.torch_dtype), _ptr(indices, "indices", torch.int32),
                            _ptr(cu_seqlens, "cu_seqlens", torch.int32),
@@ -373,15 +373,15 @@ def compress(layer: Layer, q_window, K, V, row_lse=None, ws=None, stream=None, b
         t = b.get(name)
         return t if t is not None else torch.empty(shape, dtype=dtype, device=dev)
 
-    sc = buf("scores", layer.num_scores, torch.float32)
-    bud = buf("budgets", layer.num_segments, torch.int32)
-    cu = buf("cu_seqlens", layer.num_segments + 1, torch.int32)
-    idx = buf("indices", layer.num_rows_out, torch.int32)
-    K_out = buf("K_out", (layer.num_rows_out, layer.d), layer.torch_dtype)
-    V_out = buf("V_out", (layer.num_rows_out, layer.d), layer.torch_dtype)
-    for t, numel, name in ((sc, layer.num_scores, "scores"), (bud, layer.num_segments, "budgets"),
-                           (cu, layer.num_segments + 1, "cu_seqlens"), (idx, layer.num_rows_out, "indices"),
-                           (K_out, layer.num_rows_out * layer.d, "K_out"), (V_out, layer.num_rows_out * layer.d, "V_out")):
+    sc = buf("scores", layer._scores, torch.float32)
+    bud = buf("budgets", layer._segments, torch.int32)
+    cu = buf("cu_seqlens", layer._segments + 1, torch.int32)
+    idx = buf("indices", layer._rows_out, torch.int32)
+    K_out = buf("K_out", (layer._rows_out, layer.d), layer.torch_dtype)
+    V_out = buf("V_out", (layer._rows_out, layer.d), layer.torch_dtype)
+    for t, numel, name in ((sc, layer._scores, "scores"), (bud, layer._segments, "budgets"),
+                           (cu, layer._segments + 1, "cu_seqlens"), (idx, layer._rows_out, "indices"),
+                           (K_out, layer._rows_out * layer.d, "K_out"), (V_out, layer._rows_out * layer.d, "V_out")):
         _need(t, numel, name)
     _check_ws(ws)
     st = lib.adakv_compress(ctypes.byref(layer.c), _ptr(q_window, "q_window", layer.torch_dtype),
@@ -408,12 +408,12 @@ def compress_static(layer: Layer, q_window, K, V, row_lse=None, stream=None, buf
     _check_kv(layer, K, "K", layer.k_strides, layer.strides_given[0])
     _check_kv(layer, V, "V", layer.v_strides, layer.strides_given[1])
     _need(row_lse, layer.batch * layer.h_q * layer.w, "row_lse")
-    want = (("scores", layer.num_scores, (layer.num_scores,), torch.float32),
-            ("budgets", layer.num_segments, (layer.num_segments,), torch.int32),
-            ("cu_seqlens", layer.num_segments + 1, (layer.num_segments + 1,), torch.int32),
-            ("indices", layer.num_rows_out, (layer.num_rows_out,), torch.int32),
-            ("K_out", layer.num_rows_out * layer.d, (layer.num_rows_out, layer.d), layer.torch_dtype),
-            ("V_out", layer.num_rows_out * layer.d, (layer.num_rows_out, layer.d), layer.torch_dtype))
+    want = (("scores", layer._scores, (layer._scores,), torch.float32),
+            ("budgets", layer._segments, (layer._segments,), torch.int32),
+            ("cu_seqlens", layer._segments + 1, (layer._segments + 1,), torch.int32),
+            ("indices", layer._rows_out, (layer._rows_out,), torch.int32),
+            ("K_out", layer._rows_out * layer.d, (layer._rows_out, layer.d), layer.torch_dtype),
+            ("V_out", layer._rows_out * layer.d, (layer._rows_out, layer.d), layer.torch_dtype))
     out = {}
     for name, numel, shape, dtype in want:
         t = b.get(name)
@@ -483,8 +483,8 @@ def _check_cache(layer, headroom, K_cache, V_cache):
 
 def _check_decode_bufs(layer, headroom, K_cache, V_cache, cu_seqlens, seg_len, out, lse, ws):
     _check_cache(layer, headroom, K_cache, V_cache)
-    _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
-    _need(seg_len, layer.num_segments, "seg_len")
+    _need(cu_seqlens, layer._segments + 1, "cu_seqlens")
+    _need(seg_len, layer._segments, "seg_len")
     _need(out, layer.batch * layer.h_q * layer.d, "out")
     _need(lse, layer.batch * layer.h_q, "lse")
     _check_ws(ws)
@@ -505,15 +505,15 @@ def cache_build(layer: Layer, K, V, indices, cu_seqlens, headroom, K_cache=None,
     if V_cache is None:
         V_cache = torch.empty((rows, layer.d), dtype=layer.torch_dtype, device=K.device)
     if seg_len is None:
-        seg_len = torch.empty(layer.num_segments, dtype=torch.int32, device=K.device)
-    if K_cache.shape[0] < rows or V_cache.shape[0] < rows or seg_len.numel() < layer.num_segments:
+        seg_len = torch.empty(layer._segments, dtype=torch.int32, device=K.device)
+    if K_cache.shape[0] < rows or V_cache.shape[0] < rows or seg_len.numel() < layer._segments:
         raise ValueError("cache or seg_len too small for this layer and head-room")
     _check_kv(layer, K, "K", layer.k_strides, layer.strides_given[0])
     _check_kv(layer, V, "V", layer.v_strides, layer.strides_given[1])
-    _need(indices, layer.num_rows_out, "indices")
-    _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
+    _need(indices, layer._rows_out, "indices")
+    _need(cu_seqlens, layer._segments + 1, "cu_seqlens")
     _check_cache(layer, headroom, K_cache, V_cache)
-    _need(seg_len, layer.num_segments, "seg_len")
+    _need(seg_len, layer._segments, "seg_len")
     st = lib.adakv_cache_build(ctypes.byref(layer.c), _ptr(K, "K", layer.torch_dtype),
                                _ptr(V, "V", layer.torch_dtype), _ptr(indices, "indices", torch.int32),
                                _ptr(cu_seqlens, "cu_seqlens", torch.int32), int(headroom),
@@ -538,8 +538,8 @@ def append(layer: Layer, k_new, v_new, cu_seqlens, headroom, K_cache, V_cache, s
     if K_cache.size(0) < rows or V_cache.size(0) < rows:
         raise ValueError("cache too small for this layer and head-room")
     _check_cache(layer, headroom, K_cache, V_cache)
-    _need(cu_seqlens, layer.num_segments + 1, "cu_seqlens")
-    _need(seg_len, layer.num_segments, "seg_len")
+    _need(cu_seqlens, layer._segments + 1, "cu_seqlens")
+    _need(seg_len, layer._segments, "seg_len")
     _need(overflow, 1, "overflow")
     st = lib.adakv_append(ctypes.byref(layer.c), _ptr(k_new, "k_new", layer.torch_dtype),
                           _ptr(v_new, "v_new", layer.torch_dtype),
