@@ -241,16 +241,18 @@ template <int D> struct RowTile {
 __device__ __forceinline__ unsigned pooled_row(unsigned i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
 
 // keysum += e, pooled over `radius` keys to either side, one at a time: three-operand maxima in place; what lies next
-// to the half's first and last key comes from the other half, at a tile's ends it is the key itself.
+// to the half's first and last key comes from the other half, at a tile's ends it is the key itself.  Weights are not
+// negative, so their bit patterns order like they do, and in an unsigned maximum a NaN, whatever its sign, wins (a
+// floating-point maximum would drop it): it poisons every mean whose window holds it, which pool_and_file stores as -inf.
 __device__ __forceinline__ void pool_rows(floatx16 &e, int radius, float (&keysum)[16]) {
   for (int t = 0; t < radius; ++t) {
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(e[0]), __float_as_uint(e[15]), false, false);
-    float left = __uint_as_float(sw[0]);               // lower half: its own e[0]; upper half: the lower one's e[15]
-    const float right = __uint_as_float(sw[1]);        // lower half: the upper one's e[0]; upper half: its own e[15]
+    unsigned left = sw[0];                             // lower half: its own e[0]; upper half: the lower one's e[15]
+    const unsigned right = sw[1];                      // lower half: the upper one's e[0]; upper half: its own e[15]
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float own = e[i];
-      e[i] = fmaxf(fmaxf(left, own), i < 15 ? e[i < 15 ? i + 1 : 15] : right);
+      const unsigned own = __float_as_uint(e[i]);
+      e[i] = __uint_as_float(max(max(left, own), i < 15 ? __float_as_uint(e[i < 15 ? i + 1 : 15]) : right));
       left = own;
     }
   }

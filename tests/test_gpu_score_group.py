@@ -66,3 +66,29 @@ def test_scores_at_the_edges(case, pool_first, given_lse):
         assert tol < 2e-3 and np.all(got[layer.num_scores:] == -7.0)
         err = np.abs(got[:layer.num_scores] - want) / want
         assert err.max() <= tol, (k, err.max(), tol)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("h_q,d,w,dt", [(2, 64, 20, torch.float16), (8, 128, 32, torch.bfloat16), (16, 128, 31, torch.bfloat16),
+                                        (16, 64, 64, torch.bfloat16)], ids=["20rows", "128rows", "248rows", "512rows"])
+def test_a_nan_key_spoils_every_window_that_holds_it(h_q, d, w, dt):
+    """The row-pooling order with a log-sum-exp from elsewhere: a key that is a NaN, of either sign, makes the scores
+    within the pool radius of it in its head -inf, so that none of them is kept, and no other."""
+    h, n, k = 2, 700, 7
+    print("a NaN in the row-pooling order", h_q, d, w, flush=True)
+    wl = synth.small_workload(h_q, h, d, w, k, [n], [h * w], dtype=dt, seed=47)
+    q, K, _ = synth.generate(wl, device=DEV)
+    lse = synth.prefill_row_lse(wl, q, K)
+    layer = adakv.Layer.from_workload(wl, flags=4)
+    assert adakv.describe(layer)["score"] == "mfma-pool-first"
+    clean = adakv.score(layer, q, K, row_lse=lse).reshape(h, n)
+    assert bool(torch.isfinite(clean).all())
+    for at, sign in ((0, 1), (15, -1), (16, 1), (28, 1), (31, -1), (32, 1), (333, -1), (n - 1, 1)):
+        bad = K.clone()
+        bits = 0x7E00 if dt == torch.float16 else 0x7FC0
+        bad.view(torch.int16)[at, 1, d // 3] = bits if sign > 0 else bits - 0x8000
+        got = adakv.score(layer, q, bad, row_lse=lse).reshape(h, n)
+        want = torch.zeros((h, n), dtype=torch.bool, device=DEV)
+        want[1, max(at - k // 2, 0):at + k // 2 + 1] = True
+        assert torch.equal(got == -torch.inf, want), (at, (got == -torch.inf).nonzero().tolist())
+        assert torch.equal(got[~want], clean[~want]), at
