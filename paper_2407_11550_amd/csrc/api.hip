@@ -407,9 +407,9 @@ int adakv_describe(const adakv_layer *L, int have_row_lse, char *out, size_t out
   if (on_mfma(dm, L)) {
     const MfmaVariant v = choose_mfma_variant(st, dm);
     len = snprintf(out, out_bytes,
-                   "score=%s dtype=%s d=%d rows=%d mb=%d rs=%d kg=%d chunk=%d keys=%d stats=%s lse=%s pool=%s topk=%s",
+                   "score=%s dtype=%s d=%d rows=%d mb=%d rs=%d kg=%d chunk=%d keys=%d stat_keys=%d stats=%s lse=%s pool=%s topk=%s",
                    pool_first(L) ? "mfma-pool-first" : "mfma", dt, dm.d, dm.g * dm.w, v.mb, v.rs, v.kg,
-                   v.chunk, v.len, stats, have_row_lse ? "caller" : v.fuse_lse ? "fused" : "kernel",
+                   v.chunk, v.len, v.part_len, stats, have_row_lse ? "caller" : v.fuse_lse ? "fused" : "kernel",
                    pool_first(L) ? "rows" : v.fuse_pool ? "fused" : "kernel", topk);
   } else {
     len = snprintf(out, out_bytes, "score=%s dtype=%s d=%d rows=%d stats=%s lse=%s pool=%s topk=%s",

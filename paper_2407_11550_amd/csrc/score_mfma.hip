@@ -184,12 +184,39 @@ __device__ __forceinline__ float sum_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// A sum taken against a reference that was not its maximum may be a large one; where it is later scaled to a
-// larger reference, the factor would fall out of the range of fp32 before the product does.
+// A row's running statistics: reference rm (base 2) and sum rl of exp2(x - rm).  A sum against a kept reference needs
+// no search for a maximum in every tile.  It is as accurate as one against the running maximum while the largest
+// terms lie near the reference: x - rm is rounded at its own size, which is 3e-7 of a term 16 above it, what the
+// log-sum-exp of such a row is rounded to as well, but 1.3e-6 at 60 and 2.6e-6 at 110.  So a lane's terms of a row
+// block (16 of them) whose sum goes beyond KEPT_MOST are taken again with the maximum of all so far as the new
+// reference, and with them everything that is not a number or not finite.
+constexpr float KEPT_MOST = 0x1p16f;
+__device__ __forceinline__ void fold_rows(const floatx16 &a, float c_log2, float &rm, float &rl) {
+  float tm = a[0];
+#pragma unroll
+  for (int r = 1; r < 16; ++r) tm = fmaxf(tm, a[r]);
+  const float m = fmaxf(rm, tm * c_log2), ref = (m == -INFINITY) ? 0.0f : m;
+  float sum = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    sum += fast_exp2(fmaf(a[r], c_log2, -ref));
+    asm volatile("" : "+v"(sum));                      // (one at a time: this is rare, and registers are few around it)
+  }
+  rl = rl * fast_exp2(rm - ref) + sum;
+  rm = m;
+}
+__device__ __forceinline__ void add_kept(const floatx16 &a, float c_log2, float sum, float &rm, float &rl) {
+  if (__builtin_expect(__any(!(sum <= KEPT_MOST)), 0)) fold_rows(a, c_log2, rm, rl);
+  else rl += sum;
+}
+// Many tiles make a large sum all the same; its logarithm is rounded at the size of its exponent, which therefore
+// moves into the reference (the factor is that of the two references as they are stored).
 __device__ __forceinline__ void settle(float &m, float &l) {
-  const int e = l > 0x1p16f ? __builtin_amdgcn_frexp_expf(l) : 0;
-  m += (float)e;
-  l = ldexpf(l, -e);
+  if (l > KEPT_MOST) {
+    const float to = m + (float)__builtin_amdgcn_frexp_expf(l);
+    l *= fast_exp2(m - to);
+    m = to;
+  }
 }
 
 // A wavefront's view of rows of D 16-bit elements in LDS: 32 rows at a time, 16-byte words swizzled so that
@@ -326,17 +353,11 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
     if (key0 + TILE <= n) T::whole(sb, tok_bytes, ld_off, load);
     else T::clamped(sb, tok_bytes, 0, n - 1 - key0, lane, load);
   };
-  auto start = [&]() {
-#pragma unroll
-    for (int j = 0; j < NBUF; ++j)
-      if (j < iters) issue(j, j);
-  };
   // tile `it` has arrived; those asked for behind it, at most NBUF - 1, may be on their way
   auto await = [&](int it) {
     const int behind = min(iters - 1 - it, NBUF - 1);
     if (behind == NBUF - 1) wait_vmem<(NBUF - 1) * LD>();
-    else if (NBUF > 2 && behind == NBUF - 2) wait_vmem<(NBUF > 2 ? NBUF - 2 : 0) * LD>();
-    else if (NBUF > 3 && behind == NBUF - 3) wait_vmem<(NBUF > 3 ? NBUF - 3 : 0) * LD>();
+    else if (behind == NBUF - 2) wait_vmem<(NBUF - 2) * LD>();
     else wait_vmem<0>();
   };
 
@@ -350,12 +371,13 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
                           min(row, (unsigned)R - 1u) * (D * 2) + ((lane % T::ROW16) ^ T::swz(row)) * 16u, 0u,
                           &qs[(wv * QI + i) * 64]);
   }
-  start();
+#pragma unroll
+  for (int j = 0; j < NBUF; ++j)
+    if (j < iters) issue(j, j);
   {
     const int asked = min(iters, NBUF);
     if (asked == NBUF) wait_vmem<NBUF * LD>();
-    else if (NBUF > 3 && asked == 3) wait_vmem<3 * LD>();
-    else if (NBUF > 2 && asked == 2) wait_vmem<2 * LD>();
+    else if (asked == 2) wait_vmem<2 * LD>();
     else if (asked == 1) wait_vmem<LD>();
     else wait_vmem<0>();
   }
@@ -374,11 +396,6 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
   bf16x8 kf[KS];
   floatx16 acc[2];                                     // products of the current row block and of the one before
   float rm[RB], rl[RB];                                // running maximum (or reference) and sum of the row this lane owns
-  auto read_first = [&]() {
-    await(0);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[wv][0][rd[s]]);
-  };
   // the vector work on one row block's products, in KS shares
   float ref = 0.0f, nmx = 0.0f, usum = 0.0f;
   auto share = [&](auto lazy_tag, floatx16 &a, int mb, int s) {
@@ -386,7 +403,7 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
       if (s == 0) usum = 0.0f;
 #pragma unroll
       for (int v = s * 16 / KS; v < (s + 1) * 16 / KS; ++v) usum += fast_exp2(fmaf(a[v], c_log2, -rm[mb]));
-      if (s == KS - 1) rl[mb] += usum;
+      if (s == KS - 1) add_kept(a, c_log2, usum, rm[mb], rl[mb]);
     } else {
       if (s == 0) {
         float tm = a[0];
@@ -443,18 +460,17 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
       for (int s = 0; s < KS; ++s) share(lazy_tag, last, RB - 1, s);
     }
   };
-  auto reset = [&]() {
 #pragma unroll
-    for (int mb = 0; mb < RB; ++mb) { rm[mb] = -INFINITY; rl[mb] = 0.0f; }
+  for (int mb = 0; mb < RB; ++mb) { rm[mb] = -INFINITY; rl[mb] = 0.0f; }
+  auto read_first = [&]() {                            // (in either branch below: both start from its registers)
+    await(0);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[wv][0][rd[s]]);
   };
-  reset();
-  if (iters > 0) read_first();
-  // A sum of exp2(x - ref) is as accurate for one reference as for another unless it overflows, and what
-  // underflows is negligible beside the term that set the reference.  So with several tiles to come the
-  // first one's maxima serve all of them, without a search in every tile (50 instead of 70 vector
-  // instructions per row block: 18.2 -> 16.9 us at 32768 keys, 61.5 -> 58.6 at 131072); if a sum is not finite in the end, all is done again the careful way.
-  bool careful = plain < 4;
-  if (!careful) {
+  // With several tiles to come the first one's maxima are kept as reference (50 instead of 70 vector instructions
+  // per row block: 18.2 -> 16.9 us at 32768 keys, 61.5 -> 58.6 at 131072).
+  if (plain >= 4) {
+    read_first();
 #pragma unroll
     for (int mb = 0; mb < RB; ++mb) {
       floatx16 a = {0};
@@ -468,22 +484,12 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
       __builtin_amdgcn_sched_barrier(0);
     }
     loop(std::true_type{});
-    bool bad = false;
 #pragma unroll
-    for (int mb = 0; mb < RB; ++mb) bad |= !(rl[mb] < INFINITY);
-    if (__any(bad)) {
-      careful = true;
-      wait_vmem<0>();
-      wait_lds();
-      reset();
-      start();
-      read_first();
-    } else {
-#pragma unroll
-      for (int mb = 0; mb < RB; ++mb) settle(rm[mb], rl[mb]);
-    }
+    for (int mb = 0; mb < RB; ++mb) settle(rm[mb], rl[mb]);
+  } else {
+    if (iters > 0) read_first();
+    loop(std::false_type{});
   }
-  if (careful) loop(std::false_type{});
   if (plain < iters) {
     const int base = (first + plain * stride) * TILE;
 #pragma unroll
@@ -986,7 +992,7 @@ __device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp
       if (s == 0) usum = 0.0f;
 #pragma unroll
       for (int v = s * 16 / KS; v < (s + 1) * 16 / KS; ++v) usum += fast_exp2(fmaf(a[v], c_log2, -rm[mb]));
-      if (s == KS - 1) rl[mb] += usum;
+      if (s == KS - 1) add_kept(a, c_log2, usum, rm[mb], rl[mb]);
     } else {
       if (s == 0) {
         float tm = a[0];
@@ -1004,17 +1010,6 @@ __device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp
         rm[mb] = nmx;
       }
     }
-  };
-  auto reset = [&]() {
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) { rm[mb] = -INFINITY; rl[mb] = 0.0f; }
-  };
-  // the first two sets have been asked for: the first one is there for everybody
-  auto read_first = [&]() {
-    if (iters > 1 && stt == ST) wait_vmem<G::LDW>(); else wait_vmem<0>();
-    lds_barrier();
-#pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[0][rd[s]]);
   };
   // the sequence's last tile, if it is not full, is the last of its workgroup and comes after the loop
   const bool tail = iters > 0 && first + (iters - 1) * stride == nsets - 1 && n % TILE != 0;
@@ -1055,11 +1050,16 @@ __device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp
     }
   };
   static_assert(MB % 2 == 0, "a row block's products alternate between two places");
-  reset();
-  if (iters > 0) read_first();
-  // (the kept reference as in stats_own; all wavefronts go the same way, because they meet at barriers)
-  bool careful = plain < 4;
-  if (!careful) {
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) { rm[mb] = -INFINITY; rl[mb] = 0.0f; }
+  lds_barrier();                                       // the first set is there for everybody
+  auto read_first = [&]() {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt[0][rd[s]]);
+  };
+  // (the kept reference as in stats_own)
+  if (plain >= 4) {
+    read_first();
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       floatx16 a = {0};
@@ -1073,22 +1073,12 @@ __device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp
       __builtin_amdgcn_sched_barrier(0);
     }
     loop(std::true_type{});
-    bool bad = false;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) bad |= !(rl[mb] < INFINITY);
-    wait_vmem<0>();
-    if (__syncthreads_or(bad)) {
-      careful = true;
-      reset();
-      issue(0);
-      if (iters > 1) issue(1);
-      read_first();
-    } else {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) settle(rm[mb], rl[mb]);
-    }
+    for (int mb = 0; mb < MB; ++mb) settle(rm[mb], rl[mb]);
+  } else {
+    if (iters > 0) read_first();
+    loop(std::false_type{});
   }
-  if (careful) loop(std::false_type{});
   if (tail) {
     const int base = (ntiles - 1) * TILE;
 #pragma unroll
