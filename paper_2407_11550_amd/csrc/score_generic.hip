@@ -486,6 +486,8 @@ size_t score_workspace(const SeqTab &st, const Dims &dm, int part_chunk) {
 // f32_pool_fused().  Whole call, us, 128 / 256 keys: 8191 keys x 8 heads, 128 rows 53.4 / 51.4, 5000 keys 49.8 / 46.2,
 // d = 64 37.4 / 34.9; 8000 x 8 heads, 8 rows 25.8 / 23.2; 8000 x 4 heads, 32 rows, d = 64 (half a compute unit's
 // share more) 17.0 / 14.1.  Refused: 5000 x 4 heads, 128 rows 31.8 / 36.4; five of up to 6000 keys 107.2 / 110.0.
+// The row-pooling order keeps the kernel, and half the partials help it all the same: 8191 x 8 heads, 128 rows 165.9 /
+// 165.0, 5000 x 8 heads, 16 rows 35.3 / 33.7, 8000 x 8 heads, 32 rows, d = 64 37.2 / 35.9.
 static bool f32_wide_stats(const SeqTab &st, const Dims &dm) {
   int longest = 0;
   for (int b = 0; b < st.batch; ++b) longest = st.n[b] > longest ? st.n[b] : longest;
