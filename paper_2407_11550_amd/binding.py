@@ -588,8 +588,12 @@ def decode_step(layer: Layer, q_new, k_new, v_new, cu_seqlens, headroom, K_cache
     """adakv_decode_step: append k_new/v_new to every segment and attend, in one call."""
     lib = load_library()
     if _marshal is not None and out is not None and ws is not None and (lse is not None or not want_lse):
+        try:
+            handle = _stream(stream)
+        except (RuntimeError, AttributeError):      # no GPU, or no stream: the tensors are looked at first
+            handle = None
         st = _marshal.decode_step(_decode_step_address, ctypes.addressof(layer.c), q_new, k_new, v_new, cu_seqlens,
-                                  headroom, K_cache, V_cache, seg_len, overflow, out, lse, ws, _stream(stream))
+                                  headroom, K_cache, V_cache, seg_len, overflow, out, lse, ws, handle)
         if st == 0:
             return out if lse is None else (out, lse)
         if st is not None:

@@ -154,3 +154,10 @@ def test_a_flat_cache_and_rows_further_on(lib):
             adakv.decode_step(FLAT, **dict(a, **{name: f(128)}))
     wide = torch.zeros(3, 4, 128, device="cuda:0")[:, :2]        # the first [2, 128] lie together
     assert adakv.decode_step(FLAT, **dict(a, out=wide)) is wide and len(calls) == 1
+
+
+def test_host_tensors_are_named_where_there_is_no_gpu(lib):
+    """... and not the missing GPU, which the stream is asked of."""
+    layer, a = arguments("cpu")
+    with pytest.raises(ValueError, match="q_new must be a device tensor"):
+        adakv.decode_step(layer, **a)
