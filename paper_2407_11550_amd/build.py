@@ -60,6 +60,8 @@ def build_marshal(verbose: bool = False) -> str:
     home = os.path.dirname(torch.__file__)
     out = os.path.join(HERE, "lib", "_marshal.so")
     os.makedirs(os.path.dirname(out), exist_ok=True)
+    if os.path.exists(out):                     # an older build would check layers of an older layout
+        os.remove(out)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-I", os.path.join(ROOT, "include"),
            "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(home, "include"),

@@ -161,3 +161,18 @@ def test_host_tensors_are_named_where_there_is_no_gpu(lib):
     layer, a = arguments("cpu")
     with pytest.raises(ValueError, match="q_new must be a device tensor"):
         adakv.decode_step(layer, **a)
+
+
+@pytest.mark.parametrize("why", [RuntimeError("g++ failed on marshal.cpp"), FileNotFoundError("g++")])
+def test_the_library_is_built_without_the_native_checks(why, monkeypatch, capsys, lib):
+    import __graft_entry__ as entry
+    from paper_2407_11550_amd import build
+
+    def fails():
+        raise why
+    monkeypatch.setattr(build, "build", lambda: adakv.library_path())
+    monkeypatch.setattr(build, "build_marshal", fails)
+    monkeypatch.setattr(build, "build_abi_driver", lambda: "driver")
+    entry.build()
+    said = capsys.readouterr().out
+    assert "built " + adakv.library_path() in said and f"not built: a decoding step's native checks, the ones in Python do the same ({why})" in said
