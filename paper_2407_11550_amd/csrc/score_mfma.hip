@@ -922,13 +922,14 @@ __device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp
   const int n = st.n[b];
   const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
   const size_t head_row0 = (size_t)b * RQ + (size_t)c * R;
-  // Sets of fewer tiles where whole ones would give some workgroups a sixteenth (two tiles instead of four) or a tenth
-  // (one) more than their part_len keys.  256 rows, 20000 keys x 8 heads, 63 workgroups of 320 keys a head: 157 sets of
-  // four are 12 tiles for some, 313 of two 10 for all.
-  const int ntiles = (n + TILE - 1) / TILE, share_of = part_len / TILE;
-  int stt = ST;
-  if ((-share_of & (ST - 1)) * 16 > share_of) stt = 2;
-  if (stt < ST && (share_of & 1) * 10 > share_of) stt = 1;
+  // Sets of two tiles where those of four would give some workgroups two or three tiles more than their part_len keys
+  // are, an eighth of these or more.  The sweep in us, sets of four / two / one, 8 heads, d = 128, by tiles a workgroup:
+  //   256 rows   3: 6.5 / 7.4 / 7.2     5: 8.9 / 8.5 / 8.7     6: 9.5 / 8.8 / 9.5     7: 9.5 / 10.0 / 10.4
+  //              9: 11.8 / 11.3 / 11.7  10: 11.9 / 11.3 / 12.2  11: 12.0 / 12.5 / 13.1  18: 16.6 / 16.6 / 18.6
+  //              21: 19.3 / 19.4 / 21.0  26: 21.1 / 21.4 / 23.9  30: 23.2 / 23.7 / 26.7
+  //   512 rows   5: 14.3 / 13.2 / 13.0  7: 15.0 / 15.0 / 14.8  10: 18.4 / 17.2 / 17.8  11: 18.7 / 18.9 / 18.6
+  const int ntiles = (n + TILE - 1) / TILE, share_of = part_len / TILE, over = -share_of & (ST - 1);
+  const int stt = over >= 2 && over * 8 >= share_of ? 2 : ST;
   const int nsets = (ntiles + stt - 1) / stt;
   const int iters = first < nsets ? (nsets - 1 - first) / stride + 1 : 0;
   const char *kbase = reinterpret_cast<const char *>(K) +
