@@ -1617,7 +1617,7 @@ hipError_t launch_score_mfma(const SeqTab &st, const Dims &dm, int dtype, const 
 }
 
 // The printed order of Alg. 2 l.4 (pool every row, then average) runs on the matrix cores as long
-// as a tile keeps at least 18 of its 32 lanes (pool radius up to 7); wider pools take the FMA path.
+// as a tile has at least 18 inner keys of its 32 (pool radius up to 7); wider pools take the FMA path.
 bool mfma_pool_rows_supported(const Dims &dm, int dtype) {
   return mfma_path_supported(dm, dtype) && dm.pool_k / 2 <= MFMA_POOL_ROWS_MAX_RADIUS;
 }

@@ -1169,8 +1169,10 @@ constexpr long long TOPK_ROW_MAX = 4 * BLK_NT;         // of a head; gather and 
 // Longer rows: finish and the head's gather in one launch where every block has a compute unit to itself (each
 // repeats the layer scope with a compute unit's whole issue rate, on plateaus too: scores all equal, 32768 x 8
 // 81.9 / 80.7 us a step with four kernels / three, 131072 x 8 181 / 177, 20000 x 32 122 / 119) and where the
-// head's lists fit into what the scoring sweeps have done with.  Below four segments a scope leaves most of the
-// chip idle either way and the kernels stay apart, each scope with a time of its own in a trace.
+// head's lists fit into what the scoring sweeps have done with.  Below four segments the line is not one of speed: a
+// trace of a layer that small is to show each scope's kernels with times of their own.  The step with four kernels /
+// three, one to three heads of 20000 to 131072 keys: 48.7 / 46.3, 58.6 / 56.4, 50.0 / 48.7, 84.4 / 82.0; all scores
+// equal 63.9 / 62.9, 117.7 / 115.0.
 constexpr int FUSED_BLOCKS = 256, FUSED_SEGMENTS = 4;
 size_t topk_spare_bytes(const SeqTab &st, const Dims &dm) {
   if (longest_row(st) <= SELECT_CARRIED_MAX || st.batch * dm.h_kv < FUSED_SEGMENTS) return 0;

@@ -173,10 +173,10 @@ def test_512_rows_with_4096_key_chunks(dt):
 
 @pytest.mark.parametrize("h_q, rs", [(8, "4"), (16, "8")])      # 256 and 512 rows per KV head
 def test_statistics_sweep_survives_logits_far_above_its_first_tile(h_q, rs):
-    """The statistics sweep of the many-row shapes keeps the reference its first tile gave a row
-    and only looks for a new maximum when a sum overflows.  Here the first 64 keys are tiny and
-    later keys give logits more than 128 powers of two above them, so that path is taken (in the
-    512-row shape from inside the loop of tile pairs)."""
+    """The first 64 keys are tiny and later keys give logits more than 128 powers of two above them.
+    A workgroup gets two tiles here and keeps no reference, so what meets these logits is its running
+    maximum and the combination of the partials, whose references are as far apart; workgroups with
+    more tiles, and a kept reference, are in test_gpu_score_reference.py."""
     _say(f"statistics sweep: overflow of the kept reference, {h_q} query heads")
     wl = synth.small_workload(h_q, 2, 128, 64, 7, 3000, 2 * 300, dtype=torch.bfloat16, seed=77)
     q, K, V = synth.generate(wl, device=DEV)

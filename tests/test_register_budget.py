@@ -1,9 +1,9 @@
 """CPU-side check of what the compiler made of the scoring kernels: registers and scratch.
 
-The scoring sweeps are laid out for two wavefronts per SIMD (a SIMD has 512 registers per lane):
-a kernel of four-wavefront workgroups that needs more than 256 registers still runs, one
-wavefront per SIMD, at a little over half the speed, and a spill inside the tile loop puts
-scratch loads between the K loads.  Neither shows in a parity test, and both have happened
+The weights sweeps and the statistics sweeps beyond 128 rows are laid out for two wavefronts per SIMD
+(a SIMD has 512 registers per lane): a kernel of four-wavefront workgroups that needs more than 256
+registers still runs, one wavefront per SIMD, at a little over half the speed, and a spill inside the
+tile loop puts scratch loads between the K loads.  Neither shows in a parity test, and both have happened
 after changes that looked harmless, so the build's own metadata is read back here (from the
 code objects inside the built library, with the ROCm LLVM tools; nothing is launched)."""
 import os
@@ -67,21 +67,20 @@ def score_kernels(lib):
 
 
 def test_two_wavefronts_per_simd_where_the_layout_counts_on_them(score_kernels):
-    """The 128-row kernels (four wavefronts, two workgroups per compute unit) and the 256- and
-    512-row kernels, in both sweeps and both 16-bit types, and the row-pooling form of the 128-row
-    weights sweep (which takes one row block at a time for it): at most 256 registers (vector plus
-    accumulation registers).  The row-pooling form of the 256- and 512-row kernels keeps both row
-    blocks in flight, needs more on d = 128 and is left out; so are the 32- and 64-row forms with
-    four key groups, which are bound by memory with one wavefront per SIMD as well."""
+    """The 128-, 256- and 512-row kernels in both sweeps and both 16-bit types, and the row-pooling
+    form of their weights sweeps: at most 256 registers (vector plus accumulation registers).  (The
+    statistics sweep of up to 128 rows at d = 128 has the compute unit to itself for its tiles in LDS,
+    one wavefront per SIMD; what it needs beyond 256 would be moved into accumulation registers.)  The
+    32- and 64-row forms are bound by memory with one wavefront per SIMD as well."""
     checked = 0
     for (d, mb, rs, kg, chunk, sweep, f16, pool_rows), md in score_kernels.items():
-        if (mb, rs, kg) not in (((2, 2, 2),) if pool_rows else ((2, 2, 2), (2, 4, 1), (2, 8, 1))):
+        if (mb, rs, kg) not in ((2, 2, 2), (2, 4, 1), (2, 8, 1), (4, 4, 1)):
             continue
         assert md["vgpr"] + md["agpr"] <= 256, ((d, mb, rs, kg, chunk, sweep, f16, pool_rows), md)
         checked += 1
-    # types x sweeps x (d = 128: four chunk lengths, 256 rows and 512 rows with two each;
-    # d = 64: the first six), and types x d x four chunk lengths of the row-pooling sweep
-    assert checked == 2 * 2 * (8 + 6) + 2 * 2 * 4
+    # types x (two sweeps and the row-pooling one) x (d = 128: four chunk lengths, 256 rows and 512 rows
+    # with two each; d = 64: the first six and 512 rows with one)
+    assert checked == 2 * 3 * (8 + 7)
 
 
 def test_no_scoring_kernel_spills(score_kernels):
