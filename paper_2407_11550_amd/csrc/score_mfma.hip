@@ -206,8 +206,12 @@ __device__ __forceinline__ void fold_rows(const floatx16 &a, float c_log2, float
   rm = m;
 }
 __device__ __forceinline__ void add_kept(const floatx16 &a, float c_log2, float sum, float &rm, float &rl) {
-  if (__builtin_expect(__any(!(sum <= KEPT_MOST)), 0)) fold_rows(a, c_log2, rm, rl);
-  else rl += sum;
+  const float before = rl;                             // (added in any case: a choice would be a second branch in the loop)
+  rl += sum;
+  if (__builtin_expect(__any(!(sum <= KEPT_MOST)), 0)) {
+    rl = before;
+    fold_rows(a, c_log2, rm, rl);
+  }
 }
 // Many tiles make a large sum all the same; its logarithm is rounded at the size of its exponent, which therefore
 // moves into the reference (the factor is that of the two references as they are stored).
@@ -321,7 +325,8 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
   constexpr int NW = 4, NT = 64 * NW, KS = T::KS, LD = T::LD;
   constexpr int RPAD = 32 * RB;
   constexpr int NBUF = 3;                             // tiles a wavefront has room for
-  constexpr int UN = RB % 2 == 1 && NBUF % 2 == 1 ? 2 * NBUF : NBUF;     // (a row block's products alternate between two places)
+  constexpr int UN = NBUF;
+  static_assert(UN * RB % 3 == 0, "a row block's products take turns in three places");
   __shared__ u32x4 kt[NW][NBUF][T::WORDS];
   __shared__ u32x4 qs[RB * T::WORDS];
 
@@ -394,16 +399,31 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
   }
 
   bf16x8 kf[KS];
-  floatx16 acc[2];                                     // products of the current row block and of the one before
+  floatx16 acc[3];                                     // products of the current row block and of the two before
   float rm[RB], rl[RB];                                // running maximum (or reference) and sum of the row this lane owns
-  // the vector work on one row block's products, in KS shares
-  float ref = 0.0f, nmx = 0.0f, usum = 0.0f;
-  auto share = [&](auto lazy_tag, floatx16 &a, int mb, int s) {
+  // The vector work on one row block's products, in KS shares.  Against a kept reference two row blocks of a tile are
+  // looked at together (p: the first one's products): a branch per row block took 1 us of 64 at 32768 keys and 3 of 172
+  // over six sequences of 217 000 keys.
+  float ref = 0.0f, nmx = 0.0f, usum = 0.0f, kept[2] = {0.0f, 0.0f};
+  auto share = [&](auto lazy_tag, const floatx16 &p, const floatx16 &a, int mb, int s) {
     if constexpr (decltype(lazy_tag)::value) {
-      if (s == 0) usum = 0.0f;
+      const int o = mb & 1, of = RB > 1 ? mb & ~1 : mb;
+      if (s == 0) kept[o] = 0.0f;
 #pragma unroll
-      for (int v = s * 16 / KS; v < (s + 1) * 16 / KS; ++v) usum += fast_exp2(fmaf(a[v], c_log2, -rm[mb]));
-      if (s == KS - 1) add_kept(a, c_log2, usum, rm[mb], rl[mb]);
+      for (int v = s * 16 / KS; v < (s + 1) * 16 / KS; ++v) kept[o] += fast_exp2(fmaf(a[v], c_log2, -rm[mb]));
+      if (s == KS - 1 && (RB == 1 || o == 1)) {
+        const float both = RB > 1 ? kept[0] + kept[1] : kept[0], first_before = rl[of], before = rl[mb];
+        rl[of] += kept[0];                             // (added in any case: a choice would be a second branch)
+        if (RB > 1) rl[mb] += kept[1];
+        if (__builtin_expect(__any(!(both <= KEPT_MOST)), 0)) {
+          rl[of] = first_before;
+          if (RB > 1) {
+            fold_rows(p, c_log2, rm[of], rl[of]);
+            rl[mb] = before;
+          }
+          fold_rows(a, c_log2, rm[mb], rl[mb]);
+        }
+      }
     } else {
       if (s == 0) {
         float tm = a[0];
@@ -427,7 +447,7 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
   // All full tiles, the first of them in kf; behind it kf holds the tile after them, if there is one.
   auto loop = [&](auto lazy_tag) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = -INFINITY;    // (nothing before the first: no weight)
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = acc[2][r] = -INFINITY;      // (nothing before the first: no weight)
     for (int it0 = 0; it0 < plain; it0 += UN) {
 #pragma unroll
       for (int j = 0; j < UN; ++j) {
@@ -437,27 +457,34 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
           if (it + NBUF < iters) issue(it + NBUF, j % NBUF);
 #pragma unroll
           for (int mb = 0; mb < RB; ++mb) {
-            const int cur = (j * RB + mb) & 1, pmb = mb == 0 ? RB - 1 : mb - 1;
+            const int cur = (j * RB + mb) % 3, pmb = mb == 0 ? RB - 1 : mb - 1;
             if (mb == RB - 1) await(it + 1);
             floatx16 a = {0};
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
               a = mfma16<F16>(kf[s], qf[mb][s], a);
+              if (s == 0) __builtin_amdgcn_sched_barrier(0);     // (else the vector work, which waits for the block before, goes first)
               if (mb == RB - 1) kf[s] = as_bf16(kt[wv][(j + 1) % NBUF][rd[s]]);   // (whatever lies there behind the last)
-              share(lazy_tag, acc[1 - cur], pmb, s);
+              share(lazy_tag, acc[(cur + 1) % 3], acc[(cur + 2) % 3], pmb, s);
               __builtin_amdgcn_sched_barrier(0);
             }
             acc[cur] = a;
-            asm volatile("" : "+v"(rl[pmb]), "+v"(rm[pmb]));   // the vector work stays in front of this point
+            // the vector work stays in front of this point
+            if constexpr (RB > 1) asm volatile("" : "+v"(rl[pmb & ~1]), "+v"(rm[pmb & ~1]), "+v"(rl[pmb | 1]), "+v"(rm[pmb | 1]), "+v"(kept[pmb & 1]));
+            else asm volatile("" : "+v"(rl[pmb]), "+v"(rm[pmb]));
           }
         }
       }
     }
     if (plain > 0) {
-      floatx16 last = acc[1];
-      if (RB % 2 == 1 && (plain & 1)) last = acc[0];
+      auto finish = [&](const floatx16 &p, const floatx16 &last) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) share(lazy_tag, last, RB - 1, s);
+        for (int s = 0; s < KS; ++s) share(lazy_tag, p, last, RB - 1, s);
+      };
+      const int at = (plain * RB + 2) % 3;             // the last row block's place
+      if (at == 0) finish(acc[2], acc[0]);
+      else if (at == 1) finish(acc[0], acc[1]);
+      else finish(acc[1], acc[2]);
     }
   };
 #pragma unroll
@@ -501,7 +528,7 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
       for (int r = 0; r < 16; ++r)                     // key base + 8 (r/4) + 4 half + r%4
         if (base + 8 * (r / 4) + 4 * half + (r % 4) >= n) a[r] = -INFINITY;
 #pragma unroll
-      for (int s = 0; s < KS; ++s) share(std::false_type{}, a, mb, s);
+      for (int s = 0; s < KS; ++s) share(std::false_type{}, a, a, mb, s);
       asm volatile("" : "+v"(rl[mb]));
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -1036,6 +1063,7 @@ __device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
             a = mfma16<F16>(kf[s], qf[mb][s], a);
+            if (s == 0) __builtin_amdgcn_sched_barrier(0);       // (as in stats_own)
             if (mb == MB - 1) kf[s] = as_bf16(src[rd[s]]);
             share(lazy_tag, acc[1 - cur], pmb, s);
             __builtin_amdgcn_sched_barrier(0);
