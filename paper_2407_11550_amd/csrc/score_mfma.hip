@@ -1409,7 +1409,7 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
 
 // MB row blocks of 32 window rows times RS are a workgroup's rows, RS * KG its wavefronts.  Up to 128 rows a
 // wavefront takes all of them and the wavefronts split the keys; beyond, RS wavefronts share a tile.  CHUNK: what
-// a workgroup has room for (sweep 1 of up to 128 rows does not depend on it).
+// a workgroup of sweep 2 has room for (sweep 1 keeps no scores: 0).
 template <int D, int MB, int RS, int KG, int CHUNK, int PASS, bool F16, bool PR = false>
 __global__ __launch_bounds__(64 * RS * KG, MB * RS <= 4 ? 2 : 1) void score_mfma_kernel(
     SeqTab st, ChunkTab ct, ChunkTab cp, Dims dm, float c_log2, const unsigned short *__restrict__ q,
@@ -1441,7 +1441,7 @@ void run_mfma(const MfmaVariant &v, const SeqTab &st, const Dims &dm, const void
   const float *use_lse = row_lse;              // the caller's in the natural-log domain, the combined one in base 2
   const float lse_mul = row_lse ? LOG2E : 1.0f;
   if (!row_lse) {
-    ADAKV_LAUNCH("score_stats_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 1, F16>), dim3(cp.off[st.batch] * dm.h_kv),
+    ADAKV_LAUNCH("score_stats_mfma", (score_mfma_kernel<D, MB, RS, KG, 0, 1, F16>), dim3(cp.off[st.batch] * dm.h_kv),
                  block, s, st, cp, cp, dm, c_log2, (const unsigned short *)q,
                  (const unsigned short *)K, (const float *)nullptr, 1.0f, part,
                  (float *)nullptr, 0, v.part_len, tc);

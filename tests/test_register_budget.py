@@ -78,9 +78,15 @@ def test_two_wavefronts_per_simd_where_the_layout_counts_on_them(score_kernels):
             continue
         assert md["vgpr"] + md["agpr"] <= 256, ((d, mb, rs, kg, chunk, sweep, f16, pool_rows), md)
         checked += 1
-    # types x (two sweeps and the row-pooling one) x (d = 128: four chunk lengths, 256 rows and 512 rows
-    # with two each; d = 64: the first six and 512 rows with one)
-    assert checked == 2 * 3 * (8 + 7)
+    # types x (the statistics sweep of three row counts per d, and two weights sweeps x (d = 128: four chunk
+    # lengths, 256 rows and 512 rows with two each; d = 64: the first six and 512 rows with one))
+    assert checked == 2 * (2 * 3 + 2 * (8 + 7))
+
+
+def test_the_statistics_sweep_is_built_once_per_row_count(score_kernels):
+    """It does not depend on how many scores a workgroup of the weights sweep has room for."""
+    kinds = [key[:4] + key[5:] for key in score_kernels if key[5] == 1]
+    assert len(kinds) == len(set(kinds)) == 2 * 2 * 5
 
 
 def test_no_scoring_kernel_spills(score_kernels):
