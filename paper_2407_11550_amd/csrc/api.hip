@@ -416,7 +416,7 @@ int adakv_describe(const adakv_layer *L, int have_row_lse, char *out, size_t out
                    pool_first(L) ? "fma-pool-first" : "fma", dt, dm.d, dm.g * dm.w, stats,
                    have_row_lse ? "caller"
                    : !pool_first(L) && f32_lse_fused(st, plan_score(st, dm, L->dtype, false).part_chunk) ? "fused" : "kernel",
-                   !pool_first(L) && f32_pool_fused(st, dm) ? "fused" : "kernel", topk);
+                   !pool_first(L) && f32_pool_fused(st, dm, L->dtype) ? "fused" : "kernel", topk);
   }
   return (len < 0 || (size_t)len >= out_bytes) ? ADAKV_EINVAL : ADAKV_OK;
 }

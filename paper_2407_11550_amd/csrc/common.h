@@ -87,7 +87,7 @@ ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma);
 size_t score_workspace(const SeqTab &st, const Dims &dm, int part_chunk);   // with partial statistics per part_chunk keys
 bool mfma_path_supported(const Dims &dm, int dtype);
 bool f32_lse_fused(const SeqTab &st, int part_chunk);    // ... and combines the statistics itself
-bool f32_pool_fused(const SeqTab &st, const Dims &dm);   // the fp32 weights sweep applies the max-pool itself
+bool f32_pool_fused(const SeqTab &st, const Dims &dm, int dtype);   // the fp32 weights sweep applies the max-pool itself
 
 hipError_t launch_score_generic(const SeqTab &st, const Dims &dm, int dtype, const void *q,
                                 const void *K, const float *row_lse, float *scores, char *ws,

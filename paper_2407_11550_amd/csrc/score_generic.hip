@@ -7,6 +7,8 @@
 // weights.
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace adakv {
@@ -359,6 +361,454 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
   }
 }
 
+// ---- the same, with every fp32 product made of bf16 products ---------------------------------------
+//
+// An fp32 value is the sum of three bf16 values of 8 bits each (rounded to nearest, x = h + m + l without a
+// rest), so a product of two is nine products of 16-bit values, each exact in fp32, on instructions sixteen times as
+// fast as v_mfma_f32_32x32x2_f32.  Six are taken (hh, hm, mh, hl, lh, mm); the three left out are below 2^-25 of the
+// whole, less than fp32 rounds a product to.  The five small ones have an accumulator of their own, so that a logit
+// is rounded at its own size 8 times where d = 128, and not 64: error against 64 bits 8191 keys x 8 heads, 128 rows
+// 6.7e-7 -> 4.7e-7, 16384 7.9e-7 -> 5.4e-7, d = 64, 64 rows, 16000 keys 8.1e-7 -> 6.6e-7.
+// What 16-bit parts cannot hold goes through the fp32 instruction, for the keys and rows concerned: values from
+// 2^60 on, infinities among them (an infinite part times a part that is zero would be a NaN, and products could
+// overflow with different signs).  What lies below bf16's range is less than 2^-133 of a value and moves no logit.
+//
+// Keys, rows and workgroups as above.  A row block's matrix instructions (48 at d = 128) are issued with other work in
+// between: the exponentials of the block before, a stage of a value at a time, and the cut of the next block's rows,
+// which were fetched a block before that.  Bound by these (matrix instructions 0.8 us of a row block's 1.6 with one
+// wavefront per SIMD) and, with few row blocks, by K, which has to be there before the first block is done (34 MB of
+// 8191 keys x 8 heads: 6.7 us).  Kernel times in us, fp32 instruction / this, statistics + weights, d = 128: 8191 keys
+// x 8 heads, 128 rows 23 + 25.5 / 19 + 20; 16384 45 + 50 / 32 + 31.5; 4000, 512 rows 43.5 + 45.5 / 31 + 32; 1500, 64
+// rows 8.5 + 9.7 / 8.0 + 9.2.  (Few rows keep the fp32 instruction: f32_cut().)
+constexpr int PARTS = 3;
+constexpr float CUT_MOST = 0x1p60f;                    // values of this size and more are not cut into parts
+constexpr int PANEL = 2048;                            // rows whose log-sum-exp sweep 2 keeps at a time
+constexpr float LOW_MID = -138.0f, LOW_WIDE = 13.0f;   // exponents of subnormal results (-150 to -126) lie this near to that
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+__device__ __forceinline__ floatx16 mfma_bf16(const uint4 &a, const uint4 &b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Two values on their way through the parts, a stage each; most: the larger magnitude (a NaN does not count: its
+// first part is one).
+struct Pair {
+  float a, b, most;
+  __device__ __forceinline__ void begin(const uint4 *raw, int k) {
+    float x[8];
+    Elem<float>::unpack(raw[0], x);
+    Elem<float>::unpack(raw[1], x + 4);
+    a = x[2 * k];
+    b = x[2 * k + 1];
+    most = fmaxf(fabsf(a), fabsf(b));
+  }
+  __device__ __forceinline__ unsigned stage(int p) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const unsigned v = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));
+    if (p < PARTS - 1) {
+      a -= __uint_as_float(v << 16);
+      b -= __uint_as_float(v & 0xFFFF0000u);
+    }
+    return v;
+  }
+};
+// Eight elements of a row as operand words of the matrix instructions, one word per part; the largest magnitude.
+__device__ __forceinline__ float cut8(const uint4 *raw, uint4 (&o)[PARTS]) {
+  unsigned w[PARTS][4];
+  float most = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    Pair x;
+    x.begin(raw, k);
+    most = fmaxf(most, x.most);
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) w[p][k] = x.stage(p);
+  }
+#pragma unroll
+  for (int p = 0; p < PARTS; ++p) o[p] = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+  return most;
+}
+
+// The 32 window rows r0 .. r0+31 travel memory -> registers (fetch) -> LDS, cut into operand words of eight values, a
+// word per part (store).  Rows past R are fetched from row R-1; their products are left out of every result.
+template <int D, int NT>
+struct CutRows {
+  static constexpr int ROW8 = D / 8;                   // operand words per row and part
+  static constexpr int WORDS = 32 * ROW8;
+  static constexpr int LD = (WORDS + NT - 1) / NT;     // of them per thread
+  static constexpr int STRIDE = ROW8 + 1;              // padded LDS row, in words
+  static constexpr int PART = 32 * STRIDE;
+  static_assert(WORDS % NT == 0 || WORDS < NT, "the row block must split evenly over the threads");
+  uint4 g[LD][2];
+  __device__ __forceinline__ void fetch(int i, const float *qhead, int r0, int R) {
+    const unsigned wi = min(threadIdx.x + i * NT, (unsigned)WORDS - 1u);
+    const unsigned at = min(r0 + wi / ROW8, (unsigned)R - 1u) * (D * 4u) + wi % ROW8 * 32u;
+    const uint4 *src = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(qhead) + at);
+    g[i][0] = src[0];
+    g[i][1] = src[1];
+  }
+  // In STEPS: a stage of two elements each, then the word's store.  Rows with values that cannot be cut are marked with
+  // the row block's number (marks of other blocks mean nothing).
+  static constexpr int PER = 4 * PARTS, STEPS = PER * LD;
+  unsigned w[PARTS][4];
+  float most;
+  Pair x;
+  __device__ __forceinline__ void store(int step, uint4 *buf, int *mark, int block) {
+    const int i = step / PER, k = step % PER / PARTS, p = step % PARTS, wi = threadIdx.x + i * NT;
+    if (p == 0) {
+      x.begin(g[i], k);
+      most = k == 0 ? x.most : fmaxf(most, x.most);
+      asm volatile("" : "+v"(most));                   // (a step's work stays where it is called)
+    }
+    w[p][k] = x.stage(p);
+    asm volatile("" : "+v"(w[p][k]));
+    if (step % PER < PER - 1 || (WORDS < NT && wi >= WORDS)) return;
+    if (most >= CUT_MOST) mark[wi / ROW8] = block;
+#pragma unroll
+    for (int o = 0; o < PARTS; ++o)
+      buf[o * PART + wi / ROW8 * STRIDE + wi % ROW8] = make_uint4(w[o][0], w[o][1], w[o][2], w[o][3]);
+  }
+};
+
+// The same 32 x 32 logits by the fp32 instruction, straight from memory: of every two 16-byte words of a row the
+// lower half of the wavefront takes the first, the upper half the second, in both operands.
+template <int D, bool KEYS_FIRST>
+__device__ __forceinline__ floatx16 fp32_products(const float *krow, const float *qrow, int half) {
+  floatx16 acc = {0}, acc1 = {0};
+#pragma unroll 1
+  for (int s = 0; s < D / 8; ++s) {
+    float k[4], q[4];
+    Elem<float>::unpack(*reinterpret_cast<const uint4 *>(krow + s * 8 + half * 4), k);
+    Elem<float>::unpack(*reinterpret_cast<const uint4 *>(qrow + s * 8 + half * 4), q);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      floatx16 &a = (i & 1) ? acc1 : acc;
+      a = KEYS_FIRST ? __builtin_amdgcn_mfma_f32_32x32x2f32(k[i], q[i], a, 0, 0, 0)
+                     : __builtin_amdgcn_mfma_f32_32x32x2f32(q[i], k[i], a, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] += acc1[i];
+  return acc;
+}
+
+// op of a lane's value and that of the lane 32 further, in both.
+template <class Op> __device__ __forceinline__ float over_halves(float x, Op op) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// As score_f32_kernel.
+template <int D, int PASS, int NW, bool COMBINE>
+__global__ __launch_bounds__(64 * NW, 2) void score_cut_kernel(
+    SeqTab st, ChunkTab ct, Dims dm, float c_log2, int pool_r, int lse_natural,
+    const float *__restrict__ q, const float *__restrict__ K, const float *__restrict__ lse,
+    float2 *__restrict__ part, int part_chunk, float *__restrict__ out) {
+  typedef CutRows<D, 64 * NW> RB;
+  constexpr int KEYS = 32 * NW;
+  constexpr int KS = D / 16;                           // matrix instructions per row block and product
+  constexpr int PRODUCTS = 6, SLOTS = KS * PRODUCTS;
+  __shared__ uint4 qs[2][PARTS * RB::PART];
+  __shared__ int sh_mark[2][32];                       // rows whose values could not be cut
+  __shared__ float sh_a[2][NW][32], sh_b[2][NW][32];   // sweep 1: per-wavefront row statistics
+  __shared__ __align__(16) float sh_l2[PASS == 2 ? PANEL : 4];     // sweep 2: the rows' log-sum-exp, PANEL rows at a time
+  __shared__ float sh_raw[KEYS];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = find_seq(ct, st.batch, blockIdx.x);
+  const int chunk = blockIdx.x - ct.off[b];
+  const int c = blockIdx.y;
+  const int n = st.n[b];
+  const int R = dm.g * dm.w, RQ = dm.h_q * dm.w;
+  const int r = PASS == 2 && pool_r > 0 ? pool_r : 0;
+  const int own = KEYS - 2 * r;
+  const int k0 = chunk * own - r;                      // first key of the workgroup; keys outside [0, n) are masked
+  const int key = k0 + wv * 32 + l32;
+  const float *qhead = q + ((size_t)b * RQ + (size_t)c * R) * D;
+  const size_t lse0 = (size_t)b * RQ + (size_t)c * R;
+
+  RB rb;
+#pragma unroll
+  for (int i = 0; i < RB::LD; ++i) rb.fetch(i, qhead, 0, R);
+  const float *krow = K + (st.tok_off[b] + min(max(key, 0), n - 1)) * dm.k_stride_tok + c * dm.k_stride_head;
+  uint4 raw[KS][2];                                // of every 16 elements the lower half of the wavefront holds the first 8
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) raw[s][k] = reinterpret_cast<const uint4 *>(krow + s * 16 + half * 8)[k];
+  if (tid < 64) sh_mark[tid >> 5][tid & 31] = -1;
+  // Sweep 2, rows r0 .. r0 + PANEL - 1: the log-sum-exp in the base-2 domain; +inf on padding rows, whose weights
+  // are exactly zero.  COMBINE: from sweep 1's partials (at most F32_FUSE_CHUNKS of them per sequence), by `share`
+  // neighbouring threads a row, so that few rows keep all threads busy.
+  static_assert(!COMBINE || PASS == 2, "the weights sweep combines");
+  const float2 *pp = part;
+  int np = 0;
+  if (COMBINE) {
+    size_t part0 = 0;
+    for (int i = 0; i < b; ++i) part0 += (st.n[i] + part_chunk - 1) / part_chunk;
+    np = (n + part_chunk - 1) / part_chunk;
+    pp += part0 * RQ + (size_t)c * R;
+  }
+  auto panel = [&](int r0) {
+    const int share = !COMBINE || R > 32 * NW ? 1 : R > 16 * NW ? 2 : R > 8 * NW ? 4 : 8;
+    for (int at = tid / share; at < PANEL && r0 + (at & ~31) < R; at += 64 * NW / share) {
+      const int row = min(r0 + at, R - 1);
+      float v;
+      if (COMBINE) {
+        constexpr int CB = F32_FUSE_CHUNKS / 2;        // partials asked for at a time
+        const int own = tid % share;
+        float M = -INFINITY, L = 0.0f;
+        auto merge = [&](float m, float l) {
+          const float t = fmaxf(M, m), rf = (t == -INFINITY) ? 0.0f : t;
+          L = L * fast_exp2(M - rf) + l * fast_exp2(m - rf);
+          M = t;
+        };
+        for (int p0 = own; p0 < np; p0 += CB * share) {
+          float2 ml[CB];
+#pragma unroll
+          for (int u = 0; u < CB; ++u) ml[u] = pp[(unsigned)min(p0 + u * share, np - 1) * (unsigned)RQ + row];
+          float m = ml[0].x, l = 0.0f;
+#pragma unroll
+          for (int u = 1; u < CB; ++u) m = fmaxf(m, ml[u].x);
+          const float rf = (m == -INFINITY) ? 0.0f : m;
+#pragma unroll
+          for (int u = 0; u < CB; ++u)
+            if (p0 + u * share < np) l += ml[u].y * fast_exp2(ml[u].x - rf);
+          merge(m, l);
+        }
+        for (int o = 1; o < share; o <<= 1) {
+          const float m = __shfl_xor(M, o), l = __shfl_xor(L, o);
+          merge(m, l);
+        }
+        v = M + __builtin_amdgcn_logf(L);
+      } else {
+        v = lse[lse0 + row] * (lse_natural ? LOG2E : 1.0f);
+      }
+      if (!COMBINE || tid % share == 0) sh_l2[at] = r0 + at < R ? v : INFINITY;
+    }
+  };
+  __syncthreads();                                     // the marks are cleared
+#pragma unroll
+  for (int i = 0; i < RB::STEPS; ++i) rb.store(i, qs[0], sh_mark[0], 0);
+  if (R > 32) {
+#pragma unroll
+    for (int i = 0; i < RB::LD; ++i) rb.fetch(i, qhead, 32, R);
+  }
+  if (PASS == 2) panel(0);
+  __syncthreads();
+
+  // The loop over row blocks: a block's matrix instructions are issued with the vector work on the block before in
+  // between (SLOTS of them, a value in every SLOTS/16 or several in one), in the first block with the keys' cut,
+  // as they arrive.  One barrier a block.
+  uint4 kf[KS][PARTS];
+  float most = 0.0f;
+  unsigned big_keys = 0u;                              // keys whose values could not be cut
+  const int blocks = (R + 31) / 32;
+  const bool whole = k0 + wv * 32 + 32 <= n;           // (sweep 1: k0 >= 0) no key to mask
+  floatx16 prev;                                       // products of the block before
+  float total = 0.0f, before = 0.0f, low = 0.0f, kept = 0.0f;      // sweep 2
+  float ref = 0.0f, top = 0.0f, usum = 0.0f;           // sweep 1
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  f32x4 l2[4];
+  // sweep 1: prev[i] is key k0 + wv*32 + 8*(i/4) + 4*half + i%4, window row pb*32 + l32; sweep 2: window row
+  // pb*32 + 8*(i/4) + 4*half + i%4, key k0 + wv*32 + l32
+  auto begin = [&](int pb) {
+    if (PASS == 1) {
+      if (!whole) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (k0 + wv * 32 + 8 * (i / 4) + 4 * half + i % 4 >= n) prev[i] = -INFINITY;
+      }
+      float m = prev[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) m = fmaxf(m, prev[i]);
+      m = over_halves(m, [](float x, float y) { return fmaxf(x, y); });
+      top = m * c_log2;
+      ref = (top == -INFINITY) ? 0.0f : top;
+      usum = 0.0f;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) l2[i] = *reinterpret_cast<const f32x4 *>(&sh_l2[pb * 32 % PANEL + 8 * i + 4 * half]);
+      before = total;
+      low = INFINITY;
+    }
+  };
+  // One value in three stages, so that none waits for the one before: exponent, exponential, sum.
+  float x[2], e = 0.0f;
+  auto exponent = [&](int i) {
+    if (PASS == 1) {
+      x[i & 1] = fmaf(prev[i], c_log2, -ref);
+    } else {
+      x[i & 1] = fmaf(prev[i], c_log2, -l2[i / 4][i % 4]);
+      low = fminf(low, fabsf(x[i & 1] - LOW_MID));
+      asm volatile("" : "+v"(low));
+    }
+    asm volatile("" : "+v"(x[i & 1]));                 // (stays between the matrix instructions)
+  };
+  auto exponential = [&](int i) {
+    e = fast_exp2(x[i & 1]);
+    asm volatile("" : "+v"(e));
+  };
+  auto sum = [&]() {
+    float &s = PASS == 1 ? usum : total;
+    s += e;
+    asm volatile("" : "+v"(s));
+  };
+  auto value = [&](int i) {
+    exponent(i);
+    exponential(i);
+    sum();
+  };
+  auto end = [&](int pb) {
+    if (PASS == 1) {
+      const float l = over_halves(usum, [](float x, float y) { return x + y; });
+      if (half == 0) { sh_a[pb & 1][wv][l32] = top; sh_b[pb & 1][wv][l32] = l; }
+    } else if (pb * 32 + 32 > R || __any(low <= LOW_WIDE)) {
+      // padding rows (row R-1 once more, and an infinite logit against their infinite log-sum-exp would be a NaN), or
+      // weights below the normal range
+      total = before;
+#pragma unroll
+      for (int j = 0; j < 16; j += 4) {
+        if (pb * 32 + 2 * j >= R) break;
+#pragma unroll
+        for (int i = j; i < j + 4; ++i) {
+          const float w = exp2_small(fmaf(prev[i], c_log2, -l2[i / 4][i % 4]));
+          total += pb * 32 + 8 * (i / 4) + 4 * half + i % 4 < R ? w : 0.0f;
+        }
+      }
+    }
+  };
+  auto file = [&](int pb) {                            // sweep 1: the wavefronts' statistics of a block together
+    if (PASS == 1 && wv == pb % NW && half == 0 && pb * 32 + l32 < R) {
+      const int at = pb & 1;
+      float M = sh_a[at][0][l32];
+#pragma unroll
+      for (int i = 1; i < NW; ++i) M = fmaxf(M, sh_a[at][i][l32]);
+      const float rf = (M == -INFINITY) ? 0.0f : M;
+      float L = 0.0f;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) L += sh_b[at][i][l32] * fast_exp2(sh_a[at][i][l32] - rf);
+      part[(size_t)blockIdx.x * RQ + (size_t)c * R + pb * 32 + l32] = make_float2(M, L);
+    }
+  };
+  auto block = [&](int ib, auto first_tag) {
+    constexpr bool FIRST = decltype(first_tag)::value;
+    const int cur = ib & 1;
+    const uint4 *qrow = qs[cur] + l32 * RB::STRIDE + half;
+    uint4 qv[2][PARTS];                             // operand words of this step and the next
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) qv[0][p] = qrow[p * RB::PART];
+    int mark = 0;
+    if (FIRST) most = cut8(raw[0], kf[0]);
+    else begin(ib - 1);
+    floatx16 acc = {0}, small = {0};
+    auto add = [&](floatx16 &a, const uint4 &k, const uint4 &qv) { a = PASS == 1 ? mfma_bf16(k, qv, a) : mfma_bf16(qv, k, a); };
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+#pragma unroll
+      for (int t = 0; t < PRODUCTS; ++t) {
+        const uint4 (&v)[PARTS] = qv[s & 1];
+        if (t == PRODUCTS - 1) add(acc, kf[s][0], v[0]);
+        else if (t == 0) add(small, kf[s][PARTS - 1], v[0]);
+        else if (t == 1) add(small, kf[s][1], v[1]);
+        else if (t == 2) add(small, kf[s][0], v[PARTS - 1]);
+        else if (t == 3) add(small, kf[s][1], v[0]);
+        else add(small, kf[s][0], v[1]);
+        if (t == 0 && s + 1 < KS) {
+#pragma unroll
+          for (int p = 0; p < PARTS; ++p) qv[(s + 1) & 1][p] = qrow[p * RB::PART + 2 * (s + 1)];
+        }
+        const int slot = s * PRODUCTS + t;
+        if constexpr (FIRST) {
+          if (t == PRODUCTS / 2 && s + 1 < KS) most = fmaxf(most, cut8(raw[s + 1], kf[s + 1]));
+        } else {
+#pragma unroll
+          for (int i = slot * 16 / SLOTS; i < (slot + 1) * 16 / SLOTS; ++i) {
+            if (i > 1) sum();
+            if (i > 0) exponential(i - 1);
+            exponent(i);
+          }
+        }
+        // the next block's rows, fetched a block ago, and then the fetch of those after it
+        constexpr int LAST = SLOTS - 1;
+#pragma unroll
+        for (int i = 0; i < RB::STEPS; ++i)
+          if (slot == min(1 + i * (SLOTS - 4) / RB::STEPS, LAST) && (!FIRST || blocks > 1)) {
+            rb.store(i, qs[cur ^ 1], sh_mark[cur ^ 1], ib + 1);
+            if (i % RB::PER == RB::PER - 1) rb.fetch(i / RB::PER, qhead, (ib + 2) * 32, R);
+          }
+        if (slot == SLOTS / 2) mark = sh_mark[cur][l32];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (!FIRST) {
+      sum();
+      exponential(15);
+      sum();
+      end(ib - 1);
+    }
+    if (PASS == 2 && !FIRST && ib * 32 % PANEL == 0) total = kept;
+    const unsigned big_rows = (unsigned)__ballot(mark == ib);
+    if (FIRST) {
+      const unsigned long long big = __ballot(most >= CUT_MOST);
+      big_keys = (unsigned)(big >> 32) | (unsigned)big;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) prev[i] = acc[i] + small[i];
+    if (__builtin_expect((big_keys | big_rows) != 0u, 0)) {
+      const floatx16 exact = fp32_products<D, PASS == 1>(krow, qhead + (size_t)min(ib * 32 + l32, R - 1) * D, half);
+      const unsigned col = (PASS == 1 ? big_rows : big_keys) >> l32 & 1u, rows = PASS == 1 ? big_keys : big_rows;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (col | (rows >> (8 * (i / 4) + 4 * half + i % 4) & 1u)) prev[i] = exact[i];
+    }
+    __syncthreads();
+    // (the buffers of this row block are written again two barriers from here)
+    if (!FIRST) file(ib - 1);
+    if (PASS == 2 && (ib + 1) * 32 % PANEL == 0 && ib + 1 < blocks) {
+      // the panel's last block gets its vector work here, what the next block does once more is thrown away
+      begin(ib);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) value(i);
+      end(ib);
+      kept = total;
+      __syncthreads();
+      panel((ib + 1) * 32);
+      __syncthreads();
+    }
+  };
+  block(0, std::true_type{});
+  for (int ib = 1; ib < blocks; ++ib) block(ib, std::false_type{});
+  begin(blocks - 1);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) value(i);
+  end(blocks - 1);
+  if (PASS == 1) {
+    __syncthreads();
+    file(blocks - 1);
+  }
+  if (PASS == 2) {
+    total += __shfl_xor(total, 32);
+    const float mean = total * (1.0f / (float)R);
+    float *dst = out + st.score_off[b] + (size_t)c * n;
+    if (pool_r < 0) {
+      if (half == 0 && key < n) dst[key] = mean;
+      return;
+    }
+    // (a window that leaves the sequence takes the key at its end more than once: the same maximum, and
+    // scores that are NaN stay so)
+    if (half == 0) sh_raw[wv * 32 + l32] = mean;
+    __syncthreads();
+    const int lo = max(-k0, 0), hi = min(KEYS, n - k0) - 1;
+    if (tid < own && k0 + r + tid < n) {
+      float m = sh_raw[min(max(tid, lo), hi)];
+      for (int t = 1; t <= 2 * r; ++t) m = fmaxf(m, sh_raw[min(max(tid + t, lo), hi)]);
+      dst[k0 + r + tid] = m;
+    }
+  }
+}
+
 // The other order of Alg. 2 l.4 (as printed there): every window row is max-pooled along the keys
 // first, then the g*w rows of the head are averaged.  A block scores 256 consecutive keys and owns
 // the middle 256 - 2*radius of them, so that every owned key finds its pool window in LDS; keys
@@ -462,6 +912,11 @@ __global__ __launch_bounds__(256) void pool_kernel(SeqTab st, ChunkTab ct, int p
   scores[base + j] = m;
 }
 
+// fp32 inputs: whether products are made of bf16 parts.  A wavefront's keys have to be cut first, which one row block of
+// 128 columns or two of 64 do not bring in again (us a call, fp32 instruction / parts: 8000 keys x 8 heads, d = 128, 16
+// rows 23.0 / 26.9; d = 64, 64 rows 22.2 / 23.0; but d = 128, 64 rows 33.4 / 32.2, d = 64, 128 rows, 3000 x 4 19.5 / 17.0).
+static bool f32_cut(const Dims &dm) { return dm.g * dm.w * dm.d > 32 * 128; }
+
 static ScorePlan plan_score_chunk(const SeqTab &st, const Dims &dm, int part_chunk) {
   ScorePlan p;
   // partial statistics: one (max, sum) pair per window row and chunk of keys
@@ -537,11 +992,15 @@ void launch_pool(const SeqTab &st, const Dims &dm, const float *raw, float *scor
 // every wavefront (4096 cycles = 1.8 us at d = 128) per row block.  8191 keys x 8 heads, 128 rows:
 // 544 workgroups fused (three on some of the 256 compute units) 34.2 us, 512 and a pool kernel
 // 24.3 + 4.1 us.
-bool f32_pool_fused(const SeqTab &st, const Dims &dm) {
+// Where the products are cut into parts two workgroups fit on a compute unit and a third makes a second round, which
+// takes longer than the pool kernel however few row blocks there are (fused / apart: 64 rows, d = 128, 8000 keys x 8
+// heads 34.1 / 32.2, 16000 x 4 34.0 / 31.9).
+bool f32_pool_fused(const SeqTab &st, const Dims &dm, int dtype) {
   const int r = dm.pool_k / 2;
   if (r == 0 || r > F32_POOL_MAX) return r == 0;
   const int most = (count_chunks(st, F32_KEYS - 2 * r) * dm.h_kv + 255) / 256;
   const int most_apart = (count_chunks(st, F32_KEYS) * dm.h_kv + 255) / 256;
+  if (dtype == ADAKV_FP32 && f32_cut(dm) && (most + 1) / 2 > (most_apart + 1) / 2) return false;
   const int row_blocks = (dm.g * dm.w + 31) / 32;
   return (most - most_apart) * row_blocks * 1.8f * dm.d / 128 <= 4.0f;
 }
@@ -561,15 +1020,21 @@ static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const v
   float2 *part = (float2 *)(ws + pl.part);
   float *lse = (float *)(ws + pl.lse), *raw = (float *)(ws + pl.raw);
   const float *use_lse = row_lse;
+  const bool cut = std::is_same<T, float>::value && f32_cut(dm);
   if (!row_lse) {
     const ChunkTab ct = make_chunks(st, pl.part_chunk);
     const dim3 grid(ct.off[st.batch], dm.h_kv);
-    if (pl.part_chunk == F32_KEYS)
-      ADAKV_LAUNCH("score_stats_fma", (score_f32_kernel<T, D, 1, 4, false>), grid, block, s, st, ct, dm, c_log2, -1,
-                   0, (const T *)q, (const T *)K, (const float *)nullptr, part, pl.part_chunk, (float *)nullptr);
-    else
-      ADAKV_LAUNCH("score_stats_fma", (score_f32_kernel<T, D, 1, 8, false>), grid, dim3(512), s, st, ct, dm, c_log2,
-                   -1, 0, (const T *)q, (const T *)K, (const float *)nullptr, part, pl.part_chunk, (float *)nullptr);
+#define ADAKV_GO(KERNEL, NW)                                                                      \
+  ADAKV_LAUNCH("score_stats_fma", KERNEL, grid, dim3(64 * NW), s, st, ct, dm, c_log2, -1, 0, (const T *)q, \
+               (const T *)K, (const float *)nullptr, part, pl.part_chunk, (float *)nullptr)
+    const bool narrow = pl.part_chunk == F32_KEYS;
+    if constexpr (std::is_same<T, float>::value) {
+      if (cut && narrow) ADAKV_GO((score_cut_kernel<D, 1, 4, false>), 4);
+      else if (cut) ADAKV_GO((score_cut_kernel<D, 1, 8, false>), 8);
+    }
+    if (!cut && narrow) ADAKV_GO((score_f32_kernel<T, D, 1, 4, false>), 4);
+    else if (!cut) ADAKV_GO((score_f32_kernel<T, D, 1, 8, false>), 8);
+#undef ADAKV_GO
     // Up to 32 partials per row (4096 keys) sweep 2 combines them itself, a launch of 4 us less: 2011
     // keys x 8 heads x 128 rows 33.0 -> 29.0 us for both sweeps, 4000 x 512 rows 100.1 -> 97.5; with 64
     // partials its workgroups read more of those than of keys (8000 x 4 heads x 512 rows, d = 64: 65.6 -> 67.6).
@@ -587,15 +1052,18 @@ static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const v
     return;
   }
   const int r = dm.pool_k / 2;
-  const bool fused = f32_pool_fused(st, dm);
+  const bool fused = f32_pool_fused(st, dm, std::is_same<T, float>::value ? ADAKV_FP32 : ADAKV_BF16);
   const ChunkTab ct = make_chunks(st, fused ? F32_KEYS - 2 * r : F32_KEYS);
   const dim3 grid(ct.off[st.batch], dm.h_kv);
-#define ADAKV_GO(COMBINE)                                                                         \
-  ADAKV_LAUNCH("score_weights_fma", (score_f32_kernel<T, D, 2, 4, COMBINE>), grid, block, s, st, ct, dm, \
-               c_log2, fused ? r : -1, row_lse ? 1 : 0, (const T *)q, (const T *)K, use_lse, part, \
-               pl.part_chunk, fused ? scores : raw)
-  if (use_lse) ADAKV_GO(false);
-  else ADAKV_GO(true);
+#define ADAKV_GO(KERNEL)                                                                          \
+  ADAKV_LAUNCH("score_weights_fma", KERNEL, grid, block, s, st, ct, dm, c_log2, fused ? r : -1, row_lse ? 1 : 0, \
+               (const T *)q, (const T *)K, use_lse, part, pl.part_chunk, fused ? scores : raw)
+  if constexpr (std::is_same<T, float>::value) {
+    if (cut && use_lse) ADAKV_GO((score_cut_kernel<D, 2, 4, false>));
+    else if (cut) ADAKV_GO((score_cut_kernel<D, 2, 4, true>));
+  }
+  if (!cut && use_lse) ADAKV_GO((score_f32_kernel<T, D, 2, 4, false>));
+  else if (!cut) ADAKV_GO((score_f32_kernel<T, D, 2, 4, true>));
 #undef ADAKV_GO
   if (!fused) launch_pool(st, dm, raw, scores, s);
 }
