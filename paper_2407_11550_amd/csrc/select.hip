@@ -102,60 +102,71 @@ __device__ __forceinline__ int wave_sum(int x) {       // the same in all lanes
   return __builtin_amdgcn_readlane(wave_scan_incl(x), 63);
 }
 
-// This thread's NB/256 consecutive bins of a finished histogram, as 16-byte loads.  Kept apart
-// from locate() so that callers can issue these loads together with everything else they need
-// from memory (one round trip instead of a chain of them).
-template <int NB> struct Bins { unsigned v[NB / 256]; };
-template <int NB> __device__ __forceinline__ Bins<NB> load_bins(const unsigned *__restrict__ bins) {
-  constexpr int PER = NB / 256;
-  Bins<NB> r;
-  // threads past the first 256 of a wider block own no bins
-  const uint4 *p = reinterpret_cast<const uint4 *>(bins + (threadIdx.x & 255) * PER);
-  const unsigned keep = threadIdx.x < 256 ? 0xFFFFFFFFu : 0u;
+// A finished histogram is searched by one wavefront, without a barrier: a lane adds up NB/64 consecutive bins, a scan
+// over the lanes finds the lane whose bins hold the rank, a second one over that lane's bins, read once more, finds
+// the bin.  (By the threads of a block, eight bins each, with three barriers, as before, a search took 0.6 to 0.8 us of
+// which there are up to six one after the other in a kernel; this one 0.25.)  The loads are apart from the search so that
+// they travel together with everything else a kernel needs from memory; in LDS every lane starts at another word, so
+// that they do not meet on the same banks.
+template <int NB> struct WaveBins { uint4 v[NB / 256]; };
+template <int NB> __device__ __forceinline__ WaveBins<NB> load_bins(const unsigned *__restrict__ bins) {
+  WaveBins<NB> r;
+  const uint4 *p = reinterpret_cast<const uint4 *>(bins) + (threadIdx.x & 63) * (NB / 256);
 #pragma unroll
-  for (int i = 0; i < PER / 4; ++i) {
-    const uint4 q = p[i];
-    r.v[4 * i] = q.x & keep; r.v[4 * i + 1] = q.y & keep;
-    r.v[4 * i + 2] = q.z & keep; r.v[4 * i + 3] = q.w & keep;
-  }
+  for (int i = 0; i < NB / 256; ++i) r.v[i] = p[i];
+  return r;
+}
+template <int NB> __device__ __forceinline__ WaveBins<NB> lds_bins(const unsigned *bins) {
+  WaveBins<NB> r;
+  const int lane = threadIdx.x & 63;
+  const uint4 *p = reinterpret_cast<const uint4 *>(bins) + lane * (NB / 256);
+#pragma unroll
+  for (int i = 0; i < NB / 256; ++i) r.v[i] = p[(i + lane) & (NB / 256 - 1)];
   return r;
 }
 
-// All threads of a block (the first 256 hold the bins): given a finished histogram (NB bins, this
-// thread's part in `mine`) and the rank krem >= 1 among the elements it counts, find the digit
-// whose bin holds that rank, counting from the largest digit down.  Returns the digit and the
-// rank inside its bin (>= 1).  A rank beyond the histogram's total gives digit 0 and the rank
-// unchanged (callers clamp what they derive from it).
+// All lanes of a wavefront: given a finished histogram (`mine`: this lane's part) and the rank krem >= 1 among the
+// elements it counts, find the digit whose bin holds that rank, counting from the largest digit down.  Gives the digit
+// and the rank inside its bin (>= 1).  A rank beyond the histogram's total gives digit 0 and the rank unchanged
+// (callers clamp what they derive from it).
 template <int NB>
-__device__ __forceinline__ void locate(const Bins<NB> &mine, int krem, unsigned &digit,
-                                       int &rank_in_bin, unsigned *sh /*[8]*/) {
-  constexpr int PER = NB / 256;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+__device__ __forceinline__ void wave_locate(const WaveBins<NB> &mine, const unsigned *bins, int krem, unsigned &digit,
+                                            int &rank_in_bin) {
+  constexpr int PER = NB / 64;
+  const int lane = threadIdx.x & 63;
   unsigned s = 0;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) s += mine.v[i];
+  for (int i = 0; i < NB / 256; ++i) s += (mine.v[i].x + mine.v[i].y) + (mine.v[i].z + mine.v[i].w);
   const unsigned upto = (unsigned)wave_scan_incl((int)s);                      // lanes up to this one
-  const unsigned all = (unsigned)__builtin_amdgcn_readlane((int)upto, 63);
-  __syncthreads();                                     // sh may be in use by the caller
-  if (lane == 0 && wv < 4) sh[wv] = all;
-  if (tid == 0) { sh[4] = 0u; sh[5] = (unsigned)krem; }   // fallback keeps later reads in bounds
-  __syncthreads();
-  unsigned above = all - upto;                         // elements in bins owned by higher threads
-  for (int i = wv + 1; i < 4; ++i) above += sh[i];
-  if (tid < 256 && above < (unsigned)krem && (unsigned)krem <= above + s) {
-    unsigned acc = above;
-#pragma unroll
-    for (int i = PER - 1; i >= 0; --i) {
-      if (acc < (unsigned)krem && (unsigned)krem <= acc + mine.v[i]) {
-        sh[4] = (unsigned)(tid * PER + i);
-        sh[5] = (unsigned)krem - acc;
-      }
-      acc += mine.v[i];
-    }
+  const unsigned above = (unsigned)__builtin_amdgcn_readlane((int)upto, 63) - upto;
+  const unsigned long long in_lane = __ballot(above < (unsigned)krem && (unsigned)krem <= above + s);
+  digit = 0u;
+  rank_in_bin = krem;
+  if (in_lane == 0) return;
+  const int L = __ffsll(in_lane) - 1;
+  const unsigned r = (unsigned)krem - (unsigned)__builtin_amdgcn_readlane((int)above, L);
+  const unsigned x = lane < PER ? bins[L * PER + PER - 1 - lane] : 0u;         // from the largest digit down
+  const unsigned cum = (unsigned)wave_scan_incl((int)x);
+  const unsigned long long in_bin = __ballot(lane < PER && cum - x < r && r <= cum);
+  if (in_bin == 0) return;
+  const int j = __ffsll(in_bin) - 1;
+  digit = (unsigned)(L * PER + PER - 1 - j);
+  rank_in_bin = (int)(r - (unsigned)__builtin_amdgcn_readlane((int)(cum - x), j));
+}
+// The same for a block, whose first wavefront searches a histogram in LDS that is finished for everybody (a barrier has
+// passed); sh: two words that nobody else uses until everybody has passed another barrier.
+template <int NB>
+__device__ __forceinline__ void block_locate(const unsigned *bins, int krem, unsigned &digit, int &rank_in_bin,
+                                             unsigned *sh /*[2]*/) {
+  if (threadIdx.x < 64) {
+    unsigned d;
+    int r;
+    wave_locate<NB>(lds_bins<NB>(bins), bins, krem, d, r);
+    if (threadIdx.x == 0) { sh[0] = d; sh[1] = (unsigned)r; }
   }
   __syncthreads();
-  digit = sh[4];
-  rank_in_bin = (int)sh[5];
+  digit = sh[0];
+  rank_in_bin = (int)sh[1];
 }
 
 __global__ __launch_bounds__(256) void topk_init_kernel(unsigned *__restrict__ zero_begin,
@@ -202,70 +213,54 @@ __global__ __launch_bounds__(256) void topk_digit0_kernel(SeqTab st, ChunkTab ct
   }
 }
 
-// The gather step of a block of NT threads: `sc` holds its scores (position j0 + tid + NT i, clamped
-// to j1 - 1), `mine` this thread's part of the scope's first digits, krem > 0 the rank sought, gh the
-// scope's second digits.  The caller has cleared lh and *sh_above.
-template <int NT>
-__device__ __forceinline__ void gather_block(const float (&sc)[SEL_CHUNK / NT], int j0, int j1,
-                                             const Bins<RADIX_BINS> &mine, int krem, const TopkBufs &tb, size_t blk,
-                                             unsigned *gh, unsigned *lh /*[RADIX_BINS]: second-digit counts, then running bucket fill*/,
-                                             unsigned *sh /*[8]*/, int *sh_above, int *sh_wave /*[NT/64]*/) {
-  constexpr int EPB = SEL_CHUNK / NT, PER = RADIX_BINS / NT;
+constexpr int GATHER_NT = 1024;
+// The gather step of a block: `sc` holds its scores (position j0 + tid + GATHER_NT i, clamped to j1 - 1), d0 the scope's
+// first digit, gh the scope's second digits.  The caller has cleared lh and *sh_above; a barrier has passed since.
+// (Sixteen wavefronts with four positions a lane: in four with sixteen the counting alone took 1.1 us, now 0.6.  The
+// kernel, 64 blocks 4.6 -> 4.1 us, 256 5.2 -> 4.3, 300 7.1 -> 5.8, 500 and more the same.)
+__device__ __forceinline__ void gather_block(const float (&sc)[SEL_CHUNK / GATHER_NT], int j0, int j1, unsigned d0, const TopkBufs &tb,
+                                             size_t blk, unsigned *gh,
+                                             unsigned *lh /*[RADIX_BINS]: second-digit counts, then running bucket fill*/,
+                                             int *sh_above, int *sh_wave /*[GATHER_NT / 64]*/) {
+  constexpr int NT = GATHER_NT, EPT = SEL_CHUNK / NT, WV = NT / 64;
+  static_assert(RADIX_BINS == 2 * NT, "two bins per thread");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  unsigned d0;
-  int r0;
-  locate<RADIX_BINS>(mine, krem, d0, r0, sh);          // its barriers also publish the cleared lh
-  unsigned keys[EPB];
+  unsigned keys[EPT];
   int above = 0;
 #pragma unroll
-  for (int i = 0; i < EPB; ++i) {
+  for (int i = 0; i < EPT; ++i) {
     const bool in = j0 + tid + NT * i < j1;
     const unsigned key = key_of(sc[i]);
     keys[i] = key;
     const unsigned dg = key >> 21;
     if (in && dg == d0) atomicAdd(&lh[(key >> 10) & 2047u], 1u);
-    above += in && dg > d0;
+    above += __popcll(__ballot(in && dg > d0));
   }
-  above = wave_sum(above);
-  if (lane == 0) atomicAdd(sh_above, above);
+  if (lane == 0 && above) atomicAdd(sh_above, above);
   __syncthreads();
   // bucket starts, largest digit first is not needed: buckets are addressed by digit.  Thread t
-  // owns PER bins from PER t: exclusive scan over the block.
-  unsigned cnt[PER];
-  unsigned tsum = 0;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) { cnt[i] = lh[tid * PER + i]; tsum += cnt[i]; }
+  // owns two bins from 2 t: exclusive scan over the block.
+  const uint2 cnt = reinterpret_cast<const uint2 *>(lh)[tid];
+  const unsigned tsum = cnt.x + cnt.y;
   const unsigned inc = (unsigned)wave_scan_incl((int)tsum);
   if (lane == 63) sh_wave[wv] = (int)inc;
   __syncthreads();
-  unsigned base = inc - tsum;
-  for (int i = 0; i < wv; ++i) base += (unsigned)sh_wave[i];
+  const unsigned wsum = lane < WV ? (unsigned)sh_wave[lane & (WV - 1)] : 0u;
+  const unsigned wupto = (unsigned)wave_scan_incl((int)wsum);
+  const unsigned s0 = inc - tsum + (unsigned)__builtin_amdgcn_readlane((int)(wupto - wsum), __builtin_amdgcn_readfirstlane(wv));
+  const unsigned s1 = s0 + cnt.x;
   // starts to memory (one store), counts to the scope's histograms, starts into lh
-  unsigned stt[PER];
-  unsigned run = base;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) { stt[i] = run; run += cnt[i]; }
-  if constexpr (PER == 8) {
-    uint4 packed;
-    packed.x = stt[0] | (stt[1] << 16); packed.y = stt[2] | (stt[3] << 16);
-    packed.z = stt[4] | (stt[5] << 16); packed.w = stt[6] | (stt[7] << 16);
-    reinterpret_cast<uint4 *>(tb.starts + blk * RADIX_BINS)[tid] = packed;
-  } else {
-    static_assert(PER == 2, "two or eight bins per thread");
-    reinterpret_cast<unsigned *>(tb.starts + blk * RADIX_BINS)[tid] = stt[0] | (stt[1] << 16);
-  }
-  if (tid == NT - 1) { tb.note[blk].entries = (int)run; tb.note[blk].above = *sh_above; }
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    if (cnt[i]) atomicAdd(&gh[tid * PER + i], cnt[i]);
-    lh[tid * PER + i] = stt[i];
-  }
+  reinterpret_cast<unsigned *>(tb.starts + blk * RADIX_BINS)[tid] = s0 | (s1 << 16);
+  if (tid == NT - 1) { tb.note[blk].entries = (int)(s1 + cnt.y); tb.note[blk].above = *sh_above; }
+  reinterpret_cast<uint2 *>(lh)[tid] = make_uint2(s0, s1);
+  if (cnt.x) atomicAdd(&gh[tid * 2], cnt.x);
+  if (cnt.y) atomicAdd(&gh[tid * 2 + 1], cnt.y);
   __syncthreads();
   // (the order inside a bucket follows the atomics, but only the multiset of a bucket's last
   // digits is ever used)
   unsigned short *ent = tb.entries + blk * ENT_PER_BLOCK;
 #pragma unroll
-  for (int i = 0; i < EPB; ++i) {
+  for (int i = 0; i < EPT; ++i) {
     const bool in = j0 + tid + NT * i < j1;
     if (in && (keys[i] >> 21) == d0) {
       const unsigned slot = atomicAdd(&lh[(keys[i] >> 10) & 2047u], 1u);
@@ -277,13 +272,13 @@ __device__ __forceinline__ void gather_block(const float (&sc)[SEL_CHUNK / NT], 
 // The gather kernel of either scope.  grid as above.  LAYER: the threshold is sought over all
 // heads of a sequence (rank B'), else inside the block's own head (rank budgets[segment]).
 template <bool LAYER>
-__global__ __launch_bounds__(256) void topk_gather_kernel(SeqTab st, ChunkTab ct, int h,
-                                                          const float *__restrict__ scores,
-                                                          const int *__restrict__ budgets,
-                                                          TopkBufs tb) {
-  __shared__ unsigned lh[RADIX_BINS];
-  __shared__ unsigned sh[8];
-  __shared__ int sh_above, sh_wave[4];
+__global__ __launch_bounds__(GATHER_NT) void topk_gather_kernel(SeqTab st, ChunkTab ct, int h,
+                                                              const float *__restrict__ scores,
+                                                              const int *__restrict__ budgets,
+                                                              TopkBufs tb) {
+  __shared__ __align__(16) unsigned lh[RADIX_BINS];
+  __shared__ unsigned sh[2];
+  __shared__ int sh_above, sh_wave[GATHER_NT / 64];
   const int tid = threadIdx.x;
   const int b = find_seq(ct, st.batch, blockIdx.x);
   // the first sequence's facts sit at fixed places of the kernel arguments and arrive with the
@@ -299,21 +294,29 @@ __global__ __launch_bounds__(256) void topk_gather_kernel(SeqTab st, ChunkTab ct
   const float *row = scores + soff + (size_t)c * n;
   const int j0 = chunk * SEL_CHUNK;
   const int j1 = min(n, j0 + SEL_CHUNK);
-  constexpr int EPB = SEL_CHUNK / 256;
-  float sc[EPB];
+  constexpr int NT = GATHER_NT, EPT = SEL_CHUNK / NT;
+  float sc[EPT];
 #pragma unroll
-  for (int i = 0; i < EPB; ++i) sc[i] = row[min(j0 + tid + 256 * i, j1 - 1)];
-  const Bins<RADIX_BINS> mine = load_bins<RADIX_BINS>(
-      LAYER ? tb.hist_tot0 + (size_t)b * RADIX_BINS : tb.hist0 + (size_t)seg * RADIX_BINS);
+  for (int i = 0; i < EPT; ++i) sc[i] = row[min(j0 + tid + NT * i, j1 - 1)];
+  const unsigned *hist = LAYER ? tb.hist_tot0 + (size_t)b * RADIX_BINS : tb.hist0 + (size_t)seg * RADIX_BINS;
+  WaveBins<RADIX_BINS> mine;
+  if (tid < 64) mine = load_bins<RADIX_BINS>(hist);
   const int krem = LAYER ? st.Bp[b] : budgets[seg];
-  for (int i = tid; i < RADIX_BINS; i += 256) lh[i] = 0u;
+  reinterpret_cast<uint2 *>(lh)[tid] = make_uint2(0u, 0u);
   if (tid == 0) sh_above = 0;
   if (krem <= 0) {                                     // nothing to select in this scope
     if (tid == 0) { tb.note[blk].entries = 0; tb.note[blk].above = 0; }
     return;
   }
+  if (tid < 64) {
+    unsigned d0;
+    int r0;
+    wave_locate<RADIX_BINS>(mine, hist, krem, d0, r0);
+    if (tid == 0) sh[0] = d0;
+  }
+  __syncthreads();
   unsigned *gh = LAYER ? tb.hist1_tot + (size_t)b * RADIX_BINS : tb.hist1 + (size_t)seg * RADIX_BINS;
-  gather_block<256>(sc, j0, j1, mine, krem, tb, blk, gh, lh, sh, &sh_above, sh_wave);
+  gather_block(sc, j0, j1, sh[0], tb, blk, gh, lh, &sh_above, sh_wave);
 }
 
 // Bucket d1 of one gather block: [first, first + count) in its entries.
@@ -436,80 +439,118 @@ __device__ __forceinline__ void for_bucket(const unsigned short *ent, int first,
   }
 }
 
-// Last digit among the elements sharing the 22-bit prefix, from a finished 1024-bin histogram in
-// LDS: digit d2 whose bin holds rank r1, and the rank inside it = the number of ties to take.
-__device__ __forceinline__ void locate_last(const unsigned *lh2, int r1, unsigned &d2, int &ties,
-                                            unsigned *sh) {
-  Bins<1024> m;
-  const int t = threadIdx.x & 255;
-  const unsigned keep = threadIdx.x < 256 ? 0xFFFFFFFFu : 0u;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) m.v[i] = lh2[t * 4 + i] & keep;
-  locate<1024>(m, r1, d2, ties, sh);
-}
-
 // What a block that knows a sequence's whole layer scope holds in LDS: per head the elements above
 // the layer's threshold and at it, then the budgets.
 constexpr int FIN_NT = 1024;                           // sixteen wavefronts
 struct LayerCounts {
   int gt[64], eq[64];
-  long long rem[64];
   int base[64];                                        // the budgets, when safeguard() is done
 };
+
+// Words of LDS that the searches of one scope share.
+struct Searches {
+  unsigned prefix[4];                                  // first digit, second digit, rank among those that share both
+  unsigned last[2];                                    // last digit, how many at the threshold are taken
+  unsigned total, many;                                // elements that share the prefix; 1: a bucket too long for one thread
+};
+// First and second digit from two finished histograms in memory, by the first wavefront of a block; the barrier that
+// shows them to the others is the caller's.
+__device__ __forceinline__ void locate_prefix(const WaveBins<RADIX_BINS> &m0, const WaveBins<RADIX_BINS> &m1,
+                                              const unsigned *hist0, const unsigned *hist1, int krem, Searches &sr) {
+  unsigned d0, d1;
+  int r0, r1;
+  wave_locate<RADIX_BINS>(m0, hist0, krem, d0, r0);
+  wave_locate<RADIX_BINS>(m1, hist1, r0, d1, r1);
+  if ((threadIdx.x & 63) == 0) {
+    sr.prefix[0] = d0;
+    sr.prefix[1] = d1;
+    sr.prefix[2] = (unsigned)r1;
+  }
+}
+constexpr int EARLY = 4;                               // entries of a thread's bucket asked for before anybody knows how many there are
+struct Bucket {
+  int first, count;
+  unsigned short early[EARLY];
+};
+__device__ __forceinline__ void load_early(const TopkBufs &tb, size_t blk, Bucket &bk) {
+  const unsigned short *ent = tb.entries + blk * ENT_PER_BLOCK + bk.first;
+#pragma unroll
+  for (int i = 0; i < EARLY; ++i) bk.early[i] = i < bk.count ? ent[i] : (unsigned short)0;
+}
 
 // Layer scope from the gather kernel's results, by a block of sixteen wavefronts: Algorithm 1's
 // counts.  Returns the number of threshold-valued elements to take, in flat order.
 // scratch: 1024 + HOLD_LAYER words of LDS.
 __device__ __forceinline__ int layer_counts(const ChunkTab &ct, int h, int b, int Bp, const TopkBufs &tb,
-                                            LayerCounts &lc, unsigned *sh, int *sh_scan,
-                                            unsigned *scratch) {
+                                            LayerCounts &lc, Searches &sr, unsigned *scratch) {
   unsigned *lh2 = scratch, *held = scratch + 1024;     // held: (last digit << 6) | head
   int *sh_gt = lc.gt, *sh_eq = lc.eq;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (tid < 64) { sh_gt[tid] = 0; sh_eq[tid] = 0; }
-  for (int i = tid; i < 1024; i += FIN_NT) lh2[i] = 0u;
-  const Bins<RADIX_BINS> m0 = load_bins<RADIX_BINS>(tb.hist_tot0 + (size_t)b * RADIX_BINS);
-  const Bins<RADIX_BINS> m1 = load_bins<RADIX_BINS>(tb.hist1_tot + (size_t)b * RADIX_BINS);
-  unsigned d0 = 0, d1 = 0, d2 = 0;
-  int r0 = 0, r1 = 0, ties = 0;
+  const unsigned *hist0 = tb.hist_tot0 + (size_t)b * RADIX_BINS, *hist1 = tb.hist1_tot + (size_t)b * RADIX_BINS;
+  WaveBins<RADIX_BINS> m0, m1;
+  if (tid < 64) {
+    m0 = load_bins<RADIX_BINS>(hist0);
+    m1 = load_bins<RADIX_BINS>(hist1);
+    sh_gt[tid] = 0;
+    sh_eq[tid] = 0;
+  }
+  lh2[tid] = 0u;
+  static_assert(FIN_NT == 1024, "a bin per thread");
+  if (tid == 0) sr.total = sr.many = 0u;
+  unsigned d2 = 0;
+  int ties = 0;
   const int blk0 = ct.off[b] * h, blk1 = ct.off[b + 1] * h;      // this sequence's gather blocks
   if (Bp > 0) {
-    locate<RADIX_BINS>(m0, Bp, d0, r0, sh);
-    locate<RADIX_BINS>(m1, r0, d1, r1, sh);
+    if (tid < 64) locate_prefix(m0, m1, hist0, hist1, Bp, sr);
+    __syncthreads();
+    const unsigned d1 = sr.prefix[1];
+    const int r1 = (int)sr.prefix[2];
     // the elements under (d0, d1): bucket d1 of every block.  Count them first.
     // The block's elements above the prefix go to its head's count right away: those above d0,
     // and under d0 those in the buckets after d1.
     int mine_cnt = 0, longest = 0;
-    int first0 = 0, count0 = 0;                        // the first of this thread's blocks, kept
+    Bucket mine = {0, 0, {0}};                         // the first of this thread's blocks
     for (int k = blk0 + tid; k < blk1; k += FIN_NT) {
       int first, count;
       bucket_of(tb, (size_t)k, d1, first, count);
-      if (k == blk0 + tid) { first0 = first; count0 = count; }
+      if (k == blk0 + tid) {
+        mine.first = first;
+        mine.count = count;
+        load_early(tb, (size_t)k, mine);
+      }
       mine_cnt += count;
       longest = max(longest, count);
       const int total = min(max(tb.note[k].entries, 0), ENT_PER_BLOCK);
       const int over = tb.note[k].above + (total - first - count);
       if (over) atomicAdd(&sh_gt[k % h], over);
     }
-    int incl;
-    const int total = block_scan_incl<FIN_NT>(mine_cnt, incl, sh_scan);
+    // (the held elements' order is of no account, so that a thread's place among them needs no scan)
+    unsigned at = 0;
+    if (mine_cnt) at = atomicAdd(&sr.total, (unsigned)mine_cnt);
+    if (longest > SERIAL_MAX) sr.many = 1u;
+    __syncthreads();
+    const int total = (int)sr.total;
     // (a thread copies its blocks' buckets one element after the other: only short ones)
-    if (total <= HOLD_LAYER && !__syncthreads_or(longest > SERIAL_MAX)) {
+    if (total <= HOLD_LAYER && !sr.many) {
       // few: every thread copies its blocks' buckets into LDS, then digit and counts from there
-      int at = incl - mine_cnt;
       for (int k = blk0 + tid; k < blk1; k += FIN_NT) {
-        int first = first0, count = count0;
-        if (k != blk0 + tid) bucket_of(tb, (size_t)k, d1, first, count);
+        const bool own = k == blk0 + tid;
+        int first = mine.first, count = mine.count;
+        if (!own) bucket_of(tb, (size_t)k, d1, first, count);
         const unsigned short *ent = tb.entries + (size_t)k * ENT_PER_BLOCK + first;
         const unsigned head = (unsigned)(k % h);
-        for (int i = 0; i < count; ++i) {
-          const unsigned v = (((unsigned)ent[i] & 1023u) << 6) | head;
+        auto hold = [&](unsigned e) {
+          const unsigned v = ((e & 1023u) << 6) | head;
           held[at++] = v;
           atomicAdd(&lh2[v >> 6], 1u);
-        }
+        };
+#pragma unroll
+        for (int i = 0; i < EARLY; ++i)
+          if (own && i < count) hold(mine.early[i]);
+        for (int i = own ? EARLY : 0; i < count; ++i) hold(ent[i]);
       }
       __syncthreads();
-      locate_last(lh2, r1, d2, ties, sh);
+      block_locate<1024>(lh2, r1, d2, ties, sr.last);
       for (int i = tid; i < total; i += FIN_NT) {
         const unsigned v = held[i];
         if ((v >> 6) > d2) atomicAdd(&sh_gt[v & 63u], 1);
@@ -529,7 +570,7 @@ __device__ __forceinline__ int layer_counts(const ChunkTab &ct, int h, int b, in
       }
       wh.flush();
       __syncthreads();
-      locate_last(lh2, r1, d2, ties, sh);
+      block_locate<1024>(lh2, r1, d2, ties, sr.last);
       if (blk0 + wv < blk1) bucket_of(tb, (size_t)(blk0 + wv), d1, nfirst, ncount);
       for (int k = blk0 + wv; k < blk1; k += FIN_NT / 64) {
         const int first = nfirst, count = ncount;
@@ -548,54 +589,34 @@ __device__ __forceinline__ int layer_counts(const ChunkTab &ct, int h, int b, in
 }
 
 // The safeguard of Alg. 2 l.8 on the counts, by the first wavefront of a block (the others pass
-// through; a barrier makes the budgets in lc.base visible to them).  One lane per head (h <= 64):
-// every step is a count over the other heads, so the lanes never wait for each other and the 64-bit
-// divisions run side by side.
+// through; a barrier makes the budgets in lc.base visible to them).  One lane per head (h <= 64), and
+// nothing between them but scans and lane reads (through LDS, a read per head and step, it took 0.9 us at
+// eight heads, now 0.3).
 __device__ __forceinline__ void safeguard(int h, int Bp, int alpha_fix, int ties, LayerCounts &lc) {
   if (threadIdx.x >= 64) return;
-  const int *sh_gt = lc.gt, *sh_eq = lc.eq;
-  long long *sh_rem = lc.rem;
-  int *sh_base = lc.base;
   const int c = threadIdx.x;
   const bool live = c < h;
+  const int gt = lc.gt[c], eq = lc.eq[c];              // (zero past the last head)
   const long long one = 65536, a = alpha_fix;
-  long long rem = -1;
-  int base = 0;
-  if (live) {
-    long long before = 0;                              // threshold-valued elements of earlier heads
-    for (int i = 0; i < c; ++i) before += sh_eq[i];
-    long long avail = (long long)ties - before;        // ties still to take when head c's turn comes
-    if (avail < 0) avail = 0;
-    const long long take = sh_eq[c] < avail ? sh_eq[c] : avail;
-    const long long f = (long long)sh_gt[c] + take;     // Algorithm 1: B*_c = f_c
-    const long long num = (one - a) * h * f + a * (long long)Bp;   // x_c = num / den, den = 65536 h
-    // num / 65536 = (1-alpha) h f + alpha B' <= h f + B' < 2^32 (both sums are below 2^31), so
-    // the division by den is a shift and one 32-bit division; the remainders recombine exactly
-    const unsigned t = (unsigned)(num >> 16);
-    const unsigned tq = t / (unsigned)h, tr = t - tq * (unsigned)h;
-    base = (int)tq;
-    rem = ((long long)tr << 16) | (num & 0xFFFF);
-  }
-  sh_rem[c] = rem;
-  sh_base[c] = base;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  if (!live) return;
-  long long given = 0;
+  // threshold-valued elements of earlier heads, at most all of a sequence's scores
+  const int before = wave_scan_incl(eq) - eq;
+  const int avail = max(ties - before, 0);             // ties still to take when head c's turn comes
+  const long long f = (long long)gt + min(eq, avail);  // Algorithm 1: B*_c = f_c
+  const long long num = (one - a) * h * f + a * (long long)Bp;   // x_c = num / den, den = 65536 h
+  // num / 65536 = (1-alpha) h f + alpha B' <= h f + B' < 2^32 (both sums are below 2^31), so
+  // the division by den is a shift and one 32-bit division; the remainders recombine exactly
+  const unsigned t = (unsigned)(num >> 16);
+  const unsigned tq = t / (unsigned)h, tr = t - tq * (unsigned)h;
+  int base = live ? (int)tq : 0;
+  const int rem = live ? (int)((tr << 16) | (unsigned)(num & 0xFFFF)) : -1;      // below 65536 h <= 2^22
+  const int left = Bp - wave_sum(base);                // 0 <= left < h
   int rank = 0;                                        // heads that come first for a spare unit
   for (int i = 0; i < h; ++i) {
-    given += sh_base[i];
-    rank += (sh_rem[i] > rem) || (sh_rem[i] == rem && i < c);
+    const int other = __builtin_amdgcn_readlane(rem, i);
+    rank += other > rem || (other == rem && i < c);
   }
-  const int left = (int)((long long)Bp - given);       // 0 <= left < h
-  if (rank < left) base += 1;                          // largest remainders, ties to the lower head
-  // (every lane has read the others' floors before any of them is replaced: one wavefront, and the
-  // fence below keeps the order)
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  sh_base[c] = base;
+  if (live && rank < left) base += 1;                  // largest remainders, ties to the lower head
+  lc.base[c] = base;
 }
 
 // Layer scope, second kernel.  One block per sequence.
@@ -603,13 +624,12 @@ __global__ __launch_bounds__(FIN_NT) void alloc_finish_kernel(SeqTab st, ChunkTa
                                                               int alpha_fix, TopkBufs tb,
                                                               int *__restrict__ budgets,
                                                               int *__restrict__ cu) {
-  __shared__ unsigned sh[8];
-  __shared__ int sh_scan[FIN_NT / 64];
-  __shared__ unsigned scratch[1024 + HOLD_LAYER];
+  __shared__ Searches sr;
+  __shared__ __align__(16) unsigned scratch[1024 + HOLD_LAYER];
   __shared__ LayerCounts lc;
   const int b = blockIdx.x, c = threadIdx.x;
   const int Bp = st.Bp[b];
-  const int ties = layer_counts(ct, h, b, Bp, tb, lc, sh, sh_scan, scratch);
+  const int ties = layer_counts(ct, h, b, Bp, tb, lc, sr, scratch);
   safeguard(h, Bp, alpha_fix, ties, lc);
   __syncthreads();
   if (c >= h) return;
@@ -627,13 +647,15 @@ __global__ __launch_bounds__(FIN_NT) void alloc_finish_kernel(SeqTab st, ChunkTa
 // block in the time in which one block does it.  What it saves is a launch: finish + gather / this kernel, us,
 // 32768 keys x 8 heads 12.5 / 10.0 (the whole step 67.3 / 65.2), 131072 x 8 14.6 / 11.0 (135.1 / 131.2), four of up
 // to 30000 x 8 29.6 / 25.8 (86.4 / 82.3).
+static_assert(FIN_NT == GATHER_NT, "both halves take the same block");
 __global__ __launch_bounds__(FIN_NT) void finish_gather_kernel(SeqTab st, ChunkTab ct, int h, int w, int alpha_fix,
                                                                const float *__restrict__ scores, TopkBufs layer,
                                                                TopkBufs head, int *__restrict__ budgets,
                                                                int *__restrict__ cu) {
-  __shared__ unsigned sh[8];
-  __shared__ int sh_scan[FIN_NT / 64], sh_above;
-  __shared__ unsigned scratch[1024 + HOLD_LAYER];      // the layer scope's, then the head's second digits
+  __shared__ Searches sr;
+  __shared__ int sh_wave[FIN_NT / 64], sh_above;
+  __shared__ unsigned sh_first;
+  __shared__ __align__(16) unsigned scratch[1024 + HOLD_LAYER];      // the layer scope's, then the head's second digits
   __shared__ LayerCounts lc;
   static_assert(RADIX_BINS <= 1024 + HOLD_LAYER, "the digits fit into the scratch words");
   const int tid = threadIdx.x;
@@ -645,16 +667,27 @@ __global__ __launch_bounds__(FIN_NT) void finish_gather_kernel(SeqTab st, ChunkT
   const float *row = scores + st.score_off[b] + (size_t)c * n;
   const int j0 = chunk * SEL_CHUNK;
   const int j1 = min(n, j0 + SEL_CHUNK);
-  float sc[SEL_CHUNK / FIN_NT];
+  constexpr int EPT = SEL_CHUNK / FIN_NT;
+  float sc[EPT];
 #pragma unroll
-  for (int i = 0; i < SEL_CHUNK / FIN_NT; ++i) sc[i] = row[min(j0 + tid + FIN_NT * i, j1 - 1)];
-  const Bins<RADIX_BINS> mine = load_bins<RADIX_BINS>(head.hist0 + (size_t)seg * RADIX_BINS);
-  const int ties = layer_counts(ct, h, b, Bp, layer, lc, sh, sh_scan, scratch);
+  for (int i = 0; i < EPT; ++i) sc[i] = row[min(j0 + tid + FIN_NT * i, j1 - 1)];
+  const unsigned *hist = head.hist0 + (size_t)seg * RADIX_BINS;
+  WaveBins<RADIX_BINS> mine;
+  if (tid < 64) mine = load_bins<RADIX_BINS>(hist);
+  const int ties = layer_counts(ct, h, b, Bp, layer, lc, sr, scratch);
   safeguard(h, Bp, alpha_fix, ties, lc);
-  __syncthreads();                                     // the budgets; and nobody reads the scratch words any more
-  const int bud = lc.base[c];
-  for (int i = tid; i < RADIX_BINS; i += FIN_NT) scratch[i] = 0u;
+  // (nobody reads the scratch words any more)
+  reinterpret_cast<uint2 *>(scratch)[tid] = make_uint2(0u, 0u);
   if (tid == 0) sh_above = 0;
+  if (tid < 64) {                                      // (the wavefront that has the budgets)
+    unsigned d0 = 0;
+    int r0;
+    const int own = __builtin_amdgcn_readfirstlane(lc.base[c]);
+    if (own > 0) wave_locate<RADIX_BINS>(mine, hist, own, d0, r0);
+    if (tid == 0) sh_first = d0;
+  }
+  __syncthreads();                                     // the budgets, the first digit and the cleared words
+  const int bud = lc.base[c];
   if (chunk == 0 && tid == 0) {
     int run = st.out_off[b] + bud + w;
     for (int i = 0; i < c; ++i) run += lc.base[i] + w;
@@ -667,23 +700,22 @@ __global__ __launch_bounds__(FIN_NT) void finish_gather_kernel(SeqTab st, ChunkT
     if (tid == 0) { head.note[blk].entries = 0; head.note[blk].above = 0; }
     return;
   }
-  gather_block<FIN_NT>(sc, j0, j1, mine, bud, head, blk, head.hist1 + (size_t)seg * RADIX_BINS, scratch, sh, &sh_above,
-                       sh_scan);
+  gather_block(sc, j0, j1, sh_first, head, blk, head.hist1 + (size_t)seg * RADIX_BINS, scratch, &sh_above, sh_wave);
 }
 
-constexpr int EPT = SEL_CHUNK / 256;   // positions per thread in the emit kernel, 256 apart
-
 // Head scope, second kernel.  Block (chunk, head) writes the kept positions of its 4096.
-__global__ __launch_bounds__(256) void emit_write_kernel(
+template <int NT>
+__global__ __launch_bounds__(NT) void emit_write_kernel(
     SeqTab st, ChunkTab ct, int h, int w, const float *__restrict__ scores, TopkBufs tb,
     const int *__restrict__ budgets, const int *__restrict__ cu, int *__restrict__ indices,
     int rows_total) {
-  __shared__ unsigned sh[8];
-  __shared__ int sh_scan[4];
-  __shared__ int tab[EPT * 4];                         // per round and wavefront: above << 16 | at the threshold
-  __shared__ unsigned lh2[1024];
+  constexpr int EPT = SEL_CHUNK / NT, WV = NT / 64;    // positions per thread, NT apart; wavefronts
+  __shared__ Searches sr;
+  __shared__ int tab[EPT * WV];                   // per round and wavefront: above << 16 | at the threshold
+  __shared__ __align__(16) unsigned lh2[1024];
   __shared__ unsigned held[HOLD_HEAD];                 // (last digit << 1) | (lies in an earlier block)
   __shared__ int sh_cnt[2];
+  static_assert(EPT * WV == 64, "a lane per table entry");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int b = find_seq(ct, st.batch, blockIdx.x);
   int n = st.n[0], cfirst = ct.off[0], soff = st.score_off[0];   // as in the gather kernel
@@ -696,37 +728,46 @@ __global__ __launch_bounds__(256) void emit_write_kernel(
   const int bud = budgets[seg];
   const float *row = scores + soff + (size_t)c * n;
 
-  // Positions are dealt out round by round (chunk start + 256 i + tid): the loads are whole lines, and
-  // position order is round, wavefront, lane, where a ballot gives every lane its place.  (16
-  // consecutive positions per thread, as before, made every load instruction touch 64 lines.)  Issued
-  // before the scans below; places past the end get key 0, which is never above or at a threshold.
+  // Positions are dealt out round by round (chunk start + NT i + tid): the loads are whole lines, and
+  // position order is round, wavefront, lane, where a ballot gives every lane its place.  Issued
+  // before the searches below; places past the end get key 0, which is never above or at a threshold.
   const int j0 = chunk * SEL_CHUNK + tid;
   unsigned keys[EPT];
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) keys[i] = __float_as_uint(row[min(j0 + 256 * i, n - 1)]);
-  const Bins<RADIX_BINS> m0 = load_bins<RADIX_BINS>(tb.hist0 + (size_t)seg * RADIX_BINS);
-  const Bins<RADIX_BINS> m1 = load_bins<RADIX_BINS>(tb.hist1 + (size_t)seg * RADIX_BINS);
-  for (int i = tid; i < 1024; i += 256) lh2[i] = 0u;
+  for (int i = 0; i < EPT; ++i) keys[i] = __float_as_uint(row[min(j0 + NT * i, n - 1)]);
+  const unsigned *hist0 = tb.hist0 + (size_t)seg * RADIX_BINS, *hist1 = tb.hist1 + (size_t)seg * RADIX_BINS;
+  WaveBins<RADIX_BINS> m0, m1;
+  if (tid < 64) {
+    m0 = load_bins<RADIX_BINS>(hist0);
+    m1 = load_bins<RADIX_BINS>(hist1);
+  }
+  for (int i = tid; i < 1024; i += NT) lh2[i] = 0u;
   if (tid < 2) sh_cnt[tid] = 0;
+  if (tid == 0) sr.total = sr.many = 0u;
 
   unsigned thr = 0xFFFFFFFFu;                          // no key is above, no tie is taken
   int ties = 0;
   int pg = 0, pe = 0;                                  // kept / threshold-valued positions of earlier blocks
   if (bud > 0) {
-    unsigned d0, d1, d2;
-    int r0, r1;
-    locate<RADIX_BINS>(m0, bud, d0, r0, sh);
-    locate<RADIX_BINS>(m1, r0, d1, r1, sh);
-    // Every block of the head (thread k takes block k, k + 256, ...): how many of its elements
+    if (tid < 64) locate_prefix(m0, m1, hist0, hist1, bud, sr);
+    __syncthreads();
+    const unsigned d0 = sr.prefix[0], d1 = sr.prefix[1];
+    const int r1 = (int)sr.prefix[2];
+    unsigned d2;
+    // Every block of the head (thread k takes block k, k + NT, ...): how many of its elements
     // share the prefix (d0, d1), and, for the blocks in front of this one, how many lie above it:
     // those above d0, and under d0 those in the buckets after d1.
     int mine_cnt = 0, longest = 0;
-    int first0 = 0, count0 = 0;                        // the first of this thread's blocks, kept
-    for (int k = tid; k < nchunks; k += 256) {
+    Bucket mine = {0, 0, {0}};                         // the first of this thread's blocks
+    for (int k = tid; k < nchunks; k += NT) {
       const size_t kb = (size_t)(cfirst + k) * h + c;
       int first, count;
       bucket_of(tb, kb, d1, first, count);
-      if (k == tid) { first0 = first; count0 = count; }
+      if (k == tid) {
+        mine.first = first;
+        mine.count = count;
+        load_early(tb, kb, mine);
+      }
       mine_cnt += count;
       longest = max(longest, count);
       if (k < chunk) {
@@ -734,25 +775,32 @@ __global__ __launch_bounds__(256) void emit_write_kernel(
         pg += tb.note[kb].above + (total - first - count);
       }
     }
-    int incl;
-    const int total = block_scan_incl<256>(mine_cnt, incl, sh_scan);
-    if (total <= HOLD_HEAD && !__syncthreads_or(longest > SERIAL_MAX)) {
-      int at = incl - mine_cnt;
-      for (int k = tid; k < nchunks; k += 256) {
+    unsigned at = 0;                                   // (as in layer_counts)
+    if (mine_cnt) at = atomicAdd(&sr.total, (unsigned)mine_cnt);
+    if (longest > SERIAL_MAX) sr.many = 1u;
+    __syncthreads();
+    const int total = (int)sr.total;
+    if (total <= HOLD_HEAD && !sr.many) {
+      for (int k = tid; k < nchunks; k += NT) {
         const size_t kb = (size_t)(cfirst + k) * h + c;
-        int first = first0, count = count0;
-        if (k != tid) bucket_of(tb, kb, d1, first, count);
+        const bool own = k == tid;
+        int first = mine.first, count = mine.count;
+        if (!own) bucket_of(tb, kb, d1, first, count);
         const unsigned short *ent = tb.entries + kb * ENT_PER_BLOCK + first;
         const unsigned earlier = k < chunk ? 1u : 0u;
-        for (int i = 0; i < count; ++i) {
-          const unsigned v = ent[i] & 1023u;
+        auto hold = [&](unsigned e) {
+          const unsigned v = e & 1023u;
           held[at++] = (v << 1) | earlier;
           atomicAdd(&lh2[v], 1u);
-        }
+        };
+#pragma unroll
+        for (int i = 0; i < EARLY; ++i)
+          if (own && i < count) hold(mine.early[i]);
+        for (int i = own ? EARLY : 0; i < count; ++i) hold(ent[i]);
       }
       __syncthreads();
-      locate_last(lh2, r1, d2, ties, sh);
-      for (int i = tid; i < total; i += 256) {
+      block_locate<1024>(lh2, r1, d2, ties, sr.last);
+      for (int i = tid; i < total; i += NT) {
         const unsigned v = held[i];
         if (v & 1u) {
           pg += (v >> 1) > d2;
@@ -764,21 +812,21 @@ __global__ __launch_bounds__(256) void emit_write_kernel(
       WaveHist wh(lh2);
       int nfirst = 0, ncount = 0;
       if (wv < nchunks) bucket_of(tb, (size_t)(cfirst + wv) * h + c, d1, nfirst, ncount);
-      for (int k = wv; k < nchunks; k += 4) {
+      for (int k = wv; k < nchunks; k += WV) {
         const size_t kb = (size_t)(cfirst + k) * h + c;
         const int first = nfirst, count = ncount;
-        if (k + 4 < nchunks) bucket_of(tb, (size_t)(cfirst + k + 4) * h + c, d1, nfirst, ncount);
+        if (k + WV < nchunks) bucket_of(tb, (size_t)(cfirst + k + WV) * h + c, d1, nfirst, ncount);
         for_bucket(tb.entries + kb * ENT_PER_BLOCK, first, count, wh);
       }
       wh.flush();
       __syncthreads();
-      locate_last(lh2, r1, d2, ties, sh);
+      block_locate<1024>(lh2, r1, d2, ties, sr.last);
       CountAbove ca(d2);
       if (wv < chunk) bucket_of(tb, (size_t)(cfirst + wv) * h + c, d1, nfirst, ncount);
-      for (int k = wv; k < chunk; k += 4) {
+      for (int k = wv; k < chunk; k += WV) {
         const size_t kb = (size_t)(cfirst + k) * h + c;
         const int first = nfirst, count = ncount;
-        if (k + 4 < chunk) bucket_of(tb, (size_t)(cfirst + k + 4) * h + c, d1, nfirst, ncount);
+        if (k + WV < chunk) bucket_of(tb, (size_t)(cfirst + k + WV) * h + c, d1, nfirst, ncount);
         for_bucket(tb.entries + kb * ENT_PER_BLOCK, first, count, ca);
       }
       pg += ca.gt;
@@ -786,40 +834,41 @@ __global__ __launch_bounds__(256) void emit_write_kernel(
     }
     thr = (d0 << 21) | (d1 << 10) | d2;
     if (thr == 0u) ties = 0;                           // (no key of a score: inconsistent input)
+  } else {
+    __syncthreads();                                   // the cleared counters
   }
-  __syncthreads();
-  pg = wave_sum(pg);
-  pe = wave_sum(pe);
-  if (lane == 0) { atomicAdd(&sh_cnt[0], pg); atomicAdd(&sh_cnt[1], pe); }
+  if (__ballot((pg | pe) != 0)) {
+    pg = wave_sum(pg);
+    pe = wave_sum(pe);
+    if (lane == 0) { atomicAdd(&sh_cnt[0], pg); atomicAdd(&sh_cnt[1], pe); }
+  }
 
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     const unsigned key = key_of(__uint_as_float(keys[i]));
-    keys[i] = j0 + 256 * i < n ? key : 0u;
+    keys[i] = j0 + NT * i < n ? key : 0u;
     const int g = __popcll(__ballot(keys[i] > thr)), e = __popcll(__ballot(keys[i] == thr));
-    if (lane == 0) tab[i * 4 + wv] = (g << 16) | e;    // (a block holds 4096 positions: 13 bits each)
+    if (lane == 0) tab[i * WV + wv] = (g << 16) | e;    // (a block holds 4096 positions: 13 bits each)
   }
   __syncthreads();
-  if (wv == 0) {
-    const int v = tab[lane];
-    tab[lane] = wave_scan_incl(v) - v;
-  }
-  __syncthreads();
+  // every wavefront scans the table for itself
+  const int in_table = tab[lane], upto = wave_scan_incl(in_table) - in_table;
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     const unsigned long long bg = __ballot(keys[i] > thr), be = __ballot(keys[i] == thr);
     if ((bg | be) == 0) continue;
     // over all earlier positions of the head
-    const int ng = sh_cnt[0] + (tab[i * 4 + wv] >> 16) +
+    const int front = __builtin_amdgcn_readlane(upto, i * WV + __builtin_amdgcn_readfirstlane(wv));
+    const int ng = sh_cnt[0] + (front >> 16) +
                    (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bg >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bg, 0u));
-    const int ne = sh_cnt[1] + (tab[i * 4 + wv] & 0xFFFF) +
+    const int ne = sh_cnt[1] + (front & 0xFFFF) +
                    (int)__builtin_amdgcn_mbcnt_hi((unsigned)(be >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)be, 0u));
     const int pos = out0 + ng + min(ne, ties);
     if ((keys[i] > thr || (keys[i] == thr && ne < ties)) && (unsigned)pos < (unsigned)rows_total)
-      indices[pos] = j0 + 256 * i;
+      indices[pos] = j0 + NT * i;
   }
   if (chunk == 0) {
-    for (int rr = tid; rr < w; rr += 256)
+    for (int rr = tid; rr < w; rr += NT)
       if ((unsigned)(out0 + bud + rr) < (unsigned)rows_total) indices[out0 + bud + rr] = n + rr;
   }
 }
@@ -835,15 +884,6 @@ __global__ __launch_bounds__(256) void emit_write_kernel(
 // ballot per round gives a lane its place.  Bound by latency: one load of the scores (4 bytes per
 // lane, all rounds in flight), three searches of a histogram, one scan.
 constexpr int BLK_NT = 1024, BLK_WV = BLK_NT / 64;
-
-template <int NB> __device__ __forceinline__ Bins<NB> lds_bins(const unsigned *lh) {
-  Bins<NB> m;
-  const int t = threadIdx.x & 255;
-  const unsigned keep = threadIdx.x < 256 ? 0xFFFFFFFFu : 0u;
-#pragma unroll
-  for (int i = 0; i < NB / 256; ++i) m.v[i] = lh[t * (NB / 256) + i] & keep;
-  return m;
-}
 
 // Rounds past the last element are skipped (uniformly); places past it get key 0, which no score has
 // and which is never above or at a threshold.
@@ -875,18 +915,24 @@ __device__ __forceinline__ void count_digit(unsigned *bins, unsigned digit, bool
 constexpr int BLK_LDS = RADIX_BINS + 1024 + RADIX_BINS;   // second, last and first digits
 
 // The key of rank krem >= 1 among the n keys of the block, and how many equal to it are taken.
-// `first`: the scope's finished first-digit histogram (CARRIED).
+// CARRIED: `hist` is the scope's finished first-digit histogram, `first` the first wavefront's part of it.
 template <int EPT, bool CARRIED>
-__device__ __forceinline__ void block_threshold(const unsigned (&keys)[EPT], int n, int krem,
-                                                const Bins<RADIX_BINS> &first, unsigned *lds,
-                                                unsigned *sh, unsigned &thr, int &ties) {
+__device__ __forceinline__ void block_threshold(const unsigned (&keys)[EPT], int n, int krem, const unsigned *hist,
+                                                const WaveBins<RADIX_BINS> &first, unsigned *lds,
+                                                Searches &sr, unsigned &thr, int &ties) {
   const int tid = threadIdx.x;
   unsigned d0, d1, d2;
   int r0, r1;
   __syncthreads();                                     // the caller may still use lds
   for (int i = tid; i < BLK_LDS; i += BLK_NT) lds[i] = 0u;
   if (CARRIED) {
-    locate<RADIX_BINS>(first, krem, d0, r0, sh);       // its barriers also publish the cleared bins
+    if (tid < 64) {
+      wave_locate<RADIX_BINS>(first, hist, krem, d0, r0);
+      if (tid == 0) { sr.prefix[0] = d0; sr.prefix[1] = (unsigned)r0; }
+    }
+    __syncthreads();
+    d0 = sr.prefix[0];
+    r0 = (int)sr.prefix[1];
   } else {
     __syncthreads();
     unsigned *lh0 = lds + RADIX_BINS + 1024;
@@ -894,19 +940,19 @@ __device__ __forceinline__ void block_threshold(const unsigned (&keys)[EPT], int
     for (int i = 0; i < EPT; ++i)
       if (i * BLK_NT < n) count_digit(lh0, keys[i] >> 21, keys[i] != 0u);
     __syncthreads();
-    locate<RADIX_BINS>(lds_bins<RADIX_BINS>(lh0), krem, d0, r0, sh);
+    block_locate<RADIX_BINS>(lh0, krem, d0, r0, sr.prefix);
   }
 #pragma unroll
   for (int i = 0; i < EPT; ++i)
     if (i * BLK_NT < n) count_digit(lds, (keys[i] >> 10) & 2047u, keys[i] >> 21 == d0);
   __syncthreads();
-  locate<RADIX_BINS>(lds_bins<RADIX_BINS>(lds), r0, d1, r1, sh);
+  block_locate<RADIX_BINS>(lds, r0, d1, r1, sr.prefix + 2);
   const unsigned prefix = (d0 << 11) | d1;
 #pragma unroll
   for (int i = 0; i < EPT; ++i)
     if (i * BLK_NT < n) count_digit(lds + RADIX_BINS, keys[i] & 1023u, keys[i] >> 10 == prefix);
   __syncthreads();
-  locate<1024>(lds_bins<1024>(lds + RADIX_BINS), r1, d2, ties, sh);
+  block_locate<1024>(lds + RADIX_BINS, r1, d2, ties, sr.last);
   thr = (prefix << 10) | d2;
   if (thr == 0u) ties = 0;                             // (no key of a score: inconsistent input)
 }
@@ -916,17 +962,18 @@ __device__ __forceinline__ void block_threshold(const unsigned (&keys)[EPT], int
 template <int EPT, bool CARRIED>
 __device__ __forceinline__ int block_layer_counts(const float *__restrict__ scores, int h, int n, int Bp,
                                                   const TopkBufs &tb, int b, unsigned *lds,
-                                                  unsigned *sh, LayerCounts &lc) {
+                                                  Searches &sr, LayerCounts &lc) {
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int total = h * n;
   if (tid < 64) { lc.gt[tid] = 0; lc.eq[tid] = 0; }
   int ties = 0;
   if (Bp > 0) {
     unsigned keys[EPT], thr;
-    Bins<RADIX_BINS> first;
-    if (CARRIED) first = load_bins<RADIX_BINS>(tb.hist_tot0 + (size_t)b * RADIX_BINS);
+    const unsigned *hist = tb.hist_tot0 + (size_t)b * RADIX_BINS;
+    WaveBins<RADIX_BINS> first;
+    if (CARRIED && tid < 64) first = load_bins<RADIX_BINS>(hist);
     load_keys<EPT>(scores, total, keys);
-    block_threshold<EPT, CARRIED>(keys, total, Bp, first, lds, sh, thr, ties);
+    block_threshold<EPT, CARRIED>(keys, total, Bp, hist, first, lds, sr, thr, ties);
     int c = 0, at = wv * 64;                           // head and position of the wavefront's first element
     while (at >= n && c < h) { at -= n; ++c; }
 #pragma unroll
@@ -958,13 +1005,13 @@ __device__ __forceinline__ int block_layer_counts(const float *__restrict__ scor
 // lds: BLK_LDS words; tab: two words per round and wavefront.
 template <int EPT, bool CARRIED>
 __device__ __forceinline__ void block_select(const unsigned (&keys)[EPT], int n, int bud,
-                                             const Bins<RADIX_BINS> &first, int out0, int w,
+                                             const unsigned *hist, const WaveBins<RADIX_BINS> &first, int out0, int w,
                                              int *__restrict__ indices, int rows_total, unsigned *lds,
-                                             unsigned *sh, int *sh_scan, int (&tab)[2][BLK_WV * 16]) {
+                                             Searches &sr, int *sh_scan, int (&tab)[2][BLK_WV * 16]) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   unsigned thr = 0xFFFFFFFFu;                          // no key is above, no tie is taken
   int ties = 0;
-  if (bud > 0) block_threshold<EPT, CARRIED>(keys, n, bud, first, lds, sh, thr, ties);
+  if (bud > 0) block_threshold<EPT, CARRIED>(keys, n, bud, hist, first, lds, sr, thr, ties);
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     int g = 0, e = 0;
@@ -1006,11 +1053,11 @@ __global__ __launch_bounds__(BLK_NT) void alloc_block_kernel(SeqTab st, int h, i
                                                              const float *__restrict__ scores,
                                                              int *__restrict__ budgets,
                                                              int *__restrict__ cu) {
-  __shared__ unsigned sh[8];
-  __shared__ unsigned lds[BLK_LDS];
+  __shared__ Searches sr;
+  __shared__ __align__(16) unsigned lds[BLK_LDS];
   __shared__ LayerCounts lc;
   const int b = blockIdx.x, c = threadIdx.x, Bp = st.Bp[b];
-  const int ties = block_layer_counts<EPT, false>(scores + st.score_off[b], h, st.n[b], Bp, TopkBufs(), b, lds, sh, lc);
+  const int ties = block_layer_counts<EPT, false>(scores + st.score_off[b], h, st.n[b], Bp, TopkBufs(), b, lds, sr, lc);
   safeguard(h, Bp, alpha_fix, ties, lc);
   __syncthreads();
   if (c >= h) return;
@@ -1029,17 +1076,18 @@ __global__ __launch_bounds__(BLK_NT) void select_block_kernel(SeqTab st, int h, 
                                                               const int *__restrict__ budgets,
                                                               const int *__restrict__ cu,
                                                               int *__restrict__ indices, int rows_total) {
-  __shared__ unsigned sh[8];
+  __shared__ Searches sr;
   __shared__ int sh_scan[BLK_WV];
-  __shared__ unsigned lds[BLK_LDS];
+  __shared__ __align__(16) unsigned lds[BLK_LDS];
   __shared__ int tab[2][BLK_WV * 16];
   const int seg = blockIdx.x, b = seg / h, c = seg % h, n = st.n[b];
   unsigned keys[EPT];
-  Bins<RADIX_BINS> first;
+  const unsigned *hist = hist0 + (size_t)seg * RADIX_BINS;
+  WaveBins<RADIX_BINS> first;
   const int out0 = cu[seg], bud = budgets[seg];
-  if (CARRIED) first = load_bins<RADIX_BINS>(hist0 + (size_t)seg * RADIX_BINS);
+  if (CARRIED && threadIdx.x < 64) first = load_bins<RADIX_BINS>(hist);
   load_keys<EPT>(scores + st.score_off[b] + (size_t)c * n, n, keys);
-  block_select<EPT, CARRIED>(keys, n, bud, first, out0, w, indices, rows_total, lds, sh, sh_scan, tab);
+  block_select<EPT, CARRIED>(keys, n, bud, hist, first, out0, w, indices, rows_total, lds, sr, sh_scan, tab);
 }
 
 // Layer scope and head scope of one segment in one block (pipeline mode): every block of a sequence
@@ -1052,18 +1100,20 @@ __global__ __launch_bounds__(BLK_NT) void topk_block_kernel(SeqTab st, ChunkTab 
                                                             int *__restrict__ budgets, int *__restrict__ cu,
                                                             int *__restrict__ indices, int rows_total) {
   static_assert(1024 + HOLD_LAYER >= BLK_LDS, "the head scope's histograms take the layer scope's place");
-  __shared__ unsigned sh[8];
+  __shared__ Searches sr;
   __shared__ int sh_scan[BLK_WV];
-  __shared__ unsigned lds[SHORT ? BLK_LDS : 1024 + HOLD_LAYER];
+  __shared__ __align__(16) unsigned lds[SHORT ? BLK_LDS : 1024 + HOLD_LAYER];
   __shared__ int tab[2][BLK_WV * 16];
   __shared__ LayerCounts lc;
   const int seg = blockIdx.x, b = seg / h, c = seg % h, n = st.n[b], Bp = st.Bp[b];
   const float *all = scores + st.score_off[b];
   unsigned keys[EPT];                                  // requested first, used last
   load_keys<EPT>(all + (size_t)c * n, n, keys);
-  const Bins<RADIX_BINS> first = load_bins<RADIX_BINS>(tb.hist0 + (size_t)seg * RADIX_BINS);
-  const int ties = SHORT ? block_layer_counts<EPT, true>(all, h, n, Bp, tb, b, lds, sh, lc)
-                         : layer_counts(ct, h, b, Bp, tb, lc, sh, sh_scan, lds);
+  const unsigned *hist = tb.hist0 + (size_t)seg * RADIX_BINS;
+  WaveBins<RADIX_BINS> first;
+  if (threadIdx.x < 64) first = load_bins<RADIX_BINS>(hist);
+  const int ties = SHORT ? block_layer_counts<EPT, true>(all, h, n, Bp, tb, b, lds, sr, lc)
+                         : layer_counts(ct, h, b, Bp, tb, lc, sr, lds);
   safeguard(h, Bp, alpha_fix, ties, lc);
   __syncthreads();
   int out0 = st.out_off[b];
@@ -1074,7 +1124,7 @@ __global__ __launch_bounds__(BLK_NT) void topk_block_kernel(SeqTab st, ChunkTab 
     cu[seg + 1] = out0 + bud + w;
     if (seg == 0) cu[0] = 0;
   }
-  block_select<EPT, true>(keys, n, bud, first, out0, w, indices, rows_total, lds, sh, sh_scan, tab);
+  block_select<EPT, true>(keys, n, bud, hist, first, out0, w, indices, rows_total, lds, sr, sh_scan, tab);
 }
 
 }  // namespace
@@ -1149,7 +1199,8 @@ static int longest_row(const SeqTab &st) {
 }
 
 // Where one block per sequence or segment beats the kernels that spread a scope over the chip: a
-// block's passes cost it 0.4 to 0.6 us per 1024 scores, in one compute unit; a launch costs 4 us.
+// block's passes cost it 0.4 to 0.6 us per 1024 scores, in one compute unit; a launch costs 4 us.  (Measured with searches
+// of 0.7 us; those of 0.25 took 2 to 3.5 us off either side.)
 // Sums of kernel times in us, spread-out kernels / block (w = 8, h = 8 unless said):
 //   allocate alone   4800 scores 20.0 / 10.6   16088 20.0 / 16.6; the counts per head make more heads dearer in
 //                    a block (us per call): h = 32 8192 scores 18.1 / 16.1, 12 288 17.8 / 18.3, 16 384 17.5 / 20.3,
@@ -1179,6 +1230,29 @@ size_t topk_spare_bytes(const SeqTab &st, const Dims &dm) {
   const size_t blocks = (size_t)count_chunks(st, SEL_CHUNK) * dm.h_kv;
   return blocks <= FUSED_BLOCKS ? list_bytes(blocks) : 0;
 }
+static void launch_gather(bool layer, const SeqTab &st, const ChunkTab &ct, int h, const float *scores, const int *budgets,
+                          const TopkBufs &tb, hipStream_t s) {
+  const dim3 grid(ct.off[st.batch], h), block(GATHER_NT);
+  if (layer) ADAKV_LAUNCH("alloc_gather", (topk_gather_kernel<true>), grid, block, s, st, ct, h, scores, budgets, tb);
+  else ADAKV_LAUNCH("select_gather", (topk_gather_kernel<false>), grid, block, s, st, ct, h, scores, budgets, tb);
+}
+// Emit has as many threads as leave every block resident at once (its registers let a compute unit hold one block of
+// 1024, two of 512): the fewer positions a lane has to go through, the better, but a second round costs it all again.
+// us, 256 / 512 / 1024 threads: 64 blocks 8.2 / 6.3 / 5.9, 256 8.6 / 6.9 / 6.6, 300 10.2 / 8.5 / 11.6, 400 10.6 / 8.9 / 12.1,
+// 560 11.3 / 13.7 / 17.1 (before, with 256: 9.1, 9.4, 10.5, 10.6, 11.6).
+static void launch_emit(const SeqTab &st, const ChunkTab &ct, int h, int w, const float *scores, const TopkBufs &tb,
+                        const int *budgets, const int *cu, int *indices, int rows, hipStream_t s) {
+  const dim3 grid(ct.off[st.batch], h);
+#define ADAKV_GO(NT)                                                                              \
+  ADAKV_LAUNCH("select_emit", (emit_write_kernel<NT>), grid, dim3(NT), s, st, ct, h, w, scores, tb, budgets, cu, indices, \
+               rows)
+  const int blocks = ct.off[st.batch] * h;
+  if (blocks <= 256) ADAKV_GO(1024);
+  else if (blocks <= 512) ADAKV_GO(512);
+  else ADAKV_GO(256);
+#undef ADAKV_GO
+}
+
 hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores, int *budgets,
                            int *cu_seqlens, char *ws, bool carried, hipStream_t s) {
   const TopkWs p = plan(st, dm);
@@ -1196,9 +1270,7 @@ hipError_t launch_allocate(const SeqTab &st, const Dims &dm, const float *scores
   }
   const ChunkTab ct = make_chunks(st, SEL_CHUNK);
   if (!carried) first_digits("alloc_init", "alloc_pass0", st, ct, h, scores, ws, p, s);
-  dim3 grid(ct.off[st.batch], h), block(256);
-  ADAKV_LAUNCH("alloc_gather", (topk_gather_kernel<true>), grid, block, s, st, ct, h, scores,
-               (const int *)nullptr, tb);
+  launch_gather(true, st, ct, h, scores, nullptr, tb, s);
   ADAKV_LAUNCH("alloc_finish", alloc_finish_kernel, dim3(st.batch), dim3(FIN_NT), s, st, ct, h, dm.w,
                dm.alpha_fix, tb, budgets, cu_seqlens);
   return hipGetLastError();
@@ -1227,11 +1299,8 @@ hipError_t launch_select(const SeqTab &st, const Dims &dm, const float *scores,
   }
   const ChunkTab ct = make_chunks(st, SEL_CHUNK);
   if (!carried) first_digits("select_init", "select_pass0", st, ct, h, scores, ws, p, s);
-  dim3 grid(ct.off[st.batch], h), block(256);
-  ADAKV_LAUNCH("select_gather", (topk_gather_kernel<false>), grid, block, s, st, ct, h, scores,
-               budgets, tb);
-  ADAKV_LAUNCH("select_emit", emit_write_kernel, grid, block, s, st, ct, h, dm.w, scores, tb, budgets,
-               cu_seqlens, indices, rows);
+  launch_gather(false, st, ct, h, scores, budgets, tb, s);
+  launch_emit(st, ct, h, dm.w, scores, tb, budgets, cu_seqlens, indices, rows, s);
   return hipGetLastError();
 }
 
@@ -1250,8 +1319,7 @@ hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, in
     const TopkBufs tb = bufs_of(ws, plan(st, dm));
     const ChunkTab ct = make_chunks(st, SEL_CHUNK);
     if (!in_block)
-      ADAKV_LAUNCH("alloc_gather", (topk_gather_kernel<true>), dim3(ct.off[st.batch], h), dim3(256), s, st, ct, h,
-                   scores, (const int *)nullptr, tb);
+      launch_gather(true, st, ct, h, scores, nullptr, tb, s);
 #define ADAKV_GO(EPT, SHORT)                                                                     \
   ADAKV_LAUNCH("topk_block", (topk_block_kernel<EPT, SHORT>), dim3(nseg), dim3(BLK_NT), s, st, ct, h, dm.w, \
                dm.alpha_fix, scores, tb, budgets, cu_seqlens, indices, rows)
@@ -1265,12 +1333,10 @@ hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, in
   if (carried && lists && lists <= spare_bytes) {
     const ChunkTab ct = make_chunks(st, SEL_CHUNK);
     const TopkBufs tb = bufs_of(ws, plan(st, dm)), head = lists_in(tb, spare, (size_t)ct.off[st.batch] * h);
-    const dim3 grid(ct.off[st.batch], h), block(256);
-    ADAKV_LAUNCH("alloc_gather", (topk_gather_kernel<true>), grid, block, s, st, ct, h, scores, (const int *)nullptr, tb);
-    ADAKV_LAUNCH("topk_finish_gather", finish_gather_kernel, grid, dim3(FIN_NT), s, st, ct, h, dm.w, dm.alpha_fix,
-                 scores, tb, head, budgets, cu_seqlens);
-    ADAKV_LAUNCH("select_emit", emit_write_kernel, grid, block, s, st, ct, h, dm.w, scores, head, budgets, cu_seqlens,
-                 indices, rows);
+    launch_gather(true, st, ct, h, scores, nullptr, tb, s);
+    ADAKV_LAUNCH("topk_finish_gather", finish_gather_kernel, dim3(ct.off[st.batch], h), dim3(FIN_NT), s, st, ct, h, dm.w,
+                 dm.alpha_fix, scores, tb, head, budgets, cu_seqlens);
+    launch_emit(st, ct, h, dm.w, scores, head, budgets, cu_seqlens, indices, rows, s);
     return hipGetLastError();
   }
   const hipError_t e = launch_allocate(st, dm, scores, budgets, cu_seqlens, ws, carried, s);
