@@ -93,63 +93,86 @@ __device__ __forceinline__ int rows_held(const int *cu, const int *seg_len, int 
   return held + (held < cap ? grow : 0);
 }
 
-// Blocks of `split` rows per segment, summed over the segments in front of segment `s_first` of
-// this thread's run (thread t owns segments t*per .. t*per+per-1).  Returns the exclusive prefix;
-// *total gets the sum over all segments.  One call per kernel, by all NWV wavefronts of the
-// workgroup; uses sh[0..NWV-1].
+// What a workgroup works on: part `j` of the `parts` that the `rows` rows of segment s are split into.
+struct Work {
+  int s, j, parts, rows, first_row;
+  bool appended;                               // the last row is the one the call appends
+};
+
+// Finds it from a prefix sum, over the segments, of the parts that their lengths make (blocks of `split` rows).  The
+// same in all lanes.  False: the workgroup has nothing to do (the launch is an upper bound).  The merge kernel finds a
+// segment's partial results through seg_tab; the launch has at least one workgroup per segment, and workgroup s
+// files the entry of segment s.
+//
+// Up to 64 segments every wavefront does it for itself, a segment a lane, without LDS or a barrier (by the other way a
+// workgroup knew its rows 1.5 us after it had started; the kernel over 8 segments of 512 rows 5.4 -> 4.8 us, over 64 of
+// 1500 13.3 -> 12.6).  Beyond, thread t of
+// the workgroup takes segments t*per .. t*per+per-1 and the result goes through sh[0..21].
 template <int NWV = 4>
-__device__ __forceinline__ int scan_blocks(int nseg, int per, int split, int headroom, int grow,
-                                           const int *cu, const int *seg_len, int *sh,
-                                           int *total) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+__device__ __forceinline__ bool find_work(int nseg, int per, int split, int headroom, int grow, const int *cu,
+                                          const int *seg_len, int *sh, int4 *seg_tab, Work &wk) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, blk = (int)blockIdx.x;
+  if (nseg <= 64) {
+    const int s = min(lane, nseg - 1);
+    const int from = cu[s], cap = cu[s + 1] - from + headroom;
+    const int held = min(max(seg_len[s], 0), cap);       // (as in rows_held)
+    const int now = held + (held < cap ? grow : 0);
+    const int nb = lane < nseg ? (now + split - 1) / split : 0;
+    const int upto = wave_scan_incl(nb), first = upto - nb;
+    if (lane == blk && lane < nseg && wv == 0) seg_tab[s] = make_int4(first, nb, now, now - held);
+    const unsigned long long here = __ballot(blk >= first && blk < upto);
+    if (here == 0) return false;
+    const int L = __ffsll(here) - 1;
+    wk.s = L;
+    wk.j = blk - __builtin_amdgcn_readlane(first, L);
+    wk.parts = __builtin_amdgcn_readlane(nb, L);
+    wk.rows = __builtin_amdgcn_readlane(now, L);
+    wk.first_row = __builtin_amdgcn_readlane(from, L);
+    wk.appended = __builtin_amdgcn_readlane(now - held, L) != 0;
+    return true;
+  }
   int mine = 0;
   for (int i = 0; i < per; ++i) {
     const int s = tid * per + i;
     if (s < nseg) mine += (rows_held(cu, seg_len, s, headroom, grow) + split - 1) / split;
   }
-  int inc = mine;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
-  }
+  const int inc = wave_scan_incl(mine);
   if (lane == 63) sh[wv] = inc;
   __syncthreads();
-  int before = 0, all = 0;
+  int before = 0, total = 0;
 #pragma unroll
   for (int i = 0; i < NWV; ++i) {
     const int v = sh[i];
     if (i < wv) before += v;
-    all += v;
+    total += v;
   }
-  *total = all;
-  return before + inc - mine;
-}
-
-// The thread whose run holds this workgroup's segment writes it to sh[16..21] (segment, split, rows,
-// first row, 1 if the last row is the one the call appends, splits of the segment).  The merge kernel finds a segment's
-// partial results through seg_tab; the launch has at least one workgroup per segment, and workgroup
-// s files the entry of segment s.
-__device__ __forceinline__ void find_block(int excl, int nseg, int per, int split, int headroom, int grow,
-                                           const int *cu, const int *seg_len, int *sh, int4 *seg_tab) {
-  int first = excl;
+  int first = before + inc - mine;
   for (int i = 0; i < per; ++i) {
-    const int s = threadIdx.x * per + i;
+    const int s = tid * per + i;
     if (s >= nseg) break;
     const int now = rows_held(cu, seg_len, s, headroom, grow);
     const int appended = now - rows_held(cu, seg_len, s, headroom, 0);
     const int nb = (now + split - 1) / split;
-    if ((int)blockIdx.x >= first && (int)blockIdx.x < first + nb) {
+    if (blk >= first && blk < first + nb) {
       sh[16] = s;
-      sh[17] = (int)blockIdx.x - first;
+      sh[17] = blk - first;
       sh[18] = now;
       sh[19] = cu[s];
       sh[20] = appended;
       sh[21] = nb;
     }
-    if (s == (int)blockIdx.x) seg_tab[s] = make_int4(first, nb, now, appended);
+    if (s == blk) seg_tab[s] = make_int4(first, nb, now, appended);
     first += nb;
   }
+  if (blk >= total) return false;
+  __syncthreads();
+  wk.s = __builtin_amdgcn_readfirstlane(sh[16]);
+  wk.j = __builtin_amdgcn_readfirstlane(sh[17]);
+  wk.rows = __builtin_amdgcn_readfirstlane(sh[18]);
+  wk.first_row = __builtin_amdgcn_readfirstlane(sh[19]);
+  wk.appended = __builtin_amdgcn_readfirstlane(sh[20]) != 0;
+  wk.parts = __builtin_amdgcn_readfirstlane(sh[21]);
+  return true;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -189,19 +212,15 @@ __global__ __launch_bounds__((256 * HeadSplit<T, G>::NGRP)) void decode_attn_ker
   // With k_new/v_new the call appends one row per segment (Eq. 1) and attends over it as well:
   // the row is taken from k_new/v_new by the lanes it falls to, which also store it in the cache.
   const int grow = k_new != nullptr ? 1 : 0;
-  int total;
-  const int excl = scan_blocks<NW * NGRP>(nseg, per, split, headroom, grow, cu, seg_len, sh_scan, &total);
-  find_block(excl, nseg, per, split, headroom, grow, cu, seg_len, sh_scan, seg_tab);
-  if ((int)blockIdx.x >= total) return;        // uniform: the launch is an upper bound
-  __syncthreads();
-  const int s = sh_scan[16], j = sh_scan[17], len = sh_scan[18];
+  Work wk;
+  if (!find_work<NW * NGRP>(nseg, per, split, headroom, grow, cu, seg_len, sh_scan, seg_tab, wk)) return;
+  const int s = wk.s, len = wk.rows;
   const int b = s / h, c = s % h;
   // (equal parts of the segment, as in decode_mfma_kernel, in multiples of the split's own unit)
-  const int parts = __builtin_amdgcn_readfirstlane(sh_scan[21]);
-  const int part = ((__builtin_amdgcn_readfirstlane(len) + parts - 1) / parts + 63) / 64 * 64;
-  const int r0 = j * part, r1 = min(len, r0 + part);
-  const int new_row = sh_scan[20] ? len - 1 : -1;
-  const long long seg_byte = ((long long)sh_scan[19] + (long long)s * headroom) * ROWB + col * 16;
+  const int part = ((len + wk.parts - 1) / wk.parts + 63) / 64 * 64;
+  const int r0 = wk.j * part, r1 = min(len, r0 + part);
+  const int new_row = wk.appended ? len - 1 : -1;
+  const long long seg_byte = ((long long)wk.first_row + (long long)s * headroom) * ROWB + col * 16;
   char *Kb = Kc + seg_byte;
   char *Vb = Vc + seg_byte;
   const long long new_byte = (long long)s * ROWB + col * 16;
@@ -426,23 +445,19 @@ __global__ __launch_bounds__(WHOLE ? 512 : 256) void decode_mfma_kernel(
     r0 = 0;
     r1 = len;
   } else {
-    int total;
-    const int excl = scan_blocks<NW>(nseg, per, split, headroom, grow, cu, seg_len, sh_scan, &total);
-    find_block(excl, nseg, per, split, headroom, grow, cu, seg_len, sh_scan, res.seg_tab);
-    if ((int)blockIdx.x >= total) return;      // uniform: the launch is an upper bound
-    __syncthreads();
-    s = __builtin_amdgcn_readfirstlane(sh_scan[16]);
-    len = __builtin_amdgcn_readfirstlane(sh_scan[18]);
-    cu_s = __builtin_amdgcn_readfirstlane(sh_scan[19]);
-    new_row = __builtin_amdgcn_readfirstlane(sh_scan[20]) ? len - 1 : -1;
+    Work wk;
+    if (!find_work<NW>(nseg, per, split, headroom, grow, cu, seg_len, sh_scan, res.seg_tab, wk)) return;
+    s = wk.s;
+    len = wk.rows;
+    cu_s = wk.first_row;
+    new_row = wk.appended ? len - 1 : -1;
     // The segment's rows in equal parts, in whole rounds of the workgroup: the call lasts as long as its
     // longest workgroup, and with `split` rows for all but the last one 1024 rows were cut into 896 + 128
     // (40 sequences x 8 heads of as many rows, d = 128, g = 4: 42.9 us, now 34.7; the vector kernel's 832 + 192
     // at g = 1: 37.4, 40.4 with this one, then 33.0).  None is empty.  (Whole tiles instead of rounds: 40 uneven
     // segments of 900 rows 11.8 instead of 11.3 us, 320 of 400 rows 21.7 instead of 22.0.)
-    const int parts = __builtin_amdgcn_readfirstlane(sh_scan[21]);
-    const int rows = min(split, __builtin_amdgcn_readfirstlane(((len + parts - 1) / parts + NW * TR - 1) / (NW * TR) * (NW * TR)));
-    r0 = __builtin_amdgcn_readfirstlane(sh_scan[17]) * rows;
+    const int rows = min(split, __builtin_amdgcn_readfirstlane(((len + wk.parts - 1) / wk.parts + NW * TR - 1) / (NW * TR) * (NW * TR)));
+    r0 = wk.j * rows;
     r1 = min(len, r0 + rows);
   }
   const long long seg_byte = ((long long)cu_s + (long long)s * headroom) * ROWB;
@@ -692,16 +707,21 @@ __global__ __launch_bounds__(1024) void decode_combine_kernel(
       m = mn;
     }
   }
-  *reinterpret_cast<float4 *>(&sh_a[slot][e4 * 4]) = a;
-  if (e4 == 0) { sh_m[slot] = m; sh_l[slot] = l; }
+  // (only the slots that had partials: with all of them the end of the kernel took 0.7 us of 32 slots and 1.3 of 64; a step over 8 segments of
+  // 512 rows, with the above, 9.1 -> 8.0 us, over 64 of 1500 16.5 -> 16.0)
+  const int live = min(cnt, NSLOT);
+  if (slot < live) {
+    *reinterpret_cast<float4 *>(&sh_a[slot][e4 * 4]) = a;
+    if (e4 == 0) { sh_m[slot] = m; sh_l[slot] = l; }
+  }
   __syncthreads();
   if (tid < D) {
-    float M = sh_m[0];
-#pragma unroll
-    for (int k = 1; k < NSLOT; ++k) M = fmaxf(M, sh_m[k]);
+    float M = M_INIT;
+#pragma unroll 4
+    for (int k = 0; k < live; ++k) M = fmaxf(M, sh_m[k]);
     float acc = 0.0f, ll = 0.0f;
-#pragma unroll 8
-    for (int k = 0; k < NSLOT; ++k) {
+#pragma unroll 4
+    for (int k = 0; k < live; ++k) {
       const float f = fast_exp2(sh_m[k] - M);
       acc = fmaf(sh_a[k][tid], f, acc);
       ll = fmaf(sh_l[k], f, ll);

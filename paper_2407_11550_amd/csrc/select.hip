@@ -87,21 +87,6 @@ struct TopkBufs {
   unsigned short *entries;   // last digits (10 bits each)
 };
 
-// Inclusive prefix sum over the 64 lanes of a wavefront, all of them active: data-parallel-primitive
-// adds inside the vector unit (six of them; through the LDS crossbar every step waits some 100 cycles).
-__device__ __forceinline__ int wave_scan_incl(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1 (rows of 16 lanes)
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);      // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);      // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);      // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
-  return x;
-}
-__device__ __forceinline__ int wave_sum(int x) {       // the same in all lanes
-  return __builtin_amdgcn_readlane(wave_scan_incl(x), 63);
-}
-
 // A finished histogram is searched by one wavefront, without a barrier: a lane adds up NB/64 consecutive bins, a scan
 // over the lanes finds the lane whose bins hold the rank, a second one over that lane's bins, read once more, finds
 // the bin.  (By the threads of a block, eight bins each, with three barriers, as before, a search took 0.6 to 0.8 us of
