@@ -45,6 +45,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int TILE = 32;           // keys per MFMA tile
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int MFMA_POOL_ROWS_MAX_RADIUS = 7;
+// From this radius on a row is pooled in steps of up to two keys.  32768 keys x 8 heads, 128 rows, us a call, one key a
+// step / up to two: kernel 7 41.4 / 38.7, kernel 13 52.1 / 47.2; a radius of 2 needs two steps of one either way.
+constexpr int POOL_WIDE_RADIUS = 3;
 constexpr int OWN_MOST = 3840;     // keys of a chunk at 128 rows, d = 128: beside 64 KiB of tiles in half of a compute unit's LDS
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -271,21 +274,37 @@ template <int D> struct RowTile {
 // one, which is in every window that reaches them.
 __device__ __forceinline__ unsigned pooled_row(unsigned i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
 
-// keysum += e, pooled over `radius` keys to either side, one at a time: three-operand maxima in place; what lies next
-// to the half's first and last key comes from the other half, at a tile's ends it is the key itself.  Weights are not
+// e, pooled over so far `a` keys to either side, goes on to a + S (S <= 2 a + 1, so that no key between is left out):
+// three-operand maxima in place.  What lies next to the half's first and last keys comes from the other half; at a
+// tile's ends some key of its own stands in, which spoils only what lacks neighbours there anyway.
+template <int S> __device__ __forceinline__ void widen(floatx16 &e) {
+  unsigned left[S], right[S];
+#pragma unroll
+  for (int k = 0; k < S; ++k) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(e[k]), __float_as_uint(e[16 - S + k]), false, false);
+    left[k] = sw[0];                                   // upper half: the lower one's e[16 - S + k]
+    right[k] = sw[1];                                  // lower half: the upper one's e[k]
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const unsigned own = __float_as_uint(e[i]);
+    e[i] = __uint_as_float(max(max(left[i % S], own), i + S < 16 ? __float_as_uint(e[i + S < 16 ? i + S : 15]) : right[i + S < 16 ? 0 : i + S - 16]));
+    left[i % S] = own;
+  }
+}
+// keysum += e, pooled over `radius` keys to either side.  WIDE (radius >= POOL_WIDE_RADIUS): steps of 1, then 2 (of 3 would
+// need more registers than there are): two for radius 3, four for 7.  A kernel of its own, because loops for both step
+// lengths in one kernel cost the short radii 2 to 4 %.  Weights are not
 // negative, so their bit patterns order like they do, and in an unsigned maximum a NaN, whatever its sign, wins (a
 // floating-point maximum would drop it): it poisons every mean whose window holds it, which pool_and_file stores as -inf.
+template <bool WIDE>
 __device__ __forceinline__ void pool_rows(floatx16 &e, int radius, float (&keysum)[16]) {
-  for (int t = 0; t < radius; ++t) {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(e[0]), __float_as_uint(e[15]), false, false);
-    unsigned left = sw[0];                             // lower half: its own e[0]; upper half: the lower one's e[15]
-    const unsigned right = sw[1];                      // lower half: the upper one's e[0]; upper half: its own e[15]
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const unsigned own = __float_as_uint(e[i]);
-      e[i] = __uint_as_float(max(max(left, own), i < 15 ? __float_as_uint(e[i < 15 ? i + 1 : 15]) : right));
-      left = own;
-    }
+  if constexpr (WIDE) {
+    widen<1>(e);
+    if (!(radius & 1)) widen<1>(e);
+    for (int t = 2 - (radius & 1); t < radius; t += 2) widen<2>(e);
+  } else {
+    for (int t = 0; t < radius; ++t) widen<1>(e);
   }
 #pragma unroll
   for (int i = 0; i < 16; ++i) keysum[i] += e[i];
@@ -566,7 +585,7 @@ __device__ __forceinline__ void stats_own(const SeqTab &st, const ChunkTab &cp, 
 // Sweep 2.  A workgroup owns chunk_len consecutive keys (the pool wants neighbours); its wavefronts take the
 // chunk's tiles in turn, backwards from a point that differs from workgroup to workgroup: concurrently running
 // workgroups then do not ask for addresses that are equal modulo the distance of their chunks.
-template <int D, int MB, int RS, int CHUNK, bool F16, bool PR>
+template <int D, int MB, int RS, int CHUNK, bool F16, bool PR, bool WIDE>
 __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct, const ChunkTab &cp, const Dims &dm,
                                             float c_log2, const unsigned short *__restrict__ q,
                                             const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
@@ -646,12 +665,15 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
            min(row, (unsigned)R - 1u) * (D * 2) + ((lane % T::ROW16) ^ T::swz(row)) * 16u, 0u, qs + (wv * QI + i) * 64);
     }
   };
-  unsigned rd[KS], rk[KS];                             // operand words of the queries, of a tile
+  unsigned rd[KS];                                     // operand words of the queries and (PR: not) of a tile
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    rd[s] = T::operand(l32, half, s);
-    rk[s] = PR ? T::operand(pooled_row(l32), half, s) : rd[s];
-  }
+  for (int s = 0; s < KS; ++s) rd[s] = T::operand(l32, half, s);
+  // PR: word s of a tile is the first one with 2 s exclusive-ored in, worked out for every tile, because registers are few
+  unsigned tile_word = T::operand(pooled_row(l32), half, 0);
+  auto tile_words = [&]() {
+    if constexpr (PR) asm volatile("" : "+v"(tile_word));
+  };
+  auto word = [&](int s) { return PR ? tile_word ^ (2u * s) : rd[s]; };
   bf16x8 qf[RB][KS];                                   // kept for the whole chunk
   auto queries = [&]() {
     lds_barrier();
@@ -811,7 +833,7 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
   if (iters > 0) {
     if (iters > 1) wait_vmem<LD>(); else wait_vmem<0>();
 #pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt0[wv][rk[s]]);
+    for (int s = 0; s < KS; ++s) kf[s] = as_bf16(kt0[wv][word(s)]);
   }
   int prev = 0;                                        // tile before the current one
   for (int it0 = 0; it0 < iters; it0 += 2) {
@@ -821,6 +843,7 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
       if (it < iters) {
         const int tile = tile_of(it);
         wait_lds();                                    // the tile is in registers: its place is free
+        tile_words();
         if (it + 2 < iters) issue(tile_of(it + 2), j);
 #pragma unroll
         for (int mb = 0; mb < RB; ++mb) {
@@ -832,13 +855,13 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
             a = PR ? mfma16<F16>(kf[s], qf[mb][s], a) : mfma16<F16>(qf[mb][s], kf[s], a);
-            if (mb == RB - 1) kf[s] = as_bf16(j == 0 ? kt1[wv][rk[s]] : kt0[wv][rk[s]]);   // (whatever lies there behind the last)
+            if (mb == RB - 1) kf[s] = as_bf16(j == 0 ? kt1[wv][word(s)] : kt0[wv][word(s)]);   // (whatever lies there behind the last)
             share(acc[1 - cur], pmb, mb, s);
             __builtin_amdgcn_sched_barrier(0);
           }
           acc[cur] = a;
           if constexpr (PR) {
-            pool_rows(acc[1 - cur], pool_r, keysum);
+            pool_rows<WIDE>(acc[1 - cur], pool_r, keysum);
 #pragma unroll
             for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(keysum[i]));
             __builtin_amdgcn_sched_barrier(0);
@@ -859,7 +882,7 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
     if (RB % 2 == 1 && (iters & 1)) last = acc[0];
 #pragma unroll
     for (int s = 0; s < KS; ++s) share(last, RB - 1, RB - 1, s);
-    if constexpr (PR) pool_rows(last, pool_r, keysum);
+    if constexpr (PR) pool_rows<WIDE>(last, pool_r, keysum);
     file(prev);
   }
   wait_vmem<0>();                                      // (a wavefront without tiles has asked for one as well)
@@ -1137,7 +1160,7 @@ __device__ __forceinline__ void stats_group(const SeqTab &st, const ChunkTab &cp
 }
 
 // Sweep 2: a workgroup owns chunk_len consecutive keys, as in weights_own.
-template <int D, int MB, int RS, int CHUNK, bool F16, bool PR>
+template <int D, int MB, int RS, int CHUNK, bool F16, bool PR, bool WIDE>
 __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &ct, const ChunkTab &cp, const Dims &dm,
                                               float c_log2, const unsigned short *__restrict__ q,
                                               const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
@@ -1379,7 +1402,7 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
         }
         acc[cur] = a;
         if constexpr (PR) {
-          pool_rows(acc[1 - cur], pool_r, keysum);
+          pool_rows<WIDE>(acc[1 - cur], pool_r, keysum);
 #pragma unroll
           for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(keysum[i]));
           __builtin_amdgcn_sched_barrier(0);
@@ -1394,7 +1417,7 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
   }
 #pragma unroll
   for (int s = 0; s < KS; ++s) share(acc[1], MB - 1, s);
-  if constexpr (PR) pool_rows(acc[1], pool_r, keysum);
+  if constexpr (PR) pool_rows<WIDE>(acc[1], pool_r, keysum);
   file(prev_it, prev_t);
   wait_vmem<0>();
   __syncthreads();
@@ -1410,7 +1433,7 @@ __device__ __forceinline__ void weights_group(const SeqTab &st, const ChunkTab &
 // MB row blocks of 32 window rows times RS are a workgroup's rows, RS * KG its wavefronts.  Up to 128 rows a
 // wavefront takes all of them and the wavefronts split the keys; beyond, RS wavefronts share a tile.  CHUNK: what
 // a workgroup of sweep 2 has room for (sweep 1 keeps no scores: 0).
-template <int D, int MB, int RS, int KG, int CHUNK, int PASS, bool F16, bool PR = false>
+template <int D, int MB, int RS, int KG, int CHUNK, int PASS, bool F16, bool PR = false, bool WIDE = false>
 __global__ __launch_bounds__(64 * RS * KG, MB * RS <= 4 ? 2 : 1) void score_mfma_kernel(
     SeqTab st, ChunkTab ct, ChunkTab cp, Dims dm, float c_log2, const unsigned short *__restrict__ q,
     const unsigned short *__restrict__ K, const float *__restrict__ lse, float lse_mul,
@@ -1419,11 +1442,11 @@ __global__ __launch_bounds__(64 * RS * KG, MB * RS <= 4 ? 2 : 1) void score_mfma
   if constexpr (MB * RS <= 4 && PASS == 1)
     stats_own<D, MB * RS, F16>(st, cp, dm, c_log2, q, K, part, tc);
   else if constexpr (MB * RS <= 4)
-    weights_own<D, MB, RS, CHUNK, F16, PR>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
+    weights_own<D, MB, RS, CHUNK, F16, PR, WIDE>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
   else if constexpr (PASS == 1)
     stats_group<D, MB, RS, F16>(st, cp, dm, c_log2, q, K, part, chunk_len, tc);
   else
-    weights_group<D, MB, RS, CHUNK, F16, PR>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
+    weights_group<D, MB, RS, CHUNK, F16, PR, WIDE>(st, ct, cp, dm, c_log2, q, K, lse, lse_mul, part, out, halo, chunk_len, tc);
 }
 
 template <bool F16, int D, int MB, int RS, int KG, int CHUNK>
@@ -1454,7 +1477,9 @@ void run_mfma(const MfmaVariant &v, const SeqTab &st, const Dims &dm, const void
   }
   if (pool_rows) {
     // the printed order of Alg. 2 l.4: the sweep pools every row itself and writes final scores
-    ADAKV_LAUNCH("score_weights_mfma", (score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16, true>), dim3(nblk), block, s, st, ct, cp,
+    auto *kernel = dm.pool_k / 2 >= POOL_WIDE_RADIUS ? score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16, true, true>
+                                                     : score_mfma_kernel<D, MB, RS, KG, CHUNK, 2, F16, true>;
+    ADAKV_LAUNCH("score_weights_mfma", kernel, dim3(nblk), block, s, st, ct, cp,
                  dm, c_log2, (const unsigned short *)q, (const unsigned short *)K, use_lse, lse_mul, part, scores, 0, v.len, tc);
     return;
   }
