@@ -371,7 +371,9 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
 // 6.7e-7 -> 4.7e-7, 16384 7.9e-7 -> 5.4e-7, d = 64, 64 rows, 16000 keys 8.1e-7 -> 6.6e-7.
 // What 16-bit parts cannot hold goes through the fp32 instruction, for the keys and rows concerned: values from
 // 2^60 on, infinities among them (an infinite part times a part that is zero would be a NaN, and products could
-// overflow with different signs).  What lies below bf16's range is less than 2^-133 of a value and moves no logit.
+// overflow with different signs).  At the other end a part may lie below bf16's range and be lost, less than 2^-126 of a
+// value (2^-134 with subnormal parts), at most 2 * 128 * 2^-126 * 2^60 = 2^-58 of a sum of products: a logit moves by
+// less than 2^-27 up to a scale of 2^30, beyond which the caller gets the fp32 instruction (f32_cut()).
 //
 // Keys, rows and workgroups as above.  A row block's matrix instructions (48 at d = 128) are issued with other work in
 // between: the exponentials of the block before, a stage of a value at a time, and the cut of the next block's rows,
@@ -382,6 +384,7 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
 // rows 8.5 + 9.7 / 8.0 + 9.2.  (Few rows keep the fp32 instruction: f32_cut().)
 constexpr int PARTS = 3;
 constexpr float CUT_MOST = 0x1p60f;                    // values of this size and more are not cut into parts
+constexpr float CUT_MOST_SCALE = 0x1p30f;              // with larger scales of the logits nothing is
 constexpr int PANEL = 2048;                            // rows whose log-sum-exp sweep 2 keeps at a time
 constexpr float LOW_MID = -138.0f, LOW_WIDE = 13.0f;   // exponents of subnormal results (-150 to -126) lie this near to that
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -915,7 +918,7 @@ __global__ __launch_bounds__(256) void pool_kernel(SeqTab st, ChunkTab ct, int p
 // fp32 inputs: whether products are made of bf16 parts.  A wavefront's keys have to be cut first, which one row block of
 // 128 columns or two of 64 do not bring in again (us a call, fp32 instruction / parts: 8000 keys x 8 heads, d = 128, 16
 // rows 23.0 / 26.9; d = 64, 64 rows 22.2 / 23.0; but d = 128, 64 rows 33.4 / 32.2, d = 64, 128 rows, 3000 x 4 19.5 / 17.0).
-static bool f32_cut(const Dims &dm) { return dm.g * dm.w * dm.d > 32 * 128; }
+static bool f32_cut(const Dims &dm) { return dm.g * dm.w * dm.d > 32 * 128 && dm.scale <= CUT_MOST_SCALE; }
 
 static ScorePlan plan_score_chunk(const SeqTab &st, const Dims &dm, int part_chunk) {
   ScorePlan p;

@@ -69,3 +69,26 @@ def test_an_infinite_row_is_its_own_affair():
     logit = q[0, 0, keep].double().cpu() @ K[:n, 0].double().cpu().t() / d ** 0.5
     want = torch.exp(logit - lse[0, 0, keep].double().cpu()[:, None]).sum(dim=0) / w
     assert torch.all((got - want).abs() <= 1e-4 * want)
+
+
+@pytest.mark.parametrize("given_lse", [False, True], ids=["sweep", "row_lse"])
+@pytest.mark.parametrize("d,w", [(128, 40), (64, 70)])
+def test_a_scale_that_makes_small_values_count(d, w, given_lse):
+    """Logits of 0 to 63/64 out of keys near 2^-120 and a scale of 2^127: what tells the keys apart are multiples of
+    2^-137, which no bf16 number holds.  Every product and sum of a logit is exact in fp32.  An exponent is below 16, with
+    units of 2^-20: one for the logarithm, half of one for the scaled logit, the log-sum-exp and their difference each,
+    and 1e-6 for the exponential and the sums."""
+    print("parts small values", d, w, given_lse, flush=True)
+    h, n = 2, 300
+    t = (torch.arange((n + w) * h, device=DEV).reshape(n + w, h) * 5 % 64).double()
+    K = torch.zeros((n + w, h, d), device=DEV)
+    K[..., 6] = (2.0 ** -120 * (1 + t * 2.0 ** -17)).float()
+    K[..., 40] = 2.0 ** -120
+    q = torch.zeros((1, h, w, d), device=DEV)
+    q[..., 6], q[..., 40] = 16.0, -16.0
+    layer = adakv.Layer(torch.float32, h, h, d, w, 1, 0.2, [n], [h * w], scale=2.0 ** 127)
+    x = (t[:n] / 64).cpu().numpy().T
+    lse = torch.full((1, h, w), 2.0, device=DEV) if given_lse else None
+    got = adakv.score(layer, q, K, row_lse=lse).cpu().numpy().astype(np.float64).reshape(h, n)
+    want = np.exp(x - 2) if given_lse else np.exp(x) / np.exp(x).sum(axis=1, keepdims=True)
+    assert np.all(np.abs(got - want) <= (2.5 * 2.0 ** -20 * np.log(2) + 1e-6) * want)
