@@ -338,8 +338,10 @@ const char *adakv_trace_name(int i);
  * Diagnostic (host only, launches nothing): which kernels a layer of this shape is scored and
  * selected with, as one line of "key=value" words, e.g.
  *   score=mfma dtype=bf16 d=128 rows=128 mb=2 rs=2 kg=2 chunk=2048 keys=1600 stat_keys=3200 stats=sweep lse=fused pool=fused topk=carried
- * score: mfma (16-bit matrix products) | fma (fp32 multiply-adds, on the fp32 matrix instructions) |
- * fma-pool-first (ADAKV_FLAG_POOL_THEN_MEAN, fp32 multiply-adds on the vector units);
+ * score: mfma (16-bit matrix products) | fma (32-bit products on the matrix units) | fma-pool-first
+ * (ADAKV_FLAG_POOL_THEN_MEAN: the statistics sweep like fma, weights by fp32 multiply-adds on the vector units);
+ * products, of the latter two: fp32 (the fp32 matrix instruction) | parts (fp32 inputs with g*w*d > 4096 and a scale of
+ * at most 2^30: every fp32 product as a sum of six products of bf16 parts);
  * rows = g*w window rows per KV head; mb/rs/kg/chunk: 32-row blocks per wavefront, wavefronts
  * along rows and along keys, keys a workgroup has room for; keys, stat_keys: those that one of the weights and of the
  * statistics sweep is given; stats: sweep (the statistics sweep runs) | caller (row_lse given); lse / pool: fused into the weights sweep | a kernel of their own;

@@ -412,10 +412,12 @@ int adakv_describe(const adakv_layer *L, int have_row_lse, char *out, size_t out
                    v.chunk, v.len, v.part_len, stats, have_row_lse ? "caller" : v.fuse_lse ? "fused" : "kernel",
                    pool_first(L) ? "rows" : v.fuse_pool ? "fused" : "kernel", topk);
   } else {
-    len = snprintf(out, out_bytes, "score=%s dtype=%s d=%d rows=%d stats=%s lse=%s pool=%s topk=%s",
-                   pool_first(L) ? "fma-pool-first" : "fma", dt, dm.d, dm.g * dm.w, stats,
+    const int stat_keys = plan_score(st, dm, L->dtype, false).part_chunk;
+    len = snprintf(out, out_bytes, "score=%s dtype=%s d=%d rows=%d products=%s stat_keys=%d stats=%s lse=%s pool=%s topk=%s",
+                   pool_first(L) ? "fma-pool-first" : "fma", dt, dm.d, dm.g * dm.w,
+                   f32_cut(dm, L->dtype) ? "parts" : "fp32", stat_keys, stats,
                    have_row_lse ? "caller"
-                   : !pool_first(L) && f32_lse_fused(st, plan_score(st, dm, L->dtype, false).part_chunk) ? "fused" : "kernel",
+                   : !pool_first(L) && f32_lse_fused(st, stat_keys) ? "fused" : "kernel",
                    !pool_first(L) && f32_pool_fused(st, dm, L->dtype) ? "fused" : "kernel", topk);
   }
   return (len < 0 || (size_t)len >= out_bytes) ? ADAKV_EINVAL : ADAKV_OK;

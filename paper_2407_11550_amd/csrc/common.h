@@ -101,6 +101,7 @@ struct ScorePlan {                  // byte offsets into the workspace
 ScorePlan plan_score(const SeqTab &st, const Dims &dm, int dtype, bool on_mfma);
 size_t score_workspace(const SeqTab &st, const Dims &dm, int part_chunk);   // with partial statistics per part_chunk keys
 bool mfma_path_supported(const Dims &dm, int dtype);
+bool f32_cut(const Dims &dm, int dtype);                 // fp32 products are made of bf16 parts
 bool f32_lse_fused(const SeqTab &st, int part_chunk);    // ... and combines the statistics itself
 bool f32_pool_fused(const SeqTab &st, const Dims &dm, int dtype);   // the fp32 weights sweep applies the max-pool itself
 

@@ -1,5 +1,6 @@
-// Observation-window scoring (Alg. 2 lines 1-5, group mean of Section 3.5) with fp32 multiply-adds:
-// fp32 inputs and every shape the 16-bit matrix kernels do not take.  It also hosts the two small
+// Observation-window scoring (Alg. 2 lines 1-5, group mean of Section 3.5) in 32 bits, on the fp32 matrix instruction
+// or, for fp32 inputs with many window rows, with fp32 products made of bf16 ones: fp32 inputs and every shape the
+// 16-bit matrix kernels do not take.  It also hosts the two small
 // kernels both paths share (the combination of partial softmax statistics, and the max-pool).
 //
 // The softmax of Alg. 2 l.3 needs each window row's denominator before rows can be added up,
@@ -918,7 +919,9 @@ __global__ __launch_bounds__(256) void pool_kernel(SeqTab st, ChunkTab ct, int p
 // fp32 inputs: whether products are made of bf16 parts.  A wavefront's keys have to be cut first, which one row block of
 // 128 columns or two of 64 do not bring in again (us a call, fp32 instruction / parts: 8000 keys x 8 heads, d = 128, 16
 // rows 23.0 / 26.9; d = 64, 64 rows 22.2 / 23.0; but d = 128, 64 rows 33.4 / 32.2, d = 64, 128 rows, 3000 x 4 19.5 / 17.0).
-static bool f32_cut(const Dims &dm) { return dm.g * dm.w * dm.d > 32 * 128 && dm.scale <= CUT_MOST_SCALE; }
+bool f32_cut(const Dims &dm, int dtype) {
+  return dtype == ADAKV_FP32 && dm.g * dm.w * dm.d > 32 * 128 && dm.scale <= CUT_MOST_SCALE;
+}
 
 static ScorePlan plan_score_chunk(const SeqTab &st, const Dims &dm, int part_chunk) {
   ScorePlan p;
@@ -1003,7 +1006,7 @@ bool f32_pool_fused(const SeqTab &st, const Dims &dm, int dtype) {
   if (r == 0 || r > F32_POOL_MAX) return r == 0;
   const int most = (count_chunks(st, F32_KEYS - 2 * r) * dm.h_kv + 255) / 256;
   const int most_apart = (count_chunks(st, F32_KEYS) * dm.h_kv + 255) / 256;
-  if (dtype == ADAKV_FP32 && f32_cut(dm) && (most + 1) / 2 > (most_apart + 1) / 2) return false;
+  if (f32_cut(dm, dtype) && (most + 1) / 2 > (most_apart + 1) / 2) return false;
   const int row_blocks = (dm.g * dm.w + 31) / 32;
   return (most - most_apart) * row_blocks * 1.8f * dm.d / 128 <= 4.0f;
 }
@@ -1023,7 +1026,8 @@ static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const v
   float2 *part = (float2 *)(ws + pl.part);
   float *lse = (float *)(ws + pl.lse), *raw = (float *)(ws + pl.raw);
   const float *use_lse = row_lse;
-  const bool cut = std::is_same<T, float>::value && f32_cut(dm);
+  const int dtype = std::is_same<T, float>::value ? ADAKV_FP32 : ADAKV_BF16;
+  const bool cut = f32_cut(dm, dtype);
   if (!row_lse) {
     const ChunkTab ct = make_chunks(st, pl.part_chunk);
     const dim3 grid(ct.off[st.batch], dm.h_kv);
@@ -1055,7 +1059,7 @@ static void run_generic(const SeqTab &st, const Dims &dm, const void *q, const v
     return;
   }
   const int r = dm.pool_k / 2;
-  const bool fused = f32_pool_fused(st, dm, std::is_same<T, float>::value ? ADAKV_FP32 : ADAKV_BF16);
+  const bool fused = f32_pool_fused(st, dm, dtype);
   const ChunkTab ct = make_chunks(st, fused ? F32_KEYS - 2 * r : F32_KEYS);
   const dim3 grid(ct.off[st.batch], dm.h_kv);
 #define ADAKV_GO(KERNEL)                                                                          \

@@ -11,6 +11,13 @@ from test_gpu_score_f32 import DEV, _reference
 pytestmark = pytest.mark.gpu
 
 
+def _cut(layer):
+    """The layer, which has to be one that is scored with products of parts."""
+    desc = adakv.describe(layer)
+    assert (desc["score"], desc["products"]) == ("fma", "parts")
+    return layer
+
+
 def _compare(h_q, h, d, w, k, n, given_lse, change=None):
     print("parts", h_q, h, d, w, k, n, given_lse, flush=True)
     wl = synth.small_workload(h_q, h, d, w, k, n, [h * w] * len(n), dtype=torch.float32, seed=17, temps=(0.25, 1.0))
@@ -18,21 +25,27 @@ def _compare(h_q, h, d, w, k, n, given_lse, change=None):
     if change:
         change(q, K)
     lse = synth.prefill_row_lse(wl, q, K) if given_lse else None
-    got = adakv.score(adakv.Layer.from_workload(wl), q, K, row_lse=lse).cpu().numpy().astype(np.float64)
+    got = adakv.score(_cut(adakv.Layer.from_workload(wl)), q, K, row_lse=lse).cpu().numpy().astype(np.float64)
     want, tol = _reference(wl, q, K, lse)      # d roundings of a logit at the size of its products' magnitudes
     assert tol < 2e-3
     err = np.abs(got - want) / want
     assert err.max() <= tol, (err.max(), tol)
 
 
-@pytest.mark.parametrize("given_lse", [False, True], ids=["sweep", "row_lse"])
-@pytest.mark.parametrize("h_q,h,d,w,n", [
+EDGES = [
     (2, 2, 128, 33, [31, 300]),                # a row block and one row
-    (4, 2, 128, 32, [129, 4097]),              # two whole ones; statistics combined in the sweep, by a kernel
+    (4, 2, 128, 32, [129, 4097]),              # two whole ones; statistics combined by a kernel
     (10, 2, 64, 13, [128, 1]),                 # d = 64: 65 rows
+    (4, 2, 64, 33, [33, 4100]),                # 66; statistics combined by a kernel
+    (16, 8, 128, 32, [5000]),                  # statistics per 256 keys, combined in the sweep
+    (16, 8, 64, 33, [5001]),
     (64, 1, 128, 32, [200]),                   # 2048 rows, all log-sum-exps at once
     (64, 1, 64, 33, [140]),                    # 2112: a second lot
-])
+]
+
+
+@pytest.mark.parametrize("given_lse", [False, True], ids=["sweep", "row_lse"])
+@pytest.mark.parametrize("h_q,h,d,w,n", EDGES)
 def test_edges(h_q, h, d, w, n, given_lse):
     _compare(h_q, h, d, w, 7, n, given_lse)
 
@@ -64,7 +77,7 @@ def test_an_infinite_row_is_its_own_affair():
     K[..., 7] = K[..., 7].abs() + 0.1
     lse = synth.prefill_row_lse(wl, q, K)
     q[0, 0, 35, 7] = -float("inf")
-    got = adakv.score(adakv.Layer.from_workload(wl), q, K, row_lse=lse).double().cpu()
+    got = adakv.score(_cut(adakv.Layer.from_workload(wl)), q, K, row_lse=lse).double().cpu()
     keep = [r for r in range(w) if r != 35]
     logit = q[0, 0, keep].double().cpu() @ K[:n, 0].double().cpu().t() / d ** 0.5
     want = torch.exp(logit - lse[0, 0, keep].double().cpu()[:, None]).sum(dim=0) / w

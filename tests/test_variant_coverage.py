@@ -11,6 +11,7 @@ from paper_2407_11550_amd import synth
 
 import test_gpu_decode as GD
 import test_gpu_parity as G
+import test_gpu_score_cut as GC
 
 
 def _variants_reached():
@@ -61,6 +62,32 @@ def test_gpu_shapes_reach_every_scoring_variant(lib):
             want.add(("fma-pool-first", dt, d)) # fp32 d = 128 is reached by the plain order only
     missing = sorted(map(str, want - seen))
     assert not missing, "no GPU parity shape reaches: " + ", ".join(missing)
+
+
+def test_gpu_shapes_reach_every_kernel_with_products_of_parts(lib):
+    """fp32 scoring with products of bf16 parts: the statistics sweep with partials per 128 and per 256 keys, the
+    weights sweep that combines them itself and the one that takes a log-sum-exp."""
+    seen = set()
+    for h_q, h, d, w, n in GC.EDGES:
+        wl = synth.small_workload(h_q, h, d, w, 7, n, [h * w] * len(n), dtype=torch.float32)
+        v = adakv.describe(adakv.Layer.from_workload(wl))
+        assert v["products"] == "parts", (h_q, h, d, w, n)
+        seen |= {("stats", d, int(v["stat_keys"])), ("weights", d, v["lse"])}
+    assert seen == {s for d in (64, 128) for s in (("stats", d, 128), ("stats", d, 256), ("weights", d, "fused"), ("weights", d, "kernel"))}
+
+
+def test_where_products_of_parts_begin_and_end(lib):
+    """More than 4096 values of window rows per KV head, in fp32, up to a scale of 2^30."""
+    def products(dt, h_q, h, d, w, scale=0.0, flags=0):
+        return adakv.describe(adakv.Layer(dt, h_q, h, d, w, 7, 0.2, [300], [h * w], scale=scale, flags=flags)).get("products")
+    for d, most in ((128, 32), (64, 64)):
+        assert products(torch.float32, 2, 2, d, most) == "fp32"
+        assert products(torch.float32, 2, 2, d, most + 1) == "parts"
+        assert products(torch.float32, 4, 2, d, most // 2 + 1, flags=adakv.binding.ADAKV_FLAG_POOL_THEN_MEAN) == "parts"
+        assert products(torch.float32, 2, 2, d, most + 1, scale=2.0 ** 30) == "parts"
+        assert products(torch.float32, 2, 2, d, most + 1, scale=2.0 ** 30 * (1 + 2.0 ** -23)) == "fp32"
+        assert products(torch.bfloat16, 18, 2, d, 64) == "fp32"            # 576 rows of 16-bit inputs
+        assert products(torch.bfloat16, 2, 2, d, most) is None
 
 
 def test_describe_follows_flags_and_rejects_what_score_rejects(lib):
