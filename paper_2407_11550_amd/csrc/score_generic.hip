@@ -366,8 +366,9 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
 //
 // An fp32 value is the sum of three bf16 values of 8 bits each (rounded to nearest, x = h + m + l without a
 // rest), so a product of two is nine products of 16-bit values, each exact in fp32, on instructions sixteen times as
-// fast as v_mfma_f32_32x32x2_f32.  Six are taken (hh, hm, mh, hl, lh, mm); the three left out are below 2^-25 of the
-// whole, less than fp32 rounds a product to.  The five small ones have an accumulator of their own, so that a logit
+// fast as v_mfma_f32_32x32x2_f32.  Six are taken (hh, hm, mh, hl, lh, mm).  A second part is at most 2^-8 of a value, a
+// third 2^-17, so ml and lm, the larger of those left out, are below 2^-25 each and all three below 2^-24 of the whole: no
+// more than fp32 rounds a product by.  The five small ones have an accumulator of their own, so that a logit
 // is rounded at its own size 8 times where d = 128, and not 64: error against 64 bits 8191 keys x 8 heads, 128 rows
 // 6.7e-7 -> 4.7e-7, 16384 7.9e-7 -> 5.4e-7, d = 64, 64 rows, 16000 keys 8.1e-7 -> 6.6e-7.
 // What 16-bit parts cannot hold goes through the fp32 instruction, for the keys and rows concerned: values from
