@@ -859,12 +859,15 @@ DecodePlan plan_decode(const SeqTab &st, const Dims &dm, int dtype, int headroom
   const int unit = mfma && want > 64 && want <= 256 ? 128 : 64;
   const int split = (int)((want + unit - 1) / unit * unit);
   // One workgroup of eight wavefronts per segment, and no merge kernel, where no segment can be long: a
-  // compute unit walks it alone, and what that takes follows its bytes.  us per step, split / whole, d = 128,
-  // g = 4, by rows of the longest segment: 256 10.2 / 7.1, 512 10.8 / 8.7, 768 11.0 / 11.6, 1024 10.6 / 13.1,
-  // 2048 10.7 / 21.8, 4096 10.6 / 38.9; d = 64: 512 10.5 / 7.3, 1024 10.7 / 8.9.  Heads are budgeted unevenly
-  // (the longest of a layer holds three to four times the average), so, head-room full, four times the
-  // average may reach 768 rows of 256 bytes, where both take the same, and the most that the layer allows,
-  // one head with all of its sequence's prefix budget, 1024.  And 384 rows of capacity on average.
+  // compute unit walks it alone, and what that takes follows its bytes.  us per step, split / whole, by rows of the
+  // longest segment (the others a sixth to a half of it), 8 segments, bf16, d = 128, g = 4: 256 8.2 / 7.0, 384 8.3 / 8.1,
+  // 512 8.4 / 9.2, 768 8.6 / 11.2, 1024 9.0 / 13.2; 64 segments 8.6 / 7.2, 8.9 / 9.3, 9.1 / 10.3, 10.1 / 12.5, 11.1 / 14.8;
+  // g = 8, 8 segments 9.0 / 7.9, 9.1 / 9.0, 9.3 / 10.0, 9.4 / 12.2, 9.7 / 14.3; d = 64, fp16, g = 4: 512 7.6 / 6.9, 768 7.8 /
+  // 8.3, 1024 7.9 / 9.6.  Heads are budgeted unevenly (the longest of a layer holds three to four times the
+  // average), so the line is on four times the average, head-room full: 768 rows of 256 bytes; the most that the
+  // layer allows, one head with all of its sequence's prefix budget, 1024; and 384 rows of capacity on average.  (768
+  // is where both took the same while the split form's workgroups found their rows 1.5 us later.  They meet near 400
+  // rows now: a layer at the line, with half to all of its 768 rows in use, takes up to 2.6 us more than in parts.)
   long long likely = 0, longest = 0;
   for (int b = 0; b < st.batch; ++b) {
     const long long most = st.Bp[b] < st.n[b] ? st.Bp[b] : st.n[b];

@@ -379,11 +379,13 @@ __global__ __launch_bounds__(64 * NW) void score_f32_kernel(
 //
 // Keys, rows and workgroups as above.  A row block's matrix instructions (48 at d = 128) are issued with other work in
 // between: the exponentials of the block before, a stage of a value at a time, and the cut of the next block's rows,
-// which were fetched a block before that.  Bound by these (matrix instructions 0.8 us of a row block's 1.6 with one
-// wavefront per SIMD) and, with few row blocks, by K, which has to be there before the first block is done (34 MB of
-// 8191 keys x 8 heads: 6.7 us).  Kernel times in us, fp32 instruction / this, statistics + weights, d = 128: 8191 keys
-// x 8 heads, 128 rows 23 + 25.5 / 19 + 20; 16384 45 + 50 / 32 + 31.5; 4000, 512 rows 43.5 + 45.5 / 31 + 32; 1500, 64
-// rows 8.5 + 9.7 / 8.0 + 9.2.  (Few rows keep the fp32 instruction: f32_cut().)
+// which were fetched a block before that.  Bound by these (two wavefronts of a SIMD take 2.3 us of sweep 1 and 2.75 of
+// sweep 2 for a row block each, of which the matrix instructions are 1.3; one alone takes 1.3 to 1.5, with 0.65) and, with
+// few row blocks, by K, which has to be there before the first block is done (34 MB of 8191 keys x 8 heads: 6.7 us).  A
+// wavefront with values that are not cut takes 2.6 times as long.
+// Kernel times in us, fp32 instruction / this, statistics + weights, d = 128: 8191 keys x 8 heads, 128 rows 23 + 25.5 /
+// 19 + 20; 16384 45 + 50 / 32 + 31.5; 4000, 512 rows 43.5 + 45.5 / 31 + 32; 1500, 64 rows 8.5 + 9.7 / 8.0 + 9.2.  (Few rows
+// keep the fp32 instruction: f32_cut().)
 constexpr int PARTS = 3;
 constexpr float CUT_MOST = 0x1p60f;                    // values of this size and more are not cut into parts
 constexpr float CUT_MOST_SCALE = 0x1p30f;              // with larger scales of the logits nothing is
@@ -918,8 +920,9 @@ __global__ __launch_bounds__(256) void pool_kernel(SeqTab st, ChunkTab ct, int p
 }
 
 // fp32 inputs: whether products are made of bf16 parts.  A wavefront's keys have to be cut first, which one row block of
-// 128 columns or two of 64 do not bring in again (us a call, fp32 instruction / parts: 8000 keys x 8 heads, d = 128, 16
-// rows 23.0 / 26.9; d = 64, 64 rows 22.2 / 23.0; but d = 128, 64 rows 33.4 / 32.2, d = 64, 128 rows, 3000 x 4 19.5 / 17.0).
+// 128 columns or two of 64 do not bring in again.  us a call, 8 heads, fp32 instruction / parts: 8191 keys, d = 128, 32
+// rows 22.9 / 25.3, 40 rows 33.5 / 31.8; d = 64, 64 rows 21.9 / 22.7, 80 rows 28.0 / 24.8; 600 keys 12.9 / 13.7, 17.8 / 17.5,
+// 12.9 / 13.0, 15.9 / 14.6.  (From some 16000 keys on parts would win with fewer rows too: d = 128, 32 rows 41.4 / 37.8.)
 bool f32_cut(const Dims &dm, int dtype) {
   return dtype == ADAKV_FP32 && dm.g * dm.w * dm.d > 32 * 128 && dm.scale <= CUT_MOST_SCALE;
 }
@@ -947,7 +950,10 @@ size_t score_workspace(const SeqTab &st, const Dims &dm, int part_chunk) {
 // takes as long as two of four, so the fullest compute unit may get more to do: 1.8 us per unit and row block as in
 // f32_pool_fused().  Whole call, us, 128 / 256 keys: 8191 keys x 8 heads, 128 rows 53.4 / 51.4, 5000 keys 49.8 / 46.2,
 // d = 64 37.4 / 34.9; 8000 x 8 heads, 8 rows 25.8 / 23.2; 8000 x 4 heads, 32 rows, d = 64 (half a compute unit's
-// share more) 17.0 / 14.1.  Refused: 5000 x 4 heads, 128 rows 31.8 / 36.4; five of up to 6000 keys 107.2 / 110.0.
+// share more) 17.0 / 14.1.  Refused: 5000 x 4 heads, 128 rows 31.8 / 36.4; five of up to 6000 keys 107.2 / 110.0.  With
+// products of parts the same layers are on either side: 8191 x 8 heads, 128 rows 39.5 / 38.5, 5000 35.5 / 33.1, 64 rows
+// 28.1 / 26.5 (8191 30.7 / 31.0), d = 64, 128 rows, 5000 24.0 / 22.8; refused: 5000 x 4 heads 25.0 / 27.3, 8000 x 4 28.1 /
+// 30.7, d = 64 21.9 / 23.1, five of up to 6000 x 8 75.5 / 83.6.
 // The row-pooling order keeps the kernel, and half the partials help it all the same: 8191 x 8 heads, 128 rows 165.9 /
 // 165.0, 5000 x 8 heads, 16 rows 35.3 / 33.7, 8000 x 8 heads, 32 rows, d = 64 37.2 / 35.9.
 static bool f32_wide_stats(const SeqTab &st, const Dims &dm) {
@@ -1001,7 +1007,10 @@ void launch_pool(const SeqTab &st, const Dims &dm, const float *raw, float *scor
 // 24.3 + 4.1 us.
 // Where the products are cut into parts two workgroups fit on a compute unit and a third makes a second round, which
 // takes longer than the pool kernel however few row blocks there are (fused / apart: 64 rows, d = 128, 8000 keys x 8
-// heads 34.1 / 32.2, 16000 x 4 34.0 / 31.9).
+// heads 33.4 / 31.0, 16000 x 4 34.0 / 31.9; 128 rows, 8191 x 8 42.8 / 38.6, 16000 x 4 43.5 / 39.9).  Fewer: 128 rows,
+// 2011 x 8 23.0 / 25.4, 5000 33.2 / 35.7, 4000 29.4 / 26.4 (apart), 512 rows, 2011 53.2 / 55.5.  A second workgroup
+// on a unit that had one costs more than these 1.8 us a row block, which the line does not see where there are few:
+// 64 rows, 4000 x 8 23.8 / 21.5 and, d = 64, 128 rows 20.8 / 19.9 are fused.
 bool f32_pool_fused(const SeqTab &st, const Dims &dm, int dtype) {
   const int r = dm.pool_k / 2;
   if (r == 0 || r > F32_POOL_MAX) return r == 0;

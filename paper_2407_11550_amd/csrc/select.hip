@@ -630,8 +630,8 @@ __global__ __launch_bounds__(FIN_NT) void alloc_finish_kernel(SeqTab st, ChunkTa
 // left behind; the head's lists go to memory of their own (`head`), since other blocks still read the layer's.
 // A chain of dependent trips to memory bounds it, so that sixteen wavefronts repeat the layer scope in every
 // block in the time in which one block does it.  What it saves is a launch: finish + gather / this kernel, us,
-// 32768 keys x 8 heads 12.5 / 10.0 (the whole step 67.3 / 65.2), 131072 x 8 14.6 / 11.0 (135.1 / 131.2), four of up
-// to 30000 x 8 29.6 / 25.8 (86.4 / 82.3).
+// 32768 keys x 8 heads 5.3 + 4.0 / 7.5, 131072 x 8 6.0 + 4.3 / 8.3, four of up to 30000 x 8 5.2 + 4.7 / 8.3 (whole
+// steps: FUSED_BLOCKS).
 static_assert(FIN_NT == GATHER_NT, "both halves take the same block");
 __global__ __launch_bounds__(FIN_NT) void finish_gather_kernel(SeqTab st, ChunkTab ct, int h, int w, int alpha_fix,
                                                                const float *__restrict__ scores, TopkBufs layer,
@@ -1184,31 +1184,36 @@ static int longest_row(const SeqTab &st) {
 }
 
 // Where one block per sequence or segment beats the kernels that spread a scope over the chip: a
-// block's passes cost it 0.4 to 0.6 us per 1024 scores, in one compute unit; a launch costs 4 us.  (Measured with searches
-// of 0.7 us; those of 0.25 took 2 to 3.5 us off either side.)
-// Sums of kernel times in us, spread-out kernels / block (w = 8, h = 8 unless said):
-//   allocate alone   4800 scores 20.0 / 10.6   16088 20.0 / 16.6; the counts per head make more heads dearer in
-//                    a block (us per call): h = 32 8192 scores 18.1 / 16.1, 12 288 17.8 / 18.3, 16 384 17.5 / 20.3,
-//                    h = 64 8192 19.9 / 20.2, 12 288 19.9 / 22.4 (with eight sequences 23.1 / 20.8, 23.2 / 23.3)
-//   select alone     4096 per head 22.0 / 7.9   16384 22.2 / 14.9   32768 22.6 / 25.3
-//   select carried   4096 13.0 / 7.5   8192 13.1 / 11.4   16384 13.0 / 15.7
-//   both in one      4800 18.0 / 15.0   8044 (h = 4) 18.0 / 16.7   16088 19.0 / 20.3
-// The whole step of few segments (d = 128, 128 rows): 1 x 2048 43.5 / 30.3, 2 x 5000 49.2 / 40.4, 3 x 4096
-// 46.7 / 39.7, 2 x 8192 50.5 / 47.5, 1 x 12288 49.2 / 42.0.
+// block's passes cost it 0.5 to 0.6 us per 1024 scores, in one compute unit; a launch costs 4 us.
+// us a call, spread-out kernels / block (w = 8, h = 8 unless said):
+//   allocate alone   4096 scores 14.6 / 9.4, 8192 14.6 / 12.0, 16 384 14.6 / 16.0; eight sequences 15.3 / 8.9, 15.4 / 11.8,
+//                    15.5 / 16.0, and 12 288 15.3 / 14.1.  The counts per head make more heads dearer in a block:
+//                    h = 32 8192 15.8 / 14.8, 12 288 15.7 / 17.4, h = 64 4096 18.1 / 15.4, 8192 18.0 / 19.3 (eight
+//                    sequences 21.3 / 19.7, 12 288 21.3 / 21.7)
+//   select alone     4096 per head 15.7 / 8.7, 8192 16.0 / 11.7, 16 384 16.1 / 15.5; eight sequences 18.0 / 15.6 at the last
+// A step, d = 128, 128 rows, h = 8, by positions per head: three spread-out kernels / two of them and a block per head /
+// one and a block per head / all in a block: 600 36.3 / 32.7 / 31.3 / 30.5, 1000 37.4 / 33.8 / 32.2 / 32.3, 1536 37.3 /
+// 34.7 / 32.7 / 34.3, 4096 40.1 / 37.2 / 35.8, 8192 43.8 / 43.6, 10 000 45.2 / 46.0; h = 1, 12 288 39.7 / 40.3 / - / 38.0,
+// 16 384 42.2 / 43.3 / - / 43.0.  So the block per head ends at 8192; everything in a block pays up to 12 288 scores where
+// rows are too long for the form before it, and up to some 8000 where they are not (beyond, up to the same line, it
+// costs 1 to 2 us).  (The line on allocation lies where the two met while a search took 0.7 us instead of 0.25 and the
+// gather had 256 threads; with one sequence at the line itself the block is behind by 1.3 to 1.7 us now.)
 constexpr long long alloc_block_max(int h) {           // scores of a sequence
   return (h <= 8 ? 16 : h <= 32 ? 12 : 8) * BLK_NT;
 }
 constexpr long long SELECT_BLOCK_MAX = 16 * BLK_NT;    // of a head; first digits counted here
 constexpr long long SELECT_CARRIED_MAX = 8 * BLK_NT;   // of a head; first digits from the scoring kernel
 constexpr long long TOPK_BLOCK_MAX = 12 * BLK_NT;      // of a sequence; both scopes in one launch
-constexpr long long TOPK_ROW_MAX = 4 * BLK_NT;         // of a head; gather and the rest in one launch (16088: 18.3 -> 16.3)
-// Longer rows: finish and the head's gather in one launch where every block has a compute unit to itself (each
-// repeats the layer scope with a compute unit's whole issue rate, on plateaus too: scores all equal, 32768 x 8
-// 81.9 / 80.7 us a step with four kernels / three, 131072 x 8 181 / 177, 20000 x 32 122 / 119) and where the
-// head's lists fit into what the scoring sweeps have done with.  Below four segments the line is not one of speed: a
-// trace of a layer that small is to show each scope's kernels with times of their own.  The step with four kernels /
-// three, one to three heads of 20000 to 131072 keys: 48.7 / 46.3, 58.6 / 56.4, 50.0 / 48.7, 84.4 / 82.0; all scores
-// equal 63.9 / 62.9, 117.7 / 115.0.
+constexpr long long TOPK_ROW_MAX = 4 * BLK_NT;         // of a head; gather and the rest in one launch
+// Longer rows: finish and the head's gather in one launch where every block has a compute unit to itself, each
+// repeating the layer scope with a compute unit's whole issue rate, and where the head's lists fit into what the scoring
+// sweeps have done with.  A step (d = 128, 128 rows) with four kernels / three, us: 16384 keys x 8 heads 52.1 / 50.8,
+// 131072 x 8 139.4 / 137.9, four of up to 30000 x 8 109.0 / 107.5, 20000 x 32 111.9 / 109.4, 32768 x 32 (256 blocks)
+// 150.6 / 149.3, but 32768 x 33 160.1 / 162.1, 20000 x 64 189 / 193, two of up to 131072 x 8 193.5 / 195.  On plateaus
+// too (scores all equal): 32768 x 8 94.8 / 92.4, 131072 x 8 225 / 220, 20000 x 32 169 / 163.  Below four segments the
+// line is not one of speed: a trace of a layer that small is to show each scope's kernels with times of their own (three
+// heads of 20000 46.5 / 45.9, two of 60000 52.2 / 51.6, one of 131072 52.4 / 51.6; all scores equal 77.4 / 76.6, 83.0 /
+// 81.5).
 constexpr int FUSED_BLOCKS = 256, FUSED_SEGMENTS = 4;
 size_t topk_spare_bytes(const SeqTab &st, const Dims &dm) {
   if (longest_row(st) <= SELECT_CARRIED_MAX || st.batch * dm.h_kv < FUSED_SEGMENTS) return 0;
@@ -1296,9 +1301,10 @@ hipError_t launch_topk(const SeqTab &st, const Dims &dm, const float *scores, in
   const long long most = (long long)longest_row(st) * h;
   // Every block repeats the layer scope with a compute unit's whole issue rate (sixteen wavefronts), so there
   // are no more of them than compute units; two on one take turns.  The whole step, us, block / the kernels
-  // that spread a scope over the chip, d = 64, 8 rows: 4 x 64 heads x 4096 88 / 88, on plateaus (scores in one
-  // 22-bit prefix, which every block streams) 160 / 160; 5 x 64 120 / 109, 262 / 188; 8 x 64 166 / 154, 311 / 234;
-  // 8 x 64 heads x 190 72 / 46; 32 x 8 x 1500 55 / 56; 64 x 8 x 1500 89 / 78.
+  // that spread a scope over the chip, d = 64, 8 rows: 4 x 64 heads x 4096 103.9 / 104.6, on plateaus (scores all
+  // equal, which every block streams; lengths spread below 4096) 96.7 / 97.6; 5 x 64 145.8 / 133.8, 141 / 116; 8 x 64
+  // 177.5 / 164.5, 180 / 151; 8 x 64 heads x 190 62.7 / 45.6; 32 x 8 x 1500 50.0 / 55.0; 40 x 8 71.6 / 67.1; 64 x 8
+  // 91.7 / 92.7.
   const bool in_block = most <= TOPK_BLOCK_MAX;
   if (carried && nseg <= 256 && (in_block || longest_row(st) <= TOPK_ROW_MAX)) {
     const TopkBufs tb = bufs_of(ws, plan(st, dm));
