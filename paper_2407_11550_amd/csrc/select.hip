@@ -459,8 +459,19 @@ struct Bucket {
 };
 __device__ __forceinline__ void load_early(const TopkBufs &tb, size_t blk, Bucket &bk) {
   const unsigned short *ent = tb.entries + blk * ENT_PER_BLOCK + bk.first;
+  const int count = bk.count > SERIAL_MAX ? 0 : bk.count;                  // (a longer one is streamed)
 #pragma unroll
-  for (int i = 0; i < EARLY; ++i) bk.early[i] = i < bk.count ? ent[i] : (unsigned short)0;
+  for (int i = 0; i < EARLY; ++i) bk.early[i] = i < count ? ent[i] : (unsigned short)0;
+}
+// Where a thread puts its `count` elements among those that share the prefix, their order being of no account: a scan
+// in its wavefront and an atomic per wavefront, without a barrier.  (With an atomic per thread the compiler goes through
+// the active lanes one after the other: allocation alone, 8 heads, scores all equal, 20000 of them 35.5 us, 33.7 with this,
+// 131072 91.4 / 89.0.)  All lanes of the wavefront take part.
+__device__ __forceinline__ unsigned place(int count, Searches &sr) {
+  const int upto = wave_scan_incl(count);
+  unsigned first = 0;
+  if ((threadIdx.x & 63) == 63 && upto) first = atomicAdd(&sr.total, (unsigned)upto);
+  return (unsigned)__builtin_amdgcn_readlane((int)first, 63) + (unsigned)(upto - count);
 }
 
 // Layer scope from the gather kernel's results, by a block of sixteen wavefronts: Algorithm 1's
@@ -509,9 +520,7 @@ __device__ __forceinline__ int layer_counts(const ChunkTab &ct, int h, int b, in
       const int over = tb.note[k].above + (total - first - count);
       if (over) atomicAdd(&sh_gt[k % h], over);
     }
-    // (the held elements' order is of no account, so that a thread's place among them needs no scan)
-    unsigned at = 0;
-    if (mine_cnt) at = atomicAdd(&sr.total, (unsigned)mine_cnt);
+    unsigned at = place(mine_cnt, sr);
     if (longest > SERIAL_MAX) sr.many = 1u;
     __syncthreads();
     const int total = (int)sr.total;
@@ -760,8 +769,7 @@ __global__ __launch_bounds__(NT) void emit_write_kernel(
         pg += tb.note[kb].above + (total - first - count);
       }
     }
-    unsigned at = 0;                                   // (as in layer_counts)
-    if (mine_cnt) at = atomicAdd(&sr.total, (unsigned)mine_cnt);
+    unsigned at = place(mine_cnt, sr);
     if (longest > SERIAL_MAX) sr.many = 1u;
     __syncthreads();
     const int total = (int)sr.total;
