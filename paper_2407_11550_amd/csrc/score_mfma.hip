@@ -665,15 +665,20 @@ __device__ __forceinline__ void weights_own(const SeqTab &st, const ChunkTab &ct
            min(row, (unsigned)R - 1u) * (D * 2) + ((lane % T::ROW16) ^ T::swz(row)) * 16u, 0u, qs + (wv * QI + i) * 64);
     }
   };
-  unsigned rd[KS];                                     // operand words of the queries and (PR: not) of a tile
+  unsigned rd[KS], rk[KS];                             // operand words of the queries, of a tile
 #pragma unroll
-  for (int s = 0; s < KS; ++s) rd[s] = T::operand(l32, half, s);
-  // PR: word s of a tile is the first one with 2 s exclusive-ored in, worked out for every tile, because registers are few
+  for (int s = 0; s < KS; ++s) {
+    rd[s] = T::operand(l32, half, s);
+    rk[s] = PR ? T::operand(pooled_row(l32), half, s) : rd[s];
+  }
+  // WIDE: word s of a tile is the first one with 2 s exclusive-ored in, worked out for every tile, because registers are
+  // few.  (In the short radii's kernel, which has them, it costs 3 %: 32768 keys x 8 heads, 128 rows, kernel 3 37.4 /
+  // 38.4 us a call, kernel 5 39.6 / 40.7.)
   unsigned tile_word = T::operand(pooled_row(l32), half, 0);
   auto tile_words = [&]() {
-    if constexpr (PR) asm volatile("" : "+v"(tile_word));
+    if constexpr (WIDE) asm volatile("" : "+v"(tile_word));
   };
-  auto word = [&](int s) { return PR ? tile_word ^ (2u * s) : rd[s]; };
+  auto word = [&](int s) { return WIDE ? tile_word ^ (2u * s) : rk[s]; };
   bf16x8 qf[RB][KS];                                   // kept for the whole chunk
   auto queries = [&]() {
     lds_barrier();
